@@ -314,7 +314,10 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_kernel(const Problem p_arg, con
     unsigned *const own = queued ? pa.queue + kQueueStride * ((int)blockIdx.x & 7) : nullptr;
     if (queued) {
       bid = take_item(pa.queue, pa.grid_items, drawn, ticket, &claim);
-      if (bid < 0) return;
+      if (bid < 0) {
+        leave_queues(pa.queue);
+        return;
+      }
     }
     ticket = bwd_dq_item<D, HS>(p, pa, a, bid, smem, own);
     drawn = true;
@@ -357,12 +360,6 @@ static hipError_t launch_dq(const Problem &p, const BwdArgs &a, hipStream_t st) 
   if (launch != grid_q || (p.tune_queue >= 2 && grid_q > 1 && resident > 0)) {
     pa.queue = item_queue_for(st);
     if (!pa.queue) launch = grid_q;
-  }
-  std::unique_lock<std::mutex> pair;  // reset and launch enter the stream back to back
-  if (pa.queue) {
-    pair = std::unique_lock<std::mutex>(item_queue_launch_mutex());
-    hipError_t e = item_queue_reset(pa.queue, st);
-    if (e != hipSuccess) return e;
   }
   if (hs == 4) hipLaunchKernelGGL((bwd_dq_kernel<D, 4>), dim3((unsigned)launch), dim3(256), 0, st, p, pa, a);
   else if (hs == 2) hipLaunchKernelGGL((bwd_dq_kernel<D, 2>), dim3((unsigned)launch), dim3(256), 0, st, p, pa, a);

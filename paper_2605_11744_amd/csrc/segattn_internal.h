@@ -170,17 +170,15 @@ inline void prepare_resolve_divs(const Problem &p, PrefillArgs &a, int heads_per
 constexpr int kQueueStride = 32;  // unsigned words between two queue counters (128 bytes)
 // Host side of the item queues (segattn_prefill_mfma.hip): the counters of this (device, stream),
 // or nullptr where the launch has to run one workgroup per item (stream under capture, no set
-// left); and the kernel that clears them, to be launched in front of every queued launch.
-// The reset and the launch that uses the counters must enter the stream back to back: hold
-// item_queue_launch_mutex() around the pair (two host threads may launch into one stream).
+// left).  The counters are zero between launches: the last workgroup to leave a launch clears
+// them (leave_queues in segattn_work.h).
 unsigned *item_queue_for(hipStream_t st);
-hipError_t item_queue_reset(unsigned *queue, hipStream_t st);
-std::mutex &item_queue_launch_mutex();
+constexpr int kQueueWords = 9 * kQueueStride;  // of one set: eight queue counters, workgroups that have left
 // Grid of a launch of `items` work items whose kernel fits `resident` workgroups on the chip at
 // once, under Problem::tune_queue: `items` (one workgroup per item, no queues), or fewer
 // workgroups that take their items from the queues.  The library's own choice is the resident
 // grid whenever a workgroup would get more than two items (with fewer there is little to balance
-// and the counters' reset kernel and first round trip are not earned back).
+// and the counters' round trips are not earned back).
 inline long long item_queue_grid(const Problem &p, long long items, long long resident) {
   if (resident <= 0 || p.tune_queue == 1) return items;
   if (p.tune_queue >= 2 ? items <= 1 : items <= 2 * resident) return items;

@@ -825,8 +825,8 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
 // most items left, so a fast XCD goes on with the slowest one's items; when all eight are empty
 // it leaves.  Nothing waits for another workgroup.  The ticket for the next round is drawn while
 // the output of this one is being written (prefill_mfma_item), so the round trip to the counter
-// is hidden.  Each queue's counter has a 128-byte line of its own; a one-wave kernel in front of
-// the launch clears them.
+// is hidden.  Each queue's counter has a 128-byte line of its own; the last workgroup of a launch
+// clears them.
 template <int D, int HS, int QB, int NW>
 __global__ __launch_bounds__(64 * NW, 8 / (NW * QB)) void prefill_mfma_kernel(const Problem p_arg, const PrefillArgs a_arg) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -852,27 +852,15 @@ __global__ __launch_bounds__(64 * NW, 8 / (NW * QB)) void prefill_mfma_kernel(co
     unsigned *const own = queued ? a.queue + kQueueStride * ((int)blockIdx.x & 7) : nullptr;
     if (queued) {
       bid = take_item(a.queue, a.grid_items, drawn, ticket, claim);
-      if (bid < 0) return;
+      if (bid < 0) {
+        leave_queues(a.queue);
+        return;
+      }
     }
     ticket = prefill_mfma_item<D, HS, QB, NW>(p, a, bid, smem, own);
     drawn = true;
     if (!queued) return;
   }
-}
-
-// Clears a set of queue counters (launched in front of every queued launch, on its stream).
-__global__ void item_queue_reset_kernel(unsigned *queue) {
-  if (threadIdx.x < 8) queue[kQueueStride * threadIdx.x] = 0;
-}
-
-std::mutex &item_queue_launch_mutex() {
-  static std::mutex mu;
-  return mu;
-}
-
-hipError_t item_queue_reset(unsigned *queue, hipStream_t st) {
-  hipLaunchKernelGGL(item_queue_reset_kernel, dim3(1), dim3(64), 0, st, queue);
-  return hipGetLastError();
 }
 
 // =============================================================================================
@@ -924,7 +912,7 @@ hipError_t launch_prefill_fp32(const Problem &p, const PrefillArgs &a, long long
 static int heads_per_wg(const Problem &p) { return (p.g % 4 == 0) ? 4 : (p.g % 2 == 0) ? 2 : 1; }
 
 // ---- counters of the queued form of the kernel
-// Eight counters per set, each on a 128-byte line of its own.  Launches on one stream run one
+// Nine counters per set, each on a 128-byte line of its own, zero between launches.  Launches on one stream run one
 // after the other and share a set; launches on different streams may overlap, so every (device, stream) pair that asks gets a
 // set of its own, for as long as the process lives.  When the sets are used up, and for a stream
 // that is being captured (the graph may later be replayed on any stream, next to anything), the
@@ -933,7 +921,7 @@ static int device_cus();
 
 constexpr int kQueueSets = 64;
 constexpr int kQueueDevices = 16;
-static __device__ unsigned g_queue_sets[kQueueSets][8 * kQueueStride];
+static __device__ unsigned g_queue_sets[kQueueSets][kQueueWords];
 
 unsigned *item_queue_for(hipStream_t st) {
   struct Owner {
@@ -969,7 +957,7 @@ unsigned *item_queue_for(hipStream_t st) {
     owners[n_owners] = Owner{dev, st};
     set = n_owners++;
   }
-  return base[dev] + 8 * kQueueStride * set;
+  return base[dev] + kQueueWords * set;
 }
 
 template <int D, int HS, int QB, int NW>
@@ -997,14 +985,6 @@ static hipError_t launch_mfma(const Problem &p, const PrefillArgs &a_in, long lo
     a.queue = item_queue_for(st);
     if (!a.queue) launch = grid;
   }
-  if (!a.queue) {
-    hipLaunchKernelGGL(kern, dim3((unsigned)launch), dim3(64 * NW), lds, st, p, a);
-    return hipGetLastError();
-  }
-  // reset and launch go into the stream back to back, also when several host threads use it
-  std::lock_guard<std::mutex> pair(item_queue_launch_mutex());
-  hipError_t e = item_queue_reset(a.queue, st);
-  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)launch), dim3(64 * NW), lds, st, p, a);
   return hipGetLastError();
 }
