@@ -209,18 +209,16 @@ segattn_status seg_attn_fwd(segattn_ctx *ctx, const void *q, const void *k, cons
   a.geom = ctx->g;
   a.n_rows = m;
   a.n_seg = 1;
-  a.min_past_prefix = 0;
-  if (ctx->g.part_max > 1) {  // fewest prefix rows among the PAST windows: how far their work can be split
-    long long least = -1;
-    for (int b = 0; b < p.B; ++b)
-      for (int h = 0; h < p.Hkv; ++h)
-        if (p.policy[h] & SEGATTN_PAST) {
-          const size_t i = (size_t)b * p.Hkv + h;
-          const long long rows = ctx->pool[i] - ctx->lo[i] + ctx->fill[b];
-          if (least < 0 || rows < least) least = rows;
-        }
-    a.min_past_prefix = least < 0 ? 0 : least;
-  }
+  // longest prefixes: how far the launch's work should be split
+  for (int b = 0; b < p.B; ++b)
+    for (int h = 0; h < p.Hkv; ++h) {
+      const size_t i = (size_t)b * p.Hkv + h;
+      const bool past = p.policy[h] & SEGATTN_PAST;
+      const long long before = past ? (ctx->g.ret_cap ? ctx->ret[b] : ctx->pool[i] - ctx->lo[i])
+                                    : (p.policy[h] & SEGATTN_TAIL) ? ctx->tail[b] : 0;
+      long long &most = past && ctx->g.ret_cap == 0 ? a.max_first_prefix : a.max_other_prefix;
+      if (before + ctx->fill[b] > most) most = before + ctx->fill[b];
+    }
   return hip_status(launch_prefill(p, a, (hipStream_t)stream));
 }
 

@@ -29,7 +29,7 @@ enum MetaSlot { META_POOL = 0, META_TAIL = 1, META_FILL = 2, META_LO = 3, META_R
 struct CacheGeom {
   unsigned long long meta_off, ws_off, kv_off, view_off;
   unsigned long long part_off;         // split-prefix workspace of the segment-by-segment prefill (0: none)
-  int part_max;                        // most parts a PAST head's prefix may be cut into (1: never split)
+  int part_max;                        // the split-prefix workspace holds this many whole segments of the PAST heads (1: none)
   unsigned long long rows_per_seq;     // sum of cap(h) over heads
   unsigned long long pool_cap;         // rows per PAST head
   int ret_cap;                         // rows of retrieved prefix a view can hold; 0: no views
@@ -100,7 +100,7 @@ __host__ __device__ inline int fast_mod(int n, const FastDiv &f) { return n - fa
 // divides as written.
 struct ResolveDivs {
   int ok;
-  FastDiv per, parts, nqb, nhs, n_first, n_other, batch, per_sub, sub, groups;
+  FastDiv per, parts, parts_other, nqb, nhs, n_first, n_other, batch, per_sub, sub, groups;
 };
 
 struct PrefillArgs {
@@ -117,13 +117,19 @@ struct PrefillArgs {
   int pair_stride;       // spreads the (segment, sequence, head) groups of non-PAST heads over the XCDs (0 = 1)
   int sub_groups;        // a group's query blocks are dealt into this many interleaved sub-groups (0 = 1) so that
                          // every XCD's share of the non-PAST list is a whole number of (sub-)groups
-  // CTX mode, split prefix: the prefix of every PAST head is cut into `parts` pieces, each handled
-  // by a workgroup of its own (the last one also takes the open segment); the pieces' normalised
-  // fp32 outputs and their LSEs go to the workspace and prefill_part_combine_kernel merges them.
-  int parts;             // 0 or 1: no split
-  long long min_past_prefix;  // host: fewest prefix rows among the PAST windows (sets how far to split)
-  float *part_out;       // [B][parts][n_rows][n_past*g][D]
-  float *part_lse;       // [B][parts][n_past*g][n_rows]
+  // CTX mode, split prefix: a head's prefix is cut into pieces of piece_rows rows (piece_count of
+  // them: it depends on the head's own prefix), each handled by a workgroup of its own (the last one
+  // also takes the open segment); the pieces' normalised fp32 outputs and their LSEs go to the
+  // workspace and prefill_part_combine_kernel merges them.
+  int parts, parts_other;  // most pieces of a head of the first / the common list; 0 or 1: no split
+  FastDiv piece_rows;      // .d: rows of a piece, a multiple of the 32-key step; 0: nothing is cut
+  long long max_first_prefix, max_other_prefix;  // host: most prefix rows in a window of either list
+  struct PieceList {       // workspace of the heads of one list: 0 the first, 1 the common one
+    float *out;            // [B][most][n_rows][heads][D]
+    float *lse;            // [B][most][heads][n_rows]
+    int most, heads;       // its parts / parts_other, its query heads
+    int head0;             // its first position in the list of KV heads
+  } piece_list[2];
   // Work items of the launch (0: the grid size) and, where the workgroups take their items from
   // queues, the counters: next item of XCD y's queue at queue[kQueueStride * y], zero at the start.
   int grid_items;
@@ -135,6 +141,22 @@ struct PrefillArgs {
   int ret_R;
   ResolveDivs dv;
 };
+// Heads listed first, longest work first: the PAST heads -- unless they attend to a retrieved
+// prefix of bounded size, in which case their key ranges are as short as everybody's and all heads
+// go into the common list.
+__host__ __device__ inline int heads_listed_first(const Problem &p, const PrefillArgs &a) {
+  return ((a.cache != nullptr && a.geom.ret_cap > 0) || a.ret_k != nullptr) ? 0 : p.n_past;
+}
+// Pieces that a head with n0 prefix rows and n1 rows of the open segment is cut into: piece_rows
+// rows each, the last one takes the rest of the prefix (possibly nothing) and the open segment,
+// n1/2 keys per query on average.
+__host__ __device__ inline int piece_count(int n0, int n1, const FastDiv &piece_rows, int most) {
+  const int even = fast_div(n0 + n1 / 2 + (int)piece_rows.d / 2, piece_rows);
+  const int whole = fast_div(n0, piece_rows) + 1;
+  int c = even < whole ? even : whole;
+  c = c < most ? c : most;
+  return c > 1 ? c : 1;
+}
 // Fills a.dv for a launch whose fields resolve() reads are final (q_blocks_per_seg, n_seg, parts,
 // sub_groups, pair_stride, grid_items); heads_per_wg as passed to resolve().
 inline void prepare_resolve_divs(const Problem &p, PrefillArgs &a, int heads_per_wg, long long grid) {
@@ -142,7 +164,7 @@ inline void prepare_resolve_divs(const Problem &p, PrefillArgs &a, int heads_per
   dv.ok = 0;
   const int nhs = p.g / heads_per_wg;
   const int nqb = a.q_blocks_per_seg;
-  const int n_first = ((a.cache != nullptr && a.geom.ret_cap > 0) || a.ret_k != nullptr) ? 0 : p.n_past;
+  const int n_first = heads_listed_first(p, a);
   const int n_other = p.Hkv - n_first;
   const int parts = (a.cache != nullptr && a.parts > 1) ? a.parts : 1;
   const long long past_items = (long long)p.B * n_first * nhs * a.n_seg * nqb * parts;
@@ -154,6 +176,7 @@ inline void prepare_resolve_divs(const Problem &p, PrefillArgs &a, int heads_per
   if (groups > 0 && (groups - 1) * stride >= (1ll << 31)) return;  // the shuffled group index must fit
   dv.per = fast_div_by((long long)p.B * (n_first > 0 ? n_first : 1) * nhs * parts);
   dv.parts = fast_div_by(parts);
+  dv.parts_other = fast_div_by((a.cache != nullptr && a.parts_other > 1) ? a.parts_other : 1);
   dv.nqb = fast_div_by(nqb);
   dv.nhs = fast_div_by(nhs);
   dv.n_first = fast_div_by(n_first > 0 ? n_first : 1);
@@ -162,7 +185,7 @@ inline void prepare_resolve_divs(const Problem &p, PrefillArgs &a, int heads_per
   dv.per_sub = fast_div_by(nqb / d);
   dv.sub = fast_div_by(d);
   dv.groups = fast_div_by(groups > 0 ? groups : 1);
-  const FastDiv *all[] = {&dv.per, &dv.parts, &dv.nqb, &dv.nhs, &dv.n_first, &dv.n_other, &dv.batch, &dv.per_sub, &dv.sub, &dv.groups};
+  const FastDiv *all[] = {&dv.per, &dv.parts, &dv.parts_other, &dv.nqb, &dv.nhs, &dv.n_first, &dv.n_other, &dv.batch, &dv.per_sub, &dv.sub, &dv.groups};
   for (const FastDiv *f : all)
     if (f->d == 0) return;
   dv.ok = 1;

@@ -866,33 +866,76 @@ __global__ __launch_bounds__(64 * NW, 8 / (NW * QB)) void prefill_mfma_kernel(co
 // =============================================================================================
 // split prefix (segment-by-segment prefill): merge the pieces
 // =============================================================================================
-// Every piece of a PAST head's keys left a normalised fp32 output row and its LSE in the
-// workspace; softmax over the union is the LSE-weighted mean of the pieces (the same identity the
-// decode path and a sharded prefix use).  32 lanes per (sequence, row, head), D/32 channels each.
+// Every piece of a head's keys left a normalised fp32 output row and its LSE in the workspace;
+// softmax over the union is the LSE-weighted mean of the pieces (the same identity the decode path
+// and a sharded prefix use).  32 lanes per (sequence, row, head): lane i forms the weights of the
+// pieces i, i + 32, ..., then the lanes hold D/32 channels each.  Bound by memory latency (the
+// pieces come from other XCDs' caches): one round trip for the LSEs, and the rows' loads do not
+// depend on each other and are unrolled.  Where the heads of a list have more than kWidePieces
+// pieces a workgroup takes one row: its eight lane groups take every eighth piece and meet in LDS;
+// otherwise it takes eight rows.  Measured, 173 rows of 8 heads with 35 pieces each and 24 heads with
+// two: 17.4 us with eight rows per workgroup everywhere (a round trip per eight pieces), 19.2 us with
+// one everywhere (5536 workgroups), 10.7 us like this.
+// wgs0: workgroups of list 0; rows0, rows1: (sequence, row, head) items of the lists, 0 where uncut.
+constexpr int kWidePieces = 8;
 template <int D>
-__global__ __launch_bounds__(256) void prefill_part_combine_kernel(const Problem p, const PrefillArgs a) {
+__global__ __launch_bounds__(256) void prefill_part_combine_kernel(const Problem p, const PrefillArgs a, const int wgs0,
+                                                                   const long long rows0, const long long rows1) {
   constexpr int CPL = D / 32;  // channels per lane
-  const int ph = p.n_past * p.g;
+  typedef float f32xc __attribute__((ext_vector_type(CPL)));
+  const int list = (int)blockIdx.x < wgs0 ? 0 : 1;
+  const PrefillArgs::PieceList &pl = a.piece_list[list];
+  const bool wide = pl.most > kWidePieces;
+  const int grp = threadIdx.x >> 5, lane = threadIdx.x & 31;
+  const int wg = (int)blockIdx.x - (list ? wgs0 : 0);
   const long long m = a.n_rows;
-  const long long item = (long long)blockIdx.x * 8 + (threadIdx.x >> 5);
-  if (item >= (long long)p.B * m * ph) return;
-  const int lane = threadIdx.x & 31;
-  const int hc = (int)(item % ph);
-  const long long row = (item / ph) % m;
-  const int b = (int)(item / ((long long)ph * m));
-  const int head = p.order[hc / p.g] * p.g + hc % p.g;
+  const long long item = wide ? wg : (long long)wg * 8 + grp;
+  if (item >= (list ? rows1 : rows0)) return;
+  const int hc = (int)(item % pl.heads);
+  const long long row = (item / pl.heads) % m;
+  const int b = (int)(item / (pl.heads * m));
+  const int hl = pl.head0 * p.g + hc;  // position in the list of all heads
+  const int kv = p.order[hl / p.g];
+  int lo, seg_row0;
+  const int *meta = meta_ro(a.cache, a.geom, p, b, kv);
+  window_of(p, a.geom, kv, meta, lo, seg_row0);
+  const int pieces = piece_count(seg_row0 + meta[META_FILL] - lo, a.n_rows, a.piece_rows, pl.most);
+  if (pieces < 2) return;  // written by its only workgroup
+  const int head = kv * p.g + hl % p.g;
+  const long long slot = m * pl.heads;  // rows of one piece
+  const float *lse = pl.lse + (long long)b * pl.most * slot + hc * m + row;
+  const float *src = pl.out + (((long long)b * pl.most * m + row) * pl.heads + hc) * D + lane * CPL;
   float mx = -INFINITY;
-  for (int pt = 0; pt < a.parts; ++pt)
-    mx = fmaxf(mx, a.part_lse[(((long long)b * a.parts + pt) * ph + hc) * m + row]);
+  for (int p0 = 0; p0 < pieces; p0 += 32) mx = fmaxf(mx, p0 + lane < pieces ? lse[(p0 + lane) * slot] : -INFINITY);
+#pragma unroll
+  for (int sh = 16; sh >= 1; sh >>= 1) mx = fmaxf(mx, __shfl_xor(mx, sh, 32));
   float sum = 0.f, acc[CPL];
 #pragma unroll
   for (int e = 0; e < CPL; ++e) acc[e] = 0.f;
-  for (int pt = 0; pt < a.parts; ++pt) {
-    const float wgt = __expf(a.part_lse[(((long long)b * a.parts + pt) * ph + hc) * m + row] - mx);
-    const float *src = a.part_out + ((((long long)b * a.parts + pt) * m + row) * ph + hc) * D + lane * CPL;
-    sum += wgt;
+  for (int p0 = 0; p0 < pieces; p0 += 32) {
+    const float mine = p0 + lane < pieces ? __expf(lse[(p0 + lane) * slot] - mx) : 0.f;
+    const int n = pieces - p0 < 32 ? pieces - p0 : 32;
+    sum += mine;
+#pragma unroll 8
+    for (int i = wide ? grp : 0; i < n; i += wide ? 8 : 1) {
+      const float wgt = __shfl(mine, i, 32);
+      const f32xc x = *(const f32xc *)(src + (p0 + i) * slot * D);
 #pragma unroll
-    for (int e = 0; e < CPL; ++e) acc[e] = fmaf(wgt, src[e], acc[e]);
+      for (int e = 0; e < CPL; ++e) acc[e] = fmaf(wgt, x[e], acc[e]);
+    }
+  }
+#pragma unroll
+  for (int sh = 16; sh >= 1; sh >>= 1) sum += __shfl_xor(sum, sh, 32);
+  if (wide) {
+    __shared__ float sm[8][D];
+#pragma unroll
+    for (int e = 0; e < CPL; ++e) sm[grp][lane * CPL + e] = acc[e];
+    __syncthreads();
+    if (grp > 0) return;
+#pragma unroll
+    for (int e = 0; e < CPL; ++e)
+#pragma unroll
+      for (int i = 1; i < 8; ++i) acc[e] += sm[i][lane * CPL + e];
   }
   const float inv = 1.f / sum;
   const long long o = (((long long)b * m + row) * p.Hq + head) * D + lane * CPL;
@@ -1037,36 +1080,78 @@ static int device_cus() {
   return n_cu;
 }
 
-// Segment-by-segment prefill: pieces to cut every PAST head's prefix into.  One segment has few
-// query blocks, and the ones of the PAST heads carry nearly all the work: with one workgroup per
-// block the launch takes as long as its longest workgroup while most CUs idle.  Cut so that the
-// long workgroups are about as many as the CUs (eight-wave workgroups, one per CU), every piece
-// keeping at least 1024 rows.
-static int prefix_parts(const Problem &p, const PrefillArgs &a, int hs) {
-  if (a.cache == nullptr || a.geom.part_max < 2 || p.n_past == 0 || a.geom.ret_cap > 0 || p.D != 128) return 1;
-  if (p.tune_waves != 0) return 1;  // a forced workgroup shape runs unsplit
-  const int rows8 = (8 / hs) * 32;
-  const long long long_wgs = (long long)p.B * p.n_past * (p.g / hs) * ((a.n_rows + rows8 - 1) / rows8);
-  long long parts = device_cus() / long_wgs;
-  if (parts > a.geom.part_max) parts = a.geom.part_max;
-  if (parts > a.min_past_prefix / 1024) parts = a.min_past_prefix / 1024;
-  return parts < 2 ? 1 : (int)parts;
+// Segment-by-segment prefill: how far to cut the heads' prefixes.  One launch has few query blocks (a
+// user's turn of a conversation has one to a few per head), and those of the PAST heads can have
+// tens of thousands of keys: with one workgroup per block the launch takes as long as its longest
+// workgroup while most CUs idle.  The pieces are made as long as the average work of a CU, at
+// least kMinPieceSteps steps, as long as the workspace holds their outputs: that of the arena made
+// for it, or (a few rows, or configurations without one) the decode path's, which no other call of
+// this context uses at the same time.  A workgroup costs about kItemSteps steps beyond its keys
+// (prologue and output), the merge about half of that; where the estimate with pieces is no
+// shorter than without, nothing is cut (a whole segment behind a short prefix).
+// Measured, 32/8 heads, two PAST, m = 173 rows behind 37.5K rows, whole call with the commit: 412 us with
+// four pieces at most, 66 us with 35 pieces of 34 steps; pieces of 48 and 64 steps 20 and 30 us more.
+constexpr int kMinPieceSteps = 8, kItemSteps = 12;
+static void plan_pieces(const Problem &p, PrefillArgs &a, int hs, int rows, int wgs_per_cu) {
+  a.parts = a.parts_other = 1;
+  a.piece_rows = FastDiv{0u, 0u, 0u};
+  if (a.cache == nullptr || p.tune_waves != 0) return;  // a forced workgroup shape runs unsplit
+  if (a.max_first_prefix >= (1ll << 29)) return;        // piece_count works in 32 bits
+  const int m = a.n_rows, n_first = heads_listed_first(p, a), n_other = p.Hkv - n_first;
+  const long long part_bytes = a.geom.part_max > 1 ? (long long)part_ws_bytes(p, a.geom.part_max) : 0;
+  const unsigned long long dec_off = a.geom.ws_off + ws_header_bytes(p);
+  const long long dec_bytes = (long long)(a.geom.kv_off - dec_off);
+  const bool own_ws = part_bytes >= dec_bytes;
+  const long long ws_floats = (own_ws ? part_bytes : dec_bytes) / 4;
+  const long long wgs = (long long)device_cus() * wgs_per_cu;
+  const long long blocks = (long long)p.B * (p.g / hs) * ((m + rows - 1) / rows);  // per KV head
+  auto steps = [&](long long prefix) { return (prefix + m / 2 + kStepKeys - 1) / kStepKeys; };
+  const long long sf = n_first > 0 ? steps(a.max_first_prefix) : 0, so = n_other > 0 ? steps(a.max_other_prefix) : 0;
+  const long long total = blocks * (n_first * sf + n_other * so);
+  auto span = [&](long long items, long long most) {  // estimated steps from start to end
+    const long long even = (total + kItemSteps * items + wgs - 1) / wgs;
+    return most + kItemSteps > even ? most + kItemSteps : even;
+  };
+  const long long uncut = blocks * p.Hkv, uncut_span = span(uncut, sf > so ? sf : so);
+  long long len = (total + wgs - 1) / wgs, items, row_heads;
+  if (len < kMinPieceSteps) len = kMinPieceSteps;
+  for (;; len += (len + 15) / 16) {
+    const FastDiv t = fast_div_by(len * kStepKeys);
+    const int c0 = n_first > 0 ? piece_count((int)a.max_first_prefix, m, t, 1 << 20) : 1;
+    const int c1 = n_other > 0 ? piece_count((int)a.max_other_prefix, m, t, 1 << 20) : 1;
+    if (c0 == 1 && c1 == 1) return;
+    items = blocks * (n_first * c0 + n_other * c1);
+    row_heads = (long long)p.B * m * p.g * ((c0 > 1 ? n_first * c0 : 0) + (c1 > 1 ? n_other * c1 : 0));
+    if (row_heads * (p.D + 1) > ws_floats) continue;
+    if (items > wgs && uncut <= wgs) continue;  // a second round of workgroups would double the time
+    if (span(items, len) + kItemSteps / 2 >= uncut_span) return;
+    a.parts = c0;
+    a.parts_other = c1;
+    a.piece_rows = t;
+    break;
+  }
+  const long long rows_first = a.parts > 1 ? (long long)p.B * a.parts * m * n_first * p.g : 0;
+  float *const out = (float *)(a.cache + (own_ws ? a.geom.part_off : dec_off)), *const lse = out + row_heads * p.D;
+  a.piece_list[0] = {out, lse, a.parts, n_first * p.g, 0};
+  a.piece_list[1] = {out + rows_first * p.D, lse + rows_first, a.parts_other, n_other * p.g, n_first};
 }
 
 hipError_t launch_prefill(const Problem &p, const PrefillArgs &a_in, hipStream_t st) {
   const bool fp32 = p.fp32_math != 0;
   const int hs = fp32 ? 1 : heads_per_wg(p);
   PrefillArgs a = a_in;
-  a.parts = fp32 ? 1 : prefix_parts(p, a, hs);
-  const int nw = p.D == 128 ? (a.parts > 1 ? 8 : waves_d128(p, a_in, hs)) : 4;
+  const int n_first = heads_listed_first(p, a);
+  if (!fp32) plan_pieces(p, a, hs, p.D == 128 ? (8 / hs) * 32 : (4 / hs) * 32, p.D == 128 ? 1 : 2);
+  const bool cut = a.parts > 1 || a.parts_other > 1;
+  const int nw = p.D == 128 ? (cut ? 8 : waves_d128(p, a_in, hs)) : 4;
   const int rows = fp32 ? 64 : (p.D == 128 ? (nw / hs) * 32 : (4 / hs) * 32);
   const long long seg_rows = a.n_rows < p.S ? a.n_rows : p.S;
   a.q_blocks_per_seg = (int)((seg_rows + rows - 1) / rows);
   const long long per_head = (long long)p.B * (p.g / hs) * a.n_seg * a.q_blocks_per_seg;
-  const long long grid = per_head * ((long long)p.n_past * a.parts + (p.Hkv - p.n_past));
+  const long long parts = a.parts > 1 ? a.parts : 1, parts_other = a.parts_other > 1 ? a.parts_other : 1;
+  const long long grid = per_head * (n_first * parts + (p.Hkv - n_first) * parts_other);
   if (grid <= 0 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
-  const int n_first = ((a.cache != nullptr && a.geom.ret_cap > 0) || a.ret_k != nullptr) ? 0 : p.n_past;  // as in resolve()
-  const long long groups = (long long)p.B * (p.Hkv - n_first) * (p.g / hs) * a.n_seg;
+  const long long groups = (long long)p.B * (p.Hkv - n_first) * (p.g / hs) * a.n_seg * parts_other;
   a.pair_stride = prefill_pair_stride(groups);
   // Interleaved sub-groups per group so that the XCDs' ranges are whole (sub-)groups: see resolve().
   // Only for groups whose K/V rows (segment + tail) exceed an XCD's 4 MB L2 anyway: sub-groups put
@@ -1082,10 +1167,6 @@ hipError_t launch_prefill(const Problem &p, const PrefillArgs &a_in, hipStream_t
         break;
       }
     if (a.q_blocks_per_seg % d == 0) a.sub_groups = d;
-  }
-  if (a.parts > 1) {
-    a.part_out = (float *)(a.cache + a.geom.part_off);
-    a.part_lse = a.part_out + (long long)p.B * a.parts * a.n_rows * p.n_past * p.g * p.D;
   }
   prepare_resolve_divs(p, a, hs, grid);
   if (fp32) return launch_prefill_fp32(p, a, grid, st);
@@ -1105,9 +1186,18 @@ hipError_t launch_prefill(const Problem &p, const PrefillArgs &a_in, hipStream_t
     else if (hs == 2) e = launch_mfma<64, 2, 1, 4>(p, a, grid, st);
     else e = launch_mfma<64, 1, 1, 4>(p, a, grid, st);
   }
-  if (e != hipSuccess || a.parts < 2) return e;
-  const long long items = (long long)p.B * a.n_rows * p.n_past * p.g;
-  hipLaunchKernelGGL(prefill_part_combine_kernel<128>, dim3((unsigned)((items + 7) / 8)), dim3(256), 0, st, p, a);
+  if (e != hipSuccess || !cut) return e;
+  long long row_heads[2], wgs[2];
+  for (int i = 0; i < 2; ++i) {
+    const PrefillArgs::PieceList &pl = a.piece_list[i];
+    row_heads[i] = pl.most > 1 ? (long long)p.B * a.n_rows * pl.heads : 0;
+    wgs[i] = pl.most > kWidePieces ? row_heads[i] : (row_heads[i] + 7) / 8;
+  }
+  const dim3 grid_c((unsigned)(wgs[0] + wgs[1]));
+  if (p.D == 128)
+    hipLaunchKernelGGL(prefill_part_combine_kernel<128>, grid_c, dim3(256), 0, st, p, a, (int)wgs[0], row_heads[0], row_heads[1]);
+  else
+    hipLaunchKernelGGL(prefill_part_combine_kernel<64>, grid_c, dim3(256), 0, st, p, a, (int)wgs[0], row_heads[0], row_heads[1]);
   return hipGetLastError();
 }
 

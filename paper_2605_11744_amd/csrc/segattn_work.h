@@ -104,12 +104,10 @@ __host__ __device__ inline ItemCoords item_coords(const Problem &p, const Prefil
                                                   int heads_per_wg) {
   const int nhs = p.g / heads_per_wg;
   const int nqb = a.q_blocks_per_seg;
-  // heads listed first, longest work first: the PAST heads -- unless they attend to a retrieved
-  // prefix of bounded size, in which case their key ranges are as short as everybody's and all
-  // heads go into the common list below
-  const int n_first = ((a.cache != nullptr && a.geom.ret_cap > 0) || a.ret_k != nullptr) ? 0 : p.n_past;
+  const int n_first = heads_listed_first(p, a);
   const int n_other = p.Hkv - n_first;
   const int parts = (a.cache != nullptr && a.parts > 1) ? a.parts : 1;
+  const int parts_other = (a.cache != nullptr && a.parts_other > 1) ? a.parts_other : 1;
   const long long past_items = (long long)p.B * n_first * nhs * a.n_seg * nqb * parts;
   int seg, qblk, hidx, b, hs, part = 0;
   if (a.dv.ok) {
@@ -148,6 +146,10 @@ __host__ __device__ inline ItemCoords item_coords(const Problem &p, const Prefil
       qblk = nqb - 1 - ((sg - grp * d) + d * (L - sg * (int)dv.per_sub.d));
       const long long shuffled = (long long)grp * (a.pair_stride > 0 ? a.pair_stride : 1);  // < 2^31 (host check)
       int rest = fast_mod((int)shuffled, dv.groups);
+      if (parts_other > 1) {
+        part = fast_mod(rest, dv.parts_other);
+        rest = fast_div(rest, dv.parts_other);
+      }
       hs = fast_mod(rest, dv.nhs);
       rest = fast_div(rest, dv.nhs);
       const int r2 = fast_div(rest, dv.n_other);
@@ -204,6 +206,8 @@ __host__ __device__ inline ItemCoords item_coords(const Problem &p, const Prefil
     // coprime to the group count, about an eighth of it) deals each XCD an even sample.
     const long long groups = items / nqb;
     int rest = (int)((L / nqb) * (a.pair_stride > 0 ? a.pair_stride : 1) % groups);
+    part = rest % parts_other;
+    rest /= parts_other;
     hs = rest % nhs;
     rest /= nhs;
     hidx = n_first + rest % n_other;
@@ -218,7 +222,6 @@ __host__ __device__ inline ItemCoords item_coords(const Problem &p, const Prefil
 __device__ inline WorkItem resolve(const Problem &p, const PrefillArgs &a, int bid, int rows_per_wg,
                                    int heads_per_wg) {
   WorkItem w;
-  const int parts = (a.cache != nullptr && a.parts > 1) ? a.parts : 1;
   const ItemCoords ic = item_coords(p, a, bid, a.grid_items > 0 ? a.grid_items : (int)gridDim.x, heads_per_wg);
   const int seg = ic.seg, qblk = ic.qblk, hidx = ic.hidx, b = ic.b, hs = ic.hs, part = ic.part;
   const int kv = p.order[hidx];
@@ -287,28 +290,25 @@ __device__ inline WorkItem resolve(const Problem &p, const PrefillArgs &a, int b
   w.out_heads = p.Hq;
   w.ohead0 = kv * p.g + hs * heads_per_wg;
   w.wide = p.out_fp32 != 0;
-  if (parts > 1 && (pol & SEGATTN_PAST)) {
-    // Piece `part` of the prefix.  The last piece also takes the open segment (about n1/2 keys per
-    // query on average), so the others get a little more of the prefix: t rows each, a multiple of
-    // the 32-key step, and the last one the rest (the host only splits prefixes of >= 1024 rows per
-    // piece, so the rest is never empty).
-    const int n0 = w.n0;
-    int t = ((n0 + w.n1 / 2) / parts + 31) & ~31;
-    const int t_max = ((n0 - 32) / (parts - 1)) & ~31;
-    t = t < t_max ? t : t_max;
-    const int start = part * t;
-    w.k0 += (long long)start * p.D;
-    w.v0 += (long long)start * p.D;
-    w.n0 = (part == parts - 1) ? n0 - start : t;
-    if (part != parts - 1) w.n1 = 0;
-    const int ph = p.n_past * p.g;  // heads per workspace row
-    const long long m = a.n_rows;
-    w.out = (unsigned char *)(a.part_out + (((long long)b * parts + part) * m * ph) * p.D);
-    w.lse = a.part_lse + ((long long)b * parts + part) * ph * m;
-    w.lse_head_stride = m;
-    w.out_heads = ph;
-    w.ohead0 = p.past_before[kv] * p.g + hs * heads_per_wg;
-    w.wide = true;
+  if (a.piece_rows.d != 0) {  // (the stateful form only)
+    const PrefillArgs::PieceList &pl = a.piece_list[hidx < a.piece_list[1].head0 ? 0 : 1];
+    const int pieces = piece_count(w.n0, w.n1, a.piece_rows, pl.most);
+    if (part >= pieces) {
+      w.nq = 0;  // this head's prefix is shorter: no such piece
+    } else if (pieces > 1) {
+      const int start = part * (int)a.piece_rows.d;
+      w.k0 += (long long)start * p.D;
+      w.v0 += (long long)start * p.D;
+      w.n0 = (part == pieces - 1) ? w.n0 - start : (int)a.piece_rows.d;
+      if (part != pieces - 1) w.n1 = 0;
+      const long long slot = (long long)(b * pl.most + part) * a.n_rows * pl.heads;
+      w.out = (unsigned char *)(pl.out + slot * p.D);
+      w.lse = pl.lse + slot;
+      w.lse_head_stride = a.n_rows;
+      w.out_heads = pl.heads;
+      w.ohead0 = (hidx - pl.head0) * p.g + hs * heads_per_wg;
+      w.wide = true;
+    }
   }
   w.valid = w.t0 < w.nq;
   return w;
