@@ -141,6 +141,15 @@ struct PrefillArgs {
   int ret_R;
   ResolveDivs dv;
 };
+// Row blocks of a packed batch without the holes of a (sequence x segment x block) grid: sequence b
+// gets the numbers packed_units(cu[b]) + b .. packed_units(cu[b+1]) + b, at least as many as it has
+// blocks (a segment of S rows has ceil(S / rows) blocks; floor(x) - floor(y) >= floor(x - y), and a
+// last, short segment of r rows has ceil(r / rows) <= r ceil(S / rows) / S + 1); all sequences together
+// packed_units(total) + B.
+__host__ __device__ inline long long packed_units(long long row, int S, int rows_per_block) {
+  const long long blocks_per_seg = (S + rows_per_block - 1) / rows_per_block;
+  return S % rows_per_block == 0 ? row / rows_per_block : row * blocks_per_seg / S;
+}
 // Heads listed first, longest work first: the PAST heads -- unless they attend to a retrieved
 // prefix of bounded size, in which case their key ranges are as short as everybody's and all heads
 // go into the common list.
@@ -462,6 +471,7 @@ hipError_t launch_prefill(const Problem &p, const PrefillArgs &a, hipStream_t st
 __host__ __device__ inline unsigned long long part_ws_bytes(const Problem &p, int parts) {
   return (unsigned long long)p.B * parts * p.S * p.n_past * p.g * (unsigned long long)(p.D + 1) * 4ull;
 }
+hipError_t launch_prefill_keysplit(const Problem &p, const PrefillArgs &a, int heads_per_wg, long long grid, hipStream_t st);
 hipError_t launch_decode(const Problem &p, const DecodeArgs &a, int B, hipStream_t st);
 int decode_mfma_resident(int D);  // workgroups of the matrix-core split kernel the chip holds at once (0: error)
 hipError_t launch_decode_split_mfma(const Problem &p, const DecodeArgs &a, long long blocks, hipStream_t st);

@@ -218,11 +218,10 @@ __host__ __device__ inline ItemCoords item_coords(const Problem &p, const Prefil
   return ItemCoords{seg, qblk, hidx, b, hs, part};
 }
 
-// blockIdx -> work item: the coordinates above, then the item's key spans, query rows and outputs.
-__device__ inline WorkItem resolve(const Problem &p, const PrefillArgs &a, int bid, int rows_per_wg,
-                                   int heads_per_wg) {
+// Coordinates -> the item's key spans, query rows and outputs.
+__device__ inline WorkItem resolve_at(const Problem &p, const PrefillArgs &a, const ItemCoords &ic, int rows_per_wg,
+                                      int heads_per_wg) {
   WorkItem w;
-  const ItemCoords ic = item_coords(p, a, bid, a.grid_items > 0 ? a.grid_items : (int)gridDim.x, heads_per_wg);
   const int seg = ic.seg, qblk = ic.qblk, hidx = ic.hidx, b = ic.b, hs = ic.hs, part = ic.part;
   const int kv = p.order[hidx];
   const int pol = p.policy[kv];
@@ -312,6 +311,34 @@ __device__ inline WorkItem resolve(const Problem &p, const PrefillArgs &a, int b
   }
   w.valid = w.t0 < w.nq;
   return w;
+}
+
+// Number u of a packed batch's row blocks (packed_units) -> sequence, segment and block.  Every wave
+// works it out by itself: a lane per sequence, then a count of the sequences that start at or before u.
+__device__ inline void packed_block(const Problem &p, const int *cu_seqlens, long long u, int rows_per_block, int &b,
+                                    int &seg, int &qblk) {
+  const int lane = threadIdx.x & 63;
+  int before = 0;
+  for (int b0 = 0; b0 < p.B; b0 += 64) {
+    const int i = b0 + lane;
+    const bool starts = i < p.B && packed_units(cu_seqlens[i < p.B ? i : 0], p.S, rows_per_block) + i <= u;
+    const int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(starts));
+    before += n;
+    if (n < 64) break;
+  }
+  b = before > 0 ? before - 1 : 0;
+  int v = (int)(u - packed_units(cu_seqlens[b], p.S, rows_per_block)) - b;
+  if (v < 0) v = 0x3fffffff;  // cu_seqlens[0] was not 0: a block behind every sequence's end
+  const int per_seg = (p.S + rows_per_block - 1) / rows_per_block;
+  seg = v / per_seg;
+  qblk = v - seg * per_seg;
+}
+
+// blockIdx -> work item.
+__device__ inline WorkItem resolve(const Problem &p, const PrefillArgs &a, int bid, int rows_per_wg,
+                                   int heads_per_wg) {
+  const ItemCoords ic = item_coords(p, a, bid, a.grid_items > 0 ? a.grid_items : (int)gridDim.x, heads_per_wg);
+  return resolve_at(p, a, ic, rows_per_wg, heads_per_wg);
 }
 
 __device__ inline int uniform_i32(int x) { return __builtin_amdgcn_readfirstlane(x); }
