@@ -60,18 +60,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, D == 64 ? 4 : 2) void prefill_key
   constexpr int NL = kSplitStep / RPL;         // loads per tile and tensor
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
-  ItemCoords ic;
-  if (a.cu_seqlens) {  // packed batch: the row blocks there are, from the last one on, all heads of a block side by side
-    const int nhs = p.g / HS, per = p.Hkv * nhs;
-    const int rest = (int)blockIdx.x % per;
-    ic.hidx = rest / nhs;
-    ic.hs = rest % nhs;
-    ic.part = 0;
-    packed_block(p, a.cu_seqlens, (int)(gridDim.x / per) - 1 - (int)blockIdx.x / per, R, ic.b, ic.seg, ic.qblk);
-  } else {
-    ic = item_coords(p, a, (int)blockIdx.x, (int)gridDim.x, HS);
-  }
-  WorkItem w = resolve_at(p, a, ic, R, HS);
+  WorkItem w = resolve(p, a, (int)blockIdx.x, R, HS);
   if (!w.valid) return;
   pin_uniform(w);
   const int tid = threadIdx.x, lane = tid & 63;

@@ -328,16 +328,110 @@ __device__ inline void packed_block(const Problem &p, const int *cu_seqlens, lon
   }
   b = before > 0 ? before - 1 : 0;
   int v = (int)(u - packed_units(cu_seqlens[b], p.S, rows_per_block)) - b;
-  if (v < 0) v = 0x3fffffff;  // cu_seqlens[0] was not 0: a block behind every sequence's end
+  if (v < 0) v = 0x3fffffff / p.S;  // cu_seqlens[0] was not 0: a block behind every sequence's end
   const int per_seg = (p.S + rows_per_block - 1) / rows_per_block;
   seg = v / per_seg;
   qblk = v - seg * per_seg;
 }
 
+__device__ inline int wave_sum_i32(int x) {  // over the 64 lanes: DPP inside the rows of 16, then four lanes
+  x += __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);
+  x += __builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true);
+  x += __builtin_amdgcn_mov_dpp(x, 0x141, 0xF, 0xF, true);
+  x += __builtin_amdgcn_mov_dpp(x, 0x140, 0xF, 0xF, true);
+  return (__builtin_amdgcn_readlane(x, 0) + __builtin_amdgcn_readlane(x, 16)) +
+         (__builtin_amdgcn_readlane(x, 32) + __builtin_amdgcn_readlane(x, 48));
+}
+// The u-th row block of a packed batch of at most 64 sequences in the order of descending block index
+// (longest key range first for heads that see the whole past): false if there are no more than u.
+// A lane per sequence; the block index q is found by bisection, with the number of blocks at or
+// beyond q as a sum over the lanes: about 0.5 us.
+__device__ inline bool packed_longest(const Problem &p, const int *cu_seqlens, int u, int rows_per_block, int &b, int &seg,
+                                      int &qblk) {
+  const int lane = threadIdx.x & 63;
+  const int per_seg = (p.S + rows_per_block - 1) / rows_per_block;
+  int blocks = 0;
+  if (lane < p.B) {
+    const int len = cu_seqlens[lane + 1] - cu_seqlens[lane];
+    blocks = len > 0 ? len / p.S * per_seg + (len % p.S + rows_per_block - 1) / rows_per_block : 0;
+  }
+  const int all = wave_sum_i32(blocks);
+  if (u >= all) return false;
+  int lo = 0, hi = 1, at_hi;  // more than u blocks at or beyond lo, at_hi <= u at or beyond hi
+  while ((at_hi = wave_sum_i32(blocks > hi ? blocks - hi : 0)) > u) {
+    lo = hi;
+    hi *= 2;
+  }
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    const int n = wave_sum_i32(blocks > mid ? blocks - mid : 0);
+    if (n > u) {
+      lo = mid;
+    } else {
+      hi = mid;
+      at_hi = n;
+    }
+  }
+  // block lo of the (u - at_hi)-th sequence that has one
+  const unsigned long long have = __builtin_amdgcn_ballot_w64(blocks > lo);
+  const int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(have >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)have, 0u));
+  b = (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(blocks > lo && rank == u - at_hi));
+  seg = lo / per_seg;
+  qblk = lo - seg * per_seg;
+  return true;
+}
+
+// Item index -> coordinates for a packed batch: only the row blocks there are (and at most one per
+// sequence that is not), instead of a grid of every sequence padded to the longest -- of eight
+// sequences of 65 to 9001 tokens two thirds of that grid's items were empty, and each cost its
+// workgroup a turn at the queue.  Items: units x heads x sub-groups, the PAST heads first, longest
+// first (up to 64 sequences; beyond that in the order of the batch), then the others: like in
+// item_coords an XCD takes a contiguous range of the list ordered by head and row block, from the
+// last block on.
+__device__ inline ItemCoords packed_coords(const Problem &p, const PrefillArgs &a, int bid, int total_items, int rows_per_wg,
+                                           int heads_per_wg) {
+  const int nhs = p.g / heads_per_wg, n_first = heads_listed_first(p, a);
+  const int units = total_items / (p.Hkv * nhs);
+  const int pi = units * n_first * nhs;
+  ItemCoords ic;
+  ic.part = 0;
+  if (bid < pi) {
+    const int per = n_first * nhs, u = bid / per, rest = bid - u * per;
+    ic.hidx = rest / nhs;
+    ic.hs = rest - ic.hidx * nhs;
+    if (p.B > 64) {
+      packed_block(p, a.cu_seqlens, units - 1 - u, rows_per_wg, ic.b, ic.seg, ic.qblk);
+    } else if (!packed_longest(p, a.cu_seqlens, u, rows_per_wg, ic.b, ic.seg, ic.qblk)) {
+      ic.b = ic.qblk = 0;
+      ic.seg = 0x3fffffff / p.S;  // behind the end of any sequence
+    }
+  } else {
+    const int items = total_items - pi, x = bid & 7;
+    int start = 0, first = 0;
+#pragma unroll
+    for (int xx = 0; xx < 8; ++xx) {
+      const int o = (xx - pi) & 7;  // first list position served by XCD xx
+      const int cnt = o < items ? (items - o + 7) >> 3 : 0;
+      if (xx < x) start += cnt;
+      if (xx == x) first = pi + o;
+    }
+    const int L = start + ((bid - first) >> 3), h = L / units;
+    ic.hidx = n_first + h / nhs;
+    ic.hs = h % nhs;
+    packed_block(p, a.cu_seqlens, units - 1 - (L - h * units), rows_per_wg, ic.b, ic.seg, ic.qblk);
+  }
+  ic.b = __builtin_amdgcn_readfirstlane(ic.b);  // the same in every lane: keep what follows from them in scalar registers
+  ic.seg = __builtin_amdgcn_readfirstlane(ic.seg);
+  ic.qblk = __builtin_amdgcn_readfirstlane(ic.qblk);
+  return ic;
+}
+
 // blockIdx -> work item.
 __device__ inline WorkItem resolve(const Problem &p, const PrefillArgs &a, int bid, int rows_per_wg,
                                    int heads_per_wg) {
-  const ItemCoords ic = item_coords(p, a, bid, a.grid_items > 0 ? a.grid_items : (int)gridDim.x, heads_per_wg);
+  const int items = a.grid_items > 0 ? a.grid_items : (int)gridDim.x;
+  const ItemCoords ic = a.cu_seqlens ? packed_coords(p, a, bid, items, rows_per_wg, heads_per_wg)
+                                     : item_coords(p, a, bid, items, heads_per_wg);
   return resolve_at(p, a, ic, rows_per_wg, heads_per_wg);
 }
 
@@ -369,6 +463,8 @@ __device__ inline void pin_uniform(WorkItem &w) {
   w.v0 = uniform_ptr(w.v0);
   w.k1 = uniform_ptr(w.k1);
   w.v1 = uniform_ptr(w.v1);
+  w.out = uniform_ptr(w.out);
+  w.lse = uniform_ptr(w.lse);
 }
 
 __device__ inline float bf16_bits_to_f32(unsigned short h) { return __uint_as_float((unsigned)h << 16); }
