@@ -90,7 +90,9 @@ typedef struct {
   /* Launch-shape overrides for tests and A/B timing; 0 everywhere = the library chooses.  Results
    * do not depend on them beyond rounding order. */
   int32_t prefill_waves;   /* 4 or 8: waves per workgroup of the head_dim-128 bf16 forward kernel
-                              (a forced shape also keeps seg_attn_fwd from cutting prefixes)     */
+                              (a forced shape also keeps seg_attn_fwd from cutting prefixes, and
+                              it as well as a forced queue mode every call from the forms for small
+                              launches)                                                           */
   int32_t item_queues;     /* forward and dQ kernels as a resident grid that takes its work items
                               from per-XCD queues: 1 never, 2 whenever a launch has more than one
                               item, 3 the same with a grid a third of the items (so that small

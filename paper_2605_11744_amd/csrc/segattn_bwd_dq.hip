@@ -331,7 +331,8 @@ static int bwd_heads_per_wg(const Problem &p) { return (p.g % 4 == 0) ? 4 : (p.g
 template <int D>
 static hipError_t launch_dq(const Problem &p, const BwdArgs &a, hipStream_t st) {
   const int hs = bwd_heads_per_wg(p);
-  const int rows = (4 / hs) * 32;
+  const bool split = bwd_dq_split_pays(p, a);
+  const int rows = split ? 32 / hs : (4 / hs) * 32;
   PrefillArgs pa;
   memset(&pa, 0, sizeof(pa));
   pa.q = a.q;
@@ -352,6 +353,7 @@ static hipError_t launch_dq(const Problem &p, const BwdArgs &a, hipStream_t st) 
   if (grid_q <= 0 || grid_q > 0x7fffffffLL) return hipErrorInvalidValue;
   pa.grid_items = (int)grid_q;
   prepare_resolve_divs(p, pa, hs, grid_q);
+  if (split) return launch_bwd_dq_split(p, pa, a, hs, grid_q, st);
   // resident grid + item queues where every resident workgroup would get more than two items
   const void *kern = hs == 4 ? (const void *)bwd_dq_kernel<D, 4> : hs == 2 ? (const void *)bwd_dq_kernel<D, 2>
                                                                             : (const void *)bwd_dq_kernel<D, 1>;

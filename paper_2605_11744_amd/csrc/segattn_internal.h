@@ -199,6 +199,22 @@ inline void prepare_resolve_divs(const Problem &p, PrefillArgs &a, int heads_per
     if (f->d == 0) return;
   dv.ok = 1;
 }
+// What a whole-sequence launch has to do, in steps of 32 query columns x 32 keys (a wave's unit of work):
+// all of them, the longest row of them that one 32-column block meets, the column blocks.  retrieved: rows
+// of the prefix of a PAST head where it is not its whole history, else 0.  A packed batch (total_rows > 0)
+// counts as many sequences of the longest length as its rows make up (no fewer steps than it has).
+struct StepCount {
+  double steps, longest, blocks;
+};
+inline StepCount count_steps(const Problem &p, long long n, long long total_rows, int retrieved) {
+  const double seqs = total_rows > 0 ? (double)total_rows / n : p.B;
+  const double seg = (double)(n < p.S ? n : p.S), segs = n / seg, per_seg = (seg + 31) / 32;
+  const double bounded = segs > 1 ? (retrieved ? retrieved : p.T) : 0;  // prefix of the heads without the whole past
+  const int n_long = retrieved ? 0 : p.n_past;
+  const double past = segs * per_seg * n / 64, other = segs * per_seg * (seg / 64 + bounded / 32);
+  return {seqs * p.g * (n_long * past + (p.Hkv - n_long) * other), n_long > 0 ? (n + 31) / 32. : (bounded + seg + 31) / 32,
+          seqs * p.Hq * segs * per_seg};
+}
 constexpr int kQueueStride = 32;  // unsigned words between two queue counters (128 bytes)
 // Host side of the item queues (segattn_prefill_mfma.hip): the counters of this (device, stream),
 // or nullptr where the launch has to run one workgroup per item (stream under capture, no set
@@ -494,6 +510,12 @@ hipError_t launch_bwd_delta(const Problem &p, const BwdArgs &a, hipStream_t st);
 hipError_t launch_bwd_fp32(const Problem &p, const BwdArgs &a, hipStream_t st);
 hipError_t launch_bwd_dq(const Problem &p, const BwdArgs &a, hipStream_t st);
 hipError_t launch_bwd_mfma(const Problem &p, const BwdArgs &a, hipStream_t st);
+// Forms for small launches (segattn_bwd_split.hip), and whether they are the faster ones.
+bool bwd_dq_split_pays(const Problem &p, const BwdArgs &a);
+bool bwd_dkv_split_pays(const Problem &p, const BwdArgs &a);
+hipError_t launch_bwd_dq_split(const Problem &p, const PrefillArgs &pa, const BwdArgs &a, int heads_per_wg, long long grid,
+                               hipStream_t st);
+hipError_t launch_bwd_dkv_split(const Problem &p, const BwdArgs &a, hipStream_t st);
 int prefill_pair_stride(long long groups);
 hipError_t launch_probe(void *buf, long long bytes, int mode, void *sink, hipStream_t st);
 constexpr int kClockProbeWaves = 8;  // one per XCD

@@ -1145,28 +1145,14 @@ static void plan_pieces(const Problem &p, PrefillArgs &a, int hs, int rows, int 
 //                    D = 128: 7.5 + 0.13 a step + 1.1e-3 a wave-step, 256 workgroups a round; 3 a further round
 // e.g. 2048 tokens, 4 heads, D = 64: 33.1 -> 15.0 us; 1000 tokens, 8 heads, D = 128: 25.9 -> 15.3; from about
 // 1000 tokens of 32 heads on the other form is the faster one (D = 64: 20.9 against 22.5).
-static bool use_keysplit(const Problem &p, const PrefillArgs &a, int hs) {
+static bool use_keysplit(const Problem &p, const PrefillArgs &a) {
   if (p.tune_waves != 0 || p.tune_queue != 0 || a.cache != nullptr) return false;
-  // a packed batch: as many sequences of the longest length as its rows make up
-  const long long n = a.n_rows;
-  const double seqs = a.cu_seqlens ? (double)a.total_rows / n : p.B;
-  const long long seg_rows = n < p.S ? n : p.S;
-  double steps_past = 0, steps_other = 0, longest = 0;  // per 32-row column block, over a sequence's segments
-  const double blocks = (double)((seg_rows + 31) / 32);
-  const double all_segs = (double)n / seg_rows;
-  const long long bounded = a.ret_k ? a.ret_R : p.T < n ? p.T : 0;  // prefix of the heads without the whole past
-  steps_other = all_segs * blocks * ((double)seg_rows / 64 + (all_segs > 1 ? (double)bounded / 32 : 0));
-  longest = ((all_segs > 1 ? bounded : 0) + seg_rows + 31) / 32;
-  const int n_long = a.ret_k ? 0 : p.n_past;
-  steps_past = blocks * all_segs * (double)n / 64;
-  if (n_long > 0) longest = (n + 31) / 32;
-  const double wave_steps = seqs * p.g * (n_long * steps_past + (p.Hkv - n_long) * steps_other);
-  const double wgs = seqs * p.Hq * all_segs * blocks;
+  const StepCount c = count_steps(p, a.n_rows, a.cu_seqlens ? a.total_rows : 0, a.ret_k ? a.ret_R : 0);
   const double slots = device_cus() * (p.D == 64 ? 2 : 1);
-  const double rounds = wgs <= slots ? 0 : wgs / slots;
-  const double split = p.D == 64 ? 6.5 + 0.11 * longest + 5.6e-4 * wave_steps + 3 * rounds
-                                 : 7.5 + 0.13 * longest + 1.1e-3 * wave_steps + 3 * rounds;
-  const double piped = p.D == 64 ? 7 + 0.41 * longest : 9.5 + 0.52 * longest;
+  const double rounds = c.blocks <= slots ? 0 : c.blocks / slots;
+  const double split = p.D == 64 ? 6.5 + 0.11 * c.longest + 5.6e-4 * c.steps + 3 * rounds
+                                 : 7.5 + 0.13 * c.longest + 1.1e-3 * c.steps + 3 * rounds;
+  const double piped = p.D == 64 ? 7 + 0.41 * c.longest : 9.5 + 0.52 * c.longest;
   return split < 0.95 * piped;
 }
 
@@ -1178,7 +1164,7 @@ hipError_t launch_prefill(const Problem &p, const PrefillArgs &a_in, hipStream_t
   if (!fp32) plan_pieces(p, a, hs, p.D == 128 ? (8 / hs) * 32 : (4 / hs) * 32, p.D == 128 ? 1 : 2);
   const bool cut = a.parts > 1 || a.parts_other > 1;
   const int nw = p.D == 128 ? (cut ? 8 : waves_d128(p, a_in, hs)) : 4;
-  const bool keysplit = !fp32 && use_keysplit(p, a, hs);
+  const bool keysplit = !fp32 && use_keysplit(p, a);
   const int rows = fp32 ? 64 : keysplit ? 32 / hs : (p.D == 128 ? (nw / hs) * 32 : (4 / hs) * 32);
   const long long seg_rows = a.n_rows < p.S ? a.n_rows : p.S;
   a.q_blocks_per_seg = (int)((seg_rows + rows - 1) / rows);

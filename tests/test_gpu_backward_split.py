@@ -1,0 +1,55 @@
+"""GPU parity of the backward pass at the sizes where the library shares a workgroup's steps out among its
+waves (small windows): lengths around the 32-row step, fewer steps than waves, every number of query
+heads per workgroup, carried tails that end inside a key block, segments that are no multiple of a
+block, packed batches with empty and one-token sequences, and enough key blocks for the four-wave
+dK/dV form.  The oracle is the judge; bars as in test_gpu_backward.py."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2605_11744_amd as sa
+import workloads as W
+from gpu_util import config_of, dev_bf16, to_f64
+from oracle import segattn_oracle as orc
+from test_gpu_backward import assert_grad_parity, run_backward
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D,g", [(64, 1), (64, 2), (64, 4), (128, 1), (128, 3), (128, 4)])
+@pytest.mark.parametrize("n,S,T", [(1, 64, 8), (33, 32, 32), (65, 40, 33), (255, 256, 0), (300, 128, 31), (411, 200, 100)])
+def test_small_windows(n, S, T, D, g):
+    w = W.small("bws", index=850 + n % 40, seq_len=n, seg_len=S, tail_len=T, n_q_heads=2 * g, n_kv_heads=2, head_dim=D,
+                kv_policy=[1, 3 if n % 2 else 2], batch=2 if n < 100 else 1)
+    q, k, v = W.prefill_inputs(w)
+    go = W.grad_inputs(w)
+    ref = orc.attend_backward(q, k, v, go, seg_len=S, tail_len=T, kv_policy=w.kv_policy)
+    assert_grad_parity(run_backward(w, q, k, v, go, fp32_check=False), ref, fp32_check=False, what=f"n={n}")
+
+
+@pytest.mark.parametrize("D,Hkv,g,S,T,lens", [
+    (64, 2, 4, 64, 16, (0, 1, 150, 33, 0, 64, 129)),
+    (128, 2, 2, 100, 100, (257, 3, 96)),
+    (128, 2, 4, 96, 32, (1,) * 70 + (200,)),
+    (64, 16, 1, 64, 16, (130, 31, 32, 33, 95, 96, 97, 200) * 2),   # over 768 key blocks: the four-wave form
+    (64, 8, 1, 32, 7, (64,) * 60),
+])
+def test_packed_small_windows(D, Hkv, g, S, T, lens):
+    total = sum(lens)
+    w = W.small("bwsp", index=890 + len(lens) % 50, seq_len=total, seg_len=S, tail_len=T, n_q_heads=Hkv * g, n_kv_heads=Hkv,
+                head_dim=D, kv_policy=[(3, 1, 0, 2)[h % 4] for h in range(Hkv)])
+    q, k, v = W.prefill_inputs(w)
+    go = W.grad_inputs(w)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    cfg = config_of(w, out_fp32=True, batch=len(lens))
+    qd, kd, vd, gd, cud = dev_bf16(q[0]), dev_bf16(k[0]), dev_bf16(v[0]), dev_bf16(go[0]), torch.from_numpy(cu).cuda()
+    nan = lambda *shape: torch.full(shape, float("nan"), dtype=torch.float32, device="cuda")
+    out, lse, dq, dk, dv = nan(total, Hkv * g, D), nan(Hkv * g, total), nan(total, Hkv * g, D), nan(total, Hkv, D), nan(total, Hkv, D)
+    nws = sa.seg_attn_bwd_varlen_workspace_bytes(cfg, total)
+    ws = torch.empty(nws, dtype=torch.uint8, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    sa.seg_attn_fwd_varlen(cfg, qd, kd, vd, cud, total, max(lens), out, lse, st)
+    sa.seg_attn_bwd_varlen(cfg, qd, kd, vd, out, lse, gd, cud, total, max(lens), dq, dk, dv, ws, nws, st)
+    torch.cuda.synchronize()
+    ref = orc.attend_backward_packed(q[0], k[0], v[0], go[0], cu, seg_len=S, tail_len=T, kv_policy=w.kv_policy)
+    assert_grad_parity((to_f64(dq), to_f64(dk), to_f64(dv)), ref, fp32_check=False, what=str(lens[:8]))
