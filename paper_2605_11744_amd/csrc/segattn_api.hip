@@ -878,7 +878,7 @@ segattn_status seg_attn_decode(segattn_ctx *ctx, const void *q, const void *k_ne
   if (!ctx || !q || !k_new || !v_new || !out || !lse) return SEGATTN_EINVAL;
   if (!ctx->ready) return SEGATTN_ESTATE;
   const Problem &p = ctx->p;
-  long long total_rows = 0;
+  long long total_rows = 0, chunks = 0;
   bool any_full = false;
   for (int b = 0; b < p.B; ++b) {
     for (int h = 0; h < p.Hkv; ++h) {
@@ -891,6 +891,7 @@ segattn_status seg_attn_decode(segattn_ctx *ctx, const void *q, const void *k_ne
         win = ((p.policy[h] & SEGATTN_TAIL) ? ctx->tail[b] : 0) + ctx->fill[b] + 1;
       }
       total_rows += win;
+      chunks += (win + ctx->g.decode_chunk - 1) / ctx->g.decode_chunk;
     }
     any_full |= ctx->fill[b] + 1 == p.S;
   }
@@ -902,7 +903,7 @@ segattn_status seg_attn_decode(segattn_ctx *ctx, const void *q, const void *k_ne
   ca.cache = ctx->cache;
   ca.geom = ctx->g;
   ca.m = 1;
-  if (launch_cache_decode_append(p, ca, st) != hipSuccess) return hip_failed(ctx);
+  if (!decode_appends(p) && launch_cache_decode_append(p, ca, st) != hipSuccess) return hip_failed(ctx);
   DecodeArgs da;
   memset(&da, 0, sizeof(da));
   da.q = (const unsigned short *)q;
@@ -913,6 +914,7 @@ segattn_status seg_attn_decode(segattn_ctx *ctx, const void *q, const void *k_ne
   da.cache = ctx->cache;
   da.geom = ctx->g;
   da.total_rows = total_rows;
+  da.chunks = chunks;
   if (launch_decode(p, da, p.B, st) != hipSuccess) return hip_failed(ctx);
   if (any_full && launch_cache_close(p, ctx->cache, ctx->g, 0, st) != hipSuccess) return hip_failed(ctx);
   for (int b = 0; b < p.B; ++b) {

@@ -83,12 +83,9 @@ __global__ __launch_bounds__(256, GH == 8 ? 2 : SEGATTN_DECODE_WAVES) void decod
 
   // ---- where this workgroup's slice [start, start + rows_per_wg) of the concatenated windows begins
   const int n_win = p.B * p.Hkv;
-  const long long start = (long long)blockIdx.x * a.rows_per_wg;
-  int w, off;
-  decode_slice_start(p, a, start, w, off);
+  int w, off, split;  // split: this workgroup's number among those that touch window w (windows it enters later start in it)
+  decode_slice_start(p, a, w, off, split);
   if (w < 0) return;  // the slices before this one cover every row
-  // this workgroup's ordinal among those that touch window w (windows it enters later start in it)
-  int split = (int)((long long)blockIdx.x - (start - off) / a.rows_per_wg);
   int remaining = a.rows_per_wg;
   int *counts = ws_counts(a.cache, a.geom);
   float *slots = ws_slots(a.cache, a.geom, p);
@@ -102,7 +99,7 @@ __global__ __launch_bounds__(256, GH == 8 ? 2 : SEGATTN_DECODE_WAVES) void decod
     const int c0 = lo + off;
     const int c1 = min(hi, c0 + remaining);
     if (c1 <= c0) continue;
-    remaining -= c1 - c0;
+    remaining = a.per_window ? 0 : remaining - (c1 - c0);
     const int head0 = kv * p.g + head_pass * GH;
     // heads of the group this pass covers; with a group size that is no multiple of GH the last
     // pass computes surplus heads on a repeated query row and drops them
@@ -283,6 +280,8 @@ template <int D>
 __global__ __launch_bounds__(256) void decode_combine_kernel(const Problem p, const DecodeArgs a) {
   const int b = blockIdx.x / p.Hq, head = blockIdx.x % p.Hq;
   const int kv = head / p.g;
+  if (a.pending && head % p.g == 0 && threadIdx.x == 0)  // the appended row counts from now on (nobody reads the counter here)
+    ((int *)(a.cache + a.geom.meta_off))[((long long)b * p.Hkv + kv) * kMetaInts + META_FILL] += 1;
   const int ns = ws_counts(a.cache, a.geom)[b * p.Hkv + kv];
   const float *ws = ws_slots(a.cache, a.geom, p) + ws_slot_base(p, a.geom, b, head) * ws_slot_floats(D);
   constexpr int SF = D + kWsTailFloats;
@@ -351,19 +350,32 @@ static hipError_t launch_split_gh(const Problem &p, DecodeArgs a, hipStream_t st
   return hipGetLastError();
 }
 
+// The matrix-core form appends the newest row itself; in front of the other one the caller has to.
+bool decode_appends(const Problem &p) { return !p.fp32_math && p.g >= SEGATTN_DECODE_MFMA_MIN_G; }
+
 template <int D, bool EXACT>
 static hipError_t launch_split(const Problem &p, const DecodeArgs &a, hipStream_t st) {
   if (a.total_rows < 1) return hipErrorInvalidValue;
-  if (!EXACT && p.g >= SEGATTN_DECODE_MFMA_MIN_G) {  // larger groups: the matrix-core form (segattn_decode_mfma.hip)
+  if (decode_appends(p)) {  // the matrix-core form (segattn_decode_mfma.hip)
     const int resident = decode_mfma_resident(D);
     if (resident == 0) return hipErrorUnknown;
     DecodeArgs a2 = a;
-    long long per = (a.total_rows + resident - 1) / resident;
-    if (per < a.geom.decode_chunk) per = a.geom.decode_chunk;
-    per = (per + 127) / 128 * 128;
-    if (per > 0x7fffff00LL) return hipErrorInvalidValue;
+    a2.pending = 1;
+    // Few rows: slices of the shortest length the workspace is made for, every window cut by itself.  A
+    // workgroup that goes on into a second window adds its latencies (merge, counters, first tile: 7 of
+    // then 18 us) to the step; with long slices that is little beside the even split it buys.
+    long long per = a.geom.decode_chunk, blocks = a.chunks;
+    if (blocks <= resident) {
+      a2.per_window = 1;
+    } else {
+      per = (a.total_rows + resident - 1) / resident;
+      if (per < a.geom.decode_chunk) per = a.geom.decode_chunk;
+      per = (per + 127) / 128 * 128;
+      if (per > 0x7fffff00LL) return hipErrorInvalidValue;
+      blocks = (a.total_rows + per - 1) / per;
+    }
     a2.rows_per_wg = (int)per;
-    const hipError_t e = launch_decode_split_mfma(p, a2, (a.total_rows + per - 1) / per, st);
+    const hipError_t e = launch_decode_split_mfma(p, a2, blocks, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(decode_combine_kernel<D>, dim3(p.B * p.Hq), dim3(256), 0, st, p, a2);
     return hipGetLastError();

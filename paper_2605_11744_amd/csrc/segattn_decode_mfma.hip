@@ -11,9 +11,13 @@
 // dot-product-and-reduce pass per row and head: a group of eight heads runs as fast as a group
 // of one (the vector-ALU form in segattn_decode.hip needs ~150 instructions per row and lane
 // group for eight heads and is bound by them).  Same slices of the concatenated windows, same
-// partials (acc[D], m, l) and the same combine kernel as that form.  A wave owns every fourth tile
-// of the slice; tiles go HBM -> registers (one tile ahead) -> a wave-private LDS tile with the
+// partials (acc[D], m, l) and the same combine kernel as that form.  A wave owns every fourth
+// tile of the slice; tiles go HBM -> registers (one tile ahead) -> a wave-private LDS tile with the
 // prefill kernel's chunk swizzles -> operands, so the loop needs no barrier.
+//
+// The newest row comes straight from k_new / v_new: the workgroup that holds a window's last rows reads it
+// there and writes it into the cache (a launch of its own for the 512 rows of a 64-sequence step cost
+// 3 to 5 us of every token).
 #include "segattn_decode_slices.h"
 
 namespace segattn {
@@ -57,17 +61,16 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(const Problem
   const int i16 = lane & 15, g16 = (lane >> 4) & 1;
   const float c = p.scale_log2e;
 
-  // [K tile | V tile] per wave; the merge of the four waves at the end of a window reuses it
-  __shared__ __attribute__((aligned(1024))) unsigned char tiles[4][2 * kTileBytes];
-  static_assert(4 * 2 * kTileBytes >= (int)sizeof(float) * 4 * kDecHeads * (D + 2), "merge area fits the tiles");
+  // [K tile | V tile] per wave; the merge of the waves at the end of a window reuses it
+  constexpr int NW = 4;
+  __shared__ __attribute__((aligned(1024))) unsigned char tiles[NW][2 * kTileBytes];
+  static_assert(NW * 2 * kTileBytes >= (int)sizeof(float) * NW * kDecHeads * (D + 2), "merge area fits the tiles");
 
   // ---- where this workgroup's slice begins
   const int n_win = p.B * p.Hkv;
-  const long long start = (long long)blockIdx.x * a.rows_per_wg;
-  int w, off;
-  decode_slice_start(p, a, start, w, off);
+  int w, off, split;  // split: this workgroup's number among those of the window
+  decode_slice_start(p, a, w, off, split);
   if (w < 0) return;
-  int split = (int)((long long)blockIdx.x - (start - off) / a.rows_per_wg);
   int remaining = a.rows_per_wg;
   int *counts = ws_counts(a.cache, a.geom);
   float *slots = ws_slots(a.cache, a.geom, p);
@@ -104,7 +107,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(const Problem
     const int c0 = lo + off;
     const int c1 = min(hi_, c0 + remaining);
     if (c1 <= c0) continue;
-    remaining -= c1 - c0;
+    remaining = a.per_window ? 0 : remaining - (c1 - c0);
     const int head0 = kv * p.g + head_pass * kDecHeads;
     const int live = min(kDecHeads, p.g - head_pass * kDecHeads);
 
@@ -129,6 +132,13 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(const Problem
     const unsigned char *kb = a.cache + attn_k_off(p, a.geom, b, kv);
     const unsigned char *vb = a.cache + attn_v_off(p, a.geom, b, kv);
     u32x4 nk[NL], nv[NL];  // the wave's next tile, in flight
+    // The newest row, if this slice ends with it: a 16-byte piece in each of the first 2 kChunks lanes of every
+    // wave (K, then V).  Its place in the cache is read with the others and replaced in the LDS tile.
+    const bool appends = a.pending && c1 == hi_;
+    const int piece = lane % kChunks, is_v = (lane / kChunks) & 1;
+    u32x4 newest = {0u, 0u, 0u, 0u};
+    if (appends && lane < 2 * kChunks)
+      newest = *(const u32x4 *)((const unsigned char *)(is_v ? a.v_new : a.k_new) + ((long long)b * p.Hkv + kv) * kRowBytes + piece * 16);
     auto fetch = [&](int r0) __attribute__((always_inline)) {
 #pragma unroll
       for (int i = 0; i < NL; ++i) {
@@ -141,13 +151,27 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(const Problem
     };
     const int first = c0 + kDecTile * wave;
     if (first < c1) fetch(first);
-    for (int r0 = first; r0 < c1; r0 += 4 * kDecTile) {
+    if (appends && head_pass == 0 && tid < 2 * kChunks) {  // append it (and its mirror in the attention view)
+      const int *meta = meta_ro(a.cache, a.geom, p, b, kv);
+      const long long row = ((p.policy[kv] & SEGATTN_PAST) ? meta[META_POOL] : p.T) + meta[META_FILL];
+      *(u32x4 *)(a.cache + (is_v ? v_block_off(p, a.geom, b, kv) : k_block_off(p, a.geom, b, kv)) + row * kRowBytes + piece * 16) = newest;
+      if (uses_view(p, a.geom, kv))
+        *(u32x4 *)((unsigned char *)(is_v ? vb : kb) + (long long)(c1 - 1) * kRowBytes + piece * 16) = newest;
+    }
+    for (int r0 = first; r0 < c1; r0 += NW * kDecTile) {
 #pragma unroll
       for (int i = 0; i < NL; ++i) {
         *(u32x4 *)(tile + st_k[i]) = nk[i];
         *(u32x4 *)(tile + st_v[i]) = nv[i];
       }
-      if (r0 + 4 * kDecTile < c1) fetch(r0 + 4 * kDecTile);
+      if (appends && r0 + kDecTile >= c1) {
+        // (the rows behind it too: they repeat what is in its place in the cache, which may be anything, and
+        // their weight of 0 does not take a NaN away)
+        for (int r = c1 - 1 - r0; r < kDecTile; ++r)
+          if (lane < 2 * kChunks)
+            *(u32x4 *)(tile + (is_v ? kTileBytes : 0) + r * kRowBytes + ((piece ^ (is_v ? swz_v(r) : swz_k(r))) << 4)) = newest;
+      }
+      if (r0 + NW * kDecTile < c1) fetch(r0 + NW * kDecTile);
       // S^T
       f32x16 S = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -206,7 +230,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(const Problem
     // the row sum of a head is split over the two half-waves (keys 4 hi + ...): add them up
     l_run = dec_half_sum(l_run);
 
-    // ---- this window's partial: the four waves meet in LDS (over the tiles: everyone is done)
+    // ---- this window's partial: the waves meet in LDS (over the tiles: everyone is done)
     __syncthreads();
     float *mg = (float *)&tiles[0][0];  // [wave][head][D + 2]: acc, then m, l
     if (col < live) {
@@ -223,15 +247,15 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(const Problem
       }
     }
     __syncthreads();
-    for (int idx = tid; idx < live * (D / 4); idx += 256) {
+    for (int idx = tid; idx < live * (D / 4); idx += 64 * NW) {
       const int h = idx / (D / 4), d = (idx % (D / 4)) * 4;
       float mx = -INFINITY;
 #pragma unroll
-      for (int wv = 0; wv < 4; ++wv) mx = fmaxf(mx, mg[((long long)wv * kDecHeads + h) * (D + 2) + D]);
+      for (int wv = 0; wv < NW; ++wv) mx = fmaxf(mx, mg[((long long)wv * kDecHeads + h) * (D + 2) + D]);
       float l = 0.f;
       f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int wv = 0; wv < 4; ++wv) {
+      for (int wv = 0; wv < NW; ++wv) {
         const float *src = mg + ((long long)wv * kDecHeads + h) * (D + 2);
         const float wgt = (src[D] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((src[D] - mx) * c);
         l += src[D + 1] * wgt;

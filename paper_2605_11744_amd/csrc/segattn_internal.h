@@ -267,7 +267,10 @@ struct DecodeArgs {
   unsigned char *cache;
   CacheGeom geom;
   long long total_rows;  // visible rows summed over every (sequence, KV head) window
+  long long chunks;      // slices of geom.decode_chunk rows, every window cut by itself
   int rows_per_wg;       // rows per workgroup of the split kernel (>= geom.decode_chunk); set by the launcher
+  int per_window;        // 1: every window is cut into slices of its own (a workgroup never goes on into the next window)
+  int pending;           // 1: the newest row is still to be appended: the split kernel does it, the combine kernel counts it
 };
 
 struct CopyArgs {
@@ -489,6 +492,7 @@ __host__ __device__ inline unsigned long long part_ws_bytes(const Problem &p, in
 }
 hipError_t launch_prefill_keysplit(const Problem &p, const PrefillArgs &a, int heads_per_wg, long long grid, hipStream_t st);
 hipError_t launch_decode(const Problem &p, const DecodeArgs &a, int B, hipStream_t st);
+bool decode_appends(const Problem &p);  // launch_decode also appends the newest row and counts it
 int decode_mfma_resident(int D);  // workgroups of the matrix-core split kernel the chip holds at once (0: error)
 hipError_t launch_decode_split_mfma(const Problem &p, const DecodeArgs &a, long long blocks, hipStream_t st);
 hipError_t launch_cache_reset(const Problem &p, unsigned char *cache, const CacheGeom &g, hipStream_t st);
