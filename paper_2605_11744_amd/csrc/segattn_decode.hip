@@ -273,54 +273,87 @@ __global__ __launch_bounds__(256, GH == 8 ? 2 : SEGATTN_DECODE_WAVES) void decod
   }
 }
 
-// One workgroup per (b, query head).  All threads find the global maximum over the splits; then
-// wave w accumulates the splits congruent to w mod 4 (lanes over the D outputs) and the four
-// partial sums meet in LDS.
-template <int D>
+// One workgroup per (b, query head): wave w merges the partials w, w + 4, ... (lanes over the D outputs),
+// kBatch of them per memory round trip, under a running maximum of its own; the four results meet in
+// LDS.  Bound by latency where every window is cut by itself (a.per_window, dozens of partials, few
+// windows): kAhead reads the first batch while the number of partials is still on its way (a slot
+// beyond it holds anything and is given weight 0), so the chain is one round trip for up to 48 partials
+// (a maximum over all partials first, then their rows four at a time, made it five: 4.7 -> 3.9 us).  With
+// long slices a window has two or three partials and 2048 workgroups would read 60 MB for nothing
+// (6.0 -> 9.3 us): small batches there, after the count.
+template <int D, int kBatch, bool kAhead>
 __global__ __launch_bounds__(256) void decode_combine_kernel(const Problem p, const DecodeArgs a) {
   const int b = blockIdx.x / p.Hq, head = blockIdx.x % p.Hq;
   const int kv = head / p.g;
   if (a.pending && head % p.g == 0 && threadIdx.x == 0)  // the appended row counts from now on (nobody reads the counter here)
     ((int *)(a.cache + a.geom.meta_off))[((long long)b * p.Hkv + kv) * kMetaInts + META_FILL] += 1;
+  const int slots = (p.policy[kv] & SEGATTN_PAST) ? a.geom.ws_splits_past : a.geom.ws_splits_other;
   const int ns = ws_counts(a.cache, a.geom)[b * p.Hkv + kv];
   const float *ws = ws_slots(a.cache, a.geom, p) + ws_slot_base(p, a.geom, b, head) * ws_slot_floats(D);
-  constexpr int SF = D + kWsTailFloats;
+  constexpr int SF = D + kWsTailFloats, DPL = D / 64;
+  typedef float f32xd __attribute__((ext_vector_type(DPL)));
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const float c = p.scale_log2e;
-  constexpr int DPL = D / 64;
-  __shared__ float sm_max[4], sm_l[4], sm_o[4][D];
+  __shared__ float sm_m[4], sm_l[4], sm_o[4][D];
 
-  float mx = -INFINITY;
-  for (int s = tid; s < ns; s += 256) mx = fmaxf(mx, ws[(long long)s * SF + D]);
+  float mx = -INFINITY, l = 0.f;
+  f32xd o = {};
+  const int last = kAhead ? slots - 1 : ns - 1;  // reads stay inside the head's slots
+  for (int s0 = wave; (kAhead && s0 == wave) || s0 < ns; s0 += 4 * kBatch) {
+    f32x2 ml[kBatch];
+    f32xd x[kBatch];
 #pragma unroll
-  for (int sh = 1; sh < 64; sh <<= 1) mx = fmaxf(mx, __shfl_xor(mx, sh));
-  if (lane == 0) sm_max[wave] = mx;
-  __syncthreads();
-  mx = fmaxf(fmaxf(sm_max[0], sm_max[1]), fmaxf(sm_max[2], sm_max[3]));
-
-  float l = 0.f, o[DPL];
+    for (int i = 0; i < kBatch; ++i) {
+      const int s = s0 + 4 * i < last ? s0 + 4 * i : last;
+      ml[i] = *(const f32x2 *)(ws + (long long)s * SF + D);
+      x[i] = *(const f32xd *)(ws + (long long)s * SF + lane * DPL);
+    }
+    float m_new = mx;
 #pragma unroll
-  for (int e = 0; e < DPL; ++e) o[e] = 0.f;
-#pragma unroll 4
-  for (int s = wave; s < ns; s += 4) {
-    const float *slot = ws + (long long)s * SF;
-    const float wgt = __builtin_amdgcn_exp2f((slot[D] - mx) * c);
-    l = fmaf(slot[D + 1], wgt, l);
+    for (int i = 0; i < kBatch; ++i) m_new = s0 + 4 * i < ns ? fmaxf(m_new, ml[i][0]) : m_new;
+    if (m_new == -INFINITY) continue;  // this wave has no partial (yet)
+    const float alpha = __builtin_amdgcn_exp2f((mx - m_new) * c);  // 0 the first time
+    mx = m_new;
+    l *= alpha;
+    o *= alpha;
 #pragma unroll
-    for (int e = 0; e < DPL; ++e) o[e] = fmaf(slot[lane * DPL + e], wgt, o[e]);
+    for (int i = 0; i < kBatch; ++i) {
+      const bool live = s0 + 4 * i < ns;
+      const float wgt = live ? __builtin_amdgcn_exp2f((ml[i][0] - mx) * c) : 0.f;
+      l = live ? fmaf(ml[i][1], wgt, l) : l;
+#pragma unroll
+      for (int e = 0; e < DPL; ++e) o[e] = live ? fmaf(x[i][e], wgt, o[e]) : o[e];
+    }
   }
-  if (lane == 0) sm_l[wave] = l;
+  if (lane == 0) {
+    sm_m[wave] = mx;
+    sm_l[wave] = l;
+  }
 #pragma unroll
   for (int e = 0; e < DPL; ++e) sm_o[wave][lane * DPL + e] = o[e];
   __syncthreads();
   if (tid >= D) return;
-  l = (sm_l[0] + sm_l[1]) + (sm_l[2] + sm_l[3]);
-  const float od = (sm_o[0][tid] + sm_o[1][tid]) + (sm_o[2][tid] + sm_o[3][tid]);
+  const float top = fmaxf(fmaxf(sm_m[0], sm_m[1]), fmaxf(sm_m[2], sm_m[3]));
+  l = 0.f;
+  float od = 0.f;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const float wgt = __builtin_amdgcn_exp2f((sm_m[w] - top) * c);  // 0 for a wave without partials
+    l = fmaf(sm_l[w], wgt, l);
+    od = fmaf(sm_o[w][tid], wgt, od);
+  }
   const float r = od / l;
   const long long oidx = ((long long)b * p.Hq + head) * D + tid;
   if (p.out_fp32) ((float *)a.out)[oidx] = r;
   else ((__bf16 *)a.out)[oidx] = (__bf16)r;
-  if (tid == 0) a.lse[(long long)b * p.Hq + head] = mx * p.scale + __logf(l);
+  if (tid == 0) a.lse[(long long)b * p.Hq + head] = top * p.scale + __logf(l);
+}
+
+template <int D>
+static hipError_t launch_combine(const Problem &p, const DecodeArgs &a, hipStream_t st) {
+  if (a.per_window) hipLaunchKernelGGL((decode_combine_kernel<D, 12, true>), dim3(p.B * p.Hq), dim3(256), 0, st, p, a);
+  else hipLaunchKernelGGL((decode_combine_kernel<D, 2, false>), dim3(p.B * p.Hq), dim3(256), 0, st, p, a);
+  return hipGetLastError();
 }
 
 // Workgroups of the split kernel the chip holds at once (per instantiation, asked once).
@@ -346,8 +379,7 @@ static hipError_t launch_split_gh(const Problem &p, DecodeArgs a, hipStream_t st
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(decode_combine_kernel<D>, dim3(p.B * p.Hq), dim3(256), 0, st, p, a);
-  return hipGetLastError();
+  return launch_combine<D>(p, a, st);
 }
 
 // The matrix-core form appends the newest row itself; in front of the other one the caller has to.
@@ -377,8 +409,7 @@ static hipError_t launch_split(const Problem &p, const DecodeArgs &a, hipStream_
     a2.rows_per_wg = (int)per;
     const hipError_t e = launch_decode_split_mfma(p, a2, blocks, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(decode_combine_kernel<D>, dim3(p.B * p.Hq), dim3(256), 0, st, p, a2);
-    return hipGetLastError();
+    return launch_combine<D>(p, a2, st);
   }
   // heads per pass: the smallest of 1, 2, 4, 8 that covers the group (8 for larger groups)
   if (p.g > 4) return launch_split_gh<D, 8, EXACT>(p, a, st);

@@ -64,7 +64,8 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(const Problem
   // [K tile | V tile] per wave; the merge of the waves at the end of a window reuses it
   constexpr int NW = 4;
   __shared__ __attribute__((aligned(1024))) unsigned char tiles[NW][2 * kTileBytes];
-  static_assert(NW * 2 * kTileBytes >= (int)sizeof(float) * NW * kDecHeads * (D + 2), "merge area fits the tiles");
+  constexpr int MS = D + 4;  // floats per head of the merge area: acc, then m, l; 16-byte pieces, columns on different banks
+  static_assert(NW * 2 * kTileBytes >= (int)sizeof(float) * NW * kDecHeads * MS, "merge area fits the tiles");
 
   // ---- where this workgroup's slice begins
   const int n_win = p.B * p.Hkv;
@@ -232,15 +233,14 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(const Problem
 
     // ---- this window's partial: the waves meet in LDS (over the tiles: everyone is done)
     __syncthreads();
-    float *mg = (float *)&tiles[0][0];  // [wave][head][D + 2]: acc, then m, l
+    float *mg = (float *)&tiles[0][0];  // [wave][head][MS]
     if (col < live) {
-      float *dst = mg + ((long long)wave * kDecHeads + col) * (D + 2);
+      float *dst = mg + (wave * kDecHeads + col) * MS;
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
         for (int g4 = 0; g4 < 4; ++g4)
-#pragma unroll
-          for (int x = 0; x < 4; ++x) dst[32 * nb + 8 * g4 + 4 * hi + x] = O[nb][4 * g4 + x];
+          *(f32x4 *)(dst + 32 * nb + 8 * g4 + 4 * hi) = f32x4{O[nb][4 * g4], O[nb][4 * g4 + 1], O[nb][4 * g4 + 2], O[nb][4 * g4 + 3]};
       if (hi == 0) {
         dst[D] = m_run;
         dst[D + 1] = l_run;
@@ -251,16 +251,17 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(const Problem
       const int h = idx / (D / 4), d = (idx % (D / 4)) * 4;
       float mx = -INFINITY;
 #pragma unroll
-      for (int wv = 0; wv < NW; ++wv) mx = fmaxf(mx, mg[((long long)wv * kDecHeads + h) * (D + 2) + D]);
+      for (int wv = 0; wv < NW; ++wv) mx = fmaxf(mx, mg[(wv * kDecHeads + h) * MS + D]);
       float l = 0.f;
       f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int wv = 0; wv < NW; ++wv) {
-        const float *src = mg + ((long long)wv * kDecHeads + h) * (D + 2);
+        const float *src = mg + (wv * kDecHeads + h) * MS;
         const float wgt = (src[D] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((src[D] - mx) * c);
         l += src[D + 1] * wgt;
+        const f32x4 part = *(const f32x4 *)(src + d);
 #pragma unroll
-        for (int x = 0; x < 4; ++x) o[x] += src[d + x] * wgt;
+        for (int x = 0; x < 4; ++x) o[x] += part[x] * wgt;
       }
       float *slot = slots + (ws_slot_base(p, a.geom, b, head0 + h) + split) * ws_slot_floats(D);
       *(f32x4 *)(slot + d) = o;
