@@ -547,6 +547,10 @@ segattn_status seg_kv_past_select(segattn_ctx *ctx, const int32_t *idx, int32_t 
 
 namespace {
 constexpr int kRetrieveCand = 32;
+// Workspace with 8 bytes per candidate behind `off`, in two aligned halves (callers keep the size they know).
+unsigned long long retrieval_total(unsigned long long off, unsigned long long lists) {
+  return align_up(align_up(off + lists * kRetrieveCand * 4ull) + lists * kRetrieveCand * 4ull);
+}
 // Pool rows per scoring workgroup.  4096 where that still fills the chip four times over (3
 // workgroups per CU); else 1024 -- a last, partly filled round of 1 MB workgroups costs more than
 // the extra per-chunk selections; and 512 where even 1024-row chunks are fewer than the CUs (one
@@ -574,7 +578,7 @@ int retrieve_chunk_rows(const segattn_ctx *ctx) {
   return kRetrieveChunkSmall;
 }
 bool retrieval_layout(const segattn_ctx *ctx, const segattn_retrieval *r, int &nsp, int &n_chunks,
-                      unsigned long long &off_val, unsigned long long &off_idx, unsigned long long &total) {
+                      unsigned long long &off_cand, unsigned long long &total) {
   if (!ctx || !r || ctx->p.n_past == 0) return false;
   if (r->n_queries < 1 || r->pool_window < 1 || r->tail_avg < 1 || r->n_anchors < 1 || r->n_anchors > kRetrieveCand)
     return false;
@@ -585,25 +589,24 @@ bool retrieval_layout(const segattn_ctx *ctx, const segattn_retrieval *r, int &n
   nsp = (int)((n_sum * ctx->p.g + 31) / 32 * 32);
   n_chunks = (int)((ctx->g.pool_cap + kRetrieveChunkTiny - 1) / kRetrieveChunkTiny);  // the most a call can use
   const unsigned long long heads = (unsigned long long)ctx->p.B * ctx->p.n_past;
-  off_val = align_up(heads * nsp * ctx->p.D * 2ull);
-  off_idx = align_up(off_val + heads * n_chunks * kRetrieveCand * 4ull);
-  total = align_up(off_idx + heads * n_chunks * kRetrieveCand * 4ull);
+  off_cand = align_up(heads * nsp * ctx->p.D * 2ull);
+  total = retrieval_total(off_cand, heads * n_chunks);
   return true;
 }
 }  // namespace
 
 size_t seg_kv_retrieve_workspace_bytes(const segattn_ctx *ctx, const segattn_retrieval *r) {
   int nsp, n_chunks;
-  unsigned long long a, b, total;
-  return retrieval_layout(ctx, r, nsp, n_chunks, a, b, total) ? (size_t)total : 0;
+  unsigned long long cand, total;
+  return retrieval_layout(ctx, r, nsp, n_chunks, cand, total) ? (size_t)total : 0;
 }
 
 segattn_status seg_kv_retrieve(segattn_ctx *ctx, const segattn_retrieval *r, const void *q_prev, int32_t m,
                                int32_t R, int32_t *idx_out, void *workspace, size_t workspace_bytes,
                                void *stream) {
   int nsp, n_chunks;
-  unsigned long long off_val, off_idx, total;
-  if (!retrieval_layout(ctx, r, nsp, n_chunks, off_val, off_idx, total)) return SEGATTN_EINVAL;
+  unsigned long long off_cand, total;
+  if (!retrieval_layout(ctx, r, nsp, n_chunks, off_cand, total)) return SEGATTN_EINVAL;
   if (!q_prev || !idx_out || !workspace || m < 1 || R < 1 || R > (1 << 20)) return SEGATTN_EINVAL;
   if (workspace_bytes < total || ((uintptr_t)workspace % kAlign)) return SEGATTN_EINVAL;
   if (!ctx->ready) return SEGATTN_ESTATE;
@@ -619,8 +622,7 @@ segattn_status seg_kv_retrieve(segattn_ctx *ctx, const segattn_retrieval *r, con
   a.cache = ctx->cache;
   a.geom = ctx->g;
   a.summaries = (unsigned short *)workspace;
-  a.cand_val = (float *)((unsigned char *)workspace + off_val);
-  a.cand_idx = (int *)((unsigned char *)workspace + off_idx);
+  a.cand = (unsigned long long *)((unsigned char *)workspace + off_cand);
   a.idx_out = idx_out;
   a.m = m;
   a.R = R;
@@ -657,7 +659,7 @@ bool build_retrieval_problem(const segattn_config *cfg, int64_t n, int32_t R, Pr
 }
 constexpr int kRetrieveSeqChunk = 1024;  // pool rows per scoring workgroup of the whole-prompt form
 bool retrieval_seq_layout(const Problem &p, const segattn_retrieval *r, int64_t n, int n_seg, int &nsp, int &n_chunks,
-                          unsigned long long &off_val, unsigned long long &off_idx, unsigned long long &total) {
+                          unsigned long long &off_cand, unsigned long long &total) {
   if (!r || r->n_queries < 1 || r->pool_window < 1 || r->tail_avg < 1 || r->n_anchors < 1 || r->n_anchors > kRetrieveCand)
     return false;
   if (r->win_before < 0 || r->win_after < 0 || r->win_before > (1 << 20) || r->win_after > (1 << 20)) return false;
@@ -669,9 +671,8 @@ bool retrieval_seq_layout(const Problem &p, const segattn_retrieval *r, int64_t 
   n_chunks = (int)((longest + kRetrieveSeqChunk - 1) / kRetrieveSeqChunk);
   if (n_chunks < 1) n_chunks = 1;
   const unsigned long long heads = (unsigned long long)p.B * n_seg * p.n_past;
-  off_val = align_up(heads * nsp * p.D * 2ull);
-  off_idx = align_up(off_val + heads * n_chunks * kRetrieveCand * 4ull);
-  total = align_up(off_idx + heads * n_chunks * kRetrieveCand * 4ull);
+  off_cand = align_up(heads * nsp * p.D * 2ull);
+  total = retrieval_total(off_cand, heads * n_chunks);
   return true;
 }
 }  // namespace
@@ -679,8 +680,8 @@ bool retrieval_seq_layout(const Problem &p, const segattn_retrieval *r, int64_t 
 size_t seg_kv_retrieve_seq_workspace_bytes(const segattn_config *cfg, const segattn_retrieval *r, int64_t n) {
   Problem p;
   int n_seg, nsp, n_chunks;
-  unsigned long long a, b, total;
-  if (!build_retrieval_problem(cfg, n, 1, p, n_seg) || !retrieval_seq_layout(p, r, n, n_seg, nsp, n_chunks, a, b, total))
+  unsigned long long cand, total;
+  if (!build_retrieval_problem(cfg, n, 1, p, n_seg) || !retrieval_seq_layout(p, r, n, n_seg, nsp, n_chunks, cand, total))
     return 0;
   return (size_t)total;
 }
@@ -690,9 +691,9 @@ segattn_status seg_kv_retrieve_seq(const segattn_config *cfg, const segattn_retr
                                    void *stream) {
   Problem p;
   int n_seg, nsp, n_chunks;
-  unsigned long long off_val, off_idx, total;
+  unsigned long long off_cand, total;
   if (!build_retrieval_problem(cfg, n, R, p, n_seg) ||
-      !retrieval_seq_layout(p, r, n, n_seg, nsp, n_chunks, off_val, off_idx, total))
+      !retrieval_seq_layout(p, r, n, n_seg, nsp, n_chunks, off_cand, total))
     return SEGATTN_EINVAL;
   if (!q || !k || !idx_out || !workspace || workspace_bytes < total || ((uintptr_t)workspace % kAlign)) return SEGATTN_EINVAL;
   RetrieveArgs a;
@@ -702,8 +703,7 @@ segattn_status seg_kv_retrieve_seq(const segattn_config *cfg, const segattn_retr
   a.n_rows = (int)n;
   a.n_seg = n_seg;
   a.summaries = (unsigned short *)workspace;
-  a.cand_val = (float *)((unsigned char *)workspace + off_val);
-  a.cand_idx = (int *)((unsigned char *)workspace + off_idx);
+  a.cand = (unsigned long long *)((unsigned char *)workspace + off_cand);
   a.idx_out = idx_out;
   a.m = p.S;
   a.R = R;

@@ -360,8 +360,7 @@ struct RetrieveArgs {
   unsigned char *cache;
   CacheGeom geom;
   unsigned short *summaries;     // workspace: [B, n_past, nsp, D] bf16
-  float *cand_val;               // workspace: [B, n_past, n_chunks, 32]
-  int *cand_idx;                 // workspace: same shape
+  unsigned long long *cand;      // workspace: [B, n_past, n_chunks, 32] keys of a chunk's best rows, in order
   int *idx_out;                  // [B, n_past, R]
   int m, R, nsp, n_chunks, chunk_rows;
   int n_queries, pool_window, tail_avg, n_anchors, win_before, win_after;

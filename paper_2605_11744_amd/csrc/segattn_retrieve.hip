@@ -15,7 +15,11 @@
 //                        de-duplicate, keep the best" yields.)  Two levels: every chunk of 1024
 //                        or 4096 rows (small chunks when few heads have to fill the chip)
 //                        keeps its own best n_anchors next to the scores in LDS -- scores never
-//                        go to HBM -- and one workgroup per head merges the candidates
+//                        go to HBM -- and one workgroup per head merges the candidates.  Both
+//                        levels place a row by counting the rows that are better (64-bit keys from
+//                        LDS, no chain of rounds): of the 256 threads' best rows those that at
+//                        least n_anchors others beat rule out their threads, of the chunks' best
+//                        rows likewise their chunks, and what is left is counted once more
 //   window expansion     anchors in descending score order add rows a - win_before .. a + win_after
 //                        (clipped to the visible pool, ascending, rows already in skipped) until
 //                        R rows are in; then the earliest visible rows pad to R; sorted output
@@ -29,64 +33,27 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kMaxAnchors = 32;
 
-// (value, row) pairs ordered by value descending, then row ascending
-__device__ inline bool better(float v, int i, float w, int j) { return v > w || (v == w && i < j); }
-
-// Wave-wide best (value, row); every lane gets the result.  The four exchanges inside a row of 16
-// lanes are DPP moves (a register-to-register step of a few cycles each), the exchange between
-// rows one LDS-crossbar shuffle, the one between half-waves a lane swap: a third of the latency of
-// six crossbar shuffles, and this reduction sits inside loops of n_anchors rounds.
-__device__ inline void wave_best(float &v, int &i) {
-#define SEGATTN_BEST_STEP(CTRL)                                                                         \
-  do {                                                                                                \
-    const float w_ = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true)); \
-    const int j_ = __builtin_amdgcn_mov_dpp(i, CTRL, 0xF, 0xF, true);                                   \
-    if (better(w_, j_, v, i)) {                                                                       \
-      v = w_;                                                                                         \
-      i = j_;                                                                                         \
-    }                                                                                                 \
-  } while (0)
-  SEGATTN_BEST_STEP(0xB1);   // quad_perm [1,0,3,2]
-  SEGATTN_BEST_STEP(0x4E);   // quad_perm [2,3,0,1]
-  SEGATTN_BEST_STEP(0x141);  // row_half_mirror
-  SEGATTN_BEST_STEP(0x140);  // row_mirror: all 16 lanes of a row agree
-#undef SEGATTN_BEST_STEP
-  {
-    const float w = __shfl_xor(v, 16);
-    const int j = __shfl_xor(i, 16);
-    if (better(w, j, v, i)) {
-      v = w;
-      i = j;
-    }
-  }
-  {  // the two halves: one element of each pair is the lane's own value, the other its partner's
-    const auto sv = __builtin_amdgcn_permlane32_swap(__float_as_int(v), __float_as_int(v), false, false);
-    const auto si = __builtin_amdgcn_permlane32_swap(i, i, false, false);
-    const float v0 = __int_as_float(sv[0]), v1 = __int_as_float(sv[1]);
-    const bool second = better(v1, si[1], v0, si[0]);
-    v = second ? v1 : v0;
-    i = second ? si[1] : si[0];
-  }
+// (value, row) pairs ordered by value descending, then row ascending, as one number: the larger key is the
+// better row.  0: no row (an invisible row's -inf).
+__device__ inline unsigned long long row_key(float v, int row) {
+  if (v == -INFINITY) return 0ull;
+  const unsigned bits = __float_as_uint(v + 0.f);  // -0 and 0 are the same score
+  const unsigned up = bits ^ ((bits >> 31) ? 0xffffffffu : 0x80000000u);
+  return ((unsigned long long)up << 32) | (unsigned)~row;
 }
-
-// Workgroup-wide best (value, row); every thread gets the result.  sm: 2 * 4 words of LDS.
-__device__ inline void block_best(float &v, int &i, float *sm_v, int *sm_i) {
-  wave_best(v, i);
-  const int wave = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) {
-    sm_v[wave] = v;
-    sm_i[wave] = i;
+__device__ inline int key_row(unsigned long long key) { return (int)~(unsigned)key; }
+// Keys of list[0 .. n) (LDS, 16-byte aligned, n even) that are better than `key`; *some: those that are a row.
+__device__ inline int count_better(const unsigned long long *list, int n, unsigned long long key, int *some = nullptr) {
+  typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+  int better = 0, rows = 0;
+#pragma unroll 8
+  for (int i = 0; i < n; i += 2) {
+    const u64x2 two = *(const u64x2 *)(list + i);
+    better += (two[0] > key) + (two[1] > key);
+    if (some) rows += (two[0] != 0) + (two[1] != 0);
   }
-  __syncthreads();
-  v = sm_v[0];
-  i = sm_i[0];
-#pragma unroll
-  for (int w = 1; w < 4; ++w)
-    if (better(sm_v[w], sm_i[w], v, i)) {
-      v = sm_v[w];
-      i = sm_i[w];
-    }
+  if (some) *some = rows;
+  return better;
 }
 
 // ---- query summaries: [B, n_past, NSP, D] bf16, NSP = g * n_sum rounded up to 32 (the padding
@@ -152,13 +119,9 @@ __global__ __launch_bounds__(256) void retrieve_score_kernel(const Problem p, co
   const int pool = pv.pool, lo = pv.lo;
   const int c0 = blockIdx.x * kChunkRows;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, hi = lane >> 5, col = lane & 31;
-  float *cv = a.cand_val + (((long long)b * p.n_past + np) * a.n_chunks + blockIdx.x) * kMaxAnchors;
-  int *ci = a.cand_idx + (((long long)b * p.n_past + np) * a.n_chunks + blockIdx.x) * kMaxAnchors;
+  unsigned long long *cand = a.cand + (((long long)b * p.n_past + np) * a.n_chunks + blockIdx.x) * kMaxAnchors;
   if (c0 >= pool || c0 + kChunkRows <= lo) {  // nothing visible in this chunk
-    if (tid < kMaxAnchors) {
-      cv[tid] = -INFINITY;
-      ci[tid] = 0x7fffffff;
-    }
+    if (tid < kMaxAnchors) cand[tid] = 0ull;
     return;
   }
   const unsigned short *sg = a.summaries + ((long long)b * p.n_past + np) * a.nsp * D;
@@ -216,270 +179,159 @@ __global__ __launch_bounds__(256) void retrieve_score_kernel(const Problem p, co
     for (int i = 0; i < NL; ++i) cur[i] = nxt[i];
   }
   __syncthreads();
-  // The chunk's best n_anchors rows, in order.  Every thread owns kChunkRows/256 scores.  Each wave
-  // first finds the best n_anchors of its own quarter (rounds of a wave-wide arg-max by shuffles,
-  // the winner's owner retires it: no workgroup barrier), then the first wave merges the four
-  // sorted lists (lane w < 4 holds the head of list w).
-  float mine[kChunkRows / 256];
+  // The chunk's best n_anchors rows, in order.  A thread holds E scores; only threads whose best row fewer than
+  // n_anchors other threads' best rows beat can hold one of them, and their rows are ranked once more.
+  // (Rounds of a wave-wide arg-max and a merge of the four waves' lists took 10.5 us of a 512-row
+  // chunk's 21; the scan of four pools of 61K rows: 26.0 -> 19.6 us, of a 64K prompt: 85 -> 71.)
+  constexpr int E = kChunkRows / 256;
+  unsigned long long *const best_of = (unsigned long long *)&stage[0][0];  // [256], over the tiles
+  unsigned long long *const left = best_of + 256;                         // [n_anchors][E]
+  static_assert((256 + kMaxAnchors * E) * 8 <= 4 * 32 * 2 * D, "fits the tiles");
+  unsigned long long key[E], top = 0ull;
 #pragma unroll
-  for (int e = 0; e < kChunkRows / 256; ++e) mine[e] = sc[tid + 256 * e];
-  __shared__ float wl_v[4][kMaxAnchors];
-  __shared__ int wl_i[4][kMaxAnchors];
-  for (int r = 0; r < a.n_anchors; ++r) {
-    float bv = -INFINITY;
-    int bi = 0x7fffffff;
+  for (int e = 0; e < E; ++e) {
+    key[e] = row_key(sc[tid + 256 * e], c0 + tid + 256 * e);
+    top = key[e] > top ? key[e] : top;
+  }
+  best_of[tid] = top;
+  const int n_left = a.n_anchors * E;  // even: E is
+  for (int i = tid; i < n_left; i += 256) left[i] = 0ull;
+  __syncthreads();
+  const int place = count_better(best_of, 256, top);
+  if (top != 0ull && place < a.n_anchors) {
 #pragma unroll
-    for (int e = 0; e < kChunkRows / 256; ++e)
-      if (better(mine[e], c0 + tid + 256 * e, bv, bi)) {
-        bv = mine[e];
-        bi = c0 + tid + 256 * e;
-      }
-    float v = bv;
-    int i = bi;
-    wave_best(v, i);
-    if (lane == 0) {
-      wl_v[wave][r] = v;
-      wl_i[wave][r] = v == -INFINITY ? 0x7fffffff : i;
-    }
-    if (v != -INFINITY && bi == i) {  // this lane owns the winner
-      const int off = i - c0;
-#pragma unroll
-      for (int e = 0; e < kChunkRows / 256; ++e)
-        if (e == off / 256) mine[e] = -INFINITY;
-    }
+    for (int e = 0; e < E; ++e) left[place * E + e] = key[e];
   }
   __syncthreads();
-  if (tid < 64) {
-    int hp = 0;
-    const bool list = tid < 4 && a.n_anchors > 0;
-    float hv = list ? wl_v[tid][0] : -INFINITY;
-    int hr = list ? wl_i[tid][0] : 0x7fffffff;
-    for (int r = 0; r < a.n_anchors; ++r) {
-      float v = hv;
-      int i = hr;
-#pragma unroll
-      for (int sh = 2; sh >= 1; sh >>= 1) {  // the four heads sit in lanes 0..3
-        const float w = __shfl_xor(v, sh);
-        const int j = __shfl_xor(i, sh);
-        if (better(w, j, v, i)) {
-          v = w;
-          i = j;
-        }
-      }
-      v = __shfl(v, 0);
-      i = __shfl(i, 0);
-      if (tid == 0) {
-        cv[r] = v;
-        ci[r] = v == -INFINITY ? 0x7fffffff : i;
-      }
-      if (list && v != -INFINITY && hr == i) {
-        hp += 1;
-        const bool more = hp < a.n_anchors;
-        hv = more ? wl_v[tid][more ? hp : 0] : -INFINITY;
-        hr = more ? wl_i[tid][more ? hp : 0] : 0x7fffffff;
-      }
-    }
+  for (int i = tid; i < n_left; i += 256) {
+    int rows;
+    const unsigned long long mine = left[i];
+    const int rank = count_better(left, n_left, mine, &rows);
+    if (mine != 0ull && rank < a.n_anchors) cand[rank] = mine;
+    if (i < a.n_anchors && i >= rows) cand[i] = 0ull;
   }
 }
 
-// ---- merge the candidates of all chunks, expand, pad, emit.  One workgroup per (b, PAST head).
-// The chosen rows are kept as sorted, disjoint, merged row ranges, one per lane of wave 0 (at
-// most one range per anchor window plus the padding prefix); the expansion itself is sequential
-// in the anchors' score order, but every step on the range list is a constant number of
-// wave-wide operations (ballot to locate, shuffle to insert or delete).
-constexpr int kCandLds = 4096;  // candidates held in LDS; beyond that they are re-read from memory
+// ---- merge the candidates of all chunks, expand, pad, emit.  One workgroup per (b, PAST head); every step a
+// constant number of passes over all anchors at once (a merge of the chunks' lists in n_anchors rounds and
+// an expansion anchor by anchor on a sorted list of ranges took 15 us of 20; the kernel: 22.6 -> 10.8 us for 120 chunks a pool).
+constexpr int kMaxChunks = 2048;  // 2^20 pool rows in chunks of 512
 
 __global__ __launch_bounds__(256) void retrieve_select_kernel(const Problem p, const RetrieveArgs a) {
-  __shared__ float sm_v[4];
-  __shared__ int sm_i[4];
-  __shared__ int anchors[kMaxAnchors];
-  __shared__ float lc_v[kCandLds];
-  __shared__ int lc_i[kCandLds];
-  __shared__ int p_lo[64], p_before[65];
-  __shared__ int n_pieces;
+  __shared__ __attribute__((aligned(16))) unsigned long long heads[kMaxChunks];  // best candidate of every chunk
+  __shared__ __attribute__((aligned(16))) unsigned long long cand[kMaxAnchors * (kMaxAnchors + 1) / 2 + 2];
+  __shared__ int src[kMaxAnchors], anchors[kMaxAnchors];
+  __shared__ int q_lo[kMaxAnchors], q_len[kMaxAnchors];
+  __shared__ int p_lo[2 * kMaxAnchors + 2], p_before[2 * kMaxAnchors + 2];
+  __shared__ int n_found, n_pieces;
   const int b = blockIdx.x / p.n_past, np = blockIdx.x % p.n_past;
   const int kv = p.order[np];
   const PoolView pv = pool_view(p, a, b, kv);
   const int pool = pv.pool, lo = pv.lo;
-  const int tid = threadIdx.x;
-  const long long base = ((long long)b * p.n_past + np) * a.n_chunks * kMaxAnchors;
-  // live candidates: n_anchors per chunk
-  const int n_cand = a.n_chunks * a.n_anchors;
-  const bool in_lds = n_cand <= kCandLds;
-  if (in_lds)
-    for (int c = tid; c < n_cand; c += 256) {
-      const long long src = base + (long long)(c / a.n_anchors) * kMaxAnchors + c % a.n_anchors;
-      lc_v[c] = a.cand_val[src];
-      lc_i[c] = a.cand_idx[src];
-    }
+  const int tid = threadIdx.x, n = a.n_anchors;
+  const unsigned long long *lists = a.cand + ((long long)b * p.n_past + np) * a.n_chunks * kMaxAnchors;
+  // Chunk lists are in order, so the n best candidates are among the first n - k of the chunk with the k-th
+  // best head, k < n.
+  const int n_heads = (a.n_chunks + 1) & ~1;
+  for (int c = tid; c < n_heads; c += 256) heads[c] = c < a.n_chunks ? lists[(long long)c * kMaxAnchors] : 0ull;
+  const int n_cand = (n * (n + 1) / 2 + 1) & ~1;
+  for (int i = tid; i < n_cand; i += 256) cand[i] = 0ull;
+  if (tid < n) src[tid] = -1;
   __syncthreads();
-  // anchors: the n_anchors best candidates (value desc, row asc)
-  int n_anch = 0;
-  constexpr int kHeads = 4;  // chunk lists per lane in the single-wave merge
-  if (in_lds && a.n_chunks <= 64 * kHeads) {
-    // Every chunk's list is already sorted (the score kernel emits its winners in order), so the
-    // global order is a merge of sorted lists: one wave, lane l owns the lists of chunks
-    // l, l+64, ... and keeps their heads in registers; a round takes the best head over the wave
-    // and only the owning lane moves that list on.  No workgroup barrier in the loop.
-    if (tid < 64) {
-      float hv[kHeads];
-      int hr[kHeads], hp[kHeads];
-#pragma unroll
-      for (int k = 0; k < kHeads; ++k) {
-        const int ch = tid + 64 * k;
-        const bool ok = ch < a.n_chunks && a.n_anchors > 0;
-        hp[k] = 0;
-        hv[k] = ok ? lc_v[ch * a.n_anchors] : -INFINITY;
-        hr[k] = ok ? lc_i[ch * a.n_anchors] : 0x7fffffff;
-      }
-      for (int r = 0; r < a.n_anchors; ++r) {
-        float bv = hv[0];
-        int bi = hr[0], bk = 0;
-#pragma unroll
-        for (int k = 1; k < kHeads; ++k)
-          if (better(hv[k], hr[k], bv, bi)) {
-            bv = hv[k];
-            bi = hr[k];
-            bk = k;
-          }
-        float v = bv;
-        int i = bi;
-        wave_best(v, i);
-        if (v == -INFINITY) break;
-        if (tid == 0) anchors[r] = i;
-        n_anch = r + 1;
-        if (bv == v && bi == i) {  // rows are unique over the chunks: exactly one lane owns the winner
-#pragma unroll
-          for (int k = 0; k < kHeads; ++k)
-            if (k == bk) {
-              hp[k] += 1;
-              const int src = (tid + 64 * k) * a.n_anchors + hp[k];
-              const bool more = hp[k] < a.n_anchors;
-              hv[k] = more ? lc_v[more ? src : 0] : -INFINITY;
-              hr[k] = more ? lc_i[more ? src : 0] : 0x7fffffff;
-            }
-        }
-      }
-    }
-  } else {
-    // many chunks: n_anchors rounds of a workgroup-wide arg-max over all candidates; a candidate
-    // is retired by remembering the last winner: the order is total, so "strictly after the last
-    // winner" selects the next one without writing anything
-    float last_v = INFINITY;
-    int last_i = -1;
-    for (int r = 0; r < a.n_anchors; ++r) {
-      float v = -INFINITY;
-      int i = 0x7fffffff;
-      for (int c = tid; c < n_cand; c += 256) {
-        float w;
-        int j;
-        if (in_lds) {
-          w = lc_v[c];
-          j = lc_i[c];
-        } else {
-          const long long src = base + (long long)(c / a.n_anchors) * kMaxAnchors + c % a.n_anchors;
-          w = a.cand_val[src];
-          j = a.cand_idx[src];
-        }
-        if (w == -INFINITY) continue;
-        if (better(w, j, last_v, last_i) || (w == last_v && j == last_i)) continue;  // taken already
-        if (better(w, j, v, i)) {
-          v = w;
-          i = j;
-        }
-      }
-      block_best(v, i, sm_v, sm_i);
-      if (v == -INFINITY) break;
-      if (tid == 0) anchors[r] = i;
-      last_v = v;
-      last_i = i;
-      n_anch = r + 1;
-    }
+  for (int c = tid; c < a.n_chunks; c += 256) {
+    const unsigned long long head = heads[c];
+    const int k = count_better(heads, n_heads, head);
+    if (head != 0ull && k < n) src[k] = c;
   }
-  __syncthreads();  // anchors[] is complete (the first wave uses it below)
+  __syncthreads();
+  for (int i = tid; i < n * n; i += 256) {
+    const int k = i / n, e = i - k * n;
+    if (e < n - k && src[k] >= 0) cand[k * n - k * (k - 1) / 2 + e] = lists[(long long)src[k] * kMaxAnchors + e];
+  }
+  __syncthreads();
+  for (int i = tid; i < n_cand; i += 256) {
+    int rows;
+    const unsigned long long mine = cand[i];
+    const int rank = count_better(cand, n_cand, mine, &rows);
+    if (mine != 0ull && rank < n) anchors[rank] = key_row(mine);
+    if (i == 0) n_found = rows < n ? rows : n;
+  }
+  __syncthreads();
+  const int n_anch = n_found;
   const int visible = pool - lo;
   const int want = a.R < visible ? a.R : visible;
   if (tid < 64) {
+    // Lane r: the anchor of rank r and its window, clipped to the visible pool.  Windows start and end in the
+    // order of their anchors (they are equally long but for the clipping), so what better anchors have taken
+    // of this one is a piece at its start (from anchors below) and one at its end (from anchors above):
+    // the rows it adds are one range [from, to).
     const int lane = tid;
-    int plo = 0x7fffffff, phi = 0x7fffffff;  // range `lane` of the sorted list (unused lanes: +inf)
-    int n = 0, count = 0;
-    auto add_range = [&](int s, int e) {  // rows of [s, e) not yet in, ascending, until `want`
-      int cur = s;
-      while (cur < e && count < want) {
-        const unsigned long long inside = __builtin_amdgcn_ballot_w64(plo <= cur && cur < phi);
-        if (inside) {  // cur lies in a range: continue behind it
-          cur = __builtin_amdgcn_readlane(phi, (int)__builtin_ctzll(inside));
-          continue;
-        }
-        const unsigned long long later = __builtin_amdgcn_ballot_w64(lane < n && plo > cur);
-        const int kn = later ? (int)__builtin_ctzll(later) : n;  // first range behind cur
-        int next_start = e;
-        if (later) {
-          const int ns = __builtin_amdgcn_readlane(plo, kn);
-          next_start = ns < e ? ns : e;
-        }
-        int take = next_start - cur;
-        if (take > want - count) take = want - count;
-        int j;  // the range that now ends at cur + take
-        if (kn > 0 && __builtin_amdgcn_readlane(phi, kn - 1) == cur) {  // grows the range before it
-          j = kn - 1;
-          if (lane == j) phi = cur + take;
-        } else {  // new range at position kn: ranges kn.. move up one lane
-          const int ulo = __shfl_up(plo, 1), uhi = __shfl_up(phi, 1);
-          if (lane > kn) {
-            plo = ulo;
-            phi = uhi;
-          } else if (lane == kn) {
-            plo = cur;
-            phi = cur + take;
-          }
-          j = kn;
-          n += 1;
-        }
-        if (j + 1 < n && __builtin_amdgcn_readlane(plo, j + 1) == cur + take) {  // touches the next: merge
-          const int nhi = __builtin_amdgcn_readlane(phi, j + 1);
-          const int dlo = __shfl_down(plo, 1), dhi = __shfl_down(phi, 1);
-          if (lane == j) phi = nhi;
-          else if (lane > j) {
-            plo = lane + 1 < 64 ? dlo : 0x7fffffff;
-            phi = lane + 1 < 64 ? dhi : 0x7fffffff;
-          }
-          n -= 1;
-        }
-        count += take;
-        cur += take;
+    const bool live = lane < n_anch;
+    const int an = live ? anchors[lane] : 0;
+    const int s = an - a.win_before > lo ? an - a.win_before : lo;
+    const int e = an + a.win_after + 1 < pool ? an + a.win_after + 1 : pool;
+    int from = s, to = e;
+    for (int j = 0; j + 1 < n_anch; ++j) {
+      const int aj = __builtin_amdgcn_readlane(an, j), sj = __builtin_amdgcn_readlane(s, j), ej = __builtin_amdgcn_readlane(e, j);
+      if (j < lane) {
+        if (aj < an) from = from > ej ? from : ej;
+        else to = to < sj ? to : sj;
       }
-    };
-    for (int r = 0; r < n_anch; ++r) {
-      const int an = anchors[r];
-      const int s = an - a.win_before > lo ? an - a.win_before : lo;
-      const int e = an + a.win_after + 1 < pool ? an + a.win_after + 1 : pool;
-      add_range(s, e);
     }
-    add_range(lo, pool);  // padding: the earliest visible rows not yet in
-    // rows before each range (exclusive prefix sum of the lengths)
-    int len = lane < n ? phi - plo : 0, incl = len;
+    auto prefix = [&](int x) {  // exclusive prefix sum over the lanes
+      int incl = x;
 #pragma unroll
-    for (int sh = 1; sh < 64; sh <<= 1) {
-      const int up = __shfl_up(incl, sh);
-      if (lane >= sh) incl += up;
+      for (int sh = 1; sh < 64; sh <<= 1) {
+        const int up = __shfl_up(incl, sh);
+        if (lane >= sh) incl += up;
+      }
+      return incl - x;
+    };
+    const int adds = live && to > from ? to - from : 0;
+    const int room = want - prefix(adds);  // rows still wanted when this anchor's turn comes
+    const int take = room < 0 ? 0 : room < adds ? room : adds;
+    // the ranges in row order
+    const unsigned long long used = __builtin_amdgcn_ballot_w64(take > 0);
+    const int k_used = (int)__builtin_popcountll(used);
+    int pos = 0;
+    for (int j = 0; j < n_anch; ++j) {
+      const int fj = __builtin_amdgcn_readlane(from, j), tj = __builtin_amdgcn_readlane(take, j);
+      pos += (tj > 0 && fj < from) ? 1 : 0;
     }
-    p_lo[lane] = plo;
-    p_before[lane] = incl - len;
-    if (lane == 63) p_before[64] = incl;
-    if (lane == 0) n_pieces = n;
+    if (take > 0) {
+      q_lo[pos] = from;
+      q_len[pos] = take;
+    }
+    // (one wave: LDS operations are in order)  padding: the earliest visible rows, i.e. the gaps in front of the
+    // ranges from the first on; lane k_used has the gap behind the last range
+    const int r_lo = lane < k_used ? q_lo[lane] : pool, r_len = lane < k_used ? q_len[lane] : 0;
+    int prev_end = __shfl_up(r_lo + r_len, 1);
+    if (lane == 0) prev_end = lo;
+    const int gap = lane <= k_used ? r_lo - prev_end : 0;
+    const int chosen = prefix(take) + take;  // lane 63: all rows the windows gave
+    const int missing = want - __builtin_amdgcn_readlane(chosen, 63) - prefix(gap);
+    const int pad = missing < 0 ? 0 : missing < gap ? missing : gap;
+    const int before = prefix(pad + r_len);
+    if (lane <= k_used) {
+      p_lo[2 * lane] = prev_end;
+      p_before[2 * lane] = before;
+      p_lo[2 * lane + 1] = r_lo;
+      p_before[2 * lane + 1] = before + pad;
+    }
+    if (lane == 0) n_pieces = 2 * k_used + 1;
   }
   __syncthreads();
   int *out = a.idx_out + ((long long)b * p.n_past + np) * a.R;
-  const int total = p_before[64];
   for (int o = tid; o < a.R; o += 256) {
-    int val = 0;
-    if (o < total) {
-      int k = 0;
-      while (k + 1 < n_pieces && p_before[k + 1] <= o) ++k;
-      val = p_lo[k] + (o - p_before[k]);
-    } else if (total > 0) {
-      val = pool - 1;  // unreachable when R <= visible rows (checked on the host)
+    int val = visible > 0 ? pool - 1 : 0;  // beyond the visible rows: refused on the host (an empty pool's list is not meaningful)
+    if (o < want) {
+      int l = 0, h = n_pieces;  // the last piece that starts at or before o
+      while (h - l > 1) {
+        const int mid = (l + h) >> 1;
+        if (p_before[mid] <= o) l = mid;
+        else h = mid;
+      }
+      val = p_lo[l] + (o - p_before[l]);
     }
     out[o] = val;
   }
