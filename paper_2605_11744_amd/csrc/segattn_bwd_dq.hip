@@ -322,7 +322,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_kernel(const Problem p_arg, con
     ticket = bwd_dq_item<D, HS>(p, pa, a, bid, smem, own);
     drawn = true;
     if (!queued) return;
-    __syncthreads();  // the item's last reads of the tiles come before the next item's first stores
+    lds_barrier();  // the item's last reads of the tiles come before the next item's first loads
   }
 }
 

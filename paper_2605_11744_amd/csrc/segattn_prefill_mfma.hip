@@ -262,12 +262,8 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
     }
   };
 
-  for (int i = 0; i < (kPair ? kSlots - 2 : kSlots - 1); ++i) {
-    issue_loads();
-    loader_advance();
-  }
-
-  // ---- Q^T operands: Qr[qb][kc] = Q[row(qb, col)][16 kc + 8 hi .. +7]
+  // ---- Q^T operands: Qr[qb][kc] = Q[row(qb, col)][16 kc + 8 hi .. +7].  Requested before the K/V steps: memory
+  // operations complete in order, and the first sync leaves the last steps' loads in flight, not these.
   bf16x8 Qr[QB][NC];
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
@@ -279,6 +275,11 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
       const i32x4 v = __builtin_bit_cast(i32x4, *(const uint4 *)(qrow + 16 * kc));
       Qr[qb][kc] = __builtin_bit_cast(bf16x8, v);
     }
+  }
+
+  for (int i = 0; i < (kPair ? kSlots - 2 : kSlots - 1); ++i) {
+    issue_loads();
+    loader_advance();
   }
 
   // ---- per-lane LDS read offsets inside a slot
@@ -768,7 +769,7 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
   // consecutive d of one query row per accumulator quad; it drops them into the wave's own
   // [32 rows][D] staging block (rows padded by 8 bytes against bank conflicts), and the wave
   // reads the block back row-major.
-  __syncthreads();  // every wave is past its last read of the K/V ring
+  lds_barrier();  // every wave is past its last read of the K/V ring
   const bool wide = w.wide;
   const int es = wide ? 4 : 2;                 // bytes per output element
   const int row_bytes = D * es + 8;
@@ -796,7 +797,7 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
           *(uint2 *)dst = __builtin_bit_cast(uint2, __builtin_convertvector(o, bf16x4));
         }
       }
-    __syncthreads();
+    // (the block is the wave's own: its LDS accesses are in order)
     const int piece = lane % lanes_per_row;
     for (int r = lane / lanes_per_row; r < 32; r += rows_per_pass) {
       const int tr = tw0 + 32 * qb + r;
@@ -806,8 +807,8 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
       unsigned char *gdst = (unsigned char *)w.out + (((long long)tr * w.out_heads + ohead) * D) * es + piece * 16;
       *(uint4 *)gdst = uint4{a0.x, a0.y, a1.x, a1.y};
     }
-    __syncthreads();
   }
+  if (next_from) lds_barrier();  // every wave has read its block back before the ring is used again
   return ticket;
 }
 

@@ -29,6 +29,15 @@ struct WorkItem {
   bool valid;
 };
 
+// Workgroup barrier for data handed over in LDS: waits for this wave's LDS accesses only.  __syncthreads()
+// also waits for every global store of the wave to have been written, 1 to 2 us when the output of an
+// item has just been stored.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // ---- work items from queues (kernels that run as a resident grid)
 // Queue y (counter at queue[kQueueStride * y]) holds the items y, y+8, ... of a launch of
 // `n_items`, in order: what XCD y would be dealt if every item were a workgroup of its own.  A
@@ -74,9 +83,9 @@ __device__ __forceinline__ int take_item(unsigned *queue, int n_items, bool draw
     }
     *slot = got;
   }
-  __syncthreads();
+  lds_barrier();
   const int bid = __builtin_amdgcn_readfirstlane(*slot);
-  __syncthreads();  // everyone has read it before thread 0 writes the next one
+  lds_barrier();  // everyone has read it before thread 0 writes the next one
   return bid;
 }
 
