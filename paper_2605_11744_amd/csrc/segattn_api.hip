@@ -322,8 +322,9 @@ static segattn_status bwd_seq_launch(const Problem &p, const void *q, const void
   a.dv = dv;
   a.n = (int)n;
   const hipStream_t st = (hipStream_t)stream;
+  if (!p.fp32_math) return hip_status(launch_bwd_mfma(p, a, st));
   if (launch_bwd_delta(p, a, st) != hipSuccess) return SEGATTN_EHIP;
-  return hip_status(p.fp32_math ? launch_bwd_fp32(p, a, st) : launch_bwd_mfma(p, a, st));
+  return hip_status(launch_bwd_fp32(p, a, st));
 }
 
 segattn_status seg_attn_bwd_seq(const segattn_config *cfg, const void *q, const void *k, const void *v,
@@ -423,8 +424,9 @@ segattn_status seg_attn_bwd_varlen(const segattn_config *cfg, const void *q, con
   a.cu_seqlens = cu_seqlens;
   a.total = total;
   const hipStream_t st = (hipStream_t)stream;
+  if (!p.fp32_math) return hip_status(launch_bwd_mfma(p, a, st));
   if (launch_bwd_delta(p, a, st) != hipSuccess) return SEGATTN_EHIP;
-  return hip_status(p.fp32_math ? launch_bwd_fp32(p, a, st) : launch_bwd_mfma(p, a, st));
+  return hip_status(launch_bwd_fp32(p, a, st));
 }
 
 segattn_status seg_kv_commit(segattn_ctx *ctx, const void *k, const void *v, int32_t m, void *stream) {

@@ -62,13 +62,18 @@ __device__ __forceinline__ unsigned bwd_dq_item(const Problem &p, const PrefillA
   t = row_ok ? t : last_row;
   const long long qoff = ((seg_row + t) * p.Hq + head) * D;
   const long long stat = (w.lse - a.lse) + (long long)head * w.lse_head_stride + t;  // index into the row statistics
-  const float lse2 = a.lse[stat] * kLog2e, delta = a.delta[stat];
+  const float lse = a.lse[stat], lse2 = lse * kLog2e;
 
   bf16x8 Qr[NC], Gr[NC];  // Q^T and dO^T operands: row `col`, elements 16 kc + 8 hi .. +7
 #pragma unroll
   for (int kc = 0; kc < NC; ++kc) {
     Qr[kc] = *(const bf16x8 *)(a.q + qoff + 16 * kc + 8 * hi);
     Gr[kc] = *(const bf16x8 *)(a.dout + qoff + 16 * kc + 8 * hi);
+  }
+  const float delta = row_delta<NC>(a.out, p.out_fp32 != 0, qoff, hi, Gr);
+  if (row_ok && hi == 0) {  // the row statistics the dK/dV kernel starts its accumulators at
+    a.delta[stat] = delta;
+    a.nls[stat] = -lse / p.scale;
   }
   f32x16 acc[NB];
 #pragma unroll

@@ -287,12 +287,17 @@ __global__ __launch_bounds__(64 * kDqSplitWaves, 2) void bwd_dq_split_kernel(con
   t = t < last_row ? t : last_row;
   const long long qoff = ((seg_row + t) * p.Hq + head0 + col % HS) * D;
   const long long stat = (w.lse - a.lse) + (long long)(head0 + col % HS) * w.lse_head_stride + t;
-  const float lse2 = a.lse[stat] * kLog2e, delta = a.delta[stat];
+  const float lse = a.lse[stat], lse2 = lse * kLog2e;
   bf16x8 Qr[NC], Gr[NC];
 #pragma unroll
   for (int kc = 0; kc < NC; ++kc) {
     Qr[kc] = *(const bf16x8 *)(a.q + qoff + 16 * kc + 8 * hi);
     Gr[kc] = *(const bf16x8 *)(a.dout + qoff + 16 * kc + 8 * hi);
+  }
+  const float delta = row_delta<NC>(a.out, p.out_fp32 != 0, qoff, hi, Gr);
+  if (wave == 0 && hi == 0 && w.t0 + col / HS <= last_row) {  // for the dK/dV kernel; the eight waves hold the same columns
+    a.delta[stat] = delta;
+    a.nls[stat] = -lse / p.scale;
   }
   f32x16 acc[NB];
 #pragma unroll

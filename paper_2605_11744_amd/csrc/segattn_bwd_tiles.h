@@ -38,6 +38,41 @@ struct BwdTile {
   __device__ static constexpr int at(int row, int chunk) { return row * kRowBytes + ((chunk ^ swz(row)) << 4); }
 };
 
+// delta = sum_d dO * O of the lane's query row, from the dO operand registers (elements 16 kc + 8 hi .. +7 of
+// the row at element offset qoff) and the forward's output (bf16 or fp32); both half-waves get it.  Formed where
+// dO is held anyway: a kernel of its own read dO and O once more and cost a launch (8K window, 32 heads:
+// 25 us of 1600; 6.4K packed rows, 16 heads: 11 us of 137).
+template <int NC>
+__device__ __forceinline__ float row_delta(const void *out, bool out_fp32, long long qoff, int hi, const bf16x8 (&G)[NC]) {
+  float part[NC];
+#pragma unroll
+  for (int kc = 0; kc < NC; ++kc) {
+    float o[8];
+    if (out_fp32) {
+      const f32x4 lo = *(const f32x4 *)((const float *)out + qoff + 16 * kc + 8 * hi);
+      const f32x4 up = *(const f32x4 *)((const float *)out + qoff + 16 * kc + 8 * hi + 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        o[e] = lo[e];
+        o[4 + e] = up[e];
+      }
+    } else {
+      const bf16x8 x = *(const bf16x8 *)((const unsigned short *)out + qoff + 16 * kc + 8 * hi);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] = (float)x[e];
+    }
+    part[kc] = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) part[kc] = fmaf((float)G[kc][e], o[e], part[kc]);
+  }
+#pragma unroll
+  for (int step = 1; step < NC; step *= 2)
+#pragma unroll
+    for (int kc = 0; kc < NC; kc += 2 * step) part[kc] += part[kc + step];
+  const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_int(part[0]), __float_as_int(part[0]), false, false);
+  return __int_as_float(sw[0]) + __int_as_float(sw[1]);
+}
+
 // acc += A . B
 __device__ inline void mma_acc(f32x16 &acc, const bf16x8 a, const bf16x8 b) {
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
