@@ -13,10 +13,10 @@ namespace segattn {
 
 constexpr int kMaxKvHeads = 128;
 // per (sequence, KV head): pool rows, tail rows, open-segment rows, first visible pool row,
-// rows of the retrieved prefix (retrieval mode), 3 unused
+// rows of the retrieved prefix (retrieval mode), workgroups of an append that have arrived, 2 unused
 constexpr int kMetaInts = 8;
 
-enum MetaSlot { META_POOL = 0, META_TAIL = 1, META_FILL = 2, META_LO = 3, META_RET = 4 };
+enum MetaSlot { META_POOL = 0, META_TAIL = 1, META_FILL = 2, META_LO = 3, META_RET = 4, META_ARRIVED = 5 };
 
 // Geometry of the cache arena, identical on host and device.
 //   [ counters : B*Hkv*8 int32 ][ decode workspace ][ K/V rows ][ attention views ]
@@ -279,6 +279,7 @@ struct CopyArgs {
   CacheGeom geom;
   int m;                 // rows per sequence in the source
   int kv_head;           // past_append: target head; otherwise unused
+  int counts;            // append: 1: update the counters as well (no close kernel follows)
 };
 
 // Arguments of the backward kernels (whole-sequence form, positions absolute as in SEQ mode).
