@@ -262,25 +262,30 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
     }
   };
 
-  // ---- Q^T operands: Qr[qb][kc] = Q[row(qb, col)][16 kc + 8 hi .. +7].  Requested before the K/V steps: memory
-  // operations complete in order, and the first sync leaves the last steps' loads in flight, not these.
+  // ---- Q^T operands: Qr[qb][kc] = Q[row(qb, col)][16 kc + 8 hi .. +7].  Memory operations complete in order: with
+  // four waves the queries are requested before the K/V steps (so that the first sync, which leaves the last
+  // step's loads in flight, does not wait for all of them: 554 rows, 32 heads of 64: 15.5 -> 15.4 us), with eight
+  // waves after them (64 KB in front of the first step cost more: 9000 rows, 16 heads of 128: 217.6 against 215.3).
   bf16x8 Qr[QB][NC];
+  auto load_q = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    int t = tw0 + 32 * qb + col;
-    t = t < last_row ? t : last_row;
-    const unsigned short *qrow = w.q + ((long long)t * p.Hq + head) * D + 8 * hi;
+    for (int qb = 0; qb < QB; ++qb) {
+      int t = tw0 + 32 * qb + col;
+      t = t < last_row ? t : last_row;
+      const unsigned short *qrow = w.q + ((long long)t * p.Hq + head) * D + 8 * hi;
 #pragma unroll
-    for (int kc = 0; kc < NC; ++kc) {
-      const i32x4 v = __builtin_bit_cast(i32x4, *(const uint4 *)(qrow + 16 * kc));
-      Qr[qb][kc] = __builtin_bit_cast(bf16x8, v);
+      for (int kc = 0; kc < NC; ++kc) {
+        const i32x4 v = __builtin_bit_cast(i32x4, *(const uint4 *)(qrow + 16 * kc));
+        Qr[qb][kc] = __builtin_bit_cast(bf16x8, v);
+      }
     }
-  }
-
+  };
+  if constexpr (NW == 4) load_q();
   for (int i = 0; i < (kPair ? kSlots - 2 : kSlots - 1); ++i) {
     issue_loads();
     loader_advance();
   }
+  if constexpr (NW != 4) load_q();
 
   // ---- per-lane LDS read offsets inside a slot
   // K operand of k-chunk kc: row col, logical chunk 2 kc + hi, swizzled with the row: one lane
