@@ -45,45 +45,71 @@ __device__ inline void rope_rotate8(uint4 &lo, uint4 &hi, const float (&sn)[8], 
   }
 }
 
-// One thread per (b, row, group of 8 channel pairs): the angles depend on the position and the
-// channel only, so the thread forms its 8 sines and cosines once and walks over all heads of q
-// and k with them.
+// A workgroup rotates up to kRopeRows consecutive token rows: its threads form the sines and cosines of
+// their D/2 channel pairs once, in LDS, and then walk over the rows' q and over their k in memory order, a
+// thread taking 8 channel pairs of one head at a time (16 bytes and their partners D/2 further on).
+// Bound by HBM, each element read and written in place; what counts is the order of the accesses: with a
+// thread per (row, 8 channel pairs) that walked over all heads of its row, all waves were at the same head
+// of different rows (the same few addresses modulo the row size) and formed sines first, and 32K rows of
+// 32 + 8 heads took 152 us; in memory order 135 (5.0 TB/s), 500 rows 4.7 instead of 11.8.  One 16-byte pair in flight per
+// thread: the in-place probe is fastest so (5.7 TB/s; eight pieces: 4.0).
+constexpr int kRopeRows = 16;
 template <int D>
-__global__ __launch_bounds__(256) void rope_apply_kernel(const Problem p, const RopeArgs a) {
-  constexpr int LPH = D / 16;  // threads per row
-  const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-  const int li = (int)(t % LPH);
-  const long long br = t / LPH;  // (b, row)
-  if (br >= (long long)p.B * a.rows) return;
-  const long long b = br / a.rows, r = br % a.rows;
-  const double pos = (double)((a.pos0 ? a.pos0[b] : 0) + r);
-  float sn[8], cs[8];
+__global__ __launch_bounds__(256) void rope_apply_kernel(const Problem p, const RopeArgs a, const int rows_per_wg) {
+  constexpr int LPH = D / 16, kPairs = D / 2;  // threads per head; channel pairs
+  __shared__ __attribute__((aligned(16))) float sm_sn[kRopeRows][kPairs], sm_cs[kRopeRows][kPairs];
+  const int tid = threadIdx.x;
+  const long long total = (long long)p.B * a.rows, row0 = (long long)blockIdx.x * rows_per_wg;
+  const int n_rows = total - row0 < rows_per_wg ? (int)(total - row0) : rows_per_wg;
+  for (int i = tid; i < n_rows * kPairs; i += 256) {
+    const int r = i / kPairs, c = i % kPairs;
+    const long long br = row0 + r, b = br / a.rows;
+    const double pos = (double)((a.pos0 ? a.pos0[b] : 0) + (br - b * a.rows));
+    float sn, cs;
+    rope_sincos(pos, a.inv_freq[c], sn, cs);
+    sm_sn[r][c] = sn;
+    sm_cs[r][c] = cs;
+  }
+  __syncthreads();
+  const int li = tid % LPH;
+  auto walk = [&](unsigned short *base, int heads) __attribute__((always_inline)) {
+    const int per_row = heads * LPH;  // pieces of 8 channel pairs in a row
+    unsigned short *const x = base + row0 * heads * D;
+    int r = tid / per_row, u = tid - r * per_row;  // this thread's piece: row r, piece u of the row
+    const int dr = 256 / per_row, du = 256 - dr * per_row;
+    while (r < n_rows) {
+      unsigned short *const at = x + ((long long)r * heads + u / LPH) * D + 8 * li;
+      uint4 lo = *(const uint4 *)at, hi = *(const uint4 *)(at + kPairs);
+      float sn[8], cs[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) rope_sincos(pos, a.inv_freq[8 * li + e], sn[e], cs[e]);
-  unsigned short *qrow = a.q + br * p.Hq * D + 8 * li;
-#pragma unroll 4
-  for (int h = 0; h < p.Hq; ++h, qrow += D) {
-    uint4 lo = *(const uint4 *)qrow, hi = *(const uint4 *)(qrow + D / 2);
-    rope_rotate8(lo, hi, sn, cs);
-    *(uint4 *)qrow = lo;
-    *(uint4 *)(qrow + D / 2) = hi;
-  }
-  unsigned short *krow = a.k + br * p.Hkv * D + 8 * li;
-#pragma unroll 4
-  for (int h = 0; h < p.Hkv; ++h, krow += D) {
-    uint4 lo = *(const uint4 *)krow, hi = *(const uint4 *)(krow + D / 2);
-    rope_rotate8(lo, hi, sn, cs);
-    *(uint4 *)krow = lo;
-    *(uint4 *)(krow + D / 2) = hi;
-  }
+      for (int e = 0; e < 8; ++e) {
+        sn[e] = sm_sn[r][8 * li + e];
+        cs[e] = sm_cs[r][8 * li + e];
+      }
+      rope_rotate8(lo, hi, sn, cs);
+      *(uint4 *)at = lo;
+      *(uint4 *)(at + kPairs) = hi;
+      r += dr;
+      u += du;
+      if (u >= per_row) {
+        u -= per_row;
+        ++r;
+      }
+    }
+  };
+  walk(a.q, p.Hq);
+  walk(a.k, p.Hkv);
 }
 
 hipError_t launch_rope_apply(const Problem &p, const RopeArgs &a, hipStream_t st) {
-  const long long threads = (long long)p.B * a.rows * (p.D / 16);
-  const long long blocks = (threads + 255) / 256;
+  // fewer rows per workgroup where sixteen would leave CUs idle
+  const long long total = (long long)p.B * a.rows;
+  long long rows = total / 1024;
+  rows = rows < 1 ? 1 : rows > kRopeRows ? kRopeRows : rows;
+  const long long blocks = (total + rows - 1) / rows;
   if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  if (p.D == 128) hipLaunchKernelGGL(rope_apply_kernel<128>, dim3((unsigned)blocks), dim3(256), 0, st, p, a);
-  else hipLaunchKernelGGL(rope_apply_kernel<64>, dim3((unsigned)blocks), dim3(256), 0, st, p, a);
+  if (p.D == 128) hipLaunchKernelGGL(rope_apply_kernel<128>, dim3((unsigned)blocks), dim3(256), 0, st, p, a, (int)rows);
+  else hipLaunchKernelGGL(rope_apply_kernel<64>, dim3((unsigned)blocks), dim3(256), 0, st, p, a, (int)rows);
   return hipGetLastError();
 }
 
