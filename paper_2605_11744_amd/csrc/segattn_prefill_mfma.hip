@@ -1152,8 +1152,18 @@ static void plan_pieces(const Problem &p, PrefillArgs &a, int hs, int rows, int 
 // e.g. 2048 tokens, 4 heads, D = 64: 33.1 -> 15.0 us; 1000 tokens, 8 heads, D = 128: 25.9 -> 15.3; from about
 // 1000 tokens of 32 heads on the other form is the faster one (D = 64: 20.9 against 22.5).
 static bool use_keysplit(const Problem &p, const PrefillArgs &a) {
-  if (p.tune_waves != 0 || p.tune_queue != 0 || a.cache != nullptr) return false;
-  const StepCount c = count_steps(p, a.n_rows, a.cu_seqlens ? a.total_rows : 0, a.ret_k ? a.ret_R : 0);
+  if (p.tune_waves != 0 || p.tune_queue != 0 || a.parts > 1 || a.parts_other > 1) return false;
+  StepCount c;
+  if (a.cache == nullptr) {
+    c = count_steps(p, a.n_rows, a.cu_seqlens ? a.total_rows : 0, a.ret_k ? a.ret_R : 0);
+  } else {  // a chunk behind a filled cache whose prefixes were not cut (no workspace that holds the pieces)
+    const int n_first = heads_listed_first(p, a);
+    const double blocks = (a.n_rows + 31) / 32, own = a.n_rows / 64.;
+    const double first = n_first ? a.max_first_prefix / 32. : 0, other = n_first < p.Hkv ? a.max_other_prefix / 32. : 0;
+    c.steps = p.B * p.g * blocks * (n_first * (first + own) + (p.Hkv - n_first) * (other + own));
+    c.longest = (first > other ? first : other) + a.n_rows / 32.;
+    c.blocks = p.B * p.Hq * blocks;
+  }
   const double slots = device_cus() * (p.D == 64 ? 2 : 1);
   const double rounds = c.blocks <= slots ? 0 : c.blocks / slots;
   const double split = p.D == 64 ? 6.5 + 0.11 * c.longest + 5.6e-4 * c.steps + 3 * rounds
