@@ -883,7 +883,7 @@ segattn_status seg_attn_decode(segattn_ctx *ctx, const void *q, const void *k_ne
   if (!ctx || !q || !k_new || !v_new || !out || !lse) return SEGATTN_EINVAL;
   if (!ctx->ready) return SEGATTN_ESTATE;
   const Problem &p = ctx->p;
-  long long total_rows = 0, chunks = 0;
+  long long total_rows = 0, chunks = 0, longest = 0;
   bool any_full = false;
   for (int b = 0; b < p.B; ++b) {
     for (int h = 0; h < p.Hkv; ++h) {
@@ -896,6 +896,7 @@ segattn_status seg_attn_decode(segattn_ctx *ctx, const void *q, const void *k_ne
         win = ((p.policy[h] & SEGATTN_TAIL) ? ctx->tail[b] : 0) + ctx->fill[b] + 1;
       }
       total_rows += win;
+      longest = win > longest ? win : longest;
       chunks += (win + ctx->g.decode_chunk - 1) / ctx->g.decode_chunk;
     }
     any_full |= ctx->fill[b] + 1 == p.S;
@@ -920,6 +921,7 @@ segattn_status seg_attn_decode(segattn_ctx *ctx, const void *q, const void *k_ne
   da.geom = ctx->g;
   da.total_rows = total_rows;
   da.chunks = chunks;
+  da.longest = longest;
   if (launch_decode(p, da, p.B, st) != hipSuccess) return hip_failed(ctx);
   if (any_full && launch_cache_close(p, ctx->cache, ctx->g, 0, st) != hipSuccess) return hip_failed(ctx);
   for (int b = 0; b < p.B; ++b) {

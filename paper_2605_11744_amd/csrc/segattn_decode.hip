@@ -5,7 +5,8 @@
 // reduction over an even partition of the rows:
 //   split kernel           the windows of all (sequence, KV head) pairs are laid end to end and cut
 //                          into one slice of rows_per_wg rows per workgroup, as many workgroups as
-//                          the chip holds at once; at the end of every window a workgroup touches
+//                          the chip holds at once (where every window's own slices fit at once: per
+//                          window instead); at the end of every window a workgroup touches
 //                          it writes one partial (acc[D], m, l) per query head.
 //   decode_combine_kernel  one workgroup per (b, query head): merges the partials of its window.
 // Equal slices instead of fixed chunks: no empty workgroups, no uneven tail, and few partials --
@@ -275,12 +276,14 @@ __global__ __launch_bounds__(256, GH == 8 ? 2 : SEGATTN_DECODE_WAVES) void decod
 
 // One workgroup per (b, query head): wave w merges the partials w, w + 4, ... (lanes over the D outputs),
 // kBatch of them per memory round trip, under a running maximum of its own; the four results meet in
-// LDS.  Bound by latency where every window is cut by itself (a.per_window, dozens of partials, few
-// windows): kAhead reads the first batch while the number of partials is still on its way (a slot
-// beyond it holds anything and is given weight 0), so the chain is one round trip for up to 48 partials
-// (a maximum over all partials first, then their rows four at a time, made it five: 4.7 -> 3.9 us).  With
-// long slices a window has two or three partials and 2048 workgroups would read 60 MB for nothing
-// (6.0 -> 9.3 us): small batches there, after the count.
+// LDS.  Bound by latency where a window has dozens of partials (few windows): kAhead reads the first
+// batch while the number of partials is still on its way (a slot beyond it holds anything and is given
+// weight 0), so the chain is one round trip for up to 48 partials (a maximum over all partials first,
+// then their rows four at a time, made it five: 4.7 -> 3.9 us).  With long slices a window has two or
+// three partials and 2048 workgroups would read 60 MB for nothing (6.0 -> 9.3 us): small batches there,
+// after the count.  The line is at 16 partials in the longest window, two small batches a wave.  Step in small
+// batches / in large ones / with the maximum first: 128K rows, one sequence (200 partials) 48.0 / 37.6 / 39.6 us,
+// 16 sequences (24) 113.0 / 109.2 / 114; 32 sequences (13) 249.3 / 251.2 / 259, 64 (7) 435.5 / 439.9 / 438.
 template <int D, int kBatch, bool kAhead>
 __global__ __launch_bounds__(256) void decode_combine_kernel(const Problem p, const DecodeArgs a) {
   const int b = blockIdx.x / p.Hq, head = blockIdx.x % p.Hq;
@@ -351,7 +354,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const Problem p, co
 
 template <int D>
 static hipError_t launch_combine(const Problem &p, const DecodeArgs &a, hipStream_t st) {
-  if (a.per_window) hipLaunchKernelGGL((decode_combine_kernel<D, 12, true>), dim3(p.B * p.Hq), dim3(256), 0, st, p, a);
+  if (a.per_window || a.longest > 16ll * a.rows_per_wg) hipLaunchKernelGGL((decode_combine_kernel<D, 12, true>), dim3(p.B * p.Hq), dim3(256), 0, st, p, a);
   else hipLaunchKernelGGL((decode_combine_kernel<D, 2, false>), dim3(p.B * p.Hq), dim3(256), 0, st, p, a);
   return hipGetLastError();
 }

@@ -268,6 +268,7 @@ struct DecodeArgs {
   CacheGeom geom;
   long long total_rows;  // visible rows summed over every (sequence, KV head) window
   long long chunks;      // slices of geom.decode_chunk rows, every window cut by itself
+  long long longest;     // rows of the longest window
   int rows_per_wg;       // rows per workgroup of the split kernel (>= geom.decode_chunk); set by the launcher
   int per_window;        // 1: every window is cut into slices of its own (a workgroup never goes on into the next window)
   int pending;           // 1: the newest row is still to be appended: the split kernel does it, the combine kernel counts it

@@ -1,0 +1,44 @@
+"""GPU parity of a decode step whose windows have many partial results to merge: more slices than the chip
+holds workgroups (so that windows share them), with two or three, a dozen and dozens of partials in a
+window, more than one batch of the merge kernel, a short sequence beside a long one.  Two tokens, so that the
+second reads the first one's row and count.  The oracle is the judge."""
+import numpy as np
+import pytest
+
+import workloads as W
+from gpu_util import Cache, assert_parity, fill_cache_for_decode, full_history
+from oracle import segattn_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # D, Hq, Hkv, policy, S, T, closed segments per sequence, open rows
+    (64, 8, 8, (3,) * 8, 1024, 128, (60, 3), 700),              # about 60 partials in the longest windows
+    (128, 16, 8, (3,) * 8, 1024, 1024, (12, 12, 11), 1),         # about 20
+    (128, 8, 8, (3,) * 8, 1024, 256, (8, 7, 8, 8, 7), 513),      # a dozen
+    (64, 12, 3, (3, 1, 2), 2048, 512, (90, 40), 31),             # windows of one slice beside long ones
+]
+
+
+@pytest.mark.parametrize("fp32", [False, True])
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_windows_of_many_partials(case, fp32):
+    D, Hq, Hkv, policy, S, T, closed, fill = CASES[case]
+    B = len(closed)
+    w = W.Workload(f"partials{case}", 900 + case, B, 0, Hq, Hkv, D, S, T, policy, decode=True,
+                   max_context=S * (max(closed) + 1))
+    k_done, c_fill = np.array(closed), np.full(B, fill + 1)
+    q, ks, vs, _, _ = W.decode_inputs(w, k_done, c_fill)
+    c = Cache(w, past_capacity=w.max_context, fp32_check=fp32)
+    try:
+        k_new, v_new = fill_cache_for_decode(c, w, ks, vs, k_done, c_fill)
+        hist = [full_history(ks[b], vs[b], closed[b] * S + fill + 1, Hkv, D) for b in range(B)]
+        for token in range(2):
+            o, l = c.decode(q, k_new, v_new)
+            for b in range(B):
+                if token:  # the same row again
+                    hist[b] = tuple(np.concatenate([h, orc.widen(new[b])[None]]) for h, new in zip(hist[b], (k_new, v_new)))
+                o_ref, l_ref = orc.decode_attend(q[b], *hist[b], seg_len=S, tail_len=T, kv_policy=policy)
+                assert_parity(o[b], l[b], o_ref, l_ref, fp32_check=fp32, what=f"case {case} sequence {b} token {token}")
+    finally:
+        c.close()
