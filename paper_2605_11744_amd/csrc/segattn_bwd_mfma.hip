@@ -18,9 +18,10 @@
 // As in the forward kernel the products are arranged so that the accumulator layout of the
 // score tile (lane = its column, the lane's 16 registers = rows) is the B-operand layout of
 // the products that consume P and dS; the transposed A operands (K^T, dO^T, Q^T) come from
-// row-major LDS tiles with ds_read_b64_tr_b16.  Tiles are staged HBM -> registers -> LDS,
-// double-buffered, one barrier per step; the 16-byte chunks of a row are XOR-swizzled against
-// bank conflicts.
+// row-major LDS tiles with ds_read_b64_tr_b16.  Tiles travel HBM -> LDS by DMA through a ring of
+// step buffers, one barrier per step; the 16-byte chunks of a row are XOR-swizzled against
+// bank conflicts.  Launches too short to fill the chip this way take the split forms instead
+// (segattn_bwd_split.hip).
 // This file and segattn_bwd_dq.hip are compiled with the VGPR form of the matrix products
 // (-amdgpu-mfma-vgpr-form): S and dP arrive in vector registers, where the exponentials read them.
 // In the dK/dV kernel the K and V operands sit in accumulation registers (park()), which a product

@@ -1090,14 +1090,17 @@ static int device_cus() {
 // Segment-by-segment prefill: how far to cut the heads' prefixes.  One launch has few query blocks (a
 // user's turn of a conversation has one to a few per head), and those of the PAST heads can have
 // tens of thousands of keys: with one workgroup per block the launch takes as long as its longest
-// workgroup while most CUs idle.  The pieces are made as long as the average work of a CU, at
-// least kMinPieceSteps steps, as long as the workspace holds their outputs: that of the arena made
-// for it, or (a few rows, or configurations without one) the decode path's, which no other call of
-// this context uses at the same time.  A workgroup costs about kItemSteps steps beyond its keys
-// (prologue and output), the merge about half of that; where the estimate with pieces is no
-// shorter than without, nothing is cut (a whole segment behind a short prefix).
+// workgroup while most CUs idle.  The lengths from three quarters of a CU's average work up (at least
+// kMinPieceSteps steps) whose outputs the workspace holds are compared by the rounds of workgroups
+// they take, the long list's items first and the others beside and behind them; the shortest launch
+// wins, uncut if nothing is shorter.  Workspace: that of the arena made for it, or (a few rows, or
+// configurations without one) the decode path's, which no other call of this context uses at the
+// same time.  A workgroup costs about kItemSteps steps beyond its keys (prologue and output).
 // Measured, 32/8 heads, two PAST, m = 173 rows behind 37.5K rows, whole call with the commit: 412 us with
 // four pieces at most, 66 us with 35 pieces of 34 steps; pieces of 48 and 64 steps 20 and 30 us more.
+// Long chunks, 24K to 38K rows behind them (as many pieces as fit the CUs once / the first length that
+// left no second round / compared): 32/8 heads, S = 2048, four PAST: 1602 rows 379 / 470 / 384, 2000 rows 422 / 485 /
+// 425, 1100 rows 318 / 369 / 267; two PAST, S = 4096: 1900 rows 478 / 690 / 404, a whole segment 675 / 716 / 677.
 constexpr int kMinPieceSteps = 8, kItemSteps = 12;
 static void plan_pieces(const Problem &p, PrefillArgs &a, int hs, int rows, int wgs_per_cu) {
   a.parts = a.parts_other = 1;
@@ -1115,28 +1118,47 @@ static void plan_pieces(const Problem &p, PrefillArgs &a, int hs, int rows, int 
   auto steps = [&](long long prefix) { return (prefix + m / 2 + kStepKeys - 1) / kStepKeys; };
   const long long sf = n_first > 0 ? steps(a.max_first_prefix) : 0, so = n_other > 0 ? steps(a.max_other_prefix) : 0;
   const long long total = blocks * (n_first * sf + n_other * so);
-  auto span = [&](long long items, long long most) {  // estimated steps from start to end
-    const long long even = (total + kItemSteps * items + wgs - 1) / wgs;
-    return most + kItemSteps > even ? most + kItemSteps : even;
+  // Estimated steps from start to end: workgroups take `first` items of lf steps, then `other` ones of lo.
+  auto span = [&](long long first, long long lf, long long other, long long lo) {
+    lf += kItemSteps, lo += kItemSteps;
+    const long long t0 = first / wgs * lf, busy = first % wgs, idle = wgs - busy, end = t0 + (busy ? lf : 0);
+    const long long turns = (other + idle - 1) / idle, beside = busy ? lf / lo : turns;
+    if (turns <= beside) return t0 + turns * lo > end ? t0 + turns * lo : end;
+    return end + (other - idle * beside + wgs - 1) / wgs * lo;
   };
-  const long long uncut = blocks * p.Hkv, uncut_span = span(uncut, sf > so ? sf : so);
-  long long len = (total + wgs - 1) / wgs, items, row_heads;
+  // Uncut, head_dim 128 runs half as long blocks of four waves where the chip has room for them.
+  long long best = span(blocks * n_first, sf, blocks * n_other, so);
+  if (p.D == 128 && waves_d128(p, a, hs) == 4 && 2 * blocks * (n_first > 0 ? n_first : n_other) <= wgs) best = best * 2 / 3;
+  long long len = total * 3 / (4 * wgs), row_heads = 0;
   if (len < kMinPieceSteps) len = kMinPieceSteps;
   for (;; len += (len + 15) / 16) {
-    const FastDiv t = fast_div_by(len * kStepKeys);
+    FastDiv t = fast_div_by(len * kStepKeys);
     const int c0 = n_first > 0 ? piece_count((int)a.max_first_prefix, m, t, 1 << 20) : 1;
     const int c1 = n_other > 0 ? piece_count((int)a.max_other_prefix, m, t, 1 << 20) : 1;
-    if (c0 == 1 && c1 == 1) return;
-    items = blocks * (n_first * c0 + n_other * c1);
-    row_heads = (long long)p.B * m * p.g * ((c0 > 1 ? n_first * c0 : 0) + (c1 > 1 ? n_other * c1 : 0));
-    if (row_heads * (p.D + 1) > ws_floats) continue;
-    if (items > wgs && uncut <= wgs) continue;  // a second round of workgroups would double the time
-    if (span(items, len) + kItemSteps / 2 >= uncut_span) return;
+    if (c0 == 1 && c1 == 1) break;
+    const long long rh = (long long)p.B * m * p.g * ((c0 > 1 ? n_first * c0 : 0) + (c1 > 1 ? n_other * c1 : 0));
+    if (rh * (p.D + 1) > ws_floats) continue;
+    long long even = len;  // pieces of one length instead of a last one of up to half as much again
+    if (c0 == 1 || c1 == 1) {
+      even = c0 > 1 ? (sf + c0 - 1) / c0 : (so + c1 - 1) / c1;
+      const FastDiv te = fast_div_by(even * kStepKeys);
+      if (even >= kMinPieceSteps && (n_first == 0 || piece_count((int)a.max_first_prefix, m, te, 1 << 20) == c0) &&
+          (n_other == 0 || piece_count((int)a.max_other_prefix, m, te, 1 << 20) == c1))
+        t = te;
+      else
+        even = len;
+    }
+    // the merge: half an item's steps, and its bytes at HBM speed (4.4 MB a step)
+    const long long merge = kItemSteps / 2 + rh * p.D * 8 / 4400000;
+    const long long cost = merge + span(blocks * n_first * c0, c0 > 1 ? even : sf, blocks * n_other * c1, c1 > 1 ? even : so);
+    if (cost >= best) continue;
+    best = cost;
     a.parts = c0;
     a.parts_other = c1;
     a.piece_rows = t;
-    break;
+    row_heads = rh;
   }
+  if (row_heads == 0) return;
   const long long rows_first = a.parts > 1 ? (long long)p.B * a.parts * m * n_first * p.g : 0;
   float *const out = (float *)(a.cache + (own_ws ? a.geom.part_off : dec_off)), *const lse = out + row_heads * p.D;
   a.piece_list[0] = {out, lse, a.parts, n_first * p.g, 0};
@@ -1151,6 +1173,9 @@ static void plan_pieces(const Problem &p, PrefillArgs &a, int hs, int rows, int 
 //                    D = 128: 7.5 + 0.13 a step + 1.1e-3 a wave-step, 256 workgroups a round; 3 a further round
 // e.g. 2048 tokens, 4 heads, D = 64: 33.1 -> 15.0 us; 1000 tokens, 8 heads, D = 128: 25.9 -> 15.3; from about
 // 1000 tokens of 32 heads on the other form is the faster one (D = 64: 20.9 against 22.5).
+// Chunks on a filled cache come here only if their prefixes were not cut (plan_pieces found no workspace, or no
+// gain): 173 rows behind 37.5K, four of eight KV heads with the whole past, 32 heads of 128, forward and commit:
+// 633 -> 251 us, 8 rows of it 620 -> 75; 1500 rows stay with the other form (663).
 static bool use_keysplit(const Problem &p, const PrefillArgs &a) {
   if (p.tune_waves != 0 || p.tune_queue != 0 || a.parts > 1 || a.parts_other > 1) return false;
   StepCount c;
