@@ -49,20 +49,26 @@ __global__ void cache_reset_kernel(const Problem p, unsigned char *cache, const 
 // Rows k,v [B,m,Hkv,D] -> open segment of every (b,h).  grid = (row chunks, B*Hkv).
 // A non-PAST head whose whole segment arrives in one call (fill = 0, m = S) keeps only the
 // last T rows, written straight into the tail slots; everything else of it is dropped.
-// a.counts: the counters are updated here too, by the last workgroup of a head to arrive (the others have
-// read them by then); meta[META_ARRIVED] is 0 between launches.  Only where no rows have to move on
-// closing: no segment fills up, or every one arrives whole (173 rows behind 37.5K, forward and commit:
-// 66.1 -> 63.5 us without the close kernel).
+// a.counts: the counters are updated here too, by the last workgroup of a head to arrive; meta[META_ARRIVED]
+// is 0 between launches.  A workgroup arrives only when all its waves hold the counters they read: a wave
+// still waiting for them would take the new ones and put its rows in the wrong place.  Only where no rows
+// have to move on closing: no segment fills up, or every one arrives whole.
 template <int D>
 __global__ __launch_bounds__(256) void cache_append_kernel(const Problem p, const CopyArgs a) {
   constexpr int CPR = D / 8;  // 16-byte chunks per row
   const int b = blockIdx.y / p.Hkv, h = blockIdx.y % p.Hkv;
-  const int *meta = meta_of(a.cache, a.geom, p, b, h);
-  const int fill = meta[META_FILL];
+  int *meta = meta_of(a.cache, a.geom, p, b, h);
+  const int fill = meta[META_FILL], pool = meta[META_POOL];
+  int arrived = 0;
+  if (a.counts) {
+    __builtin_amdgcn_s_waitcnt(0);  // the counters are in this wave's registers ...
+    __syncthreads();                // ... and in those of the others
+    if (threadIdx.x == 0) arrived = atomicAdd(&meta[META_ARRIVED], 1) + 1;
+  }
   const bool past = p.policy[h] & SEGATTN_PAST;
   int src0 = 0, dst0, n = a.m;
   if (past) {
-    dst0 = meta[META_POOL] + fill;
+    dst0 = pool + fill;
   } else if (fill == 0 && a.m == p.S) {
     src0 = p.S - p.T;
     n = p.T;
@@ -94,18 +100,14 @@ __global__ __launch_bounds__(256) void cache_append_kernel(const Problem p, cons
       vm[(long long)r * CPR + c] = vx;
     }
   }
-  if (a.counts && threadIdx.x == 0) {  // (thread 0 has read the counters it needs)
-    int *mine = meta_of(a.cache, a.geom, p, b, h);
-    const int pool = mine[META_POOL];
-    if (atomicAdd(&mine[META_ARRIVED], 1) + 1 == (int)gridDim.x) {
-      mine[META_ARRIVED] = 0;
-      const bool closes = fill + a.m >= p.S;
-      mine[META_FILL] = closes ? 0 : fill + a.m;
-      if (closes) {
-        mine[META_TAIL] = p.T;
-        if (past) mine[META_POOL] = pool + p.S;
-        mine[META_RET] = 0;
-      }
+  if (a.counts && threadIdx.x == 0 && arrived == (int)gridDim.x) {
+    const bool closes = fill + a.m >= p.S;
+    meta[META_ARRIVED] = 0;
+    meta[META_FILL] = closes ? 0 : fill + a.m;
+    if (closes) {
+      meta[META_TAIL] = p.T;
+      if (past) meta[META_POOL] = pool + p.S;
+      meta[META_RET] = 0;
     }
   }
 }

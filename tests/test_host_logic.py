@@ -21,6 +21,28 @@ def _build_and_run(tmp_path, name):
     return subprocess.run([str(exe)], capture_output=True, text=True, timeout=600).stdout
 
 
+def _build_and_run_on_cpu(tmp_path, name):
+    """A check that runs kernels of the library on the CPU (tests/host/emu)."""
+    clang = shutil.which("amdclang++") or "/opt/rocm/llvm/bin/clang++"
+    if not os.path.exists(clang):
+        pytest.skip("clang++ of ROCm not found")
+    exe = tmp_path / name
+    host = os.path.join(ROOT, "tests", "host")
+    subprocess.run([clang, "-O1", "-std=c++17", "-I", os.path.join(host, "emu"), "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(ROOT, "paper_2605_11744_amd", "csrc"), "-I", "/opt/rocm/include",
+                    os.path.join(host, name + ".cpp"), "-o", str(exe)], check=True, capture_output=True, timeout=600)
+    return subprocess.run([str(exe)], capture_output=True, text=True, timeout=600).stdout
+
+
+def test_commit_in_one_launch_in_any_order_of_its_waves(tmp_path):
+    """The append kernel that updates the counters itself, its waves in orders that the hardware takes rarely
+    (every workgroup's first wave before any other, the last waves first, at random): one to four
+    workgroups per head, whole segments and open ones, with and without attention views."""
+    out = _build_and_run_on_cpu(tmp_path, "append_order_check")
+    assert out.startswith("ok "), out
+    assert int(out.split()[1]) == 192
+
+
 def test_item_mapping_is_one_to_one_and_longest_first(tmp_path):
     """item_coords (the integer part of the kernels' block-index resolution) over some 10,000 launch
     shapes -- dense, packed, retrieved-prefix and split-prefix forms, every sub-group count -- maps
