@@ -961,11 +961,13 @@ hipError_t launch_prefill_fp32(const Problem &p, const PrefillArgs &a, long long
 static int heads_per_wg(const Problem &p) { return (p.g % 4 == 0) ? 4 : (p.g % 2 == 0) ? 2 : 1; }
 
 // ---- counters of the queued form of the kernel
-// Nine counters per set, each on a 128-byte line of its own, zero between launches.  Launches on one stream run one
-// after the other and share a set; launches on different streams may overlap, so every (device, stream) pair that asks gets a
-// set of its own, for as long as the process lives.  When the sets are used up, and for a stream
-// that is being captured (the graph may later be replayed on any stream, next to anything), the
-// launch falls back to one workgroup per item, which needs no counters.
+// Nine counters per set, each on a 128-byte line of its own, zero between launches.  Launches that can overlap must
+// never share a set: they would take each other's items, and nothing puts the counters right afterwards.  Launches on one
+// stream run one after the other and share a set; launches on different streams may overlap, so every (device, stream)
+// pair that asks gets a set of its own, for as long as the process lives.  When the sets are used up, for a stream
+// that is being captured (the graph may later be replayed on any stream, next to anything), and for
+// hipStreamPerThread (one handle that names a different stream in every host thread), the launch falls back to one
+// workgroup per item, which needs no counters.
 static int device_cus();
 
 constexpr int kQueueSets = 64;
@@ -981,6 +983,7 @@ unsigned *item_queue_for(hipStream_t st) {
   static Owner owners[kQueueSets];
   static int n_owners = 0;
   static unsigned *base[kQueueDevices] = {};
+  if (st == hipStreamPerThread) return nullptr;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
     (void)hipGetLastError();

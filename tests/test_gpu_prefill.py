@@ -292,6 +292,52 @@ def test_item_queues_with_two_host_threads_on_one_stream(monkeypatch):
             assert torch.equal(o, alone[0]) and torch.equal(l, alone[1])
 
 
+def test_item_queues_stay_away_from_the_per_thread_stream_handle(monkeypatch):
+    """hipStreamPerThread (2) is one handle that names another stream in every host thread: launches on it can
+    overlap, so it gets no queue counters (an ordinary stream does), and two threads' calls come out as they do
+    alone."""
+    import ctypes
+    import threading
+    import gpu_util as G
+    per_thread = 2
+    queue_for = ctypes.CDLL(G.sa.LIB_PATH)._ZN7segattn14item_queue_forEP12ihipStream_t
+    queue_for.restype, queue_for.argtypes = ctypes.c_void_p, [ctypes.c_void_p]
+    assert queue_for(per_thread) is None
+    assert queue_for(torch.cuda.Stream().cuda_stream) is not None
+    monkeypatch.setitem(G.TUNING, "item_queues", G.QUEUES_ON_SMALL_GRID)
+    probs = []
+    for i, n in enumerate((2100, 1500)):
+        w = W.small(f"per{i}", index=148 + i, seq_len=n, seg_len=512, tail_len=128, n_q_heads=8, n_kv_heads=2,
+                    head_dim=128, kv_policy=[3, 1])
+        q, k, v = W.prefill_inputs(w)
+        qd, kd, vd = G.dev_bf16(q), G.dev_bf16(k), G.dev_bf16(v)
+        cfg = G.config_of(w, out_fp32=True, batch=1)
+        alone = _fwd(G, cfg, qd, kd, vd, n)
+        outs = [(torch.full_like(alone[0], float("nan")), torch.full_like(alone[1], float("nan"))) for _ in range(6)]
+        probs.append((cfg, qd, kd, vd, n, alone, outs))
+    torch.cuda.synchronize()
+    errors = []
+
+    def work(prob):
+        cfg, qd, kd, vd, n, _, outs = prob
+        try:
+            for o, l in outs:
+                G.sa.seg_attn_fwd_seq(cfg, qd, kd, vd, n, o, l, per_thread)
+        except Exception as e:   # noqa: BLE001 - reported below
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(pr,)) for pr in probs]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors
+    for _, _, _, _, _, alone, outs in probs:
+        for o, l in outs:
+            assert torch.equal(o, alone[0]) and torch.equal(l, alone[1])
+
+
 _FIRST_CALLS_SCRIPT = r"""
 import sys, threading
 import numpy as np, torch
