@@ -314,15 +314,16 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const Problem p, co
     float m_new = mx;
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) m_new = s0 + 4 * i < ns ? fmaxf(m_new, ml[i][0]) : m_new;
-    if (m_new == -INFINITY) continue;  // this wave has no partial (yet)
-    const float alpha = __builtin_amdgcn_exp2f((mx - m_new) * c);  // 0 the first time
+    // (no maximum yet: no partial, or only ones whose scores are all NaN, and those have to reach the output)
+    const float ref = m_new == -INFINITY ? 0.f : m_new;
+    const float alpha = __builtin_amdgcn_exp2f((mx - ref) * c);  // 0 the first time
     mx = m_new;
     l *= alpha;
     o *= alpha;
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
       const bool live = s0 + 4 * i < ns;
-      const float wgt = live ? __builtin_amdgcn_exp2f((ml[i][0] - mx) * c) : 0.f;
+      const float wgt = live ? __builtin_amdgcn_exp2f((ml[i][0] - ref) * c) : 0.f;
       l = live ? fmaf(ml[i][1], wgt, l) : l;
 #pragma unroll
       for (int e = 0; e < DPL; ++e) o[e] = live ? fmaf(x[i][e], wgt, o[e]) : o[e];

@@ -42,3 +42,23 @@ def test_windows_of_many_partials(case, fp32):
                 assert_parity(o[b], l[b], o_ref, l_ref, fp32_check=fp32, what=f"case {case} sequence {b} token {token}")
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("D,S,closed", [(128, 1024, 4), (64, 1024, 4), (128, 2048, 24)])
+def test_not_a_number_in_a_whole_slice_reaches_the_output(D, S, closed):
+    """Keys of one head are NaN in every fourth slice of 512 rows, so that one wave of the merge kernel holds
+    nothing but partials without a maximum: that group's rows are NaN, the other group's are not."""
+    policy, Hq, Hkv = (3, 2), 4, 2
+    w = W.Workload("nan", 760 + D, 1, 0, Hq, Hkv, D, S, 64, policy, decode=True, max_context=S * (closed + 1))
+    k_done, c_fill = np.array([closed]), np.array([33])
+    q, ks, vs, _, _ = W.decode_inputs(w, k_done, c_fill)
+    c = Cache(w, past_capacity=w.max_context)
+    try:
+        k_new, v_new = fill_cache_for_decode(c, w, ks, vs, k_done, c_fill)
+        keys, _ = c.rows_view(0, 0)
+        keys[:closed * S].view(-1, 4, 512, D)[:, 1] = float("nan")
+        o, l = c.decode(q, k_new, v_new)
+        assert np.isnan(o[0, :2]).all() and np.isnan(l[0, :2]).all()
+        assert np.isfinite(o[0, 2:]).all() and np.isfinite(l[0, 2:]).all()
+    finally:
+        c.close()
