@@ -353,8 +353,9 @@ static hipError_t launch_dq(const Problem &p, const BwdArgs &a, hipStream_t st) 
   const long long seg_rows = a.n < p.S ? a.n : p.S;
   pa.q_blocks_per_seg = (int)((seg_rows + rows - 1) / rows);
   pa.pair_stride = prefill_pair_stride((long long)p.B * (p.Hkv - p.n_past) * (p.g / hs) * pa.n_seg);
-  const long long grid_q = a.cu_seqlens ? (packed_units(a.total, p.S, rows) + p.B) * p.Hkv * (p.g / hs)
-                                        : (long long)p.B * p.Hkv * (p.g / hs) * pa.n_seg * pa.q_blocks_per_seg;
+  pa.packed = a.cu_seqlens && number_packed(p, a.total, pa.n_seg, pa.q_blocks_per_seg, rows);
+  const long long grid_q = pa.packed ? (packed_units(a.total, p.S, rows) + p.B) * p.Hkv * (p.g / hs)
+                                     : (long long)p.B * p.Hkv * (p.g / hs) * pa.n_seg * pa.q_blocks_per_seg;
   if (grid_q <= 0 || grid_q > 0x7fffffffLL) return hipErrorInvalidValue;
   pa.grid_items = (int)grid_q;
   prepare_resolve_divs(p, pa, hs, grid_q);

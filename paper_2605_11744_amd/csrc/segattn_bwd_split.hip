@@ -95,7 +95,8 @@ struct DkvSplitGeom {
 
 template <int D, int NW>
 __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void bwd_dkv_split_kernel(const Problem p, const BwdArgs a,
-                                                                                 const int blocks_per_seg, const int n_seg) {
+                                                                                 const int blocks_per_seg, const int n_seg,
+                                                                                 const int packed) {
   using T = BwdTile<D>;
   using G = DkvSplitGeom<D, NW>;
   constexpr int NC = D / 16, NB = D / 32;
@@ -103,9 +104,9 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void bwd_dkv_split_kerne
 
   // blockIdx -> (key block, segment, KV head, sequence), longest first: the key blocks that reach into the
   // carried tail (they also see the whole next segment), then the others from the segment's start on.
-  // A packed batch numbers the key blocks there are, the heads of a block side by side.
+  // packed (number_packed): the key blocks of the batch are numbered, the heads of a block side by side.
   int kb, seg, kv, b;
-  if (a.cu_seqlens) {
+  if (packed) {
     kv = (int)blockIdx.x % p.Hkv;
     packed_block(p, a.cu_seqlens, (int)blockIdx.x / p.Hkv, kBwdStep, b, seg, kb);
   } else {
@@ -439,10 +440,11 @@ static hipError_t launch_dkv_split_d(const Problem &p, const BwdArgs &a, hipStre
   const int n_seg = (a.n + p.S - 1) / p.S;
   const long long seg_rows = a.n < p.S ? a.n : p.S;
   const int blocks_per_seg = (int)((seg_rows + kBwdStep - 1) / kBwdStep);
-  const long long grid = a.cu_seqlens ? (packed_units(a.total, p.S, kBwdStep) + p.B) * p.Hkv
-                                      : (long long)p.B * p.Hkv * n_seg * blocks_per_seg;
+  const bool packed = a.cu_seqlens && number_packed(p, a.total, n_seg, blocks_per_seg, kBwdStep);
+  const long long grid = packed ? (packed_units(a.total, p.S, kBwdStep) + p.B) * p.Hkv
+                                : (long long)p.B * p.Hkv * n_seg * blocks_per_seg;
   if (grid <= 0 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((bwd_dkv_split_kernel<D, NW>), dim3((unsigned)grid), dim3(64 * NW), lds, st, p, a, blocks_per_seg, n_seg);
+  hipLaunchKernelGGL((bwd_dkv_split_kernel<D, NW>), dim3((unsigned)grid), dim3(64 * NW), lds, st, p, a, blocks_per_seg, n_seg, (int)packed);
   return hipGetLastError();
 }
 hipError_t launch_bwd_dkv_split(const Problem &p, const BwdArgs &a, hipStream_t st) {

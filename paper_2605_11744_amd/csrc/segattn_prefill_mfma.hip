@@ -1071,8 +1071,9 @@ static int waves_d128(const Problem &p, const PrefillArgs &a, int hs) {
   const int n_cu = device_cus();
   const long long seg_rows = a.n_rows < p.S ? a.n_rows : p.S;
   const int rows8 = (8 / hs) * 32;
-  const long long blocks8 = a.cu_seqlens ? packed_units(a.total_rows, p.S, rows8) / p.B + 1
-                                         : (long long)a.n_seg * ((seg_rows + rows8 - 1) / rows8);
+  long long blocks8 = (long long)a.n_seg * ((seg_rows + rows8 - 1) / rows8);
+  if (a.cu_seqlens && packed_units(a.total_rows, p.S, rows8) / p.B + 1 < blocks8)
+    blocks8 = packed_units(a.total_rows, p.S, rows8) / p.B + 1;  // of a sequence on average
   // PAST heads carry the long key ranges unless they attend to a retrieved prefix of bounded size
   const bool long_past = p.n_past > 0 && !(a.cache != nullptr && a.geom.ret_cap > 0) && a.ret_k == nullptr;
   const long long heads = (long long)p.B * (long_past ? p.n_past : p.Hkv) * (p.g / hs);
@@ -1214,8 +1215,9 @@ hipError_t launch_prefill(const Problem &p, const PrefillArgs &a_in, hipStream_t
   a.q_blocks_per_seg = (int)((seg_rows + rows - 1) / rows);
   const long long per_head = (long long)p.B * (p.g / hs) * a.n_seg * a.q_blocks_per_seg;
   const long long parts = a.parts > 1 ? a.parts : 1, parts_other = a.parts_other > 1 ? a.parts_other : 1;
-  const long long grid = a.cu_seqlens ? (packed_units(a.total_rows, p.S, rows) + p.B) * p.Hkv * (p.g / hs)
-                                                  : per_head * (n_first * parts + (p.Hkv - n_first) * parts_other);
+  a.packed = a.cu_seqlens && number_packed(p, a.total_rows, a.n_seg, a.q_blocks_per_seg, rows);
+  const long long grid = a.packed ? (packed_units(a.total_rows, p.S, rows) + p.B) * p.Hkv * (p.g / hs)
+                                  : per_head * (n_first * parts + (p.Hkv - n_first) * parts_other);
   if (grid <= 0 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
   const long long groups = (long long)p.B * (p.Hkv - n_first) * (p.g / hs) * a.n_seg * parts_other;
   a.pair_stride = prefill_pair_stride(groups);

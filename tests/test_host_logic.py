@@ -43,6 +43,15 @@ def test_commit_in_one_launch_in_any_order_of_its_waves(tmp_path):
     assert int(out.split()[1]) == 192
 
 
+def test_items_of_packed_batches(tmp_path):
+    """The numbering of a packed batch's row blocks on the CPU: every block of every sequence once per head,
+    longest first for the heads that see the whole past (up to 64 sequences), empty sequences, segments off
+    the block size, and the search for a block's sequence in batches of up to 300,000."""
+    out = _build_and_run_on_cpu(tmp_path, "packed_items_check")
+    assert out.startswith("ok "), out
+    assert int(out.split()[1]) == 99
+
+
 def test_item_mapping_is_one_to_one_and_longest_first(tmp_path):
     """item_coords (the integer part of the kernels' block-index resolution) over some 10,000 launch
     shapes -- dense, packed, retrieved-prefix and split-prefix forms, every sub-group count -- maps
