@@ -30,7 +30,7 @@ struct DqGeom {
   static constexpr int kBytes = kBufs * kBuf;
 };
 
-template <int D, int HS>
+template <int D, int HS, bool PK>
 __device__ __forceinline__ unsigned bwd_dq_item(const Problem &p, const PrefillArgs &pa, const BwdArgs &a,
                                                 const int bid, unsigned char *const smem, unsigned *const next_from) {
   using T = BwdTile<D>;
@@ -43,7 +43,7 @@ __device__ __forceinline__ unsigned bwd_dq_item(const Problem &p, const PrefillA
   constexpr int kLoadsPerStep = 2 * LPW;  // per wave: K, V
   static_assert((NBUF - 1) * kBuf + kTile + 16 * T::kRowBytes < 65536, "LDS offsets must fit the 16-bit immediate");
 
-  WorkItem w = resolve(p, pa, bid, BQ, HS);
+  WorkItem w = resolve<PK, false>(p, pa, bid, BQ, HS);
   if (!w.valid) return (next_from && threadIdx.x == 0) ? atomicAdd(next_from, 1u) : 0u;
   pin_uniform(w);
   int tid = threadIdx.x;
@@ -298,7 +298,7 @@ __device__ __forceinline__ unsigned bwd_dq_item(const Problem &p, const PrefillA
 
 // One item per workgroup (pa.queue == nullptr), or a resident grid that takes item after item from
 // the per-XCD queues, as the forward kernel does and for the same reasons (prefill_mfma_kernel).
-template <int D, int HS>
+template <int D, int HS, bool PK>
 __global__ __launch_bounds__(256, 2) void bwd_dq_kernel(const Problem p_arg, const PrefillArgs pa_arg, const BwdArgs a_arg) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[DqGeom<D>::kBytes];  // ring of [K tile][V tile]
   __shared__ int claim;
@@ -324,7 +324,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_kernel(const Problem p_arg, con
         return;
       }
     }
-    ticket = bwd_dq_item<D, HS>(p, pa, a, bid, smem, own);
+    ticket = bwd_dq_item<D, HS, PK>(p, pa, a, bid, smem, own);
     drawn = true;
     if (!queued) return;
     lds_barrier();  // the item's last reads of the tiles come before the next item's first loads
@@ -332,6 +332,21 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_kernel(const Problem p_arg, con
 }
 
 static int bwd_heads_per_wg(const Problem &p) { return (p.g % 4 == 0) ? 4 : (p.g % 2 == 0) ? 2 : 1; }
+
+template <int D, int HS, bool PK>
+static hipError_t launch_dq_items(const Problem &p, PrefillArgs &pa, const BwdArgs &a, hipStream_t st) {
+  // resident grid + item queues where every resident workgroup would get more than two items
+  const auto kern = bwd_dq_kernel<D, HS, PK>;
+  static ResidentCount resident_count;  // asked once
+  const int resident = p.tune_queue == 1 ? 0 : resident_count.get((const void *)kern, 256, 0);
+  long long launch = item_queue_grid(p, pa.grid_items, resident);
+  if (launch != pa.grid_items || (p.tune_queue >= 2 && pa.grid_items > 1 && resident > 0)) {
+    pa.queue = item_queue_for(st);
+    if (!pa.queue) launch = pa.grid_items;
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)launch), dim3(256), 0, st, p, pa, a);
+  return hipGetLastError();
+}
 
 template <int D>
 static hipError_t launch_dq(const Problem &p, const BwdArgs &a, hipStream_t st) {
@@ -360,20 +375,14 @@ static hipError_t launch_dq(const Problem &p, const BwdArgs &a, hipStream_t st) 
   pa.grid_items = (int)grid_q;
   prepare_resolve_divs(p, pa, hs, grid_q);
   if (split) return launch_bwd_dq_split(p, pa, a, hs, grid_q, st);
-  // resident grid + item queues where every resident workgroup would get more than two items
-  const void *kern = hs == 4 ? (const void *)bwd_dq_kernel<D, 4> : hs == 2 ? (const void *)bwd_dq_kernel<D, 2>
-                                                                            : (const void *)bwd_dq_kernel<D, 1>;
-  static ResidentCount resident_count[3];  // per heads-per-workgroup instantiation, asked once
-  const int resident = p.tune_queue == 1 ? 0 : resident_count[hs == 4 ? 2 : hs == 2 ? 1 : 0].get(kern, 256, 0);
-  long long launch = item_queue_grid(p, grid_q, resident);
-  if (launch != grid_q || (p.tune_queue >= 2 && grid_q > 1 && resident > 0)) {
-    pa.queue = item_queue_for(st);
-    if (!pa.queue) launch = grid_q;
+  if (pa.packed) {
+    if (hs == 4) return launch_dq_items<D, 4, true>(p, pa, a, st);
+    if (hs == 2) return launch_dq_items<D, 2, true>(p, pa, a, st);
+    return launch_dq_items<D, 1, true>(p, pa, a, st);
   }
-  if (hs == 4) hipLaunchKernelGGL((bwd_dq_kernel<D, 4>), dim3((unsigned)launch), dim3(256), 0, st, p, pa, a);
-  else if (hs == 2) hipLaunchKernelGGL((bwd_dq_kernel<D, 2>), dim3((unsigned)launch), dim3(256), 0, st, p, pa, a);
-  else hipLaunchKernelGGL((bwd_dq_kernel<D, 1>), dim3((unsigned)launch), dim3(256), 0, st, p, pa, a);
-  return hipGetLastError();
+  if (hs == 4) return launch_dq_items<D, 4, false>(p, pa, a, st);
+  if (hs == 2) return launch_dq_items<D, 2, false>(p, pa, a, st);
+  return launch_dq_items<D, 1, false>(p, pa, a, st);
 }
 
 hipError_t launch_bwd_dq(const Problem &p, const BwdArgs &a, hipStream_t st) {

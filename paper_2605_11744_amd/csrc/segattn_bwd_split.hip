@@ -268,13 +268,13 @@ struct DqSplitGeom {
   static constexpr int kBytes = kDqSplitWaves * kWave > kMerge ? kDqSplitWaves * kWave : kMerge;
 };
 
-template <int D, int HS>
+template <int D, int HS, bool PK>
 __global__ __launch_bounds__(64 * kDqSplitWaves, 2) void bwd_dq_split_kernel(const Problem p, const PrefillArgs pa, const BwdArgs a) {
   using T = BwdTile<D>;
   using G = DqSplitGeom<D>;
   constexpr int NC = D / 16, NB = D / 32, R = 32 / HS;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  WorkItem w = resolve(p, pa, (int)blockIdx.x, R, HS);
+  WorkItem w = resolve<PK, false>(p, pa, (int)blockIdx.x, R, HS);
   if (!w.valid) return;
   pin_uniform(w);
   const int tid = threadIdx.x, lane = tid & 63;
@@ -452,13 +452,17 @@ hipError_t launch_bwd_dkv_split(const Problem &p, const BwdArgs &a, hipStream_t 
   return dkv_split_four(p, a) ? launch_dkv_split_d<64, 4>(p, a, st) : launch_dkv_split_d<64, 8>(p, a, st);
 }
 
+template <int D, int HS, bool PK>
+static hipError_t launch_dq_split_pk(const Problem &p, const PrefillArgs &pa, const BwdArgs &a, long long grid, hipStream_t st) {
+  static std::atomic<bool> ready{false};
+  const hipError_t e = allow_lds(bwd_dq_split_kernel<D, HS, PK>, DqSplitGeom<D>::kBytes, ready);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((bwd_dq_split_kernel<D, HS, PK>), dim3((unsigned)grid), dim3(64 * kDqSplitWaves), DqSplitGeom<D>::kBytes, st, p, pa, a);
+  return hipGetLastError();
+}
 template <int D, int HS>
 static hipError_t launch_dq_split_d(const Problem &p, const PrefillArgs &pa, const BwdArgs &a, long long grid, hipStream_t st) {
-  static std::atomic<bool> ready{false};
-  const hipError_t e = allow_lds(bwd_dq_split_kernel<D, HS>, DqSplitGeom<D>::kBytes, ready);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((bwd_dq_split_kernel<D, HS>), dim3((unsigned)grid), dim3(64 * kDqSplitWaves), DqSplitGeom<D>::kBytes, st, p, pa, a);
-  return hipGetLastError();
+  return pa.packed ? launch_dq_split_pk<D, HS, true>(p, pa, a, grid, st) : launch_dq_split_pk<D, HS, false>(p, pa, a, grid, st);
 }
 hipError_t launch_bwd_dq_split(const Problem &p, const PrefillArgs &pa, const BwdArgs &a, int hs, long long grid, hipStream_t st) {
   if (p.D == 128) {

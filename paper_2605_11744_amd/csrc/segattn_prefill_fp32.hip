@@ -15,7 +15,7 @@ __global__ __launch_bounds__(256) void prefill_fp32_kernel(const Problem p, cons
   constexpr int BQ = 64, TK = 32, LD = D + 4;
   __shared__ __attribute__((aligned(16))) float Ks[TK * LD];
   __shared__ __attribute__((aligned(16))) float Vs[TK * LD];
-  const WorkItem w = resolve(p, a, blockIdx.x, BQ, 1);
+  const WorkItem w = a.packed ? resolve<true, false>(p, a, blockIdx.x, BQ, 1) : resolve<false, false>(p, a, blockIdx.x, BQ, 1);
   if (!w.valid) return;
   const int tid = threadIdx.x;
   const int r = tid >> 2, part = tid & 3;

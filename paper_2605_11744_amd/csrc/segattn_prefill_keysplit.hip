@@ -51,7 +51,7 @@ struct SplitGeom {
   __device__ static constexpr int swz_v(int row) { return 4 * ((row / kRowsPer256) % (kChunks / 4)); }
 };
 
-template <int D, int HS>
+template <int D, int HS, bool PK>
 __global__ __launch_bounds__(64 * kSplitWaves, D == 64 ? 4 : 2) void prefill_keysplit_kernel(const Problem p, const PrefillArgs a) {
   using G = SplitGeom<D>;
   constexpr int NC = D / 16, NB = D / 32;
@@ -60,7 +60,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, D == 64 ? 4 : 2) void prefill_key
   constexpr int NL = kSplitStep / RPL;         // loads per tile and tensor
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
-  WorkItem w = resolve(p, a, (int)blockIdx.x, R, HS);
+  WorkItem w = resolve<PK, false>(p, a, (int)blockIdx.x, R, HS);
   if (!w.valid) return;
   pin_uniform(w);
   const int tid = threadIdx.x, lane = tid & 63;
@@ -247,9 +247,9 @@ __global__ __launch_bounds__(64 * kSplitWaves, D == 64 ? 4 : 2) void prefill_key
   }
 }
 
-template <int D, int HS>
-static hipError_t launch_split(const Problem &p, const PrefillArgs &a, long long grid, hipStream_t st) {
-  auto kern = prefill_keysplit_kernel<D, HS>;
+template <int D, int HS, bool PK>
+static hipError_t launch_split_d(const Problem &p, const PrefillArgs &a, long long grid, hipStream_t st) {
+  auto kern = prefill_keysplit_kernel<D, HS, PK>;
   static std::atomic<bool> ready{false};  // the same answer whoever asks first
   if (!ready.load(std::memory_order_acquire)) {
     const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, SplitGeom<D>::kBytes);
@@ -258,6 +258,11 @@ static hipError_t launch_split(const Problem &p, const PrefillArgs &a, long long
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * kSplitWaves), SplitGeom<D>::kBytes, st, p, a);
   return hipGetLastError();
+}
+
+template <int D, int HS>
+static hipError_t launch_split(const Problem &p, const PrefillArgs &a, long long grid, hipStream_t st) {
+  return a.packed ? launch_split_d<D, HS, true>(p, a, grid, st) : launch_split_d<D, HS, false>(p, a, grid, st);
 }
 
 hipError_t launch_prefill_keysplit(const Problem &p, const PrefillArgs &a, int hs, long long grid, hipStream_t st) {

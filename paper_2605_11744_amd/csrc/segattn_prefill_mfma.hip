@@ -109,7 +109,7 @@ __device__ inline float half_sum(float x) {
 // O^T in accumulation registers through inline-asm products; wherever the register allocator
 // then moved O^T at a control-flow merge, the move could read an accumulator whose product
 // was still in the pipeline, and results depended on register allocation.
-template <int D, int HS, int QB, int NW>
+template <int D, int HS, int QB, int NW, bool PK>
 __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const PrefillArgs &a, const int bid,
                                                       unsigned char *const smem, unsigned *const next_from) {
   // next_from: nullptr, or the queue counter this workgroup takes its next item from.  Thread 0
@@ -126,7 +126,7 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
   constexpr int kAhead = kPair ? 2 : 1;  // whole steps of loads that may still be in flight at a sync
   static_assert(LPW >= 1, "too many waves for this tile");
 
-  WorkItem w = resolve(p, a, bid, BQ, HS);
+  WorkItem w = resolve<PK, !PK>(p, a, bid, BQ, HS);
   if (!w.valid) return (next_from && threadIdx.x == 0) ? atomicAdd(next_from, 1u) : 0u;
   pin_uniform(w);
 
@@ -833,7 +833,7 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
 // the output of this one is being written (prefill_mfma_item), so the round trip to the counter
 // is hidden.  Each queue's counter has a 128-byte line of its own; the last workgroup of a launch
 // clears them.
-template <int D, int HS, int QB, int NW>
+template <int D, int HS, int QB, int NW, bool PK>
 __global__ __launch_bounds__(64 * NW, 8 / (NW * QB)) void prefill_mfma_kernel(const Problem p_arg, const PrefillArgs a_arg) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   // take_item's hand-over word lives at the start of the ring, which is idle between two items (a
@@ -863,7 +863,7 @@ __global__ __launch_bounds__(64 * NW, 8 / (NW * QB)) void prefill_mfma_kernel(co
         return;
       }
     }
-    ticket = prefill_mfma_item<D, HS, QB, NW>(p, a, bid, smem, own);
+    ticket = prefill_mfma_item<D, HS, QB, NW, PK>(p, a, bid, smem, own);
     drawn = true;
     if (!queued) return;
   }
@@ -1012,12 +1012,12 @@ unsigned *item_queue_for(hipStream_t st) {
   return base[dev] + kQueueWords * set;
 }
 
-template <int D, int HS, int QB, int NW>
+template <int D, int HS, int QB, int NW, bool PK>
 static hipError_t launch_mfma(const Problem &p, const PrefillArgs &a_in, long long grid, hipStream_t st) {
   constexpr int ring = ring_slots(NW, QB) * StepGeom<D>::kSlotBytes;
   constexpr int epilogue = NW * 32 * (D * 4 + 8);  // fp32 output staging, one block per wave
   constexpr int lds = ring > epilogue ? ring : epilogue;
-  auto kern = prefill_mfma_kernel<D, HS, QB, NW>;
+  auto kern = prefill_mfma_kernel<D, HS, QB, NW, PK>;
   // First launch of this instantiation: allow the kernel its LDS, ask how many workgroups the chip
   // holds.  Both steps give the same result whoever does them, so host threads racing through
   // their first call simply do them twice; `ready` is set only after the attribute is in place.
@@ -1239,23 +1239,25 @@ hipError_t launch_prefill(const Problem &p, const PrefillArgs &a_in, hipStream_t
   prepare_resolve_divs(p, a, hs, grid);
   if (fp32) return launch_prefill_fp32(p, a, grid, st);
   hipError_t e;
-  if (keysplit) {
-    e = launch_prefill_keysplit(p, a, hs, grid, st);
-  } else if (p.D == 128) {
-    if (nw == 8) {
-      if (hs == 4) e = launch_mfma<128, 4, 1, 8>(p, a, grid, st);
-      else if (hs == 2) e = launch_mfma<128, 2, 1, 8>(p, a, grid, st);
-      else e = launch_mfma<128, 1, 1, 8>(p, a, grid, st);
-    } else {
-      if (hs == 4) e = launch_mfma<128, 4, 1, 4>(p, a, grid, st);
-      else if (hs == 2) e = launch_mfma<128, 2, 1, 4>(p, a, grid, st);
-      else e = launch_mfma<128, 1, 1, 4>(p, a, grid, st);
+  auto launch = [&](auto packed) {
+    constexpr bool PK = decltype(packed)::value;
+    if (p.D == 128 && nw == 8) {
+      if (hs == 4) return launch_mfma<128, 4, 1, 8, PK>(p, a, grid, st);
+      if (hs == 2) return launch_mfma<128, 2, 1, 8, PK>(p, a, grid, st);
+      return launch_mfma<128, 1, 1, 8, PK>(p, a, grid, st);
     }
-  } else {
-    if (hs == 4) e = launch_mfma<64, 4, 1, 4>(p, a, grid, st);
-    else if (hs == 2) e = launch_mfma<64, 2, 1, 4>(p, a, grid, st);
-    else e = launch_mfma<64, 1, 1, 4>(p, a, grid, st);
-  }
+    if (p.D == 128) {
+      if (hs == 4) return launch_mfma<128, 4, 1, 4, PK>(p, a, grid, st);
+      if (hs == 2) return launch_mfma<128, 2, 1, 4, PK>(p, a, grid, st);
+      return launch_mfma<128, 1, 1, 4, PK>(p, a, grid, st);
+    }
+    if (hs == 4) return launch_mfma<64, 4, 1, 4, PK>(p, a, grid, st);
+    if (hs == 2) return launch_mfma<64, 2, 1, 4, PK>(p, a, grid, st);
+    return launch_mfma<64, 1, 1, 4, PK>(p, a, grid, st);
+  };
+  if (keysplit) e = launch_prefill_keysplit(p, a, hs, grid, st);
+  else if (a.packed) e = launch(std::true_type{});
+  else e = launch(std::false_type{});
   if (e != hipSuccess || !cut) return e;
   long long row_heads[2], wgs[2];
   for (int i = 0; i < 2; ++i) {

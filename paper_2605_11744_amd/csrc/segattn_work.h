@@ -228,6 +228,7 @@ __host__ __device__ inline ItemCoords item_coords(const Problem &p, const Prefil
 }
 
 // Coordinates -> the item's key spans, query rows and outputs.
+template <bool kPacked, bool kPieces>
 __device__ inline WorkItem resolve_at(const Problem &p, const PrefillArgs &a, const ItemCoords &ic, int rows_per_wg,
                                       int heads_per_wg) {
   WorkItem w;
@@ -239,11 +240,11 @@ __device__ inline WorkItem resolve_at(const Problem &p, const PrefillArgs &a, co
   w.b = b;
   w.t0 = qblk * rows_per_wg;
   const long long kv_stride = (long long)p.Hkv * p.D;
-  if (a.cache == nullptr) {  // SEQ mode: prefix read from k/v by absolute position
+  if (kPacked || a.cache == nullptr) {  // SEQ mode: prefix read from k/v by absolute position
     // dense batch: sequence b occupies rows [b*N, (b+1)*N); packed ragged batch: rows
     // [cu[b], cu[b+1]) and lse is [Hq, total rows]
     long long N = a.n_rows, base = (long long)b * N, lse_base = (long long)b * p.Hq * N, lse_stride = N;
-    if (a.cu_seqlens) {
+    if (kPacked || a.cu_seqlens) {
       base = a.cu_seqlens[b];
       N = a.cu_seqlens[b + 1] - base;
       lse_base = base;
@@ -261,7 +262,7 @@ __device__ inline WorkItem resolve_at(const Problem &p, const PrefillArgs &a, co
     w.k1 = a.k + (base + s) * kv_stride + (long long)kv * p.D;
     w.v1 = a.v + (base + s) * kv_stride + (long long)kv * p.D;
     w.stride0 = w.stride1 = kv_stride;
-    if (a.ret_k != nullptr && (pol & SEGATTN_PAST)) {
+    if (!kPacked && a.ret_k != nullptr && (pol & SEGATTN_PAST)) {
       // retrieved prefix of (b, segment, head): R dense gathered rows (none for the first segment)
       const long long slot = ((long long)b * a.n_seg + seg) * p.n_past + p.past_before[kv];
       w.n0 = seg > 0 ? a.ret_R : 0;
@@ -298,7 +299,7 @@ __device__ inline WorkItem resolve_at(const Problem &p, const PrefillArgs &a, co
   w.out_heads = p.Hq;
   w.ohead0 = kv * p.g + hs * heads_per_wg;
   w.wide = p.out_fp32 != 0;
-  if (a.piece_rows.d != 0) {  // (the stateful form only)
+  if (kPieces && a.piece_rows.d != 0) {  // (the stateful form only)
     const PrefillArgs::PieceList &pl = a.piece_list[hidx < a.piece_list[1].head0 ? 0 : 1];
     const int pieces = piece_count(w.n0, w.n1, a.piece_rows, pl.most);
     if (part >= pieces) {
@@ -441,13 +442,17 @@ __device__ inline ItemCoords packed_coords(const Problem &p, const PrefillArgs &
   return ic;
 }
 
-// blockIdx -> work item.
+// blockIdx -> work item.  kPacked: the launch has PrefillArgs::packed set; kPieces: it may cut prefixes.  Fixed per
+// instantiation, since a kernel that can do everything is slower at each (code and argument words a short
+// launch waits for; key-split form, 300 rows, 32/8 heads of 64: 9.7 us with all of it, 8.3 with its own;
+// general form, 500 rows: 14.6 and 14.3).
+template <bool kPacked, bool kPieces>
 __device__ inline WorkItem resolve(const Problem &p, const PrefillArgs &a, int bid, int rows_per_wg,
                                    int heads_per_wg) {
   const int items = a.grid_items > 0 ? a.grid_items : (int)gridDim.x;
-  const ItemCoords ic = a.packed ? packed_coords(p, a, bid, items, rows_per_wg, heads_per_wg)
-                                 : item_coords(p, a, bid, items, heads_per_wg);
-  return resolve_at(p, a, ic, rows_per_wg, heads_per_wg);
+  const ItemCoords ic = kPacked ? packed_coords(p, a, bid, items, rows_per_wg, heads_per_wg)
+                                : item_coords(p, a, bid, items, heads_per_wg);
+  return resolve_at<kPacked, kPieces>(p, a, ic, rows_per_wg, heads_per_wg);
 }
 
 __device__ inline int uniform_i32(int x) { return __builtin_amdgcn_readfirstlane(x); }
@@ -478,8 +483,6 @@ __device__ inline void pin_uniform(WorkItem &w) {
   w.v0 = uniform_ptr(w.v0);
   w.k1 = uniform_ptr(w.k1);
   w.v1 = uniform_ptr(w.v1);
-  w.out = uniform_ptr(w.out);
-  w.lse = uniform_ptr(w.lse);
 }
 
 __device__ inline float bf16_bits_to_f32(unsigned short h) { return __uint_as_float((unsigned)h << 16); }
