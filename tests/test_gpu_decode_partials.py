@@ -62,3 +62,27 @@ def test_not_a_number_in_a_whole_slice_reaches_the_output(D, S, closed):
         assert np.isfinite(o[0, 2:]).all() and np.isfinite(l[0, 2:]).all()
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("closed,fill", [(0, 0), (0, 1), (0, 31), (1, 0), (1, 32), (3, 95), (5, 512)])
+def test_what_lies_in_the_newest_rows_place_does_not_count(D, closed, fill):
+    """The split kernel takes the newest row from the caller; its place in the cache, and everything behind it,
+    holds NaN.  Windows of one row, of a whole number of 32-row tiles and one more, and slices (of 512 rows)
+    that hold nothing but the newest row."""
+    policy, S, T = (3, 1, 2, 0), 1024, 64
+    w = W.Workload("place", 770 + D + fill, 1, 0, 8, 4, D, S, T, policy, decode=True, max_context=S * (closed + 1))
+    k_done, c_fill = np.array([closed]), np.array([fill + 1])
+    q, ks, vs, _, _ = W.decode_inputs(w, k_done, c_fill)
+    c = Cache(w, past_capacity=w.max_context)
+    try:
+        for h in range(4):
+            for rows in c.rows_view(0, h):
+                rows.fill_(float("nan"))
+        k_new, v_new = fill_cache_for_decode(c, w, ks, vs, k_done, c_fill)
+        o, l = c.decode(q, k_new, v_new)
+        kf, vf = full_history(ks[0], vs[0], closed * S + fill + 1, 4, D)
+        o_ref, l_ref = orc.decode_attend(q[0], kf, vf, seg_len=S, tail_len=T, kv_policy=policy)
+        assert_parity(o[0], l[0], o_ref, l_ref, fp32_check=False, what=f"{closed} segments, {fill} rows")
+    finally:
+        c.close()
