@@ -209,15 +209,18 @@ segattn_status seg_attn_fwd(segattn_ctx *ctx, const void *q, const void *k, cons
   a.geom = ctx->g;
   a.n_rows = m;
   a.n_seg = 1;
-  // longest prefixes: how far the launch's work should be split
+  // longest prefixes: how far the launch's work should be split; shortest: whether all are cut alike
+  a.min_first_prefix = a.min_other_prefix = 1ll << 40;
   for (int b = 0; b < p.B; ++b)
     for (int h = 0; h < p.Hkv; ++h) {
       const size_t i = (size_t)b * p.Hkv + h;
       const bool past = p.policy[h] & SEGATTN_PAST;
       const long long before = past ? (ctx->g.ret_cap ? ctx->ret[b] : ctx->pool[i] - ctx->lo[i])
                                     : (p.policy[h] & SEGATTN_TAIL) ? ctx->tail[b] : 0;
-      long long &most = past && ctx->g.ret_cap == 0 ? a.max_first_prefix : a.max_other_prefix;
-      if (before + ctx->fill[b] > most) most = before + ctx->fill[b];
+      const bool first = past && ctx->g.ret_cap == 0;
+      long long &most = first ? a.max_first_prefix : a.max_other_prefix, &least = first ? a.min_first_prefix : a.min_other_prefix;
+      most = std::max(most, before + ctx->fill[b]);
+      least = std::min(least, before + ctx->fill[b]);
     }
   return hip_status(launch_prefill(p, a, (hipStream_t)stream));
 }

@@ -125,10 +125,12 @@ struct PrefillArgs {
   int parts, parts_other;  // most pieces of a head of the first / the common list; 0 or 1: no split
   FastDiv piece_rows;      // .d: rows of a piece, a multiple of the 32-key step; 0: nothing is cut
   long long max_first_prefix, max_other_prefix;  // host: most prefix rows in a window of either list
+  long long min_first_prefix, min_other_prefix;  // host: fewest
   struct PieceList {       // workspace of the heads of one list: 0 the first, 1 the common one
     float *out;            // [B][most][n_rows][heads][D]
     float *lse;            // [B][most][heads][n_rows]
     int most, heads;       // its parts / parts_other, its query heads
+    int least;             // fewest pieces of a head
     int head0;             // its first position in the list of KV heads
   } piece_list[2];
   // Work items of the launch (0: the grid size) and, where the workgroups take their items from

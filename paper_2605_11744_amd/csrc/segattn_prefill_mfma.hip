@@ -874,65 +874,91 @@ __global__ __launch_bounds__(64 * NW, 8 / (NW * QB)) void prefill_mfma_kernel(co
 // =============================================================================================
 // Every piece of a head's keys left a normalised fp32 output row and its LSE in the workspace;
 // softmax over the union is the LSE-weighted mean of the pieces (the same identity the decode path
-// and a sharded prefix use).  32 lanes per (sequence, row, head): lane i forms the weights of the
-// pieces i, i + 32, ..., then the lanes hold D/32 channels each.  Bound by memory latency (the
-// pieces come from other XCDs' caches): one round trip for the LSEs, and the rows' loads do not
-// depend on each other and are unrolled.  Where the heads of a list have more than kWidePieces
-// pieces a workgroup takes one row: its eight lane groups take every eighth piece and meet in LDS;
-// otherwise it takes eight rows.  Measured, 173 rows of 8 heads with 35 pieces each and 24 heads with
+// and a sharded prefix use).  32 lanes per (sequence, row, head), D/32 channels each.  Bound by memory
+// latency (the pieces come from other XCDs' caches), so by the round trips that depend on each other.  Heads
+// of at most kWidePieces pieces: eight rows per workgroup, all pieces and LSEs of a row requested at once,
+// before the number of pieces is known (the workspace has room for the list's most; surplus ones are left
+// out), and the head's counters asked only where not all heads of the list are cut alike.  More pieces: one
+// row per workgroup, lane i forms the weights of the pieces i, i + 32, ..., its eight lane groups take
+// every eighth piece and meet in LDS.  Measured, 173 rows of 8 heads with 35 pieces each and 24 heads with
 // two: 17.4 us with eight rows per workgroup everywhere (a round trip per eight pieces), 19.2 us with
-// one everywhere (5536 workgroups), 10.7 us like this.
+// one everywhere (5536 workgroups), 10.7 us like this; 4096 rows of 8 heads with two pieces: 13.9 us with
+// the counters, LSEs and pieces one after the other, 10.2 at once.
 // wgs0: workgroups of list 0; rows0, rows1: (sequence, row, head) items of the lists, 0 where uncut.
 constexpr int kWidePieces = 8;
 template <int D>
 __global__ __launch_bounds__(256) void prefill_part_combine_kernel(const Problem p, const PrefillArgs a, const int wgs0,
-                                                                   const long long rows0, const long long rows1) {
+                                                                   const unsigned rows0, const unsigned rows1) {
   constexpr int CPL = D / 32;  // channels per lane
   typedef float f32xc __attribute__((ext_vector_type(CPL)));
   const int list = (int)blockIdx.x < wgs0 ? 0 : 1;
   const PrefillArgs::PieceList &pl = a.piece_list[list];
   const bool wide = pl.most > kWidePieces;
   const int grp = threadIdx.x >> 5, lane = threadIdx.x & 31;
-  const int wg = (int)blockIdx.x - (list ? wgs0 : 0);
-  const long long m = a.n_rows;
-  const long long item = wide ? wg : (long long)wg * 8 + grp;
+  const unsigned wg = blockIdx.x - (list ? wgs0 : 0);
+  const unsigned m = a.n_rows;
+  const unsigned item = wide ? wg : wg * 8 + grp;
   if (item >= (list ? rows1 : rows0)) return;
-  const int hc = (int)(item % pl.heads);
-  const long long row = (item / pl.heads) % m;
-  const int b = (int)(item / (pl.heads * m));
+  const unsigned token = item / pl.heads;
+  const int hc = (int)(item - token * pl.heads), b = (int)(token / m);
+  const unsigned row = token - b * m;
   const int hl = pl.head0 * p.g + hc;  // position in the list of all heads
   const int kv = p.order[hl / p.g];
-  int lo, seg_row0;
-  const int *meta = meta_ro(a.cache, a.geom, p, b, kv);
-  window_of(p, a.geom, kv, meta, lo, seg_row0);
-  const int pieces = piece_count(seg_row0 + meta[META_FILL] - lo, a.n_rows, a.piece_rows, pl.most);
+  const long long slot = (long long)m * pl.heads;  // rows of one piece
+  const float *lse = pl.lse + b * pl.most * slot + (long long)hc * m + row;
+  const float *src = pl.out + (b * pl.most * slot + (long long)row * pl.heads + hc) * D + lane * CPL;
+  float ls[kWidePieces];
+  f32xc x[kWidePieces];
+  if (!wide) {  // (one test for all lanes: pl.most is the launch's)
+#pragma unroll
+    for (int i = 0; i < kWidePieces; ++i)
+      if (i < pl.most) {
+        ls[i] = lse[i * slot];
+        x[i] = *(const f32xc *)(src + i * slot * D);
+      }
+  }
+  int pieces = pl.most;
+  if (pl.least != pl.most) {
+    int lo, seg_row0;
+    const int *meta = meta_ro(a.cache, a.geom, p, b, kv);
+    window_of(p, a.geom, kv, meta, lo, seg_row0);
+    pieces = piece_count(seg_row0 + meta[META_FILL] - lo, a.n_rows, a.piece_rows, pl.most);
+  }
   if (pieces < 2) return;  // written by its only workgroup
   const int head = kv * p.g + hl % p.g;
-  const long long slot = m * pl.heads;  // rows of one piece
-  const float *lse = pl.lse + (long long)b * pl.most * slot + hc * m + row;
-  const float *src = pl.out + (((long long)b * pl.most * m + row) * pl.heads + hc) * D + lane * CPL;
-  float mx = -INFINITY;
-  for (int p0 = 0; p0 < pieces; p0 += 32) mx = fmaxf(mx, p0 + lane < pieces ? lse[(p0 + lane) * slot] : -INFINITY);
-#pragma unroll
-  for (int sh = 16; sh >= 1; sh >>= 1) mx = fmaxf(mx, __shfl_xor(mx, sh, 32));
-  float sum = 0.f, acc[CPL];
+  float mx = -INFINITY, sum = 0.f, acc[CPL];
 #pragma unroll
   for (int e = 0; e < CPL; ++e) acc[e] = 0.f;
-  for (int p0 = 0; p0 < pieces; p0 += 32) {
-    const float mine = p0 + lane < pieces ? __expf(lse[(p0 + lane) * slot] - mx) : 0.f;
-    const int n = pieces - p0 < 32 ? pieces - p0 : 32;
-    sum += mine;
+  if (!wide) {
+#pragma unroll
+    for (int i = 0; i < kWidePieces; ++i)
+      if (i < pieces) mx = fmaxf(mx, ls[i]);
+#pragma unroll
+    for (int i = 0; i < kWidePieces; ++i)
+      if (i < pieces) {
+        const float wgt = __expf(ls[i] - mx);
+        sum += wgt;
+#pragma unroll
+        for (int e = 0; e < CPL; ++e) acc[e] = fmaf(wgt, x[i][e], acc[e]);
+      }
+  } else {
+    for (int p0 = 0; p0 < pieces; p0 += 32) mx = fmaxf(mx, p0 + lane < pieces ? lse[(p0 + lane) * slot] : -INFINITY);
+#pragma unroll
+    for (int sh = 16; sh >= 1; sh >>= 1) mx = fmaxf(mx, __shfl_xor(mx, sh, 32));
+    for (int p0 = 0; p0 < pieces; p0 += 32) {
+      const float mine = p0 + lane < pieces ? __expf(lse[(p0 + lane) * slot] - mx) : 0.f;
+      const int n = pieces - p0 < 32 ? pieces - p0 : 32;
+      sum += mine;
 #pragma unroll 8
-    for (int i = wide ? grp : 0; i < n; i += wide ? 8 : 1) {
-      const float wgt = __shfl(mine, i, 32);
-      const f32xc x = *(const f32xc *)(src + (p0 + i) * slot * D);
+      for (int i = grp; i < n; i += 8) {
+        const float wgt = __shfl(mine, i, 32);
+        const f32xc row_x = *(const f32xc *)(src + (p0 + i) * slot * D);
 #pragma unroll
-      for (int e = 0; e < CPL; ++e) acc[e] = fmaf(wgt, x[e], acc[e]);
+        for (int e = 0; e < CPL; ++e) acc[e] = fmaf(wgt, row_x[e], acc[e]);
+      }
     }
-  }
 #pragma unroll
-  for (int sh = 16; sh >= 1; sh >>= 1) sum += __shfl_xor(sum, sh, 32);
-  if (wide) {
+    for (int sh = 16; sh >= 1; sh >>= 1) sum += __shfl_xor(sum, sh, 32);
     __shared__ float sm[8][D];
 #pragma unroll
     for (int e = 0; e < CPL; ++e) sm[grp][lane * CPL + e] = acc[e];
@@ -1141,7 +1167,7 @@ static void plan_pieces(const Problem &p, PrefillArgs &a, int hs, int rows, int 
     const int c1 = n_other > 0 ? piece_count((int)a.max_other_prefix, m, t, 1 << 20) : 1;
     if (c0 == 1 && c1 == 1) break;
     const long long rh = (long long)p.B * m * p.g * ((c0 > 1 ? n_first * c0 : 0) + (c1 > 1 ? n_other * c1 : 0));
-    if (rh * (p.D + 1) > ws_floats) continue;
+    if (rh * (p.D + 1) > ws_floats || rh >= (1ll << 31)) continue;
     long long even = len;  // pieces of one length instead of a last one of up to half as much again
     if (c0 == 1 || c1 == 1) {
       even = c0 > 1 ? (sf + c0 - 1) / c0 : (so + c1 - 1) / c1;
@@ -1165,8 +1191,9 @@ static void plan_pieces(const Problem &p, PrefillArgs &a, int hs, int rows, int 
   if (row_heads == 0) return;
   const long long rows_first = a.parts > 1 ? (long long)p.B * a.parts * m * n_first * p.g : 0;
   float *const out = (float *)(a.cache + (own_ws ? a.geom.part_off : dec_off)), *const lse = out + row_heads * p.D;
-  a.piece_list[0] = {out, lse, a.parts, n_first * p.g, 0};
-  a.piece_list[1] = {out + rows_first * p.D, lse + rows_first, a.parts_other, n_other * p.g, n_first};
+  auto least = [&](long long prefix, int most) { return most > 1 ? piece_count((int)prefix, m, a.piece_rows, most) : 1; };
+  a.piece_list[0] = {out, lse, a.parts, n_first * p.g, least(a.min_first_prefix, a.parts), 0};
+  a.piece_list[1] = {out + rows_first * p.D, lse + rows_first, a.parts_other, n_other * p.g, least(a.min_other_prefix, a.parts_other), n_first};
 }
 
 // Key-split form or hand-pipelined form?  Both are estimated in microseconds from their longest chain
@@ -1267,9 +1294,9 @@ hipError_t launch_prefill(const Problem &p, const PrefillArgs &a_in, hipStream_t
   }
   const dim3 grid_c((unsigned)(wgs[0] + wgs[1]));
   if (p.D == 128)
-    hipLaunchKernelGGL(prefill_part_combine_kernel<128>, grid_c, dim3(256), 0, st, p, a, (int)wgs[0], row_heads[0], row_heads[1]);
+    hipLaunchKernelGGL(prefill_part_combine_kernel<128>, grid_c, dim3(256), 0, st, p, a, (int)wgs[0], (unsigned)row_heads[0], (unsigned)row_heads[1]);
   else
-    hipLaunchKernelGGL(prefill_part_combine_kernel<64>, grid_c, dim3(256), 0, st, p, a, (int)wgs[0], row_heads[0], row_heads[1]);
+    hipLaunchKernelGGL(prefill_part_combine_kernel<64>, grid_c, dim3(256), 0, st, p, a, (int)wgs[0], (unsigned)row_heads[0], (unsigned)row_heads[1]);
   return hipGetLastError();
 }
 
