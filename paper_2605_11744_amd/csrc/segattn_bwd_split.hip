@@ -15,6 +15,7 @@
 // products, P and dS rounded to bf16).  The price is that every wave stages its own tiles (16 KB a
 // step at D = 128) where the other kernels share one among four waves, and that nothing is scheduled by
 // hand; the launchers take these forms only where the chain is what bounds the other one.
+#include <math.h>
 #include <string.h>
 
 #include <atomic>
@@ -377,7 +378,10 @@ static hipError_t allow_lds(K kern, int bytes, std::atomic<bool> &ready) {
 // all and the rounds of workgroups; measured on windows of 600 to 8192 rows and packed batches, 4/4,
 // 8/2, 8/8, 16/2, 16/4 and 32/8 heads.  A forced launch shape keeps the other forms.
 //   dQ     one chain per workgroup: 7 + 0.6 a step (D = 64), 8 + 0.65 (D = 128), or the wave-steps at
-//          5.9e-4 and 8e-4; split: 7 + 0.15 + 8.3e-4 and 8 + 0.2 + 1.5e-3, 5 a further round of 256 workgroups.
+//          5.9e-4 and 8e-4; split: 7 + 0.15 + 8.3e-4 and 8 + 0.2 + 1.5e-3, and for every further round of workgroups,
+//          however few they are, 4 (D = 64) or 8, less the longer the chains (0 at 64 steps: 2048 rows, 8/8 heads of 128
+//          with segments of 512, 512 workgroups, backward 80 -> 67 us; six packed sequences of 33 to 500 rows,
+//          8/2 heads of 128, 332 workgroups, would lose 3 of 34).
 //          1024 rows, 4/4 heads, D = 64: backward 49 -> 36 us; 8/8, D = 128: 62 -> 55; 32/8 never gains.
 //   dK/dV  a 128-key workgroup's chain over the whole group: 8 + 0.6 a step (D = 64), 9 + 0.85 (D = 128), or
 //          the 128-key steps at 0.5 and 0.95 a CU; split: the wave-steps at 5.9e-4 and 1.9e-3 plus half the
@@ -386,11 +390,11 @@ static hipError_t allow_lds(K kern, int bytes, std::atomic<bool> &ready) {
 bool bwd_dq_split_pays(const Problem &p, const BwdArgs &a) {
   if (p.tune_waves != 0 || p.tune_queue != 0) return false;
   const StepCount c = count_steps(p, a.n, a.cu_seqlens ? a.total : 0, 0);
-  const double rounds = c.blocks > 256 ? c.blocks / 256 - 1 : 0;
+  const double rounds = (ceil(c.blocks / device_cus()) - 1) * (c.longest < 64 ? 1 - c.longest / 64 : 0);
   const bool d64 = p.D == 64;
   const double chain = (d64 ? 0.6 : 0.65) * c.longest, even = (d64 ? 5.9e-4 : 8e-4) * c.steps;
   const double piped = (d64 ? 7 : 8) + (chain > even ? chain : even);
-  const double split = (d64 ? 7 + 0.15 * c.longest + 8.3e-4 * c.steps : 8 + 0.2 * c.longest + 1.5e-3 * c.steps) + 5 * rounds;
+  const double split = (d64 ? 7 + 0.15 * c.longest + 8.3e-4 * c.steps : 8 + 0.2 * c.longest + 1.5e-3 * c.steps) + (d64 ? 4 : 8) * rounds;
   return split < 0.9 * piped;
 }
 namespace {
@@ -399,13 +403,14 @@ struct DkvCount {
 };
 DkvCount count_dkv(const Problem &p, const BwdArgs &a) {
   const double n = a.n, seqs = a.cu_seqlens ? (double)a.total / n : p.B;
-  const double seg = n < p.S ? n : p.S, segs = n / seg, per_seg = (seg + 31) / 32;
+  const double seg = n < p.S ? n : p.S, segs = n / seg, per_seg = row_blocks((long long)seg, p.S);
   bool tails = false;
   int n_tail = 0;
   for (int h = 0; h < p.Hkv; ++h) n_tail += p.policy[h] & SEGATTN_TAIL ? 1 : 0;
   tails = n_tail > 0 && segs > 1 && p.T > 0;
   const double next = segs < 2 ? n - seg : seg;  // rows of a following segment
-  const double own = segs * per_seg * (per_seg + 1) / 2;
+  const double last = row_blocks(a.n % p.S, p.S);
+  const double own = a.n / p.S * per_seg * (per_seg + 1) / 2 + last * (last + 1) / 2;
   const double tail = tails ? (segs > 2 ? segs - 1 : 1) * ((p.T + 31) / 32) * next / 32 : 0;
   DkvCount c;
   c.steps = seqs * p.g * (p.Hkv * own + n_tail * tail);
@@ -413,7 +418,7 @@ DkvCount count_dkv(const Problem &p, const BwdArgs &a) {
   const double t128 = tails ? ((p.T > 128 ? p.T : 128) + next) / 32 : 0;
   c.longest = per_seg > t32 ? per_seg : t32;
   c.longest128 = per_seg > t128 ? per_seg : t128;
-  c.blocks = seqs * p.Hkv * segs * per_seg;
+  c.blocks = seqs * p.Hkv * row_blocks(a.n, p.S);
   return c;
 }
 }  // namespace
@@ -421,15 +426,21 @@ bool bwd_dkv_split_pays(const Problem &p, const BwdArgs &a) {
   if (p.tune_waves != 0 || p.tune_queue != 0) return false;
   const DkvCount c = count_dkv(p, a);
   const bool d64 = p.D == 64;
-  const double chain = (d64 ? 0.6 : 0.85) * c.longest128 * p.g, even = (d64 ? 0.5 : 0.95) * c.steps / 4 / 256;
+  const double chain = (d64 ? 0.6 : 0.85) * c.longest128 * p.g, even = (d64 ? 0.5 : 0.95) * c.steps / 4 / device_cus();
   const double piped = (d64 ? 8 : 9) + (chain > even ? chain : even);
   const double split = d64 ? 8 + 5.9e-4 * c.steps + 0.5 * 1.2 * c.longest * p.g / 8
                            : 9 + 1.9e-3 * c.steps + 0.5 * 2.0 * c.longest * p.g / 4;
   return split < 0.9 * piped;
 }
-// D = 64: four waves, two workgroups per CU, from three workgroups per CU on (16/4 heads, packed batch of 6.4K
-// rows, 836 blocks: 20 us saved against 11; 512 blocks, 8192 rows of 8/2 heads: 167 against 207).
-static bool dkv_split_four(const Problem &p, const BwdArgs &a) { return count_dkv(p, a).blocks >= 768; }
+// D = 64: four waves, two workgroups per CU, from two and a half workgroups per CU on, and with short chains as soon as
+// eight waves (one workgroup per CU) would take a second round.  Backward pass, four waves / eight: 700-row sequences
+// of 32/8 heads, S = 64, 704 blocks, chain 10: 40.1 / 43.4 us; 16/4 heads, S = 128, 352 blocks, chain 24: 34.5 / 37.2; S = 256,
+// chain 40: 40.3 / 39.9; 16/4 heads, S = 512, chain 80: 368 blocks 44.0 / 41.6, 752 blocks 83.2 / 86.1; 8192 rows of 8/2
+// heads, S = 1024, 512 blocks, chain 160: 207.3 / 200.0.
+static bool dkv_split_four(const Problem &p, const BwdArgs &a) {
+  const DkvCount c = count_dkv(p, a);
+  return 2 * c.blocks >= 5 * device_cus() || (c.blocks > device_cus() && c.longest * p.g <= 40);
+}
 
 template <int D, int NW>
 static hipError_t launch_dkv_split_d(const Problem &p, const BwdArgs &a, hipStream_t st) {

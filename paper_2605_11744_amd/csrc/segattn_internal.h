@@ -218,14 +218,16 @@ inline void prepare_resolve_divs(const Problem &p, PrefillArgs &a, int heads_per
 struct StepCount {
   double steps, longest, blocks;
 };
+// 32-row blocks of a sequence of n rows (no block spans two segments).
+inline double row_blocks(long long n, int S) { return (double)(n / S * ((S + 31) / 32) + (n % S + 31) / 32); }
 inline StepCount count_steps(const Problem &p, long long n, long long total_rows, int retrieved) {
   const double seqs = total_rows > 0 ? (double)total_rows / n : p.B;
-  const double seg = (double)(n < p.S ? n : p.S), segs = n / seg, per_seg = (seg + 31) / 32;
+  const double seg = (double)(n < p.S ? n : p.S), segs = n / seg, blocks = row_blocks(n, p.S);
   const double bounded = segs > 1 ? (retrieved ? retrieved : p.T) : 0;  // prefix of the heads without the whole past
   const int n_long = retrieved ? 0 : p.n_past;
-  const double past = segs * per_seg * n / 64, other = segs * per_seg * (seg / 64 + bounded / 32);
+  const double past = blocks * n / 64, other = blocks * (seg / 64 + bounded / 32);
   return {seqs * p.g * (n_long * past + (p.Hkv - n_long) * other), n_long > 0 ? (n + 31) / 32. : (bounded + seg + 31) / 32,
-          seqs * p.Hq * segs * per_seg};
+          seqs * p.Hq * blocks};
 }
 constexpr int kQueueStride = 32;  // unsigned words between two queue counters (128 bytes)
 // Host side of the item queues (segattn_prefill_mfma.hip): the counters of this (device, stream),
@@ -498,6 +500,7 @@ __device__ inline long long ws_slot_base(const Problem &p, const CacheGeom &g, i
 
 
 // ---- launchers (defined in the .hip files) ------------------------------------------------
+int device_cus();  // compute units of the device, asked once
 hipError_t launch_prefill(const Problem &p, const PrefillArgs &a, hipStream_t st);
 // bytes of split-prefix workspace for `parts` pieces (fp32 outputs + LSEs of one segment of every sequence)
 __host__ __device__ inline unsigned long long part_ws_bytes(const Problem &p, int parts) {

@@ -994,8 +994,6 @@ static int heads_per_wg(const Problem &p) { return (p.g % 4 == 0) ? 4 : (p.g % 2
 // that is being captured (the graph may later be replayed on any stream, next to anything), and for
 // hipStreamPerThread (one handle that names a different stream in every host thread), the launch falls back to one
 // workgroup per item, which needs no counters.
-static int device_cus();
-
 constexpr int kQueueSets = 64;
 constexpr int kQueueDevices = 16;
 static __device__ unsigned g_queue_sets[kQueueSets][kQueueWords];
@@ -1106,7 +1104,7 @@ static int waves_d128(const Problem &p, const PrefillArgs &a, int hs) {
   return heads * blocks8 < n_cu ? 4 : 8;
 }
 
-static int device_cus() {
+int device_cus() {
   static const int n_cu = [] {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||

@@ -3,7 +3,8 @@
 //   * every row block of every sequence appears exactly once per (head, sub-group), the surplus numbers all
 //     lie behind the end of a sequence;
 //   * the heads listed first own the first items, longest first (up to 64 sequences);
-//   * packed_block finds the sequence of a block in batches of one to 300,000 sequences.
+//   * packed_block finds the sequence of a block in batches of one to 300,000 sequences;
+//   * the launch rules count whole blocks (row_blocks, count_steps).
 // Prints "ok <batches> <items>" or the first failure.
 #include "segattn_work.h"
 
@@ -120,7 +121,24 @@ static void check_search(const Batch &x, int probes, std::mt19937 &rng) {
   items_checked += (long long)u.size();
 }
 
+// the 32-row blocks that the launch rules count are whole ones
+static void check_counts() {
+  for (int S : {1, 31, 32, 33, 64, 100, 512})
+    for (long long n = 1; n < 1200; n += 7) {
+      double blocks = 0;
+      for (long long s = 0; s < n; s += S) blocks += (double)(((n - s < S ? n - s : S) + 31) / 32);
+      Problem p;
+      memset(&p, 0, sizeof(p));
+      p.B = 2, p.Hkv = 3, p.g = 4, p.Hq = 12, p.S = S;
+      if (row_blocks(n, S) != blocks || count_steps(p, n, 0, 0).blocks != 24 * blocks) {
+        printf("FAILED: blocks of %lld rows, S=%d\n", n, S);
+        exit(1);
+      }
+    }
+}
+
 int main() {
+  check_counts();
   std::mt19937 rng(11);
   auto lens = [&](int n, int lo, int hi) {
     std::vector<int> l(n);

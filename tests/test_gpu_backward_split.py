@@ -31,7 +31,7 @@ def test_small_windows(n, S, T, D, g):
     (64, 2, 4, 64, 16, (0, 1, 150, 33, 0, 64, 129)),
     (128, 2, 2, 100, 100, (257, 3, 96)),
     (128, 2, 4, 96, 32, (1,) * 70 + (200,)),
-    (64, 16, 1, 64, 16, (130, 31, 32, 33, 95, 96, 97, 200) * 2),   # over 768 key blocks: the four-wave form
+    (64, 16, 1, 64, 16, (130, 31, 32, 33, 95, 96, 97, 200) * 2),   # over 640 key blocks: the four-wave form
     (64, 8, 1, 32, 7, (64,) * 60),
 ])
 def test_packed_small_windows(D, Hkv, g, S, T, lens):
