@@ -563,8 +563,10 @@ unsigned long long retrieval_total(unsigned long long off, unsigned long long li
 // workgroups per CU); else 1024 -- a last, partly filled round of 1 MB workgroups costs more than
 // the extra per-chunk selections; and 512 where even 1024-row chunks are fewer than the CUs (one
 // segment's retrieval on a single sequence: the call is then as long as one workgroup's chain
-// of tiles, and halving the chain halves it) as long as the merge kernel's fast path still holds
-// the lists (256 per head).  The workspace is sized for the smallest chunks.
+// of tiles, and halving the chain halves it) up to 256 chunks of the longest pool: the selection
+// compares every pair of a head's chunks, and with more of them that costs more than the shorter
+// chain saves.  One head of 128, whole call, chunks of 512 / 1024 rows: 65K rows 25.1 / 26.9 us, 131K
+// 27.3 / 31.4, 197K 37.0 / 32.9, 397K 72.2 / 45.5.  The workspace is sized for the smallest chunks.
 constexpr int kRetrieveChunkTiny = 512, kRetrieveChunkSmall = 1024, kRetrieveChunkBig = 4096;
 int retrieve_chunk_rows(const segattn_ctx *ctx) {
 #ifdef SEGATTN_RETRIEVE_CHUNK
