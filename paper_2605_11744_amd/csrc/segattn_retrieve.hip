@@ -215,7 +215,9 @@ __global__ __launch_bounds__(256) void retrieve_score_kernel(const Problem p, co
 // ---- merge the candidates of all chunks, expand, pad, emit.  One workgroup per (b, PAST head); every step a
 // constant number of passes over all anchors at once (a merge of the chunks' lists in n_anchors rounds and
 // an expansion anchor by anchor on a sorted list of ranges took 15 us of 20; the kernel: 22.6 -> 10.8 us for 120 chunks a pool).
-constexpr int kMaxChunks = 2048;  // the launchers make at most 1024: 2^20 pool rows in chunks of 1024 (shorter ones up to 256)
+// 2^20 pool rows in chunks of 512: those are chosen by the longest pool with visible rows, and the grid covers
+// the longest pool of all.
+constexpr int kMaxChunks = 2048;
 
 __global__ __launch_bounds__(256) void retrieve_select_kernel(const Problem p, const RetrieveArgs a) {
   __shared__ __attribute__((aligned(16))) unsigned long long heads[kMaxChunks];  // best candidate of every chunk
