@@ -263,9 +263,11 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
   };
 
   // ---- Q^T operands: Qr[qb][kc] = Q[row(qb, col)][16 kc + 8 hi .. +7].  Memory operations complete in order: with
-  // four waves the queries are requested before the K/V steps (so that the first sync, which leaves the last
-  // step's loads in flight, does not wait for all of them: 554 rows, 32 heads of 64: 15.5 -> 15.4 us), with eight
-  // waves after them (64 KB in front of the first step cost more: 9000 rows, 16 heads of 128: 217.6 against 215.3).
+  // D = 64 the queries are requested before the K/V steps (so that the first sync, which leaves the last
+  // step's loads in flight, does not wait for all of them: 554 rows, 32 heads of 64: 15.5 -> 15.4 us), with D = 128
+  // after them (32 or 64 KB in front of the first step cost more: eight waves, 9000 rows, 16 heads: 217.6
+  // against 215.3; four waves, 5 x 861 rows, 16/2 heads: 31.3 against 30.9).
+  constexpr bool kQFirst = D == 64;
   bf16x8 Qr[QB][NC];
   auto load_q = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -280,12 +282,12 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
       }
     }
   };
-  if constexpr (NW == 4) load_q();
+  if constexpr (kQFirst) load_q();
   for (int i = 0; i < (kPair ? kSlots - 2 : kSlots - 1); ++i) {
     issue_loads();
     loader_advance();
   }
-  if constexpr (NW != 4) load_q();
+  if constexpr (!kQFirst) load_q();
 
   // ---- per-lane LDS read offsets inside a slot
   // K operand of k-chunk kc: row col, logical chunk 2 kc + hi, swizzled with the row: one lane
