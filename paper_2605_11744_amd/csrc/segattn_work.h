@@ -350,6 +350,17 @@ __device__ inline void packed_block(const Problem &p, const int *cu_seqlens, lon
   qblk = v - seg * per_seg;
 }
 
+__device__ inline int wave_max_i32(int x) {
+  auto step = [&](int y) { x = x > y ? x : y; };
+  step(__builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true));
+  step(__builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true));
+  step(__builtin_amdgcn_mov_dpp(x, 0x141, 0xF, 0xF, true));
+  step(__builtin_amdgcn_mov_dpp(x, 0x140, 0xF, 0xF, true));
+  const int a = __builtin_amdgcn_readlane(x, 0), b = __builtin_amdgcn_readlane(x, 16);
+  const int c = __builtin_amdgcn_readlane(x, 32), d = __builtin_amdgcn_readlane(x, 48);
+  const int ab = a > b ? a : b, cd = c > d ? c : d;
+  return ab > cd ? ab : cd;
+}
 __device__ inline int wave_sum_i32(int x) {  // over the 64 lanes: DPP inside the rows of 16, then four lanes
   x += __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);
   x += __builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true);
@@ -361,7 +372,7 @@ __device__ inline int wave_sum_i32(int x) {  // over the 64 lanes: DPP inside th
 // The u-th row block of a packed batch of at most 64 sequences in the order of descending block index
 // (longest key range first for heads that see the whole past): false if there are no more than u.
 // A lane per sequence; the block index q is found by bisection, with the number of blocks at or
-// beyond q as a sum over the lanes: about 0.5 us.
+// beyond q as a sum over the lanes: a step per bit of the longest sequence's block count.
 __device__ inline bool packed_longest(const Problem &p, const int *cu_seqlens, int u, int rows_per_block, int &b, int &seg,
                                       int &qblk) {
   const int lane = threadIdx.x & 63;
@@ -373,11 +384,7 @@ __device__ inline bool packed_longest(const Problem &p, const int *cu_seqlens, i
   }
   const int all = wave_sum_i32(blocks);
   if (u >= all) return false;
-  int lo = 0, hi = 1, at_hi;  // more than u blocks at or beyond lo, at_hi <= u at or beyond hi
-  while ((at_hi = wave_sum_i32(blocks > hi ? blocks - hi : 0)) > u) {
-    lo = hi;
-    hi *= 2;
-  }
+  int lo = 0, hi = wave_max_i32(blocks), at_hi = 0;  // more than u blocks at or beyond lo, at_hi <= u at or beyond hi
   while (hi - lo > 1) {
     const int mid = (lo + hi) >> 1;
     const int n = wave_sum_i32(blocks > mid ? blocks - mid : 0);
