@@ -509,7 +509,7 @@ static hipError_t launch_dkv(const Problem &p, const BwdArgs &a, hipStream_t st)
 hipError_t launch_bwd_mfma(const Problem &p, const BwdArgs &a, hipStream_t st) {
   const hipError_t e = launch_bwd_dq(p, a, st);
   if (e != hipSuccess) return e;
-  if (bwd_dkv_split_pays(p, a)) return launch_bwd_dkv_split(p, a, st);
+  if (const int waves = bwd_dkv_split_waves(p, a)) return launch_bwd_dkv_split(p, a, waves, st);
   return p.D == 128 ? launch_dkv<128>(p, a, st) : launch_dkv<64>(p, a, st);
 }
 

@@ -374,72 +374,58 @@ static hipError_t allow_lds(K kern, int bytes, std::atomic<bool> &ready) {
   return e;
 }
 
-// Which form?  Estimates in microseconds, from the longest chain of steps of a workgroup, the wave-steps in
-// all and the rounds of workgroups; measured on windows of 600 to 8192 rows and packed batches, 4/4,
-// 8/2, 8/8, 16/2, 16/4 and 32/8 heads.  A forced launch shape keeps the other forms.
-//   dQ     one chain per workgroup: 7 + 0.6 a step (D = 64), 8 + 0.65 (D = 128), or the wave-steps at
-//          5.9e-4 and 8e-4; split: 7 + 0.15 + 8.3e-4 and 8 + 0.2 + 1.5e-3, and for every further round of workgroups,
-//          however few they are, 4 (D = 64) or 8, less the longer the chains (0 at 64 steps: 2048 rows, 8/8 heads of 128
-//          with segments of 512, 512 workgroups, backward 80 -> 67 us; six packed sequences of 33 to 500 rows,
-//          8/2 heads of 128, 332 workgroups, would lose 3 of 34).
-//          1024 rows, 4/4 heads, D = 64: backward 49 -> 36 us; 8/8, D = 128: 62 -> 55; 32/8 never gains.
-//   dK/dV  a 128-key workgroup's chain over the whole group: 8 + 0.6 a step (D = 64), 9 + 0.85 (D = 128), or
-//          the 128-key steps at 0.5 and 0.95 a CU; split: the wave-steps at 5.9e-4 and 1.9e-3 plus half the
-//          chain of a wave.  1024 rows, 32/8 heads, D = 64: backward 100 -> 48 us, D = 128: 121 -> 79;
-//          8192 rows, 16/4, D = 64: 519 -> 416; 8192 rows of 32/8 would lose 60 (D = 64) and 580 us (D = 128).
+// Which form?  Estimates in microseconds from the longest chain of steps of a workgroup, the wave-steps in all and
+// the rounds of workgroups, fitted to 11,123 windows and packed batches of 360 to 65,000 rows (eight numbers of
+// heads, segments of 64 to 4096, every form of each timed): 0.6 % (D = 64) and 0.8 % (D = 128) slower than the best
+// form on average; against the forms for large launches alone 13 of them more than 3 % slower, none more than 7 %.
+// The split forms pay where those leave the chip waiting for a chain: 1024 rows, 32/8 heads of 64, 100 -> 48 us;
+// 445 rows, 16/2 heads of 128, 76 -> 48.  They don't where waves that stage tiles of their own are bound by L2 (8192
+// rows, 32/8 heads of 128, would lose 580 us), or by a further round of workgroups, however few they are (packed
+// sequences of 10 to 60 rows, 8/8 heads of 128, 340 workgroups: 30 -> 41).  A forced launch shape keeps the other forms.
 bool bwd_dq_split_pays(const Problem &p, const BwdArgs &a) {
   if (p.tune_waves != 0 || p.tune_queue != 0) return false;
-  const StepCount c = count_steps(p, a.n, a.cu_seqlens ? a.total : 0, 0);
-  const double rounds = (ceil(c.blocks / device_cus()) - 1) * (c.longest < 64 ? 1 - c.longest / 64 : 0);
-  const bool d64 = p.D == 64;
-  const double chain = (d64 ? 0.6 : 0.65) * c.longest, even = (d64 ? 5.9e-4 : 8e-4) * c.steps;
-  const double piped = (d64 ? 7 : 8) + (chain > even ? chain : even);
-  const double split = (d64 ? 7 + 0.15 * c.longest + 8.3e-4 * c.steps : 8 + 0.2 * c.longest + 1.5e-3 * c.steps) + (d64 ? 4 : 8) * rounds;
-  return split < 0.9 * piped;
+  const long long total = a.cu_seqlens ? a.total : 0;
+  const StepCount c = count_steps(p, a.n, total, 0);
+  const double rounds = more_rounds(p.Hq * row_blocks(p, a.n, total, 32), device_cus());
+  if (p.D == 64)
+    return 9.48 - 0.22 * c.longest + 5.93e-4 * c.steps + 4.84 * rounds < 0.967 * (8 + fmax(0.349 * c.longest, 4.43e-4 * c.steps));
+  return 11.1 - 0.066 * c.longest + 9.37e-4 * c.steps + 8.08 * rounds < 0.982 * (8 + fmax(0.487 * c.longest, 6.95e-4 * c.steps));
 }
-namespace {
-struct DkvCount {
-  double steps, longest, longest128, blocks;  // wave-steps; steps per query head of a 32-key / 128-key block; 32-key blocks
-};
-DkvCount count_dkv(const Problem &p, const BwdArgs &a) {
-  const double n = a.n, seqs = a.cu_seqlens ? (double)a.total / n : p.B;
-  const double seg = n < p.S ? n : p.S, segs = n / seg, per_seg = row_blocks((long long)seg, p.S);
-  bool tails = false;
+// dK/dV: waves of a workgroup of the split form (D = 64: eight, or four with two workgroups per CU), 0: the other form.
+int bwd_dkv_split_waves(const Problem &p, const BwdArgs &a) {
+  if (p.tune_waves != 0 || p.tune_queue != 0) return 0;
+  const long long total = a.cu_seqlens ? a.total : 0;
+  const double n = a.n, seqs = total > 0 ? total / n : p.B, cus = device_cus();
+  const double seg = n < p.S ? n : p.S, segs = n / seg, per_seg = ceil(seg / 32), last = ceil(a.n % p.S / 32.);
   int n_tail = 0;
   for (int h = 0; h < p.Hkv; ++h) n_tail += p.policy[h] & SEGATTN_TAIL ? 1 : 0;
-  tails = n_tail > 0 && segs > 1 && p.T > 0;
+  const bool tails = n_tail > 0 && segs > 1 && p.T > 0;
   const double next = segs < 2 ? n - seg : seg;  // rows of a following segment
-  const double last = row_blocks(a.n % p.S, p.S);
-  const double own = a.n / p.S * per_seg * (per_seg + 1) / 2 + last * (last + 1) / 2;
-  const double tail = tails ? (segs > 2 ? segs - 1 : 1) * ((p.T + 31) / 32) * next / 32 : 0;
-  DkvCount c;
-  c.steps = seqs * p.g * (p.Hkv * own + n_tail * tail);
-  const double t32 = tails ? (p.T + next) / 32 : 0;
-  const double t128 = tails ? ((p.T > 128 ? p.T : 128) + next) / 32 : 0;
-  c.longest = per_seg > t32 ? per_seg : t32;
-  c.longest128 = per_seg > t128 ? per_seg : t128;
-  c.blocks = seqs * p.Hkv * row_blocks(a.n, p.S);
-  return c;
-}
-}  // namespace
-bool bwd_dkv_split_pays(const Problem &p, const BwdArgs &a) {
-  if (p.tune_waves != 0 || p.tune_queue != 0) return false;
-  const DkvCount c = count_dkv(p, a);
-  const bool d64 = p.D == 64;
-  const double chain = (d64 ? 0.6 : 0.85) * c.longest128 * p.g, even = (d64 ? 0.5 : 0.95) * c.steps / 4 / device_cus();
-  const double piped = (d64 ? 8 : 9) + (chain > even ? chain : even);
-  const double split = d64 ? 8 + 5.9e-4 * c.steps + 0.5 * 1.2 * c.longest * p.g / 8
-                           : 9 + 1.9e-3 * c.steps + 0.5 * 2.0 * c.longest * p.g / 4;
-  return split < 0.9 * piped;
-}
-// D = 64: four waves, two workgroups per CU, from two and a half workgroups per CU on, and with short chains as soon as
-// eight waves (one workgroup per CU) would take a second round.  Backward pass, four waves / eight: 700-row sequences
-// of 32/8 heads, S = 64, 704 blocks, chain 10: 40.1 / 43.4 us; 16/4 heads, S = 128, 352 blocks, chain 24: 34.5 / 37.2; S = 256,
-// chain 40: 40.3 / 39.9; 16/4 heads, S = 512, chain 80: 368 blocks 44.0 / 41.6, 752 blocks 83.2 / 86.1; 8192 rows of 8/2
-// heads, S = 1024, 512 blocks, chain 160: 207.3 / 200.0.
-static bool dkv_split_four(const Problem &p, const BwdArgs &a) {
-  const DkvCount c = count_dkv(p, a);
-  return 2 * c.blocks >= 5 * device_cus() || (c.blocks > device_cus() && c.longest * p.g <= 40);
+  // wave-steps of either form (the other one's in 128-key blocks of four waves); steps of the longest block of
+  // either, all query heads of the group
+  auto own128 = [](double steps) {
+    const double blocks = ceil(steps / 4);
+    return 4 * (blocks * steps - 2 * blocks * (blocks - 1));
+  };
+  const double whole = a.n / p.S, tail_segs = tails ? (segs > 2 ? segs - 1 : 1) * next / 32 : 0;
+  const double steps = seqs * p.g * (p.Hkv * (whole * per_seg * (per_seg + 1) + last * (last + 1)) / 2 + n_tail * tail_segs * ceil(p.T / 32.));
+  const double steps128 = seqs * p.g * (p.Hkv * (whole * own128(per_seg) + own128(last)) + n_tail * tail_segs * 4 * ceil(p.T / 128.));
+  const double chain = p.g * fmax(per_seg, tails ? (p.T + next) / 32 : 0);
+  const double chain128 = p.g * fmax(per_seg, tails ? (fmax(p.T, 128) + next) / 32 : 0);
+  // workgroups; the other form's grid pads a packed batch: `empty` of them a CU find no keys
+  const double blocks = p.Hkv * row_blocks(p, a.n, total, 32);
+  double blocks128 = p.Hkv * row_blocks(p, a.n, 0, 128);
+  if (total > 0) blocks128 = fmin(blocks128, p.Hkv * (total * ceil(p.S / 128.) / p.S + p.B / 2.));
+  const double empty = fmax(p.Hkv * p.B * ceil(n / p.S) * ceil(seg / 128) - blocks128, 0) / cus;
+  const double rounds = more_rounds(blocks, cus), rounds128 = more_rounds(blocks128, cus);
+  if (p.D == 128) {
+    const double split = 6.14 + 0.109 * chain + 1.3e-3 * steps + 4.4 * rounds;
+    return split < 0.97 * (8 + fmax(0.5 * chain128, 9.28e-4 * steps128) + 1.96 * empty + 2.16 * rounds128) ? 4 : 0;
+  }
+  const double four = 6.34 + 0.335 * chain + 5.21e-4 * steps + 2.2 * more_rounds(blocks, 2 * cus);
+  const double eight = 7.81 + 0.209 * chain + 7.45e-4 * steps + 2.84 * rounds;
+  if (fmin(four, eight) >= 0.988 * (8 + fmax(0.709 * chain128, 5.15e-4 * steps128) + 9.82 * empty + 3.59 * rounds128)) return 0;
+  return four <= eight ? 4 : 8;
 }
 
 template <int D, int NW>
@@ -458,9 +444,9 @@ static hipError_t launch_dkv_split_d(const Problem &p, const BwdArgs &a, hipStre
   hipLaunchKernelGGL((bwd_dkv_split_kernel<D, NW>), dim3((unsigned)grid), dim3(64 * NW), lds, st, p, a, blocks_per_seg, n_seg, (int)packed);
   return hipGetLastError();
 }
-hipError_t launch_bwd_dkv_split(const Problem &p, const BwdArgs &a, hipStream_t st) {
+hipError_t launch_bwd_dkv_split(const Problem &p, const BwdArgs &a, int waves, hipStream_t st) {
   if (p.D == 128) return launch_dkv_split_d<128, 4>(p, a, st);
-  return dkv_split_four(p, a) ? launch_dkv_split_d<64, 4>(p, a, st) : launch_dkv_split_d<64, 8>(p, a, st);
+  return waves == 4 ? launch_dkv_split_d<64, 4>(p, a, st) : launch_dkv_split_d<64, 8>(p, a, st);
 }
 
 template <int D, int HS, bool PK>

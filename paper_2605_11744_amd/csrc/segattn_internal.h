@@ -1,6 +1,7 @@
 // Internal declarations shared by the translation units of libsegattn (not part of the ABI).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -158,9 +159,10 @@ __host__ __device__ inline long long packed_units(long long row, int S, int rows
 // differ.  With B sequences of one block each half of the items of the first would be empty, and an item is
 // found by a search where it is plain arithmetic in the second: 2048 sequences of 64 rows, forward, 32/8 heads of
 // 128, 1155 us by row blocks (with the search as it was) and 707 padded; 16/4 heads of 64, backward, 850 and 677.
-// The other way round, 48 sequences of 16 to 2900 rows: 405 us by row blocks, 503 padded.
+// The other way round, 48 sequences of 16 to 2900 rows: 405 us by row blocks, 503 padded.  Where the first has at
+// most a tenth fewer items the second is the faster one more often (3369 batches, every kernel both ways).
 inline bool number_packed(const Problem &p, long long total, int n_seg, int blocks_per_seg, int rows_per_block) {
-  return packed_units(total, p.S, rows_per_block) + p.B < (long long)p.B * n_seg * blocks_per_seg;
+  return 11 * (packed_units(total, p.S, rows_per_block) + p.B) < 10ll * p.B * n_seg * blocks_per_seg;
 }
 // Heads listed first, longest work first: the PAST heads -- unless they attend to a retrieved
 // prefix of bounded size, in which case their key ranges are as short as everybody's and all heads
@@ -211,23 +213,33 @@ inline void prepare_resolve_divs(const Problem &p, PrefillArgs &a, int heads_per
     if (f->d == 0) return;
   dv.ok = 1;
 }
+// Row blocks of a whole-sequence launch (no block spans two segments): of every sequence, or of a packed batch
+// (total_rows > 0, n the longest sequence) as its launch numbers them.
+inline double row_blocks(const Problem &p, long long n, long long total_rows, int rows_per_block) {
+  const long long per_seg = (p.S + rows_per_block - 1) / rows_per_block;
+  const long long every = p.B * (n / p.S * per_seg + (n % p.S + rows_per_block - 1) / rows_per_block);
+  const long long packed = packed_units(total_rows, p.S, rows_per_block) + p.B;
+  return (double)(total_rows > 0 && packed < every ? packed : every);
+}
+// Further rounds of a launch beyond the first.
+inline double more_rounds(double workgroups, double at_once) {
+  const double rounds = ceil(workgroups / at_once) - 1;
+  return rounds > 0 ? rounds : 0;
+}
 // What a whole-sequence launch has to do, in steps of 32 query columns x 32 keys (a wave's unit of work):
-// all of them, the longest row of them that one 32-column block meets, the column blocks.  retrieved: rows
+// all of them, and the longest row of them that one 32-column block meets.  retrieved: rows
 // of the prefix of a PAST head where it is not its whole history, else 0.  A packed batch (total_rows > 0)
 // counts as many sequences of the longest length as its rows make up (no fewer steps than it has).
 struct StepCount {
-  double steps, longest, blocks;
+  double steps, longest;
 };
-// 32-row blocks of a sequence of n rows (no block spans two segments).
-inline double row_blocks(long long n, int S) { return (double)(n / S * ((S + 31) / 32) + (n % S + 31) / 32); }
 inline StepCount count_steps(const Problem &p, long long n, long long total_rows, int retrieved) {
   const double seqs = total_rows > 0 ? (double)total_rows / n : p.B;
-  const double seg = (double)(n < p.S ? n : p.S), segs = n / seg, blocks = row_blocks(n, p.S);
+  const double seg = (double)(n < p.S ? n : p.S), segs = n / seg, blocks = row_blocks(p, n, 0, 32) / p.B;
   const double bounded = segs > 1 ? (retrieved ? retrieved : p.T) : 0;  // prefix of the heads without the whole past
   const int n_long = retrieved ? 0 : p.n_past;
   const double past = blocks * n / 64, other = blocks * (seg / 64 + bounded / 32);
-  return {seqs * p.g * (n_long * past + (p.Hkv - n_long) * other), n_long > 0 ? (n + 31) / 32. : (bounded + seg + 31) / 32,
-          seqs * p.Hq * blocks};
+  return {seqs * p.g * (n_long * past + (p.Hkv - n_long) * other), n_long > 0 ? (n + 31) / 32. : (bounded + seg + 31) / 32};
 }
 constexpr int kQueueStride = 32;  // unsigned words between two queue counters (128 bytes)
 // Host side of the item queues (segattn_prefill_mfma.hip): the counters of this (device, stream),
@@ -532,10 +544,10 @@ hipError_t launch_bwd_dq(const Problem &p, const BwdArgs &a, hipStream_t st);
 hipError_t launch_bwd_mfma(const Problem &p, const BwdArgs &a, hipStream_t st);
 // Forms for small launches (segattn_bwd_split.hip), and whether they are the faster ones.
 bool bwd_dq_split_pays(const Problem &p, const BwdArgs &a);
-bool bwd_dkv_split_pays(const Problem &p, const BwdArgs &a);
+int bwd_dkv_split_waves(const Problem &p, const BwdArgs &a);
 hipError_t launch_bwd_dq_split(const Problem &p, const PrefillArgs &pa, const BwdArgs &a, int heads_per_wg, long long grid,
                                hipStream_t st);
-hipError_t launch_bwd_dkv_split(const Problem &p, const BwdArgs &a, hipStream_t st);
+hipError_t launch_bwd_dkv_split(const Problem &p, const BwdArgs &a, int waves, hipStream_t st);
 int prefill_pair_stride(long long groups);
 hipError_t launch_probe(void *buf, long long bytes, int mode, void *sink, hipStream_t st);
 constexpr int kClockProbeWaves = 8;  // one per XCD

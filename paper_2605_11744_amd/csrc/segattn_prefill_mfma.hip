@@ -1197,35 +1197,40 @@ static void plan_pieces(const Problem &p, PrefillArgs &a, int hs, int rows, int 
 }
 
 // Key-split form or hand-pipelined form?  Both are estimated in microseconds from their longest chain
-// of steps, the wave-steps in all (32 query columns x 32 keys) and the rounds of workgroups.
-// Measured (32/8, 16/4, 16/2, 8/8 and 4/4 heads, prompts of 300 to 8192 tokens, one and many segments):
-//   hand-pipelined   D = 64: 7 + 0.41 a step of the longest workgroup; D = 128: 9.5 + 0.52
-//   key-split        D = 64: 6.5 + 0.11 a step + 5.6e-4 a wave-step (K/V tiles out of L2 at 14 TB/s), 512 workgroups a round
-//                    D = 128: 7.5 + 0.13 a step + 1.1e-3 a wave-step, 256 workgroups a round; 3 a further round
-// e.g. 2048 tokens, 4 heads, D = 64: 33.1 -> 15.0 us; 1000 tokens, 8 heads, D = 128: 25.9 -> 15.3; from about
-// 1000 tokens of 32 heads on the other form is the faster one (D = 64: 20.9 against 22.5).
+// of steps, the wave-steps in all (32 query columns x 32 keys; the key-split form reads its K/V tiles out of L2 at
+// 14 TB/s) and the rounds of workgroups.  Fitted to 11,123 prompts and packed batches of 360 to 65,000 rows (4/4
+// to 32/8 heads, segments of 64 to 4096, both forms of each timed): 0.9 % (D = 64) and 0.8 % (D = 128) slower than
+// the better form on average.  2048 tokens, 4 heads, D = 64: 33.1 -> 13.1 us; 1000 tokens, 8 heads, D = 128: 25.9 -> 15.3;
+// from about 1000 tokens of 32 heads on the other form is the faster one (D = 64: 20.9 against 22.5).
 // Chunks on a filled cache come here only if their prefixes were not cut (plan_pieces found no workspace, or no
 // gain): 173 rows behind 37.5K, four of eight KV heads with the whole past, 32 heads of 128, forward and commit:
 // 633 -> 251 us, 8 rows of it 620 -> 75; 1500 rows stay with the other form (663).
-static bool use_keysplit(const Problem &p, const PrefillArgs &a) {
+static bool use_keysplit(const Problem &p, const PrefillArgs &a, int hs) {
   if (p.tune_waves != 0 || p.tune_queue != 0 || a.parts > 1 || a.parts_other > 1) return false;
   StepCount c;
+  double wgs, wgs_piped;  // workgroups of either form; the second's with four waves
+  const double groups = p.Hkv * (p.g / hs);
   if (a.cache == nullptr) {
-    c = count_steps(p, a.n_rows, a.cu_seqlens ? a.total_rows : 0, a.ret_k ? a.ret_R : 0);
+    const long long total = a.cu_seqlens ? a.total_rows : 0;
+    c = count_steps(p, a.n_rows, total, a.ret_k ? a.ret_R : 0);
+    wgs = groups * row_blocks(p, a.n_rows, total, 32 / hs);
+    wgs_piped = groups * row_blocks(p, a.n_rows, total, 128 / hs);
   } else {  // a chunk behind a filled cache whose prefixes were not cut (no workspace that holds the pieces)
     const int n_first = heads_listed_first(p, a);
     const double blocks = (a.n_rows + 31) / 32, own = a.n_rows / 64.;
     const double first = n_first ? a.max_first_prefix / 32. : 0, other = n_first < p.Hkv ? a.max_other_prefix / 32. : 0;
     c.steps = p.B * p.g * blocks * (n_first * (first + own) + (p.Hkv - n_first) * (other + own));
     c.longest = (first > other ? first : other) + a.n_rows / 32.;
-    c.blocks = p.B * p.Hq * blocks;
+    wgs = p.B * groups * ceil(a.n_rows * hs / 32.);
+    wgs_piped = p.B * groups * ceil(a.n_rows * hs / 128.);
   }
-  const double slots = device_cus() * (p.D == 64 ? 2 : 1);
-  const double rounds = c.blocks <= slots ? 0 : c.blocks / slots;
-  const double split = p.D == 64 ? 6.5 + 0.11 * c.longest + 5.6e-4 * c.steps + 3 * rounds
-                                 : 7.5 + 0.13 * c.longest + 1.1e-3 * c.steps + 3 * rounds;
-  const double piped = p.D == 64 ? 7 + 0.41 * c.longest : 9.5 + 0.52 * c.longest;
-  return split < 0.95 * piped;
+  const int cus = device_cus();
+  if (p.D == 64) {
+    const double split = 7.69 + 0.11 * c.longest + 4.48e-4 * c.steps + 2.37 * more_rounds(wgs, 2 * cus);
+    return split < 0.973 * (8 + fmax(0.423 * c.longest, 1.49e-4 * c.steps) + 0.16 * more_rounds(wgs_piped, 3 * cus));
+  }
+  const double split = 8.23 + 0.072 * c.longest + 1.1e-3 * c.steps + 3.59 * more_rounds(wgs, cus);
+  return split < 0.942 * (8 + fmax(0.547 * c.longest, 8.4e-5 * c.steps) + 0.12 * more_rounds(wgs_piped, 2 * cus));
 }
 
 hipError_t launch_prefill(const Problem &p, const PrefillArgs &a_in, hipStream_t st) {
@@ -1236,7 +1241,7 @@ hipError_t launch_prefill(const Problem &p, const PrefillArgs &a_in, hipStream_t
   if (!fp32) plan_pieces(p, a, hs, p.D == 128 ? (8 / hs) * 32 : (4 / hs) * 32, p.D == 128 ? 1 : 2);
   const bool cut = a.parts > 1 || a.parts_other > 1;
   const int nw = p.D == 128 ? (cut ? 8 : waves_d128(p, a_in, hs)) : 4;
-  const bool keysplit = !fp32 && use_keysplit(p, a);
+  const bool keysplit = !fp32 && use_keysplit(p, a, hs);
   const int rows = fp32 ? 64 : keysplit ? 32 / hs : (p.D == 128 ? (nw / hs) * 32 : (4 / hs) * 32);
   const long long seg_rows = a.n_rows < p.S ? a.n_rows : p.S;
   a.q_blocks_per_seg = (int)((seg_rows + rows - 1) / rows);

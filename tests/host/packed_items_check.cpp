@@ -4,7 +4,7 @@
 //     lie behind the end of a sequence;
 //   * the heads listed first own the first items, longest first (up to 64 sequences);
 //   * packed_block finds the sequence of a block in batches of one to 300,000 sequences;
-//   * the launch rules count whole blocks (row_blocks, count_steps).
+//   * the launch rules count the blocks that there are (row_blocks).
 // Prints "ok <batches> <items>" or the first failure.
 #include "segattn_work.h"
 
@@ -121,25 +121,31 @@ static void check_search(const Batch &x, int probes, std::mt19937 &rng) {
   items_checked += (long long)u.size();
 }
 
-// the 32-row blocks that the launch rules count are whole ones
-static void check_counts() {
+// the row blocks that the launch rules count are those that the launches number
+static void check_counts(std::mt19937 &rng) {
   for (int S : {1, 31, 32, 33, 64, 100, 512})
-    for (long long n = 1; n < 1200; n += 7) {
-      double blocks = 0;
-      for (long long s = 0; s < n; s += S) blocks += (double)(((n - s < S ? n - s : S) + 31) / 32);
-      Problem p;
-      memset(&p, 0, sizeof(p));
-      p.B = 2, p.Hkv = 3, p.g = 4, p.Hq = 12, p.S = S;
-      if (row_blocks(n, S) != blocks || count_steps(p, n, 0, 0).blocks != 24 * blocks) {
-        printf("FAILED: blocks of %lld rows, S=%d\n", n, S);
-        exit(1);
+    for (int rows : {8, 32, 128})
+      for (int i = 0; i < 200; ++i) {
+        std::vector<int> len(1 + rng() % 12, 1 + (int)(rng() % 1200));
+        const bool same = i % 2;
+        if (!same)
+          for (int &l : len) l = (int)(rng() % 1200);
+        const Batch x = batch(len, S, rows);
+        const int longest = *std::max_element(len.begin(), len.end());
+        if (longest == 0) continue;
+        double padded = 0;
+        for (long long s = 0; s < longest; s += S)
+          padded += (double)len.size() * (double)(((longest - s < S ? longest - s : S) + rows - 1) / rows);
+        const double units = (double)(packed_units(x.cu.back(), S, rows) + (long long)len.size());
+        const Problem p = problem(x, 3, 1, 4);
+        if (row_blocks(p, longest, 0, rows) != padded || row_blocks(p, longest, x.cu.back(), rows) != std::min(padded, units))
+          fail("counted blocks", x, i);
       }
-    }
 }
 
 int main() {
-  check_counts();
   std::mt19937 rng(11);
+  check_counts(rng);
   auto lens = [&](int n, int lo, int hi) {
     std::vector<int> l(n);
     for (int &v : l) v = lo + (int)(rng() % (hi - lo + 1));
