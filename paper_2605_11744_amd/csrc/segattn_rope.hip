@@ -52,7 +52,9 @@ __device__ inline void rope_rotate8(uint4 &lo, uint4 &hi, const float (&sn)[8], 
 // thread per (row, 8 channel pairs) that walked over all heads of its row, all waves were at the same head
 // of different rows (the same few addresses modulo the row size) and formed sines first, and 32K rows of
 // 32 + 8 heads took 152 us; in memory order 135 (5.0 TB/s), 500 rows 4.7 instead of 11.8.  One 16-byte pair in flight per
-// thread: the in-place probe is fastest so (5.7 TB/s; eight pieces: 4.0).
+// thread: the in-place probe is fastest so (5.7 TB/s; eight pieces: 4.0).  A thread's first piece of q is requested
+// before the sines are formed, so that the two waits do not add up: 28K rows of 4 + 4 heads of 64 9.0 -> 8.7 us (a
+// thread per row 8.8), 32K rows of 32 + 8 heads of 128 122.6 -> 121.1 in a loop over one buffer.
 constexpr int kRopeRows = 16;
 template <int D>
 __global__ __launch_bounds__(256) void rope_apply_kernel(const Problem p, const RopeArgs a, const int rows_per_wg) {
@@ -61,6 +63,14 @@ __global__ __launch_bounds__(256) void rope_apply_kernel(const Problem p, const 
   const int tid = threadIdx.x;
   const long long total = (long long)p.B * a.rows, row0 = (long long)blockIdx.x * rows_per_wg;
   const int n_rows = total - row0 < rows_per_wg ? (int)(total - row0) : rows_per_wg;
+  const int li = tid % LPH;
+  uint4 lo, hi;  // the piece in hand
+  auto load = [&](const unsigned short *at) __attribute__((always_inline)) {
+    lo = *(const uint4 *)at;
+    hi = *(const uint4 *)(at + kPairs);
+  };
+  const int r_q = tid / (p.Hq * LPH);
+  if (r_q < n_rows) load(a.q + ((row0 + r_q) * p.Hq + (tid - r_q * p.Hq * LPH) / LPH) * D + 8 * li);
   for (int i = tid; i < n_rows * kPairs; i += 256) {
     const int r = i / kPairs, c = i % kPairs;
     const long long br = row0 + r, b = br / a.rows;
@@ -71,15 +81,14 @@ __global__ __launch_bounds__(256) void rope_apply_kernel(const Problem p, const 
     sm_cs[r][c] = cs;
   }
   __syncthreads();
-  const int li = tid % LPH;
-  auto walk = [&](unsigned short *base, int heads) __attribute__((always_inline)) {
+  auto walk = [&](unsigned short *base, int heads, bool held) __attribute__((always_inline)) {
     const int per_row = heads * LPH;  // pieces of 8 channel pairs in a row
     unsigned short *const x = base + row0 * heads * D;
     int r = tid / per_row, u = tid - r * per_row;  // this thread's piece: row r, piece u of the row
     const int dr = 256 / per_row, du = 256 - dr * per_row;
-    while (r < n_rows) {
+    for (; r < n_rows; held = false) {
       unsigned short *const at = x + ((long long)r * heads + u / LPH) * D + 8 * li;
-      uint4 lo = *(const uint4 *)at, hi = *(const uint4 *)(at + kPairs);
+      if (!held) load(at);
       float sn[8], cs[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -97,8 +106,8 @@ __global__ __launch_bounds__(256) void rope_apply_kernel(const Problem p, const 
       }
     }
   };
-  walk(a.q, p.Hq);
-  walk(a.k, p.Hkv);
+  walk(a.q, p.Hq, true);
+  walk(a.k, p.Hkv, false);
 }
 
 hipError_t launch_rope_apply(const Problem &p, const RopeArgs &a, hipStream_t st) {
