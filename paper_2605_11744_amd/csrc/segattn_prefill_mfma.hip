@@ -1127,7 +1127,8 @@ int device_cus() {
 // configurations without one) the decode path's, which no other call of this context uses at the
 // same time.  A workgroup costs about kItemSteps steps beyond its keys (prologue and output).
 // Measured, 32/8 heads, two PAST, m = 173 rows behind 37.5K rows, whole call with the commit: 412 us with
-// four pieces at most, 66 us with 35 pieces of 34 steps; pieces of 48 and 64 steps 20 and 30 us more.
+// four pieces at most, 61 as planned here (252 workgroups); a plan of 258 of them, two more than CUs, made the
+// attention alone 77 us where it is 47 now.
 // Long chunks, 24K to 38K rows behind them (as many pieces as fit the CUs once / the first length that
 // left no second round / compared): 32/8 heads, S = 2048, four PAST: 1602 rows 379 / 470 / 384, 2000 rows 422 / 485 /
 // 425, 1100 rows 318 / 369 / 267; two PAST, S = 4096: 1900 rows 478 / 690 / 404, a whole segment 675 / 716 / 677.

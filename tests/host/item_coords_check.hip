@@ -118,7 +118,7 @@ int main() {
                   if (nqb % sub) continue;
                   check_launch(B, Hkv, n_past, g, hw, n_seg, nqb, 1, sub, false, false);
                 }
-                check_launch(B, Hkv, n_past, g, hw, n_seg, nqb, 1, 1, true, false);   // packed batch: rotated assignment
+                check_launch(B, Hkv, n_past, g, hw, n_seg, nqb, 1, 1, true, false);   // packed batch numbered over the padded grid: rotated assignment
                 check_launch(B, Hkv, n_past, g, hw, n_seg, nqb, 1, 1, false, true);   // retrieved prefixes: one common list
                 if (n_past > 0 && n_seg == 1)
                   for (int parts : {2, 3, 4}) check_launch(B, Hkv, n_past, g, hw, 1, nqb, parts, 1, false, false);

@@ -202,8 +202,9 @@ def _fwd(G, cfg, qd, kd, vd, n, stream=None):
 def test_item_queues_run_every_item_exactly_once(monkeypatch):
     """Queued or not, an item is the same arithmetic in the same order: over a few thousand items
     (more than fit the chip at once, so the order they are taken in varies) the two forms must
-    agree bit for bit, on repeated launches (the counters are cleared in front of each), and a
-    launch that has more workgroups than items must leave nothing unwritten."""
+    agree bit for bit, on repeated launches (the last workgroup of a launch to leave clears the
+    counters for the next), and a launch that has more workgroups than items must leave nothing
+    unwritten."""
     import gpu_util as G
     w = W.small("queued", index=143, seq_len=6000, seg_len=1024, tail_len=256, n_q_heads=16, n_kv_heads=8,
                 head_dim=128, kv_policy=[3, 1, 0, 3, 1, 1, 2, 0], batch=2)

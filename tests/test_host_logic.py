@@ -54,8 +54,8 @@ def test_items_of_packed_batches(tmp_path):
 
 def test_item_mapping_is_one_to_one_and_longest_first(tmp_path):
     """item_coords (the integer part of the kernels' block-index resolution) over some 10,000 launch
-    shapes -- dense, packed, retrieved-prefix and split-prefix forms, every sub-group count -- maps
-    the item indices one-to-one onto (segment, block, head, sequence, sub-group, piece), lists the
+    shapes -- dense, packed (numbered over the padded grid), retrieved-prefix and split-prefix forms,
+    every sub-group count -- maps the item indices one-to-one onto (segment, block, head, sequence, sub-group, piece), lists the
     full-history heads first and longest first, and gives the same answer with the host-prepared
     divisors as with plain divisions."""
     out = _build_and_run(tmp_path, "item_coords_check")
