@@ -2,7 +2,7 @@
 waves (small windows): lengths around the 32-row step, fewer steps than waves, every number of query
 heads per workgroup, carried tails that end inside a key block, segments that are no multiple of a
 block, packed batches with empty and one-token sequences, and enough key blocks for the four-wave
-dK/dV form.  The oracle is the judge; bars as in test_gpu_backward.py."""
+dK/dV form.  Compared with the oracle; bars as in test_gpu_backward.py."""
 import numpy as np
 import pytest
 import torch

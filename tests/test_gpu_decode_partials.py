@@ -1,7 +1,7 @@
 """GPU parity of a decode step whose windows have many partial results to merge: more slices than the chip
 holds workgroups (so that windows share them), with two or three, a dozen and dozens of partials in a
 window, more than one batch of the merge kernel, a short sequence beside a long one.  Two tokens, so that the
-second reads the first one's row and count.  The oracle is the judge."""
+second reads the first one's row and count.  Compared with the oracle."""
 import numpy as np
 import pytest
 

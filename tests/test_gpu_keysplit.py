@@ -2,7 +2,7 @@
 waves (few query rows): lengths around the 32-key step, the 32-column block and the eight waves of a
 workgroup (fewer key steps than waves, a last round of one), every number of query heads per
 workgroup, segments that are no multiple of a block, packed batches with empty and one-token
-sequences, bf16 and fp32 results.  The oracle is the judge."""
+sequences, bf16 and fp32 results.  Compared with the oracle."""
 import numpy as np
 import pytest
 import torch

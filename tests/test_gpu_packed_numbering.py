@@ -1,7 +1,7 @@
 """GPU parity of packed batches under both numberings of their items (row blocks there are, or every sequence
 padded to the longest, whichever is fewer): sequences of one length, more than 64 of them (the search for
 a block's sequence takes several steps), a long one among short ones; with the kernels for small
-launches and, under item_queues = 3, with the general ones.  The oracle is the judge."""
+launches and, under item_queues = 3, with the general ones.  Compared with the oracle."""
 import numpy as np
 import pytest
 import torch

@@ -1,7 +1,7 @@
 """GPU parity on seeded random small configurations: segment and tail lengths that are not
 multiples of the 32-key step, tails longer than a step, one-row segments, every GQA ratio the
 kernels specialise on, both head dimensions, both workgroup shapes, dense and packed batches,
-forward and backward.  The oracle is the judge in every case."""
+forward and backward.  Every case is compared with the oracle."""
 import numpy as np
 import pytest
 import torch

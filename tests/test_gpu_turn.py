@@ -2,7 +2,7 @@
 histories), where the library cuts the heads' prefixes into pieces and merges them: sequences of
 different lengths in one call (so that heads have different numbers of pieces, one of them none),
 prefixes that end on and off a piece, both head dimensions, a workspace of its own and the decode
-path's.  The oracle is the judge.  Then the commit of such a chunk in one launch: rows and counters bit for
+path's.  Compared with the oracle.  Then the commit of such a chunk in one launch: rows and counters bit for
 bit, and the decode step that reads them."""
 import numpy as np
 import pytest
