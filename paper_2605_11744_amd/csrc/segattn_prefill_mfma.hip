@@ -25,7 +25,7 @@
 //
 // K/V rows travel HBM -> LDS with global_load_lds_dwordx4 (no staging registers) into a ring
 // of step slots, three or more steps ahead of their use (eight-wave workgroups: 8 slots, the
-// waves meet at a barrier only every other step and fetch two steps there; otherwise 5 slots and
+// waves meet at a barrier only every other step and fetch two steps there; otherwise 5 or 6 slots and
 // a barrier per step); the 16-byte chunks of a row are XOR-swizzled by the loading lanes so that
 // both the row-wise K reads and the transposing V reads
 // are free of bank conflicts.  Steps that need an element mask (the diagonal of the query's
@@ -58,8 +58,9 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 #define GLB_AS __attribute__((address_space(1)))
 
 constexpr int kStepKeys = 32;
-// LDS ring of step slots.  Per-step sync: steps j-1 .. j+3 are resident or in flight (5 slots, one
-// step of loads may still be in flight at a sync).  Pair sync (eight-wave workgroups): the waves
+// LDS ring of step slots.  Per-step sync: steps j-1 .. j+3 (j+4) are resident or in flight (5 slots, 6 for head_dim
+// 64, where three workgroups still share a CU and rounds of an even number of steps can be unrolled; one, two
+// steps of loads may still be in flight at a sync).  Pair sync (eight-wave workgroups): the waves
 // meet only at every other step and fetch two steps there; steps j-1 .. j+6 (8 slots, two steps in
 // flight at a sync).
 __host__ __device__ constexpr bool pair_sync(int nw, int qb) {
@@ -69,7 +70,7 @@ __host__ __device__ constexpr bool pair_sync(int nw, int qb) {
   return nw == 8 && qb == 1;
 #endif
 }
-__host__ __device__ constexpr int ring_slots(int nw, int qb) { return pair_sync(nw, qb) ? 8 : 5; }
+__host__ __device__ constexpr int ring_slots(int d, int nw, int qb) { return pair_sync(nw, qb) ? 8 : d == 64 ? 6 : 5; }
 constexpr float kLazyLimit = 256.f;  // a lane's 16-weight row sum above this triggers a rescale
 
 template <int D>
@@ -122,8 +123,8 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
   constexpr int NB = D / 32;        // 32-row blocks of O^T
   constexpr int LPW = G::kInstr / NW;  // wave-wide 1 KB loads per tensor, step and wave
   constexpr bool kPair = pair_sync(NW, QB);
-  constexpr int kSlots = ring_slots(NW, QB);
-  constexpr int kAhead = kPair ? 2 : 1;  // whole steps of loads that may still be in flight at a sync
+  constexpr int kSlots = ring_slots(D, NW, QB);
+  constexpr int kAhead = kPair ? 2 : kSlots - 4;  // whole steps of loads that may still be in flight at a sync
   static_assert(LPW >= 1, "too many waves for this tile");
 
   WorkItem w = resolve<PK, !PK>(p, a, bid, BQ, HS);
@@ -146,13 +147,11 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
   const int nst0 = (w.n0 + kStepKeys - 1) / kStepKeys;
   const int nst1 = (n1_needed + kStepKeys - 1) / kStepKeys;
   const int n = nst0 + nst1;
-  int f;  // leading steps that need no element mask for this wave
-  if (w.n0 % kStepKeys) {
-    f = nst0 - 1;
-  } else {
-    const int full1 = (tw0 + 1) / kStepKeys;  // span-1 steps whose keys all precede every query
-    f = nst0 + (full1 < nst1 ? full1 : nst1);
-  }
+  // steps before f need no element mask for this wave: those up to its diagonal (f_own), but for the ragged
+  // last step of span 0, which f stops at first
+  const int full1 = (tw0 + 1) / kStepKeys;  // span-1 steps whose keys all precede every query
+  const int f_own = nst0 + (full1 < nst1 ? full1 : nst1);
+  int f = w.n0 % kStepKeys ? nst0 - 1 : f_own;
   int n_act;  // steps at or beyond this one start after the wave's last query: nothing to compute
   {
     const int s1 = (tw0 + RW - 1) / kStepKeys + 1;
@@ -215,8 +214,8 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
     }
     ld_slot = next_slot(ld_slot);
   };
-  // Branch-free advance for the hot loop: the caller guarantees that the next step is a plain
-  // full step of the same span (ld_js + 1 < ld_full_end).
+  // Branch-free advance: the caller guarantees that the next step is a plain full step of the same span
+  // (ld_js + 1 < ld_full_end).
   auto loader_advance_plain = [&]() __attribute__((always_inline)) {
     ld_js += 1;
     ld_kp += (size_t)kStepKeys * ld_stride;
@@ -225,7 +224,11 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
   };
   auto loader_advance = [&]() __attribute__((always_inline)) {  // move on to the next step, if there is one (uniform branches)
     ld_js += 1;
-    if (ld_js < n) {
+    if (__builtin_expect(ld_js < ld_full_end, 1)) {  // a plain full step of the same span
+      ld_kp += (size_t)kStepKeys * ld_stride;
+      ld_vp += (size_t)kStepKeys * ld_stride;
+      ld_left -= kStepKeys;
+    } else if (ld_js < n) {
       const bool to_span1 = ld_span == 0 && ld_js == nst0;
       if (to_span1) {
         ld_span = 1;
@@ -248,7 +251,7 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
 #define SEGATTN_VMCNT(N) __builtin_amdgcn_s_waitcnt(0x0F70 | ((N) & 15) | (((N) >> 4) << 14))
   // The sync of step j, executed by every wave in the middle of the step (in the prologue for
   // j = 0).  Per-step form: the loads of steps <= j+2 have landed for every wave and every wave is
-  // done reading the slot of step j-1, which now receives the loads of step j+4.  Pair form: only
+  // done reading the slot of step j-1, which now receives the loads of step j+4 (6 slots: j+5).  Pair form: only
   // even steps sync; the loads of steps <= j+3 have landed (the odd step that follows needs j+2
   // and j+3 and meets nobody) and the slots of steps j-2 and j-1 receive steps j+6 and j+7.
   // The loader is left at the last step fetched; the caller moves it on once more.
@@ -307,18 +310,19 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
     }
   }
 
-  // Eight-slot ring: LDS addresses of the operand reads for the ring's two halves.  A step whose
-  // ring position is known at compile time (the unrolled blocks of eight steps below) reads its
-  // operands at one of these plus an immediate offset and spends no instruction on addresses.
-  constexpr bool kStaticRing = kPair && kSlots == 8 && 4 * G::kSlotBytes <= 65536;
-  constexpr int kHalves = kStaticRing ? 2 : 1;
-  unsigned kbase[kHalves][NKA], vbase[kHalves][NB];
+  // LDS addresses of the operand reads, for the slots that an immediate offset reaches from slot 0 (and from the first
+  // slot beyond).  A step whose ring position is known at compile time (the unrolled steps below) reads
+  // its operands at one of these plus an immediate and spends no instruction on addresses.
+  constexpr int kReach = 65536 / G::kSlotBytes;  // slots that an immediate offset reaches
+  constexpr bool kFixedRounds = kSlots % 2 == 0;
+  constexpr int kBases = kFixedRounds ? (kSlots + kReach - 1) / kReach : 1;
+  unsigned kbase[kBases][NKA], vbase[kBases][NB];
 #pragma unroll
-  for (int hf = 0; hf < kHalves; ++hf) {
+  for (int bs = 0; bs < kBases; ++bs) {
 #pragma unroll
-    for (int i = 0; i < NKA; ++i) kbase[hf][i] = (unsigned)(size_t)lds + (unsigned)(koff[i] + hf * 4 * G::kSlotBytes);
+    for (int i = 0; i < NKA; ++i) kbase[bs][i] = (unsigned)(size_t)lds + (unsigned)(koff[i] + bs * kReach * G::kSlotBytes);
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) vbase[hf][nb] = (unsigned)(size_t)lds + (unsigned)(voff[nb] + hf * 4 * G::kSlotBytes);
+    for (int nb = 0; nb < NB; ++nb) vbase[bs][nb] = (unsigned)(size_t)lds + (unsigned)(voff[nb] + bs * kReach * G::kSlotBytes);
   }
 
   f32x16 O[QB][NB];
@@ -514,7 +518,7 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
         if (8 * (r >> 2) + (r & 3) >= lim) S[qb][r] = -INFINITY;
     }
   };
-  auto sync_step_hot = [&](auto plain) __attribute__((always_inline)) {
+  auto sync_step_hot = [&](auto plain) __attribute__((always_inline)) {  // sync_step, for hot_step alone (see span_scalars)
     SEGATTN_VMCNT(kAhead * 2 * LPW);
     __builtin_amdgcn_s_barrier();
     issue_loads();
@@ -532,9 +536,7 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
   // of the query's own segment, the ragged end of a span).
   // Laid out by hand as 2*NC + 4*NB slots of one matrix product
   // each; whatever else the step has to do is spread over the slots so that it issues in the
-  // shadow of the products (about six vector instructions fit under a 32x32x16 MFMA).  The
-  // sync is branch-free: exactly one step of loads stays in flight and the loads issued are a
-  // full step of the current span.
+  // shadow of the products (about six vector instructions fit under a 32x32x16 MFMA).
   //   slots 0 .. 2NC-1        S^T(j+1) products; all V^T reads; exp2 of pair i in slot 2i
   //   slots 2NC .. 2NC+2NB-1  PV(j-1), first 16 keys
   //   (sync, then the K reads of step j+2, two per slot)
@@ -547,9 +549,8 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
     if constexpr (decltype(masked)::value) mask_step(Sc, j);
     constexpr int RP = decltype(ring_pos)::value;
     constexpr bool kFixed = RP >= 0;
-    constexpr int vslot = kFixed ? RP : 0, kslot = kFixed ? (RP + 3) % 8 : 0;
-    constexpr int vimm = (vslot % 4) * G::kSlotBytes, kimm = (kslot % 4) * G::kSlotBytes;
-    static_assert(!kFixed || kStaticRing, "fixed ring positions need the eight-slot ring");
+    constexpr int vslot = kFixed ? RP : 0, kslot = kFixed ? (RP + 3) % kSlots : 0;
+    constexpr int vimm = (vslot % kReach) * G::kSlotBytes, kimm = (kslot % kReach) * G::kSlotBytes;
     constexpr int NS = QB * NC, NP = QB * NB;  // slots of the S^T product / of half a PV product
     constexpr int NSLOT = NS + 2 * NP;
     constexpr int NE = 16 * QB;                // softmax elements per lane and step
@@ -562,13 +563,10 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
     f32x16 Sacc[QB];
     int Pw[QB][8];  // P of the current step as 32-bit words: word 4 h2 + t of Pw[qb] = elements 8 h2 + 2t, +1
     float ev[NE];   // exp2 results on their way to the bf16 pairs (a few live at a time)
-    unsigned va[NB], ka[NKA];
+    unsigned va[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
-      va[nb] = kFixed ? vbase[kFixed ? vslot / 4 : 0][nb] : vbase[0][nb] + (unsigned)so_m1;
-#pragma unroll
-    for (int i = 0; i < NKA; ++i)
-      ka[i] = kFixed ? kbase[kFixed ? kslot / 4 : 0][i] : kbase[0][i] + (unsigned)so_p2;
+      va[nb] = kFixed ? vbase[vslot / kReach][nb] : vbase[0][nb] + (unsigned)so_m1;
     // vector-ALU work of one slot: exp2 of EPS elements, and half of the conversion / row-sum
     // work of an earlier pair, so that every slot carries the same four issue slots
     auto valu_chunk = [&](int slot) __attribute__((always_inline)) {
@@ -642,7 +640,9 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
       }
       if (slot > kSyncSlot && slot - kSyncSlot - 1 < NC) {
         const int kc = slot - kSyncSlot - 1;
-        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(Kr[kc]) : "v"(ka[kc]), "n"(kimm));
+        // (the address of a step anywhere in the ring is formed here: eight of them from the start are eight registers)
+        const unsigned ka = kFixed ? kbase[kslot / kReach][kc] : kbase[0][kc] + (unsigned)so_p2;
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(Kr[kc]) : "v"(ka), "n"(kimm));
       }
       valu_chunk(slot);
       __builtin_amdgcn_sched_barrier(0);
@@ -704,47 +704,71 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
     k_wait(Kr);
   }
   int j = 1;
+  if (nst0 <= 1) f = f_own;  // step 0 was the ragged end of span 0, if there is one
   advance();
   constexpr std::true_type yes{};
   constexpr std::false_type no{};
   // here and at the top of every iteration below: Sa = S^T(j), Pb = P(j-1), Kr = K operands of j+1
   constexpr std::integral_constant<int, -1> anywhere{};
+  // A pair of unmasked steps at ring positions P, P + 1; with the pair sync an odd step, which meets nobody, and
+  // the even step after it.
+#define SEGATTN_PAIR_AT(PLAIN, P)                                                                                      \
+  do {                                                                                                                 \
+    hot_step(no, PLAIN, std::integral_constant<bool, !kPair>{}, std::integral_constant<int, (P)>{}, j, Kr, Sa, Sb, Pb, \
+             Pa);                                                                                                      \
+    hot_step(no, PLAIN, yes, std::integral_constant<int, (P) + 1>{}, j + 1, Kr, Sb, Sa, Pa, Pb);                       \
+    j += 2;                                                                                                            \
+  } while (0)
+#define SEGATTN_ROUND(PLAIN)                          \
+  do {                                                \
+    SEGATTN_PAIR_AT(PLAIN, 0);                        \
+    SEGATTN_PAIR_AT(PLAIN, 2);                        \
+    SEGATTN_PAIR_AT(PLAIN, 4);                        \
+    if constexpr (kSlots == 8) SEGATTN_PAIR_AT(PLAIN, 6); \
+  } while (0)
   while (j < n_act) {
-    // Blocks of eight unmasked steps at fixed ring positions (eight-slot ring): step j sits in slot
-    // j % 8 for the whole item, so from j = 1 (mod 8) on -- where the sequence starts -- the eight
-    // steps of a block read their operands at compile-time offsets; the slot variables return to
-    // where they were after eight steps and are left alone.
-    if constexpr (kStaticRing) {
-      while ((j & 7) == 1 && j + 7 < f && ld_js + 8 < ld_full_end) {
-        hot_step(no, yes, no, std::integral_constant<int, 0>{}, j, Kr, Sa, Sb, Pb, Pa);
-        hot_step(no, yes, yes, std::integral_constant<int, 1>{}, j + 1, Kr, Sb, Sa, Pa, Pb);
-        hot_step(no, yes, no, std::integral_constant<int, 2>{}, j + 2, Kr, Sa, Sb, Pb, Pa);
-        hot_step(no, yes, yes, std::integral_constant<int, 3>{}, j + 3, Kr, Sb, Sa, Pa, Pb);
-        hot_step(no, yes, no, std::integral_constant<int, 4>{}, j + 4, Kr, Sa, Sb, Pb, Pa);
-        hot_step(no, yes, yes, std::integral_constant<int, 5>{}, j + 5, Kr, Sb, Sa, Pa, Pb);
-        hot_step(no, yes, no, std::integral_constant<int, 6>{}, j + 6, Kr, Sa, Sb, Pb, Pa);
-        hot_step(no, yes, yes, std::integral_constant<int, 7>{}, j + 7, Kr, Sb, Sa, Pa, Pb);
-        j += 8;
+    // Unmasked steps, a round of the ring at a time at fixed ring positions: from the item's start on (step j - 1
+    // sits in slot 0 there).  Issue-bound, so the fewest instructions a step: the rounds with a branch-free loader are
+    // the fast ones of the eight-wave form (32K prompt: 1521 cycles a step, 1616 with the general loader); the
+    // others cross the end of a span.  Pairs anywhere in the ring take 1718, a single step with its mask and
+    // moves 1990 to 2310: with those for all that was near the end of a span or behind a ragged one,
+    // a tenth (64K prompt in retrieval mode) to two fifths (S = 1024) of the steps were of the last kind.  Whole
+    // calls, before -> after: eight packed prompts of 65 to 9001 tokens 676 -> 646 us, 10.8K tokens in retrieval mode
+    // with S = 1024 196 -> 185, 5 x 501 tokens of 16/4 heads of 64 16.5 -> 14.6, 128K tokens 32.95 -> 32.90 ms.
+    if constexpr (kFixedRounds) {
+      if (so_m1 == 0) {
+        while (j + kSlots - 1 < f) {
+          if constexpr (kPair) {
+            while (j + kSlots - 1 < f && ld_js + kSlots < ld_full_end) SEGATTN_ROUND(yes);
+            if (j + kSlots - 1 >= f) break;
+          }
+          SEGATTN_ROUND(no);
+        }
       }
-      if (j >= n_act) break;
     }
-    // pairs of steps that need no mask while the loader stays inside plain full steps of its span
-    // (with the pair sync a pair is an odd step, which meets nobody, and the even step after it)
+    // pairs of them anywhere in the ring
     if (!kPair || (j & 1)) {
-      while (j + 1 < f && ld_js + 2 < ld_full_end) {
-        if constexpr (kPair) hot_step(no, yes, no, anywhere, j, Kr, Sa, Sb, Pb, Pa);
-        else hot_step(no, yes, yes, anywhere, j, Kr, Sa, Sb, Pb, Pa);
+      if constexpr (!kFixedRounds) {
+        while (j + 1 < f && ld_js + 2 < ld_full_end) {
+          hot_step(no, yes, yes, anywhere, j, Kr, Sa, Sb, Pb, Pa);
+          advance();
+          hot_step(no, yes, yes, anywhere, j + 1, Kr, Sb, Sa, Pa, Pb);
+          advance();
+          j += 2;
+        }
+      }
+      while (j + 1 < f) {
+        hot_step(no, no, std::integral_constant<bool, !kPair>{}, anywhere, j, Kr, Sa, Sb, Pb, Pa);
         advance();
-        hot_step(no, yes, yes, anywhere, j + 1, Kr, Sb, Sa, Pa, Pb);
+        hot_step(no, no, yes, anywhere, j + 1, Kr, Sb, Sa, Pa, Pb);
         advance();
         j += 2;
       }
       if (j >= n_act) break;
     }
-    // any other step (the loader is at a span switch, a ragged step or its last step, or the
-    // step needs a mask): the masked step with the loader's general advance; a mask that hides
-    // nothing is harmless.  Its results move back into (Sa, Pb) so that the roles stay fixed
-    // (choosing between the two register sets at run time would put them in memory).
+    // any other step: one that needs a mask, or the last before it (a mask that hides nothing is harmless).
+    // Its results move back into (Sa, Pb) so that the roles stay fixed (choosing between the two register
+    // sets at run time would put them in memory).
     if constexpr (kPair) hot_step(yes, no, !(j & 1), anywhere, j, Kr, Sa, Sb, Pb, Pa);
     else hot_step(yes, no, yes, anywhere, j, Kr, Sa, Sb, Pb, Pa);
     advance();
@@ -756,7 +780,10 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
       Pb[qb][1] = Pa[qb][1];
     }
     ++j;
+    if (j == nst0) f = f_own;  // past the ragged end of span 0
   }
+#undef SEGATTN_ROUND
+#undef SEGATTN_PAIR_AT
   // so_m1 is the slot of the wave's last step, whose P waits in Pb
   pv(so_m1, Pb);
   // steps that only other waves of the workgroup need (a workgroup with several 32-row blocks per
@@ -836,7 +863,7 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
 // is hidden.  Each queue's counter has a 128-byte line of its own; the last workgroup of a launch
 // clears them.
 template <int D, int HS, int QB, int NW, bool PK>
-__global__ __launch_bounds__(64 * NW, 8 / (NW * QB)) void prefill_mfma_kernel(const Problem p_arg, const PrefillArgs a_arg) {
+__global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 8 / (NW * QB)) void prefill_mfma_kernel(const Problem p_arg, const PrefillArgs a_arg) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   // take_item's hand-over word lives at the start of the ring, which is idle between two items (a
   // static variable of its own would be the four bytes by which two four-wave workgroups, 80 KB of
@@ -1040,7 +1067,7 @@ unsigned *item_queue_for(hipStream_t st) {
 
 template <int D, int HS, int QB, int NW, bool PK>
 static hipError_t launch_mfma(const Problem &p, const PrefillArgs &a_in, long long grid, hipStream_t st) {
-  constexpr int ring = ring_slots(NW, QB) * StepGeom<D>::kSlotBytes;
+  constexpr int ring = ring_slots(D, NW, QB) * StepGeom<D>::kSlotBytes;
   constexpr int epilogue = NW * 32 * (D * 4 + 8);  // fp32 output staging, one block per wave
   constexpr int lds = ring > epilogue ? ring : epilogue;
   auto kern = prefill_mfma_kernel<D, HS, QB, NW, PK>;

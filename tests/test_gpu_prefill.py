@@ -67,6 +67,23 @@ def test_fwd_seq_items_of_many_steps(seq_len, seg_len, tail_len, item_queues, mo
     G.assert_parity(o, l, o_ref, l_ref, fp32_check=False, what="long items")
 
 
+@pytest.mark.parametrize("head_dim,waves", [(64, 0), (128, 4), (128, 8)])
+@pytest.mark.parametrize("seq_len,seg_len,tail_len", [(1430, 620, 200), (1300, 416, 21), (901, 901, 0)])
+def test_fwd_seq_steps_in_rounds_and_pairs(seq_len, seg_len, tail_len, head_dim, waves, monkeypatch):
+    """Items of 1 to 45 key steps in every workgroup shape (rings of 6, 5 and 8 slots): whole rounds of the ring, the
+    pairs left over, and the steps with a mask -- the ragged end of a prefix (carried tails of 200 and 21 rows, a past of
+    620 or 1240) at every place in a round, with unmasked steps before and behind it, and the diagonal."""
+    import gpu_util as G
+    monkeypatch.setitem(G.TUNING, "prefill_waves", waves)
+    monkeypatch.setitem(G.TUNING, "item_queues", 1)  # (and with it not the form that shares the keys of a block out)
+    w = W.small("rounds", index=151, seq_len=seq_len, seg_len=seg_len, tail_len=tail_len, n_q_heads=8, n_kv_heads=2,
+                head_dim=head_dim, kv_policy=[3, 1])
+    q, k, v = W.prefill_inputs(w)
+    o_ref, l_ref = _oracle(w, q, k, v)
+    o, l = G.fwd_seq(w, q, k, v, fp32_check=False)
+    G.assert_parity(o, l, o_ref, l_ref, fp32_check=False, what="rounds and pairs")
+
+
 @pytest.mark.parametrize("fp32_check", [True, False])
 def test_fwd_seq_c1_full(fp32_check):
     import gpu_util as G
