@@ -729,19 +729,18 @@ __device__ __forceinline__ unsigned prefill_mfma_item(const Problem &p, const Pr
   while (j < n_act) {
     // Unmasked steps, a round of the ring at a time at fixed ring positions: from the item's start on (step j - 1
     // sits in slot 0 there).  Issue-bound, so the fewest instructions a step: the rounds with a branch-free loader are
-    // the fast ones of the eight-wave form (32K prompt: 1521 cycles a step, 1616 with the general loader); the
-    // others cross the end of a span.  Pairs anywhere in the ring take 1718, a single step with its mask and
-    // moves 1990 to 2310: with those for all that was near the end of a span or behind a ragged one,
-    // a tenth (64K prompt in retrieval mode) to two fifths (S = 1024) of the steps were of the last kind.  Whole
-    // calls, before -> after: eight packed prompts of 65 to 9001 tokens 676 -> 646 us, 10.8K tokens in retrieval mode
-    // with S = 1024 196 -> 185, 5 x 501 tokens of 16/4 heads of 64 16.5 -> 14.6, 128K tokens 32.95 -> 32.90 ms.
+    // the fast ones (32K prompt: 1521 cycles a step, 1616 with the general loader; 48K tokens of 16/4 heads of 64
+    // 2455 us, 2516 with the general loader alone); the others cross the end of a span.  Pairs anywhere in the
+    // ring take 1718, a single step with its mask and moves 1990 to 2310: with those for all that was near
+    // the end of a span or behind a ragged one, a tenth (64K prompt in retrieval mode) to two fifths
+    // (S = 1024) of the steps were of the last kind.  Whole calls, before -> after: eight packed prompts of 65 to 9001
+    // tokens 676 -> 646 us, 10.8K tokens in retrieval mode with S = 1024 196 -> 185, 5 x 501 tokens of 16/4 heads
+    // of 64 16.5 -> 14.6, 2 x 6.7K of them with S = 1000 136 -> 122, 128K tokens 32.95 -> 32.90 ms.
     if constexpr (kFixedRounds) {
       if (so_m1 == 0) {
         while (j + kSlots - 1 < f) {
-          if constexpr (kPair) {
-            while (j + kSlots - 1 < f && ld_js + kSlots < ld_full_end) SEGATTN_ROUND(yes);
-            if (j + kSlots - 1 >= f) break;
-          }
+          while (j + kSlots - 1 < f && ld_js + kSlots < ld_full_end) SEGATTN_ROUND(yes);
+          if (j + kSlots - 1 >= f) break;
           SEGATTN_ROUND(no);
         }
       }
