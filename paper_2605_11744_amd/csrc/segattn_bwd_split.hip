@@ -31,16 +31,18 @@ template <int D>
 struct TilePair {
   static constexpr int kRPL = 1024 / (2 * D), kLoads = kBwdStep / kRPL;
   u32x4 a[kLoads], b[kLoads];
-  // rows r0 .. r0 + 31 of two tensors of the same row stride; rows beyond `last` repeat it
-  __device__ __forceinline__ void fetch(const unsigned char *pa, const unsigned char *pb, unsigned row_bytes, int last, int lane) {
+  // rows r0 .. r0 + 31 of two tensors of the same row stride; rows beyond `last` repeat it.  (Global pointers
+  // by name: a load through a generic one counts as an LDS access too, and every LDS wait of a step would
+  // wait for the next step's tiles.)
+  __device__ __forceinline__ void fetch(const GLB_AS unsigned char *pa, const GLB_AS unsigned char *pb, unsigned row_bytes, int last, int lane) {
     const int lrow = lane / BwdTile<D>::kChunks;
     const unsigned lchunk = (unsigned)(lane % BwdTile<D>::kChunks) * 16;
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
       const int r = kRPL * i + lrow < last ? kRPL * i + lrow : last;
       const unsigned o = (unsigned)r * row_bytes + lchunk;
-      a[i] = *(const u32x4 *)(pa + o);
-      b[i] = *(const u32x4 *)(pb + o);
+      a[i] = *(const GLB_AS u32x4 *)(pa + o);
+      b[i] = *(const GLB_AS u32x4 *)(pb + o);
     }
   }
   __device__ __forceinline__ void store(unsigned char *ta, unsigned char *tb, int lane) const {
@@ -188,7 +190,7 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 1 : 2) void bwd_dkv_split_kerne
   auto fetch = [&](int it) __attribute__((always_inline)) {
     const int h = it / steps_per_head, q0 = (it - h * steps_per_head) * kBwdStep;
     const long long o = (head0 + (long long)h * D) * 2 + (long long)q0 * row_bytes;
-    next.fetch((const unsigned char *)a.q + o, (const unsigned char *)a.dout + o, row_bytes, n_q - 1 - q0, lane);
+    next.fetch((const GLB_AS unsigned char *)a.q + o, (const GLB_AS unsigned char *)a.dout + o, row_bytes, n_q - 1 - q0, lane);
     const int r = q0 + col < n_q ? q0 + col : n_q - 1;
     next_stat = stat_src[stat0 + h * sq.stat_stride + r];
   };
@@ -316,7 +318,7 @@ __global__ __launch_bounds__(64 * kDqSplitWaves, 2) void bwd_dq_split_kernel(con
     const bool own = j >= nst0;
     const int r0 = (own ? j - nst0 : j) * kBwdStep;
     const unsigned long long o = (unsigned long long)r0 * row_bytes;
-    next.fetch((const unsigned char *)(own ? w.k1 : w.k0) + o, (const unsigned char *)(own ? w.v1 : w.v0) + o, row_bytes,
+    next.fetch((const GLB_AS unsigned char *)(own ? w.k1 : w.k0) + o, (const GLB_AS unsigned char *)(own ? w.v1 : w.v0) + o, row_bytes,
                (own ? w.n1 : w.n0) - 1 - r0, lane);
   };
   if (wave < n) fetch(wave);

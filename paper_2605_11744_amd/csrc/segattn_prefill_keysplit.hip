@@ -30,6 +30,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 #define LDS_AS __attribute__((address_space(3)))
+#define GLB_AS __attribute__((address_space(1)))
 
 constexpr int kSplitWaves = 8;
 constexpr int kSplitStep = 32;  // keys per step
@@ -105,15 +106,17 @@ __global__ __launch_bounds__(64 * kSplitWaves, D == 64 ? 4 : 2) void prefill_key
     const bool own = j >= nst0;
     const int r0 = (own ? j - nst0 : j) * kSplitStep, rows = own ? w.n1 : w.n0;
     const unsigned stride = (unsigned)(own ? w.stride1 : w.stride0) * 2;  // bytes between rows
-    const unsigned char *kp = (const unsigned char *)(own ? w.k1 : w.k0) + (unsigned long long)r0 * stride;
-    const unsigned char *vp = (const unsigned char *)(own ? w.v1 : w.v0) + (unsigned long long)r0 * stride;
+    // (global pointers by name: they come out of scalar registers, and a load through a generic one counts as an
+    // LDS access too, so that every LDS wait of a step waited for the next step's tile as well -- no prefetch)
+    const GLB_AS unsigned char *kp = (const GLB_AS unsigned char *)(own ? w.k1 : w.k0) + (unsigned long long)r0 * stride;
+    const GLB_AS unsigned char *vp = (const GLB_AS unsigned char *)(own ? w.v1 : w.v0) + (unsigned long long)r0 * stride;
     const int last = rows - 1 - r0;
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
       const int r = RPL * i + lrow < last ? RPL * i + lrow : last;  // the ragged end of a span: repeat its last row (masked below)
       const unsigned o = (unsigned)r * stride + lchunk;
-      nk[i] = *(const u32x4 *)(kp + o);
-      nv[i] = *(const u32x4 *)(vp + o);
+      nk[i] = *(const GLB_AS u32x4 *)(kp + o);
+      nv[i] = *(const GLB_AS u32x4 *)(vp + o);
     }
   };
 
