@@ -114,6 +114,7 @@ struct PrefillArgs {
   const int *cu_seqlens; // SEQ mode, packed ragged batch: device [B+1] row offsets, else nullptr
   int packed;            // packed batch: its items are numbered over the row blocks there are (number_packed)
   long long total_rows;  // rows of the packed batch (lse is [Hq, total_rows] then)
+  int longest_steps;     // host: key steps of the longest workgroup, where the launcher has asked (use_keysplit)
   int n_seg;             // segments covered by the launch (1 in CTX mode)
   int q_blocks_per_seg;  // ceil(min(S, n_rows) / rows per workgroup); set by the launcher
   int pair_stride;       // spreads the (segment, sequence, head) groups of non-PAST heads over the XCDs (0 = 1)

@@ -4,12 +4,13 @@
 // With few rows the hand-pipelined kernel (segattn_prefill_mfma.hip) is bound by its longest
 // workgroup: one workgroup walks all keys of its rows in order, 0.5 us per step of 32 keys with one
 // wave per SIMD, while most of the chip idles.  Here the keys are what a workgroup shares out: its
-// eight waves hold the same 32 query columns (32/HS rows of HS heads of one GQA group) and wave w
-// takes the key steps w, w + 8, ...; at the end the eight partial results meet in LDS.  The chain of
+// eight (or sixteen) waves hold the same 32 query columns (32/HS rows of HS heads of one GQA group) and wave w
+// takes the key steps w, w + 8, ...; at the end the partial results meet in LDS.  The chain of
 // dependent steps is an eighth, and there are as many workgroups as 32-column blocks.  The price: every
 // wave stages its own K/V tile (16 KB of L2 traffic per wave and step, where the other kernel's
 // eight waves share one) and nothing is scheduled by hand -- so it is chosen only where the
-// other form leaves the chip waiting (use_keysplit in segattn_prefill_mfma.hip).
+// other form leaves the chip waiting (use_keysplit in segattn_prefill_mfma.hip).  The form also takes the pieces
+// of a prefix behind which a chunk has few rows (plan_pieces there).
 //
 // Products and layouts as in segattn_prefill_mfma.hip: S^T = K . Q^T, O^T += V^T . P^T with 32x32x16 bf16
 // products, P straight from the S^T accumulators, weights rounded to bf16 and summed as rounded, a
@@ -32,19 +33,18 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 #define LDS_AS __attribute__((address_space(3)))
 #define GLB_AS __attribute__((address_space(1)))
 
-constexpr int kSplitWaves = 8;
 constexpr int kSplitStep = 32;  // keys per step
 constexpr int kSplitCols = 32;  // query columns per workgroup
 
-template <int D>
+template <int D, int NW>
 struct SplitGeom {
   static constexpr int kRowBytes = 2 * D, kChunks = D / 8;
   static constexpr int kTensorBytes = kSplitStep * kRowBytes;
   static constexpr int kTileBytes = 2 * kTensorBytes;                    // [K rows][V rows] of one step
-  static constexpr int kMerge = kSplitWaves * kSplitCols * D * 4;        // the waves' O^T, fp32
-  static constexpr int kTiles = kSplitWaves * kTileBytes;
+  static constexpr int kMerge = NW * kSplitCols * D * 4;        // the waves' O^T, fp32
+  static constexpr int kTiles = NW * kTileBytes;
   static constexpr int kStats = kTiles > kMerge ? kTiles : kMerge;       // then [wave][column] m, l
-  static constexpr int kBytes = kStats + kSplitWaves * kSplitCols * 2 * 4;
+  static constexpr int kBytes = kStats + NW * kSplitCols * 2 * 4;
   static constexpr int kRowsPer256 = 256 / kRowBytes;
   // 16-byte chunks of a row XOR-swizzled as in the other forward kernel (row reads and transposing
   // reads free of bank conflicts)
@@ -52,16 +52,18 @@ struct SplitGeom {
   __device__ static constexpr int swz_v(int row) { return 4 * ((row / kRowsPer256) % (kChunks / 4)); }
 };
 
-template <int D, int HS, bool PK>
-__global__ __launch_bounds__(64 * kSplitWaves, D == 64 ? 4 : 2) void prefill_keysplit_kernel(const Problem p, const PrefillArgs a) {
-  using G = SplitGeom<D>;
+// Items: of whole sequences or an uncut chunk; of a packed batch; pieces (see resolve in segattn_work.h).  NW: waves.
+enum { kPlainItems, kPackedItems, kPieceItems };
+template <int D, int HS, int NW, int Items>
+__global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void prefill_keysplit_kernel(const Problem p, const PrefillArgs a) {
+  using G = SplitGeom<D, NW>;
   constexpr int NC = D / 16, NB = D / 32;
   constexpr int R = kSplitCols / HS;           // query rows per workgroup
   constexpr int RPL = 1024 / G::kRowBytes;     // rows per 1 KB wave load
   constexpr int NL = kSplitStep / RPL;         // loads per tile and tensor
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
-  WorkItem w = resolve<PK, false>(p, a, (int)blockIdx.x, R, HS);
+  WorkItem w = resolve<Items == kPackedItems, Items == kPieceItems>(p, a, (int)blockIdx.x, R, HS);
   if (!w.valid) return;
   pin_uniform(w);
   const int tid = threadIdx.x, lane = tid & 63;
@@ -128,14 +130,14 @@ __global__ __launch_bounds__(64 * kSplitWaves, D == 64 ? 4 : 2) void prefill_key
   float m_ref = -INFINITY, l_run = 0.f;
 
   if (wave < n) fetch(wave);
-  for (int j = wave; j < n; j += kSplitWaves) {
+  for (int j = wave; j < n; j += NW) {
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
       const int r = RPL * i + lrow, ch = lane % G::kChunks;
       *(u32x4 *)(tile + r * G::kRowBytes + ((ch ^ G::swz_k(r)) << 4)) = nk[i];
       *(u32x4 *)(tile + G::kTensorBytes + r * G::kRowBytes + ((ch ^ G::swz_v(r)) << 4)) = nv[i];
     }
-    if (j + kSplitWaves < n) fetch(j + kSplitWaves);
+    if (j + NW < n) fetch(j + NW);
     f32x16 S = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kc = 0; kc < NC; ++kc)
@@ -222,17 +224,17 @@ __global__ __launch_bounds__(64 * kSplitWaves, D == 64 ? 4 : 2) void prefill_key
     }
   }
   __syncthreads();
-  for (int idx = tid; idx < kSplitCols * kQ; idx += 64 * kSplitWaves) {
+  for (int idx = tid; idx < kSplitCols * kQ; idx += 64 * NW) {
     const int cc = idx / kQ, ch = idx % kQ;
     const int row = w.t0 + cc / HS;
     if (row > last_row) continue;
     float mx = -INFINITY;
 #pragma unroll
-    for (int wv = 0; wv < kSplitWaves; ++wv) mx = fmaxf(mx, stats[2 * (wv * kSplitCols + cc)]);
+    for (int wv = 0; wv < NW; ++wv) mx = fmaxf(mx, stats[2 * (wv * kSplitCols + cc)]);
     float l = 0.f;
     f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int wv = 0; wv < kSplitWaves; ++wv) {
+    for (int wv = 0; wv < NW; ++wv) {
       const float wgt = __builtin_amdgcn_exp2f((stats[2 * (wv * kSplitCols + cc)] - mx) * c);  // a wave without keys: 0
       l = fmaf(stats[2 * (wv * kSplitCols + cc) + 1], wgt, l);
       const f32x4 x = *(const f32x4 *)(smem + (wv * kSplitCols + cc) * (D * 4) + ((ch ^ (cc & (kQ - 1))) << 4));
@@ -250,33 +252,43 @@ __global__ __launch_bounds__(64 * kSplitWaves, D == 64 ? 4 : 2) void prefill_key
   }
 }
 
-template <int D, int HS, bool PK>
+template <int D, int HS, int NW, int Items>
 static hipError_t launch_split_d(const Problem &p, const PrefillArgs &a, long long grid, hipStream_t st) {
-  auto kern = prefill_keysplit_kernel<D, HS, PK>;
+  auto kern = prefill_keysplit_kernel<D, HS, NW, Items>;
+  constexpr int lds = SplitGeom<D, NW>::kBytes;
   static std::atomic<bool> ready{false};  // the same answer whoever asks first
   if (!ready.load(std::memory_order_acquire)) {
-    const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, SplitGeom<D>::kBytes);
+    const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     ready.store(true, std::memory_order_release);
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * kSplitWaves), SplitGeom<D>::kBytes, st, p, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * NW), lds, st, p, a);
   return hipGetLastError();
 }
 
-template <int D, int HS>
+template <int D, int HS, int NW>
 static hipError_t launch_split(const Problem &p, const PrefillArgs &a, long long grid, hipStream_t st) {
-  return a.packed ? launch_split_d<D, HS, true>(p, a, grid, st) : launch_split_d<D, HS, false>(p, a, grid, st);
+  if constexpr (NW == 8) {
+    if (a.packed) return launch_split_d<D, HS, NW, kPackedItems>(p, a, grid, st);
+    if (a.piece_rows.d != 0) return launch_split_d<D, HS, NW, kPieceItems>(p, a, grid, st);
+  }
+  return launch_split_d<D, HS, NW, kPlainItems>(p, a, grid, st);
+}
+
+template <int D, int NW>
+static hipError_t launch_split_hs(const Problem &p, const PrefillArgs &a, int hs, long long grid, hipStream_t st) {
+  if (hs == 4) return launch_split<D, 4, NW>(p, a, grid, st);
+  if (hs == 2) return launch_split<D, 2, NW>(p, a, grid, st);
+  return launch_split<D, 1, NW>(p, a, grid, st);
 }
 
 hipError_t launch_prefill_keysplit(const Problem &p, const PrefillArgs &a, int hs, long long grid, hipStream_t st) {
-  if (p.D == 128) {
-    if (hs == 4) return launch_split<128, 4>(p, a, grid, st);
-    if (hs == 2) return launch_split<128, 2>(p, a, grid, st);
-    return launch_split<128, 1>(p, a, grid, st);
-  }
-  if (hs == 4) return launch_split<64, 4>(p, a, grid, st);
-  if (hs == 2) return launch_split<64, 2>(p, a, grid, st);
-  return launch_split<64, 1>(p, a, grid, st);
+  if (p.D == 128) return launch_split_hs<128, 8>(p, a, hs, grid, st);
+  // Sixteen waves share out long chains where every workgroup has a CU to itself: 68 rows behind 33K, 16/4 heads of 64,
+  // 120 -> 99 us, 3 x 114 rows of 4/4 heads 127 -> 105.  Not worth the larger merge where a chain is short (64 steps
+  // 12.7 -> 13.1, 11 steps 7.1 -> 7.9).
+  if (grid <= device_cus() && !a.packed && a.piece_rows.d == 0 && a.longest_steps >= 96) return launch_split_hs<64, 16>(p, a, hs, grid, st);
+  return launch_split_hs<64, 8>(p, a, hs, grid, st);
 }
 
 }  // namespace segattn

@@ -904,24 +904,26 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 8 / (NW * QB)) void prefill_
 // softmax over the union is the LSE-weighted mean of the pieces (the same identity the decode path
 // and a sharded prefix use).  32 lanes per (sequence, row, head), D/32 channels each.  Bound by memory
 // latency (the pieces come from other XCDs' caches), so by the round trips that depend on each other.  Heads
-// of at most kWidePieces pieces: eight rows per workgroup, all pieces and LSEs of a row requested at once,
+// of at most kAtOnce pieces: eight rows per workgroup, all pieces and LSEs of a row requested at once,
 // before the number of pieces is known (the workspace has room for the list's most; surplus ones are left
 // out), and the head's counters asked only where not all heads of the list are cut alike.  More pieces: one
-// row per workgroup, lane i forms the weights of the pieces i, i + 32, ..., its eight lane groups take
-// every eighth piece and meet in LDS.  Measured, 173 rows of 8 heads with 35 pieces each and 24 heads with
+// row per workgroup, its eight lane groups take every eighth piece, eight of them in one round trip, and meet
+// in LDS (chunks of up to 16 rows with 50 to 240 pieces, whole calls: 27 to 35 us with a round trip for 32 pieces'
+// weights and rows at a time, 23 to 31 like this).  Measured, 173 rows of 8 heads with 35 pieces each and 24 heads with
 // two: 17.4 us with eight rows per workgroup everywhere (a round trip per eight pieces), 19.2 us with
 // one everywhere (5536 workgroups), 10.7 us like this; 4096 rows of 8 heads with two pieces: 13.9 us with
 // the counters, LSEs and pieces one after the other, 10.2 at once.
 // wgs0: workgroups of list 0; rows0, rows1: (sequence, row, head) items of the lists, 0 where uncut.
-constexpr int kWidePieces = 8;
-template <int D>
+// kAtOnce: 8 or 16, the most pieces of a row that are requested at once (16 take 26 registers more: in launches that
+// have no list of 9 to 16 pieces they cost a turn of 173 rows 1.5 %; a list of 9 to 16 pieces as a wide one 2 to 4 %).
+template <int D, int kAtOnce>
 __global__ __launch_bounds__(256) void prefill_part_combine_kernel(const Problem p, const PrefillArgs a, const int wgs0,
                                                                    const unsigned rows0, const unsigned rows1) {
   constexpr int CPL = D / 32;  // channels per lane
   typedef float f32xc __attribute__((ext_vector_type(CPL)));
   const int list = (int)blockIdx.x < wgs0 ? 0 : 1;
   const PrefillArgs::PieceList &pl = a.piece_list[list];
-  const bool wide = pl.most > kWidePieces;
+  const bool wide = pl.most > kAtOnce;
   const int grp = threadIdx.x >> 5, lane = threadIdx.x & 31;
   const unsigned wg = blockIdx.x - (list ? wgs0 : 0);
   const unsigned m = a.n_rows;
@@ -935,11 +937,11 @@ __global__ __launch_bounds__(256) void prefill_part_combine_kernel(const Problem
   const long long slot = (long long)m * pl.heads;  // rows of one piece
   const float *lse = pl.lse + b * pl.most * slot + (long long)hc * m + row;
   const float *src = pl.out + (b * pl.most * slot + (long long)row * pl.heads + hc) * D + lane * CPL;
-  float ls[kWidePieces];
-  f32xc x[kWidePieces];
+  float ls[kAtOnce];
+  f32xc x[kAtOnce];
   if (!wide) {  // (one test for all lanes: pl.most is the launch's)
 #pragma unroll
-    for (int i = 0; i < kWidePieces; ++i)
+    for (int i = 0; i < kAtOnce; ++i)
       if (i < pl.most) {
         ls[i] = lse[i * slot];
         x[i] = *(const f32xc *)(src + i * slot * D);
@@ -959,10 +961,10 @@ __global__ __launch_bounds__(256) void prefill_part_combine_kernel(const Problem
   for (int e = 0; e < CPL; ++e) acc[e] = 0.f;
   if (!wide) {
 #pragma unroll
-    for (int i = 0; i < kWidePieces; ++i)
+    for (int i = 0; i < kAtOnce; ++i)
       if (i < pieces) mx = fmaxf(mx, ls[i]);
 #pragma unroll
-    for (int i = 0; i < kWidePieces; ++i)
+    for (int i = 0; i < kAtOnce; ++i)
       if (i < pieces) {
         const float wgt = __expf(ls[i] - mx);
         sum += wgt;
@@ -970,32 +972,57 @@ __global__ __launch_bounds__(256) void prefill_part_combine_kernel(const Problem
         for (int e = 0; e < CPL; ++e) acc[e] = fmaf(wgt, x[i][e], acc[e]);
       }
   } else {
-    for (int p0 = 0; p0 < pieces; p0 += 32) mx = fmaxf(mx, p0 + lane < pieces ? lse[(p0 + lane) * slot] : -INFINITY);
+    // Group grp merges the pieces grp, grp + 8, ...: lane i has the LSE of the group's i-th piece (of 32 at a time), and
+    // the rows of eight pieces are requested at once.
+    constexpr int kBatch = 8;
+    for (int p0 = grp; p0 < pieces; p0 += 8 * 32) {
+      const int n = (pieces - p0 + 7) / 8 < 32 ? (pieces - p0 + 7) / 8 : 32;
+      const float l = lane < n ? lse[(p0 + 8 * lane) * slot] : -INFINITY;
+      float m_new = l;
 #pragma unroll
-    for (int sh = 16; sh >= 1; sh >>= 1) mx = fmaxf(mx, __shfl_xor(mx, sh, 32));
-    for (int p0 = 0; p0 < pieces; p0 += 32) {
-      const float mine = p0 + lane < pieces ? __expf(lse[(p0 + lane) * slot] - mx) : 0.f;
-      const int n = pieces - p0 < 32 ? pieces - p0 : 32;
-      sum += mine;
-#pragma unroll 8
-      for (int i = grp; i < n; i += 8) {
-        const float wgt = __shfl(mine, i, 32);
-        const f32xc row_x = *(const f32xc *)(src + (p0 + i) * slot * D);
+      for (int sh = 16; sh >= 1; sh >>= 1) m_new = fmaxf(m_new, __shfl_xor(m_new, sh, 32));
+      m_new = fmaxf(m_new, mx);
+      const float alpha = __expf(mx - m_new), mine = lane < n ? __expf(l - m_new) : 0.f;
+      mx = m_new;
+      sum = fmaf(sum, alpha, mine);
 #pragma unroll
-        for (int e = 0; e < CPL; ++e) acc[e] = fmaf(wgt, row_x[e], acc[e]);
+      for (int e = 0; e < CPL; ++e) acc[e] *= alpha;
+      for (int i0 = 0; i0 < n; i0 += kBatch) {
+        f32xc row_x[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+          if (i0 + u < n) row_x[u] = *(const f32xc *)(src + (p0 + 8 * (i0 + u)) * slot * D);
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+          const float wgt = __shfl(mine, i0 + u, 32);
+#pragma unroll
+          for (int e = 0; e < CPL; ++e) acc[e] = i0 + u < n ? fmaf(wgt, row_x[u][e], acc[e]) : acc[e];
+        }
       }
     }
 #pragma unroll
     for (int sh = 16; sh >= 1; sh >>= 1) sum += __shfl_xor(sum, sh, 32);
-    __shared__ float sm[8][D];
+    __shared__ float sm[8][D], sm_max[8], sm_sum[8];
 #pragma unroll
     for (int e = 0; e < CPL; ++e) sm[grp][lane * CPL + e] = acc[e];
+    if (lane == 0) {
+      sm_max[grp] = mx;
+      sm_sum[grp] = sum;
+    }
     __syncthreads();
     if (grp > 0) return;
 #pragma unroll
-    for (int e = 0; e < CPL; ++e)
+    for (int i = 1; i < 8; ++i) mx = fmaxf(mx, sm_max[i]);
+    sum = 0.f;
 #pragma unroll
-      for (int i = 1; i < 8; ++i) acc[e] += sm[i][lane * CPL + e];
+    for (int e = 0; e < CPL; ++e) acc[e] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float wgt = __expf(sm_max[i] - mx);
+      sum = fmaf(sm_sum[i], wgt, sum);
+#pragma unroll
+      for (int e = 0; e < CPL; ++e) acc[e] = fmaf(sm[i][lane * CPL + e], wgt, acc[e]);
+    }
   }
   const float inv = 1.f / sum;
   const long long o = (((long long)b * m + row) * p.Hq + head) * D + lane * CPL;
@@ -1151,41 +1178,58 @@ int device_cus() {
 // they take, the long list's items first and the others beside and behind them; the shortest launch
 // wins, uncut if nothing is shorter.  Workspace: that of the arena made for it, or (a few rows, or
 // configurations without one) the decode path's, which no other call of this context uses at the
-// same time.  A workgroup costs about kItemSteps steps beyond its keys (prologue and output).
+// same time.  Pieces run in the hand-pipelined form or, a few rows, in the key-split form (32 query columns a
+// workgroup instead of 256, and eight waves that each keep a tile of their own on the way: with 16 rows and less
+// the other form pads its block to 64 and has two steps of 16 KB on their way per CU); both are planned and
+// the estimates compared.  Measured, whole call with the commit, pipelined -> key-split pieces: 8 rows behind 31K, 16/2
+// heads of 128: 34.7 -> 23.3 us; 34 rows of three sequences behind 43K, 16/4 heads: 317 -> 104 (the workspace holds few
+// pieces of 64 rows); 26 rows behind 25K, 16/4 heads of 64: 97 -> 36; 36 rows, 32/8 heads, four PAST: 42 -> 34.5.
 // Measured, 32/8 heads, two PAST, m = 173 rows behind 37.5K rows, whole call with the commit: 412 us with
 // four pieces at most, 61 as planned here (252 workgroups); a plan of 258 of them, two more than CUs, made the
 // attention alone 77 us where it is 47 now.
 // Long chunks, 24K to 38K rows behind them (as many pieces as fit the CUs once / the first length that
 // left no second round / compared): 32/8 heads, S = 2048, four PAST: 1602 rows 379 / 470 / 384, 2000 rows 422 / 485 /
 // 425, 1100 rows 318 / 369 / 267; two PAST, S = 4096: 1900 rows 478 / 690 / 404, a whole segment 675 / 716 / 677.
-constexpr int kMinPieceSteps = 8, kItemSteps = 12;
-static void plan_pieces(const Problem &p, PrefillArgs &a, int hs, int rows, int wgs_per_cu) {
+constexpr int kMinPieceSteps = 8;
+// A form that pieces can run in: query rows of a workgroup, workgroups of it on a CU, steps' worth of time that a
+// workgroup costs beyond its keys, microseconds a step of 32 keys.
+struct PieceForm {
+  int rows, wgs_per_cu, item_steps;
+  double step_us;
+};
+// Plans the pieces of one form (cut_only: the uncut launch is not among its candidates); returns the estimated
+// microseconds of the launch, infinite if nothing is to be cut and that is no candidate.
+static double plan_pieces(const Problem &p, PrefillArgs &a, int hs, const PieceForm &form, bool cut_only) {
   a.parts = a.parts_other = 1;
   a.piece_rows = FastDiv{0u, 0u, 0u};
-  if (a.cache == nullptr || p.tune_waves != 0) return;  // a forced workgroup shape runs unsplit
-  if (a.max_first_prefix >= (1ll << 29)) return;        // piece_count works in 32 bits
+  if (a.cache == nullptr || p.tune_waves != 0) return INFINITY;  // a forced workgroup shape runs unsplit
+  if (a.max_first_prefix >= (1ll << 29)) return INFINITY;        // piece_count works in 32 bits
   const int m = a.n_rows, n_first = heads_listed_first(p, a), n_other = p.Hkv - n_first;
   const long long part_bytes = a.geom.part_max > 1 ? (long long)part_ws_bytes(p, a.geom.part_max) : 0;
   const unsigned long long dec_off = a.geom.ws_off + ws_header_bytes(p);
   const long long dec_bytes = (long long)(a.geom.kv_off - dec_off);
   const bool own_ws = part_bytes >= dec_bytes;
   const long long ws_floats = (own_ws ? part_bytes : dec_bytes) / 4;
-  const long long wgs = (long long)device_cus() * wgs_per_cu;
-  const long long blocks = (long long)p.B * (p.g / hs) * ((m + rows - 1) / rows);  // per KV head
+  const long long wgs = (long long)device_cus() * form.wgs_per_cu;
+  const long long blocks = (long long)p.B * (p.g / hs) * ((m + form.rows - 1) / form.rows);  // per KV head
   auto steps = [&](long long prefix) { return (prefix + m / 2 + kStepKeys - 1) / kStepKeys; };
   const long long sf = n_first > 0 ? steps(a.max_first_prefix) : 0, so = n_other > 0 ? steps(a.max_other_prefix) : 0;
   const long long total = blocks * (n_first * sf + n_other * so);
   // Estimated steps from start to end: workgroups take `first` items of lf steps, then `other` ones of lo.
   auto span = [&](long long first, long long lf, long long other, long long lo) {
-    lf += kItemSteps, lo += kItemSteps;
+    lf += form.item_steps, lo += form.item_steps;
     const long long t0 = first / wgs * lf, busy = first % wgs, idle = wgs - busy, end = t0 + (busy ? lf : 0);
     const long long turns = (other + idle - 1) / idle, beside = busy ? lf / lo : turns;
     if (turns <= beside) return t0 + turns * lo > end ? t0 + turns * lo : end;
     return end + (other - idle * beside + wgs - 1) / wgs * lo;
   };
-  // Uncut, head_dim 128 runs half as long blocks of four waves where the chip has room for them.
-  long long best = span(blocks * n_first, sf, blocks * n_other, so);
-  if (p.D == 128 && waves_d128(p, a, hs) == 4 && 2 * blocks * (n_first > 0 ? n_first : n_other) <= wgs) best = best * 2 / 3;
+  double best = INFINITY;
+  if (!cut_only) {
+    // Uncut, head_dim 128 runs half as long blocks of four waves where the chip has room for them.
+    long long uncut = span(blocks * n_first, sf, blocks * n_other, so);
+    if (p.D == 128 && waves_d128(p, a, hs) == 4 && 2 * blocks * (n_first > 0 ? n_first : n_other) <= wgs) uncut = uncut * 2 / 3;
+    best = uncut * form.step_us;
+  }
   long long len = total * 3 / (4 * wgs), row_heads = 0;
   if (len < kMinPieceSteps) len = kMinPieceSteps;
   for (;; len += (len + 15) / 16) {
@@ -1205,9 +1249,9 @@ static void plan_pieces(const Problem &p, PrefillArgs &a, int hs, int rows, int 
       else
         even = len;
     }
-    // the merge: half an item's steps, and its bytes at HBM speed (4.4 MB a step)
-    const long long merge = kItemSteps / 2 + rh * p.D * 8 / 4400000;
-    const long long cost = merge + span(blocks * n_first * c0, c0 > 1 ? even : sf, blocks * n_other * c1, c1 > 1 ? even : so);
+    // the merge: 5 us, and its bytes at HBM speed (5 MB a us)
+    const double merge = 5 + rh * p.D * 8 / 5.0e6;
+    const double cost = merge + form.step_us * span(blocks * n_first * c0, c0 > 1 ? even : sf, blocks * n_other * c1, c1 > 1 ? even : so);
     if (cost >= best) continue;
     best = cost;
     a.parts = c0;
@@ -1215,12 +1259,13 @@ static void plan_pieces(const Problem &p, PrefillArgs &a, int hs, int rows, int 
     a.piece_rows = t;
     row_heads = rh;
   }
-  if (row_heads == 0) return;
+  if (row_heads == 0) return best;
   const long long rows_first = a.parts > 1 ? (long long)p.B * a.parts * m * n_first * p.g : 0;
   float *const out = (float *)(a.cache + (own_ws ? a.geom.part_off : dec_off)), *const lse = out + row_heads * p.D;
   auto least = [&](long long prefix, int most) { return most > 1 ? piece_count((int)prefix, m, a.piece_rows, most) : 1; };
   a.piece_list[0] = {out, lse, a.parts, n_first * p.g, least(a.min_first_prefix, a.parts), 0};
   a.piece_list[1] = {out + rows_first * p.D, lse + rows_first, a.parts_other, n_other * p.g, least(a.min_other_prefix, a.parts_other), n_first};
+  return best;
 }
 
 // Key-split form or hand-pipelined form?  Both are estimated in microseconds from their longest chain
@@ -1265,10 +1310,18 @@ hipError_t launch_prefill(const Problem &p, const PrefillArgs &a_in, hipStream_t
   const int hs = fp32 ? 1 : heads_per_wg(p);
   PrefillArgs a = a_in;
   const int n_first = heads_listed_first(p, a);
-  if (!fp32) plan_pieces(p, a, hs, p.D == 128 ? (8 / hs) * 32 : (4 / hs) * 32, p.D == 128 ? 1 : 2);
+  bool cut_keysplit = false;
+  if (!fp32) {
+    const double piped = plan_pieces(p, a, hs, p.D == 128 ? PieceForm{(8 / hs) * 32, 1, 12, 0.87} : PieceForm{(4 / hs) * 32, 2, 12, 0.4}, false);
+    PrefillArgs b = a_in;
+    if (p.tune_queue == 0 && plan_pieces(p, b, hs, PieceForm{32 / hs, p.D == 128 ? 1 : 2, 19, 0.29}, true) < piped) {
+      a = b;
+      cut_keysplit = true;
+    }
+  }
   const bool cut = a.parts > 1 || a.parts_other > 1;
   const int nw = p.D == 128 ? (cut ? 8 : waves_d128(p, a_in, hs)) : 4;
-  const bool keysplit = !fp32 && use_keysplit(p, a, hs);
+  const bool keysplit = cut_keysplit || (!fp32 && use_keysplit(p, a, hs));
   const int rows = fp32 ? 64 : keysplit ? 32 / hs : (p.D == 128 ? (nw / hs) * 32 : (4 / hs) * 32);
   const long long seg_rows = a.n_rows < p.S ? a.n_rows : p.S;
   a.q_blocks_per_seg = (int)((seg_rows + rows - 1) / rows);
@@ -1318,17 +1371,18 @@ hipError_t launch_prefill(const Problem &p, const PrefillArgs &a_in, hipStream_t
   else if (a.packed) e = launch(std::true_type{});
   else e = launch(std::false_type{});
   if (e != hipSuccess || !cut) return e;
+  const auto mid = [&](int i) { return a.piece_list[i].most > 8 && a.piece_list[i].most <= 16; };
+  const int at_once = mid(0) || mid(1) ? 16 : 8;
   long long row_heads[2], wgs[2];
   for (int i = 0; i < 2; ++i) {
     const PrefillArgs::PieceList &pl = a.piece_list[i];
     row_heads[i] = pl.most > 1 ? (long long)p.B * a.n_rows * pl.heads : 0;
-    wgs[i] = pl.most > kWidePieces ? row_heads[i] : (row_heads[i] + 7) / 8;
+    wgs[i] = pl.most > at_once ? row_heads[i] : (row_heads[i] + 7) / 8;
   }
   const dim3 grid_c((unsigned)(wgs[0] + wgs[1]));
-  if (p.D == 128)
-    hipLaunchKernelGGL(prefill_part_combine_kernel<128>, grid_c, dim3(256), 0, st, p, a, (int)wgs[0], (unsigned)row_heads[0], (unsigned)row_heads[1]);
-  else
-    hipLaunchKernelGGL(prefill_part_combine_kernel<64>, grid_c, dim3(256), 0, st, p, a, (int)wgs[0], (unsigned)row_heads[0], (unsigned)row_heads[1]);
+  const auto merge = p.D == 128 ? (at_once == 8 ? prefill_part_combine_kernel<128, 8> : prefill_part_combine_kernel<128, 16>)
+                                : (at_once == 8 ? prefill_part_combine_kernel<64, 8> : prefill_part_combine_kernel<64, 16>);
+  hipLaunchKernelGGL(merge, grid_c, dim3(256), 0, st, p, a, (int)wgs[0], (unsigned)row_heads[0], (unsigned)row_heads[1]);
   return hipGetLastError();
 }
 

@@ -25,6 +25,15 @@ CASES = [
     (64, 16, 4, (3, 1, 1, 2), 512, 128, (13, 4), 11, 40),
     (64, 4, 4, (1, 1, 3, 3), 512, 512, (8,), 300, 130),
     (128, 4, 1, (1,), 2048, 2048, (1,), 1500, 20),           # tail and open rows alone are long enough
+    # few rows: pieces whose keys the waves of a workgroup share out (blocks of 8, 16 or 32 rows, the last one short)
+    (128, 8, 2, (3, 1), 512, 64, (20, 1, 0), 100, 8),
+    (128, 8, 2, (3, 1), 512, 64, (40, 3), 101, 9),
+    (128, 4, 2, (3, 1), 512, 64, (24,), 31, 17),
+    (128, 2, 2, (3, 2), 512, 0, (24,), 0, 33),
+    (64, 8, 2, (3, 1), 512, 128, (20, 2), 5, 3),
+    (64, 2, 2, (2, 1), 512, 128, (16,), 9, 31),
+    # no room for pieces: one chain of 530 steps, sixteen waves
+    (64, 16, 4, (3, 1, 1, 1), 2048, 512, (8,), 11, 68),
 ]
 
 
