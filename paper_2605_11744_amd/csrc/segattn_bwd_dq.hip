@@ -11,7 +11,9 @@
 // a chain products -> exponentials -> products with a barrier at its end).
 #include <string.h>
 
-#include "segattn_bwd_tiles.h"
+#include <atomic>
+
+#include "segattn_bwd_dkv_split.h"
 
 namespace segattn {
 
@@ -30,7 +32,8 @@ struct DqGeom {
   static constexpr int kBytes = kBufs * kBuf;
 };
 
-template <int D, int HS, bool PK>
+// kGiven: the row statistics are there already (otherwise they are formed here, for the dK/dV kernel behind).
+template <int D, int HS, bool PK, bool kGiven>
 __device__ __forceinline__ unsigned bwd_dq_item(const Problem &p, const PrefillArgs &pa, const BwdArgs &a,
                                                 const int bid, unsigned char *const smem, unsigned *const next_from) {
   using T = BwdTile<D>;
@@ -70,10 +73,15 @@ __device__ __forceinline__ unsigned bwd_dq_item(const Problem &p, const PrefillA
     Qr[kc] = *(const bf16x8 *)(a.q + qoff + 16 * kc + 8 * hi);
     Gr[kc] = *(const bf16x8 *)(a.dout + qoff + 16 * kc + 8 * hi);
   }
-  const float delta = row_delta<NC>(a.out, p.out_fp32 != 0, qoff, hi, Gr);
-  if (row_ok && hi == 0) {  // the row statistics the dK/dV kernel starts its accumulators at
-    a.delta[stat] = delta;
-    a.nls[stat] = -lse / p.scale;
+  float delta;
+  if constexpr (kGiven) {
+    delta = a.delta[stat];
+  } else {
+    delta = row_delta<NC>(a.out, p.out_fp32 != 0, qoff, hi, Gr);
+    if (row_ok && hi == 0) {  // the row statistics the dK/dV kernel starts its accumulators at
+      a.delta[stat] = delta;
+      a.nls[stat] = -lse / p.scale;
+    }
   }
   f32x16 acc[NB];
 #pragma unroll
@@ -324,7 +332,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_kernel(const Problem p_arg, con
         return;
       }
     }
-    ticket = bwd_dq_item<D, HS, PK>(p, pa, a, bid, smem, own);
+    ticket = bwd_dq_item<D, HS, PK, false>(p, pa, a, bid, smem, own);
     drawn = true;
     if (!queued) return;
     lds_barrier();  // the item's last reads of the tiles come before the next item's first loads
@@ -348,12 +356,8 @@ static hipError_t launch_dq_items(const Problem &p, PrefillArgs &pa, const BwdAr
   return hipGetLastError();
 }
 
-template <int D>
-static hipError_t launch_dq(const Problem &p, const BwdArgs &a, hipStream_t st) {
-  const int hs = bwd_heads_per_wg(p);
-  const bool split = bwd_dq_split_pays(p, a);
-  const int rows = split ? 32 / hs : (4 / hs) * 32;
-  PrefillArgs pa;
+// The items of a dQ launch in row blocks of `rows` rows per head; their number.
+static long long dq_items(const Problem &p, const BwdArgs &a, int hs, int rows, PrefillArgs &pa) {
   memset(&pa, 0, sizeof(pa));
   pa.q = a.q;
   pa.k = a.k;
@@ -369,11 +373,21 @@ static hipError_t launch_dq(const Problem &p, const BwdArgs &a, hipStream_t st) 
   pa.q_blocks_per_seg = (int)((seg_rows + rows - 1) / rows);
   pa.pair_stride = prefill_pair_stride((long long)p.B * (p.Hkv - p.n_past) * (p.g / hs) * pa.n_seg);
   pa.packed = a.cu_seqlens && number_packed(p, a.total, pa.n_seg, pa.q_blocks_per_seg, rows);
-  const long long grid_q = pa.packed ? (packed_units(a.total, p.S, rows) + p.B) * p.Hkv * (p.g / hs)
-                                     : (long long)p.B * p.Hkv * (p.g / hs) * pa.n_seg * pa.q_blocks_per_seg;
-  if (grid_q <= 0 || grid_q > 0x7fffffffLL) return hipErrorInvalidValue;
-  pa.grid_items = (int)grid_q;
-  prepare_resolve_divs(p, pa, hs, grid_q);
+  const long long items = pa.packed ? (packed_units(a.total, p.S, rows) + p.B) * p.Hkv * (p.g / hs)
+                                    : (long long)p.B * p.Hkv * (p.g / hs) * pa.n_seg * pa.q_blocks_per_seg;
+  if (items <= 0 || items > 0x7fffffffLL) return 0;
+  pa.grid_items = (int)items;
+  prepare_resolve_divs(p, pa, hs, items);
+  return items;
+}
+
+template <int D>
+static hipError_t launch_dq(const Problem &p, const BwdArgs &a, hipStream_t st) {
+  const int hs = bwd_heads_per_wg(p);
+  const bool split = bwd_dq_split_pays(p, a);
+  PrefillArgs pa;
+  const long long grid_q = dq_items(p, a, hs, split ? 32 / hs : (4 / hs) * 32, pa);
+  if (grid_q == 0) return hipErrorInvalidValue;
   if (split) return launch_bwd_dq_split(p, pa, a, hs, grid_q, st);
   if (pa.packed) {
     if (hs == 4) return launch_dq_items<D, 4, true>(p, pa, a, st);
@@ -387,6 +401,60 @@ static hipError_t launch_dq(const Problem &p, const BwdArgs &a, hipStream_t st) 
 
 hipError_t launch_bwd_dq(const Problem &p, const BwdArgs &a, hipStream_t st) {
   return p.D == 128 ? launch_dq<128>(p, a, st) : launch_dq<64>(p, a, st);
+}
+
+// ---------------------------------------------------------------------------------------------
+// dQ and dK/dV of a short window in one launch
+// ---------------------------------------------------------------------------------------------
+// Either kernel of a short window is as long as its longest chain of steps, with most of the chip idle at its end.
+// Behind a launch that forms the row statistics (about 5 us) the two need nothing of each other: their items share one
+// launch, the dK/dV items (in 32-key blocks, the longer chains) first.  Registers and LDS are the larger of either: at
+// D = 64 two workgroups per CU as in the kernels alone, at D = 128 one.  Forward and backward, two launches -> one behind the
+// statistics: 6.4K packed rows of 16/4 heads of 64 126 -> 118 us, 747 rows of 16/4 heads of 128 78 -> 57, 2 x 1402 rows of
+// 16/2 heads 189 -> 149.
+template <int D>
+constexpr int both_lds() {
+  return DkvSplitGeom<D, 4>::kBytes > DqGeom<D>::kBytes ? DkvSplitGeom<D, 4>::kBytes : DqGeom<D>::kBytes;
+}
+template <int D, int HS, bool PK>
+__global__ __launch_bounds__(256, D == 128 ? 1 : 2) void bwd_both_kernel(const Problem p, const PrefillArgs pa, const BwdArgs a,
+                                                                         const DkvSplitGrid g) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char both_smem[];
+  const int bid = (int)blockIdx.x;
+  if (bid < (int)g.items) bwd_dkv_split_item<D, 4>(p, a, g.blocks_per_seg, g.n_seg, g.packed, bid, both_smem);
+  else bwd_dq_item<D, HS, PK, true>(p, pa, a, bid - (int)g.items, both_smem, nullptr);
+}
+
+template <int D, int HS, bool PK>
+static hipError_t launch_both_items(const Problem &p, const PrefillArgs &pa, const BwdArgs &a, const DkvSplitGrid &g, hipStream_t st) {
+  const auto kern = bwd_both_kernel<D, HS, PK>;
+  static std::atomic<bool> ready{false};  // the same answer whoever asks first
+  if (!ready.load(std::memory_order_acquire)) {
+    const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, both_lds<D>());
+    if (e != hipSuccess) return e;
+    ready.store(true, std::memory_order_release);
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)(g.items + pa.grid_items)), dim3(256), both_lds<D>(), st, p, pa, a, g);
+  return hipGetLastError();
+}
+template <int D>
+static hipError_t launch_both(const Problem &p, const BwdArgs &a, hipStream_t st) {
+  const int hs = bwd_heads_per_wg(p);
+  PrefillArgs pa;
+  const DkvSplitGrid g = dkv_split_grid(p, a);
+  const long long items = dq_items(p, a, hs, (4 / hs) * 32, pa);
+  if (items == 0 || g.items <= 0 || items + g.items > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (pa.packed) {
+    if (hs == 4) return launch_both_items<D, 4, true>(p, pa, a, g, st);
+    if (hs == 2) return launch_both_items<D, 2, true>(p, pa, a, g, st);
+    return launch_both_items<D, 1, true>(p, pa, a, g, st);
+  }
+  if (hs == 4) return launch_both_items<D, 4, false>(p, pa, a, g, st);
+  if (hs == 2) return launch_both_items<D, 2, false>(p, pa, a, g, st);
+  return launch_both_items<D, 1, false>(p, pa, a, g, st);
+}
+hipError_t launch_bwd_both(const Problem &p, const BwdArgs &a, hipStream_t st) {
+  return p.D == 128 ? launch_both<128>(p, a, st) : launch_both<64>(p, a, st);
 }
 
 }  // namespace segattn

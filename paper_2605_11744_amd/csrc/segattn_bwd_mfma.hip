@@ -507,6 +507,10 @@ static hipError_t launch_dkv(const Problem &p, const BwdArgs &a, hipStream_t st)
 }
 
 hipError_t launch_bwd_mfma(const Problem &p, const BwdArgs &a, hipStream_t st) {
+  if (bwd_both_pays(p, a)) {
+    const hipError_t e = launch_bwd_delta(p, a, st);
+    return e == hipSuccess ? launch_bwd_both(p, a, st) : e;
+  }
   const hipError_t e = launch_bwd_dq(p, a, st);
   if (e != hipSuccess) return e;
   if (const int waves = bwd_dkv_split_waves(p, a)) return launch_bwd_dkv_split(p, a, waves, st);

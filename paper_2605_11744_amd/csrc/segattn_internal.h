@@ -546,6 +546,14 @@ hipError_t launch_bwd_mfma(const Problem &p, const BwdArgs &a, hipStream_t st);
 // Forms for small launches (segattn_bwd_split.hip), and whether they are the faster ones.
 bool bwd_dq_split_pays(const Problem &p, const BwdArgs &a);
 int bwd_dkv_split_waves(const Problem &p, const BwdArgs &a);
+// Work items of the split form of the dK/dV kernel, numbered by the row blocks of a packed batch where `packed`.
+struct DkvSplitGrid {
+  long long items;
+  int blocks_per_seg, n_seg, packed;
+};
+DkvSplitGrid dkv_split_grid(const Problem &p, const BwdArgs &a);
+bool bwd_both_pays(const Problem &p, const BwdArgs &a);
+hipError_t launch_bwd_both(const Problem &p, const BwdArgs &a, hipStream_t st);
 hipError_t launch_bwd_dq_split(const Problem &p, const PrefillArgs &pa, const BwdArgs &a, int heads_per_wg, long long grid,
                                hipStream_t st);
 hipError_t launch_bwd_dkv_split(const Problem &p, const BwdArgs &a, int waves, hipStream_t st);

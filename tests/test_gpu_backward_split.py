@@ -27,6 +27,22 @@ def test_small_windows(n, S, T, D, g):
     assert_grad_parity(run_backward(w, q, k, v, go, fp32_check=False), ref, fp32_check=False, what=f"n={n}")
 
 
+@pytest.mark.parametrize("D,g", [(64, 8), (128, 2), (128, 8)])
+@pytest.mark.parametrize("n,S,T", [(31, 64, 8), (129, 128, 128), (430, 200, 64)])
+def test_windows_whose_gradients_share_a_launch(n, S, T, D, g):
+    """Chains that are long against the work (groups of several heads, few keys): dQ and dK/dV items in one launch behind
+    the row statistics; a last block of one row, a short last segment; the same bits twice."""
+    w = W.small("bwb", index=930 + n % 40, seq_len=n, seg_len=S, tail_len=T, n_q_heads=g, n_kv_heads=1, head_dim=D,
+                kv_policy=[3], batch=2)
+    q, k, v = W.prefill_inputs(w)
+    go = W.grad_inputs(w)
+    ref = orc.attend_backward(q, k, v, go, seg_len=S, tail_len=T, kv_policy=w.kv_policy)
+    a = run_backward(w, q, k, v, go, fp32_check=False)
+    assert_grad_parity(a, ref, fp32_check=False, what=f"n={n}")
+    b = run_backward(w, q, k, v, go, fp32_check=False)
+    assert all(np.array_equal(x, y) for x, y in zip(a, b))  # sums in a fixed order
+
+
 @pytest.mark.parametrize("D,Hkv,g,S,T,lens", [
     (64, 2, 4, 64, 16, (0, 1, 150, 33, 0, 64, 129)),
     (128, 2, 2, 100, 100, (257, 3, 96)),
