@@ -888,7 +888,7 @@ segattn_status seg_attn_decode(segattn_ctx *ctx, const void *q, const void *k_ne
   if (!ctx || !q || !k_new || !v_new || !out || !lse) return SEGATTN_EINVAL;
   if (!ctx->ready) return SEGATTN_ESTATE;
   const Problem &p = ctx->p;
-  long long total_rows = 0, chunks = 0, longest = 0;
+  long long total_rows = 0, chunks = 0, longest = 0, most[2] = {0, 0};
   bool any_full = false;
   for (int b = 0; b < p.B; ++b) {
     for (int h = 0; h < p.Hkv; ++h) {
@@ -902,7 +902,10 @@ segattn_status seg_attn_decode(segattn_ctx *ctx, const void *q, const void *k_ne
       }
       total_rows += win;
       longest = win > longest ? win : longest;
-      chunks += (win + ctx->g.decode_chunk - 1) / ctx->g.decode_chunk;
+      const long long slices = (win + ctx->g.decode_chunk - 1) / ctx->g.decode_chunk;
+      chunks += slices;
+      long long &m = most[(p.policy[h] & SEGATTN_PAST) ? 0 : 1];
+      m = slices > m ? slices : m;
     }
     any_full |= ctx->fill[b] + 1 == p.S;
   }
@@ -927,6 +930,8 @@ segattn_status seg_attn_decode(segattn_ctx *ctx, const void *q, const void *k_ne
   da.total_rows = total_rows;
   da.chunks = chunks;
   da.longest = longest;
+  da.most_past = (int)most[0];
+  da.most_other = (int)most[1];
   if (launch_decode(p, da, p.B, st) != hipSuccess) return hip_failed(ctx);
   if (any_full && launch_cache_close(p, ctx->cache, ctx->g, 0, st) != hipSuccess) return hip_failed(ctx);
   for (int b = 0; b < p.B; ++b) {

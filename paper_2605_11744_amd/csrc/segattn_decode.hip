@@ -403,6 +403,21 @@ static hipError_t launch_split(const Problem &p, const DecodeArgs &a, hipStream_
     long long per = a.geom.decode_chunk, blocks = a.chunks;
     if (blocks <= resident) {
       a2.per_window = 1;
+      const long long n_other = p.Hkv - p.n_past, past = (long long)p.B * p.n_past * a.most_past;
+      const long long numbered = past + p.B * n_other * a.most_other;
+      // Numbered by the longest window: no search through the counters in front of the first tile (1 us of a step
+      // of 13 to 25: one sequence of 24K 17.2 -> 16.2 us, 16K with heads of 64 13.4 -> 12.7, three of up to 22K 16.6 -> 15.9).
+      // Not where the empty numbers of shorter windows put two long slices on one CU while another has none
+      // (two sequences of up to 48K 19.5 -> 22.2), though it gains where others are that uneven (three of up to 30K 24.9 -> 23.2).
+      if (numbered <= resident && (numbered <= device_cus() || 8 * numbered <= 9 * blocks)) {
+        a2.numbered = 1;
+        blocks = numbered;
+        a2.wgs_past = (int)past;
+        a2.slots_past = fast_div_by(a.most_past);
+        a2.slots_other = fast_div_by(a.most_other);
+        a2.heads_past = fast_div_by(p.n_past);
+        a2.heads_other = fast_div_by(n_other);
+      }
     } else {
       per = (a.total_rows + resident - 1) / resident;
       if (per < a.geom.decode_chunk) per = a.geom.decode_chunk;

@@ -45,7 +45,8 @@ __device__ inline float dec_half_sum(float x) {
   return __int_as_float(sw[0]) + __int_as_float(sw[1]);
 }
 
-template <int D>
+// kNumbered: a workgroup's number gives its window and slice (decode_slice_numbered).
+template <int D, bool kNumbered>
 __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(const Problem p, const DecodeArgs a,
                                                                    const int head_pass) {
   constexpr int NC = D / 16, NB = D / 32;
@@ -70,7 +71,8 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(const Problem
   // ---- where this workgroup's slice begins
   const int n_win = p.B * p.Hkv;
   int w, off, split;  // split: this workgroup's number among those of the window
-  decode_slice_start(p, a, w, off, split);
+  if constexpr (kNumbered) decode_slice_numbered(p, a, w, off, split);
+  else decode_slice_start(p, a, w, off, split);
   if (w < 0) return;
   int remaining = a.rows_per_wg;
   int *counts = ws_counts(a.cache, a.geom);
@@ -107,7 +109,10 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(const Problem
     hi_ = __builtin_amdgcn_readfirstlane(hi_);
     const int c0 = lo + off;
     const int c1 = min(hi_, c0 + remaining);
-    if (c1 <= c0) continue;
+    if (c1 <= c0) {
+      if constexpr (kNumbered) return;  // the window has fewer slices
+      continue;
+    }
     remaining = a.per_window ? 0 : remaining - (c1 - c0);
     const int head0 = kv * p.g + head_pass * kDecHeads;
     const int live = min(kDecHeads, p.g - head_pass * kDecHeads);
@@ -278,16 +283,15 @@ __global__ __launch_bounds__(256, 2) void decode_split_mfma_kernel(const Problem
 
 int decode_mfma_resident(int D) {
   static ResidentCount count[2];
-  return D == 128 ? count[1].get((const void *)decode_split_mfma_kernel<128>, 256, 0)
-                  : count[0].get((const void *)decode_split_mfma_kernel<64>, 256, 0);
+  return D == 128 ? count[1].get((const void *)decode_split_mfma_kernel<128, false>, 256, 0)
+                  : count[0].get((const void *)decode_split_mfma_kernel<64, false>, 256, 0);
 }
 
 hipError_t launch_decode_split_mfma(const Problem &p, const DecodeArgs &a, long long blocks, hipStream_t st) {
+  const auto kern = p.D == 128 ? (a.numbered ? decode_split_mfma_kernel<128, true> : decode_split_mfma_kernel<128, false>)
+                               : (a.numbered ? decode_split_mfma_kernel<64, true> : decode_split_mfma_kernel<64, false>);
   for (int pass = 0; pass < (p.g + kDecHeads - 1) / kDecHeads; ++pass) {
-    if (p.D == 128)
-      hipLaunchKernelGGL(decode_split_mfma_kernel<128>, dim3((unsigned)blocks), dim3(256), 0, st, p, a, pass);
-    else
-      hipLaunchKernelGGL(decode_split_mfma_kernel<64>, dim3((unsigned)blocks), dim3(256), 0, st, p, a, pass);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, st, p, a, pass);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

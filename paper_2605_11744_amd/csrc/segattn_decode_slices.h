@@ -83,4 +83,16 @@ __device__ inline void decode_slice_start(const Problem &p, const DecodeArgs &a,
   split_out = a.per_window ? off : (int)blockIdx.x - (start - off) / per;
 }
 
+// The same for a numbered launch: the workgroup's number gives the window and the slice, no counter
+// is read.  A slice beyond the window's last row is empty; the caller finds that out from the rows.
+__device__ inline void decode_slice_numbered(const Problem &p, const DecodeArgs &a, int &w_out, int &off_out, int &split_out) {
+  const bool past = (int)blockIdx.x < a.wgs_past;
+  const int i = (int)blockIdx.x - (past ? 0 : a.wgs_past);
+  const FastDiv slots = past ? a.slots_past : a.slots_other, heads = past ? a.heads_past : a.heads_other;
+  const int win = fast_div(i, slots), b = fast_div(win, heads);
+  split_out = i - win * (int)slots.d;
+  off_out = split_out * a.rows_per_wg;
+  w_out = b * p.Hkv + p.order[(past ? 0 : p.n_past) + win - b * (int)heads.d];
+}
+
 }  // namespace segattn

@@ -298,6 +298,11 @@ struct DecodeArgs {
   long long longest;     // rows of the longest window
   int rows_per_wg;       // rows per workgroup of the split kernel (>= geom.decode_chunk); set by the launcher
   int per_window;        // 1: every window is cut into slices of its own (a workgroup never goes on into the next window)
+  int most_past, most_other;  // host: such slices of the longest window of a PAST / another head
+  // per_window: 1: PAST heads' windows have slots_past workgroups each, wgs_past in all, the others' slots_other behind
+  // them (FastDiv d == 0: no such heads); 0: a workgroup searches for its slice
+  int numbered, wgs_past;
+  FastDiv slots_past, slots_other, heads_past, heads_other;
   int pending;           // 1: the newest row is still to be appended: the split kernel does it, the combine kernel counts it
 };
 

@@ -17,6 +17,10 @@ CASES = [
     (128, 16, 8, (3,) * 8, 1024, 1024, (12, 12, 11), 1),         # about 20
     (128, 8, 8, (3,) * 8, 1024, 256, (8, 7, 8, 8, 7), 513),      # a dozen
     (64, 12, 3, (3, 1, 2), 2048, 512, (90, 40), 31),             # windows of one slice beside long ones
+    # few slices: numbered by the longest window, the shorter ones' last numbers empty
+    (128, 8, 4, (1, 3, 0, 2), 1024, 256, (9, 1, 2), 77),
+    (64, 4, 2, (1, 1), 2048, 512, (3, 1), 600),                  # no head with the past
+    (128, 4, 2, (3, 3), 1024, 128, (5, 2), 511),                 # none without
 ]
 
 
