@@ -389,6 +389,30 @@ static hipError_t launch_split_gh(const Problem &p, DecodeArgs a, hipStream_t st
 // The matrix-core form appends the newest row itself; in front of the other one the caller has to.
 bool decode_appends(const Problem &p) { return !p.fp32_math && p.g >= SEGATTN_DECODE_MFMA_MIN_G; }
 
+// How the matrix-core form's slices are cut, where `resident` workgroups fit the chip at once.
+DecodeSlices decode_slices(const Problem &p, const DecodeArgs &a, long long resident) {
+  // Few rows: slices of the shortest length the workspace is made for, every window cut by itself.  A
+  // workgroup that goes on into a second window adds its latencies (merge, counters, first tile: 7 of
+  // then 18 us) to the step; with long slices that is little beside the even split it buys.
+  if (a.chunks > resident) {
+    long long per = (a.total_rows + resident - 1) / resident;
+    if (per < a.geom.decode_chunk) per = a.geom.decode_chunk;
+    per = (per + 127) / 128 * 128;
+    return {0, 0, per, (a.total_rows + per - 1) / per};
+  }
+  // Numbered by the longest window: no search through the counters in front of the first tile (1 us of a step
+  // of 13 to 25: one sequence of 24K 17.2 -> 16.2 us, 16K with heads of 64 13.4 -> 12.7, three of up to 22K 16.6 -> 15.9).
+  // Not where the empty numbers of shorter windows put two long slices on one CU while another has none
+  // (two sequences of up to 48K 19.5 -> 22.2), though it gains where others are that uneven (three of up to 30K 24.9 -> 23.2):
+  // above all not where the slices have a CU each and the numbers more than one (240 slices, 264 numbers,
+  // two sequences of up to 14K 18.7 -> 22.1 a token; 256 and 280, of up to 20K 20.1 -> 23.1).
+  const long long numbered = (long long)p.B * p.n_past * a.most_past + (long long)p.B * (p.Hkv - p.n_past) * a.most_other;
+  const long long cus = device_cus();
+  if (numbered <= resident && (numbered <= cus || (a.chunks > cus && 8 * numbered <= 9 * a.chunks)))
+    return {1, 1, a.geom.decode_chunk, numbered};
+  return {1, 0, a.geom.decode_chunk, a.chunks};
+}
+
 template <int D, bool EXACT>
 static hipError_t launch_split(const Problem &p, const DecodeArgs &a, hipStream_t st) {
   if (a.total_rows < 1) return hipErrorInvalidValue;
@@ -397,36 +421,20 @@ static hipError_t launch_split(const Problem &p, const DecodeArgs &a, hipStream_
     if (resident == 0) return hipErrorUnknown;
     DecodeArgs a2 = a;
     a2.pending = 1;
-    // Few rows: slices of the shortest length the workspace is made for, every window cut by itself.  A
-    // workgroup that goes on into a second window adds its latencies (merge, counters, first tile: 7 of
-    // then 18 us) to the step; with long slices that is little beside the even split it buys.
-    long long per = a.geom.decode_chunk, blocks = a.chunks;
-    if (blocks <= resident) {
-      a2.per_window = 1;
-      const long long n_other = p.Hkv - p.n_past, past = (long long)p.B * p.n_past * a.most_past;
-      const long long numbered = past + p.B * n_other * a.most_other;
-      // Numbered by the longest window: no search through the counters in front of the first tile (1 us of a step
-      // of 13 to 25: one sequence of 24K 17.2 -> 16.2 us, 16K with heads of 64 13.4 -> 12.7, three of up to 22K 16.6 -> 15.9).
-      // Not where the empty numbers of shorter windows put two long slices on one CU while another has none
-      // (two sequences of up to 48K 19.5 -> 22.2), though it gains where others are that uneven (three of up to 30K 24.9 -> 23.2).
-      if (numbered <= resident && (numbered <= device_cus() || 8 * numbered <= 9 * blocks)) {
-        a2.numbered = 1;
-        blocks = numbered;
-        a2.wgs_past = (int)past;
-        a2.slots_past = fast_div_by(a.most_past);
-        a2.slots_other = fast_div_by(a.most_other);
-        a2.heads_past = fast_div_by(p.n_past);
-        a2.heads_other = fast_div_by(n_other);
-      }
-    } else {
-      per = (a.total_rows + resident - 1) / resident;
-      if (per < a.geom.decode_chunk) per = a.geom.decode_chunk;
-      per = (per + 127) / 128 * 128;
-      if (per > 0x7fffff00LL) return hipErrorInvalidValue;
-      blocks = (a.total_rows + per - 1) / per;
+    const DecodeSlices sl = decode_slices(p, a, resident);
+    if (sl.rows > 0x7fffff00LL) return hipErrorInvalidValue;
+    a2.per_window = sl.per_window;
+    if (sl.numbered) {
+      const long long n_other = p.Hkv - p.n_past;
+      a2.numbered = 1;
+      a2.wgs_past = (int)((long long)p.B * p.n_past * a.most_past);
+      a2.slots_past = fast_div_by(a.most_past);
+      a2.slots_other = fast_div_by(a.most_other);
+      a2.heads_past = fast_div_by(p.n_past);
+      a2.heads_other = fast_div_by(n_other);
     }
-    a2.rows_per_wg = (int)per;
-    const hipError_t e = launch_decode_split_mfma(p, a2, blocks, st);
+    a2.rows_per_wg = (int)sl.rows;
+    const hipError_t e = launch_decode_split_mfma(p, a2, sl.blocks, st);
     if (e != hipSuccess) return e;
     return launch_combine<D>(p, a2, st);
   }

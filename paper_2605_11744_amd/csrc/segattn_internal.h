@@ -305,6 +305,13 @@ struct DecodeArgs {
   FastDiv slots_past, slots_other, heads_past, heads_other;
   int pending;           // 1: the newest row is still to be appended: the split kernel does it, the combine kernel counts it
 };
+// Slices of a matrix-core decode launch: cut window by window or evenly over all rows, found by number or by a
+// search through the counters; rows of a slice, workgroups.
+struct DecodeSlices {
+  int per_window, numbered;
+  long long rows, blocks;
+};
+DecodeSlices decode_slices(const Problem &p, const DecodeArgs &a, long long resident);
 
 struct CopyArgs {
   const unsigned short *k, *v;   // source rows

@@ -1,0 +1,56 @@
+"""The form that a call's launch takes, asked from the library's rules on the CPU (tests/host/launch_forms.hip): what a rule
+must not do, and that the GPU tests written for a form have shapes that take it."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+import paper_2605_11744_amd as sa
+from conftest import ROOT
+
+
+@pytest.fixture(scope="module")
+def forms(tmp_path_factory):
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not found")
+    sa.lib()  # built, and says so if not
+    pkg = os.path.join(ROOT, "paper_2605_11744_amd")
+    exe = tmp_path_factory.mktemp("forms") / "launch_forms"
+    subprocess.run([hipcc, "--offload-arch=gfx950", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(pkg, "csrc"), os.path.join(ROOT, "tests", "host", "launch_forms.hip"),
+                    "-L", pkg, "-lsegattn", "-Wl,-rpath," + pkg, "-o", str(exe)], check=True, capture_output=True, timeout=600)
+
+    def ask(lines):
+        out = subprocess.run([str(exe)], input="\n".join(lines) + "\n", capture_output=True, text=True, timeout=600)
+        assert out.returncode == 0, out.stdout + out.stderr
+        got = out.stdout.splitlines()
+        assert len(got) == len(lines)
+        return got
+
+    return ask
+
+
+def decode_line(D, Hq, Hkv, policy, S, T, closed, fill):
+    fill = [fill] * len(closed) if isinstance(fill, int) else fill
+    text = lambda xs: ",".join(str(x) for x in xs)
+    return f"decode {D} {Hq} {Hkv} {''.join(map(str, policy))} {S} {T} {S * (max(closed) + 1)} 512 {text(closed)} {text(fill)}"
+
+
+def test_numbering_the_slices_of_a_decode_step_costs_no_second_round(forms):
+    """Slices that have a compute unit each are not numbered where the numbers (with the empty ones of shorter windows) are more
+    than there are compute units: two slices then share one while another idles."""
+    uneven = [decode_line(128, 32, 8, (3, 3, 3, 3, 1, 1, 1, 1), 2048, 512, (5, 6), (1139, 1663)),
+              decode_line(128, 32, 8, (2, 2, 1, 1, 1, 1, 1, 1), 4096, 1024, (4, 4), (2374, 3909))]
+    assert [x.split()[1:] for x in forms(uneven)] == [["240", "264"], ["256", "280"]]
+    assert [x.split()[0] for x in forms(uneven)] == ["searched"] * 2
+    # two sequences of every pair of lengths: never from one round of workgroups to two
+    pairs = [decode_line(D, 32, 8, (3, 3, 3, 3, 1, 1, 1, 1), 2048, 512, (a, b), (700, 1500))
+             for D in (64, 128) for a in range(12) for b in range(12)]
+    kinds = set()
+    for answer in forms(pairs):
+        form, slices, numbers = answer.split()
+        kinds.add(form)
+        assert form != "numbered" or int(numbers) <= 256 or int(slices) > 256, answer
+    assert kinds >= {"numbered", "searched"}
