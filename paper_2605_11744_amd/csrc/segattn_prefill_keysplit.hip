@@ -9,7 +9,7 @@
 // dependent steps is an eighth, and there are as many workgroups as 32-column blocks.  The price: every
 // wave stages its own K/V tile (16 KB of L2 traffic per wave and step, where the other kernel's
 // eight waves share one) and nothing is scheduled by hand -- so it is chosen only where the
-// other form leaves the chip waiting (use_keysplit in segattn_prefill_mfma.hip).  The form also takes the pieces
+// other form leaves the chip waiting (choose_prefill in segattn_prefill_mfma.hip).  The form also takes the pieces
 // of a prefix behind which a chunk has few rows (plan_pieces there).
 //
 // Products and layouts as in segattn_prefill_mfma.hip: S^T = K . Q^T, O^T += V^T . P^T with 32x32x16 bf16

@@ -1215,9 +1215,10 @@ static double plan_pieces(const Problem &p, PrefillArgs &a, int hs, const PieceF
   auto steps = [&](long long prefix) { return (prefix + m / 2 + kStepKeys - 1) / kStepKeys; };
   const long long sf = n_first > 0 ? steps(a.max_first_prefix) : 0, so = n_other > 0 ? steps(a.max_other_prefix) : 0;
   const long long total = blocks * (n_first * sf + n_other * so);
-  // Estimated steps from start to end: workgroups take `first` items of lf steps, then `other` ones of lo.
-  auto span = [&](long long first, long long lf, long long other, long long lo) {
-    lf += form.item_steps, lo += form.item_steps;
+  // Estimated steps from start to end: workgroups take `first` items of lf steps, then `other` ones of lo, each with
+  // `more` steps beside.
+  auto span = [&](long long first, long long lf, long long other, long long lo, int more) {
+    lf += more, lo += lo + more > 0 ? more : 1;
     const long long t0 = first / wgs * lf, busy = first % wgs, idle = wgs - busy, end = t0 + (busy ? lf : 0);
     const long long turns = (other + idle - 1) / idle, beside = busy ? lf / lo : turns;
     if (turns <= beside) return t0 + turns * lo > end ? t0 + turns * lo : end;
@@ -1226,11 +1227,11 @@ static double plan_pieces(const Problem &p, PrefillArgs &a, int hs, const PieceF
   double best = INFINITY;
   if (!cut_only) {
     // Uncut, head_dim 128 runs half as long blocks of four waves where the chip has room for them.
-    long long uncut = span(blocks * n_first, sf, blocks * n_other, so);
+    long long uncut = span(blocks * n_first, sf, blocks * n_other, so, form.item_steps);
     if (p.D == 128 && waves_d128(p, a, hs) == 4 && 2 * blocks * (n_first > 0 ? n_first : n_other) <= wgs) uncut = uncut * 2 / 3;
     best = uncut * form.step_us;
   }
-  long long len = total * 3 / (4 * wgs), row_heads = 0;
+  long long len = total * 3 / (4 * wgs), row_heads = 0, steps_first = 0, steps_other = 0;
   if (len < kMinPieceSteps) len = kMinPieceSteps;
   for (;; len += (len + 15) / 16) {
     FastDiv t = fast_div_by(len * kStepKeys);
@@ -1251,9 +1252,11 @@ static double plan_pieces(const Problem &p, PrefillArgs &a, int hs, const PieceF
     }
     // the merge: 5 us, and its bytes at HBM speed (5 MB a us)
     const double merge = 5 + rh * p.D * 8 / 5.0e6;
-    const double cost = merge + form.step_us * span(blocks * n_first * c0, c0 > 1 ? even : sf, blocks * n_other * c1, c1 > 1 ? even : so);
+    const double cost = merge + form.step_us * span(blocks * n_first * c0, c0 > 1 ? even : sf, blocks * n_other * c1, c1 > 1 ? even : so, form.item_steps);
     if (cost >= best) continue;
     best = cost;
+    steps_first = c0 > 1 ? even : sf;
+    steps_other = c1 > 1 ? even : so;
     a.parts = c0;
     a.parts_other = c1;
     a.piece_rows = t;
@@ -1265,10 +1268,28 @@ static double plan_pieces(const Problem &p, PrefillArgs &a, int hs, const PieceF
   auto least = [&](long long prefix, int most) { return most > 1 ? piece_count((int)prefix, m, a.piece_rows, most) : 1; };
   a.piece_list[0] = {out, lse, a.parts, n_first * p.g, least(a.min_first_prefix, a.parts), 0};
   a.piece_list[1] = {out + rows_first * p.D, lse + rows_first, a.parts_other, n_other * p.g, least(a.min_other_prefix, a.parts_other), n_first};
-  return best;
+  if (p.D == 64 || !cut_only) return best;
+  // Key-split pieces of head dimension 128 are bound by memory as often as by their steps: 32 query columns read as many keys
+  // as 256 do, and the workgroups of a piece (row blocks, sub-groups of a group's heads) share them in an L2 only where the
+  // launch, which puts them `per` and a.parts apart, deals them to one XCD.  Fitted to 6504 timed chunks of 1 to 600 rows
+  // behind up to 100K (7 % off on average): 8 us, 4.3 a round of workgroups, the merge's bytes, and 0.172 us a step against 7.6
+  // TB/s beyond the L2s and 25 out of them.  By the steps alone 29 rows of two sequences behind 98K, 4/1 heads, took 67 us
+  // where the pipelined pieces take 40, and 25 rows behind 59K, 16/2 heads, 58 (41); of 3901 drawn chunks 29 were more than 3 %
+  // slower than with pipelined pieces alone (1.6x at worst), by the larger estimate 6 (1.1x) and 0.3 % fewer us in the mean.
+  // (Head dimension 64, half the bytes a step: 3 of 3103 by the steps.)
+  const long long first = blocks * n_first * a.parts, other = blocks * n_other * a.parts_other;
+  const long long nhs = p.g / hs, per = (long long)p.B * n_first * nhs * a.parts;
+  unsigned xcds = 0;  // that read a piece
+  for (int h = 0; h < (nhs < 8 ? nhs : 8); ++h)
+    for (int r = 0; r < 8 && r * form.rows < m; ++r) xcds |= 1u << (h * a.parts + r * per) % 8;
+  const double mb = 128e-6 * p.D, chain = 0.172 * span(first, steps_first, other, steps_other, 0);  // mb: of a step
+  const double beyond = mb * p.B * ((double)n_first * sf * __builtin_popcount(xcds) + (double)n_other * so) / 7.6, l2 = mb * total / 25;
+  const double us = 7.6 + row_heads * p.D * 8 / 5.0e6 + 4.3 * ceil((double)(first + other) / wgs) +
+                    sqrt(sqrt(chain * chain * chain * chain + beyond * beyond * beyond * beyond + l2 * l2 * l2 * l2));
+  return fmax(best, us);
 }
 
-// Key-split form or hand-pipelined form?  Both are estimated in microseconds from their longest chain
+// Key-split form or hand-pipelined form, nothing cut?  Both are estimated in microseconds from their longest chain
 // of steps, the wave-steps in all (32 query columns x 32 keys; the key-split form reads its K/V tiles out of L2 at
 // 14 TB/s) and the rounds of workgroups.  Fitted to 11,123 prompts and packed batches of 360 to 65,000 rows (4/4
 // to 32/8 heads, segments of 64 to 4096, both forms of each timed): 0.9 % (D = 64) and 0.8 % (D = 128) slower than
@@ -1277,8 +1298,11 @@ static double plan_pieces(const Problem &p, PrefillArgs &a, int hs, const PieceF
 // Chunks on a filled cache come here only if their prefixes were not cut (plan_pieces found no workspace, or no
 // gain): 173 rows behind 37.5K, four of eight KV heads with the whole past, 32 heads of 128, forward and commit:
 // 633 -> 251 us, 8 rows of it 620 -> 75; 1500 rows stay with the other form (663).
-static bool use_keysplit(const Problem &p, const PrefillArgs &a, int hs) {
-  if (p.tune_waves != 0 || p.tune_queue != 0 || a.parts > 1 || a.parts_other > 1) return false;
+struct UncutEstimate {
+  double keysplit, piped;  // microseconds
+  bool keysplit_pays;
+};
+static UncutEstimate estimate_uncut(const Problem &p, const PrefillArgs &a, int hs) {
   StepCount c;
   double wgs, wgs_piped;  // workgroups of either form; the second's with four waves
   const double groups = p.Hkv * (p.g / hs);
@@ -1299,29 +1323,38 @@ static bool use_keysplit(const Problem &p, const PrefillArgs &a, int hs) {
   const int cus = device_cus();
   if (p.D == 64) {
     const double split = 7.69 + 0.11 * c.longest + 4.48e-4 * c.steps + 2.37 * more_rounds(wgs, 2 * cus);
-    return split < 0.973 * (8 + fmax(0.423 * c.longest, 1.49e-4 * c.steps) + 0.16 * more_rounds(wgs_piped, 3 * cus));
+    const double piped = 8 + fmax(0.423 * c.longest, 1.49e-4 * c.steps) + 0.16 * more_rounds(wgs_piped, 3 * cus);
+    return {split, piped, split < 0.973 * piped};
   }
   const double split = 8.23 + 0.072 * c.longest + 1.1e-3 * c.steps + 3.59 * more_rounds(wgs, cus);
-  return split < 0.942 * (8 + fmax(0.547 * c.longest, 8.4e-5 * c.steps) + 0.12 * more_rounds(wgs_piped, 2 * cus));
+  const double piped = 8 + fmax(0.547 * c.longest, 8.4e-5 * c.steps) + 0.12 * more_rounds(wgs_piped, 2 * cus);
+  return {split, piped, split < 0.942 * piped};
+}
+
+PrefillForm choose_prefill(const Problem &p, PrefillArgs &a) {
+  const bool fp32 = p.fp32_math != 0, forced = p.tune_waves != 0 || p.tune_queue != 0;
+  const int hs = fp32 ? 1 : heads_per_wg(p);
+  const PrefillArgs a_in = a;
+  if (fp32) return {hs, p.D == 128 ? waves_d128(p, a, hs) : 4, false, false};
+  double best = plan_pieces(p, a, hs, p.D == 128 ? PieceForm{(8 / hs) * 32, 1, 12, 0.87} : PieceForm{(4 / hs) * 32, 2, 12, 0.4}, false);
+  bool cut = a.parts > 1 || a.parts_other > 1;
+  const UncutEstimate uncut = estimate_uncut(p, a, hs);
+  bool keysplit = !forced && !cut && uncut.keysplit_pays;
+  PrefillArgs b = a_in;
+  if (p.tune_queue == 0 && plan_pieces(p, b, hs, PieceForm{32 / hs, p.D == 128 ? 1 : 2, 19, 0.29}, true) < best) {
+    a = b;
+    cut = keysplit = true;
+  }
+  return {hs, p.D == 128 ? (cut ? 8 : waves_d128(p, a_in, hs)) : 4, keysplit, cut};
 }
 
 hipError_t launch_prefill(const Problem &p, const PrefillArgs &a_in, hipStream_t st) {
   const bool fp32 = p.fp32_math != 0;
-  const int hs = fp32 ? 1 : heads_per_wg(p);
   PrefillArgs a = a_in;
+  const PrefillForm form = choose_prefill(p, a);
+  const int hs = form.hs, nw = form.nw;
+  const bool keysplit = form.keysplit, cut = form.cut;
   const int n_first = heads_listed_first(p, a);
-  bool cut_keysplit = false;
-  if (!fp32) {
-    const double piped = plan_pieces(p, a, hs, p.D == 128 ? PieceForm{(8 / hs) * 32, 1, 12, 0.87} : PieceForm{(4 / hs) * 32, 2, 12, 0.4}, false);
-    PrefillArgs b = a_in;
-    if (p.tune_queue == 0 && plan_pieces(p, b, hs, PieceForm{32 / hs, p.D == 128 ? 1 : 2, 19, 0.29}, true) < piped) {
-      a = b;
-      cut_keysplit = true;
-    }
-  }
-  const bool cut = a.parts > 1 || a.parts_other > 1;
-  const int nw = p.D == 128 ? (cut ? 8 : waves_d128(p, a_in, hs)) : 4;
-  const bool keysplit = cut_keysplit || (!fp32 && use_keysplit(p, a, hs));
   const int rows = fp32 ? 64 : keysplit ? 32 / hs : (p.D == 128 ? (nw / hs) * 32 : (4 / hs) * 32);
   const long long seg_rows = a.n_rows < p.S ? a.n_rows : p.S;
   a.q_blocks_per_seg = (int)((seg_rows + rows - 1) / rows);

@@ -2,6 +2,8 @@
 // one answer per output line:
 //   decode D Hq Hkv policy S T capacity resident closed,.. fill,..
 //       -> "numbered" | "searched" (every window cut by itself) | "even", slices, numbers by the longest windows
+//   chunk D Hq Hkv policy S T capacity rows closed,.. fill,..
+//       -> "keysplit" | "piped", waves of a workgroup, pieces of the PAST heads' prefixes at most, of the others'
 // (policy: a digit per KV head; closed, fill: closed segments and open rows of each sequence).  Needs no GPU: the rules then
 // take 256 compute units.
 #include <iostream>
@@ -44,17 +46,24 @@ static long long before(const Problem &p, int h, long long closed, long long fil
   return ((p.policy[h] & SEGATTN_TAIL) ? std::min<long long>(p.T, past) : 0) + fill;
 }
 
-static bool decode(const std::string &line) {
-  std::istringstream head(line);
+// The fields behind the configuration: two numbers, then the closed segments and open rows of each sequence.
+static bool read_sequences(const std::string &line, long long &capacity, long long &number, std::vector<long long> &closed,
+                           std::vector<long long> &fill, Call &c) {
+  std::istringstream head(line), in(line);
   std::string word, closed_text, fill_text;
-  long long capacity, resident;
   for (int i = 0; i < 7; ++i) head >> word;
-  head >> capacity >> resident >> closed_text >> fill_text;
-  const std::vector<long long> closed = numbers(closed_text), fill = numbers(fill_text);
-  std::istringstream in(line);
+  head >> capacity >> number >> closed_text >> fill_text;
+  closed = numbers(closed_text);
+  fill = numbers(fill_text);
   in >> word;
+  return !head.fail() && fill.size() == closed.size() && read_call(in, (int)closed.size(), capacity, c);
+}
+
+static bool decode(const std::string &line) {
+  long long capacity, resident;
+  std::vector<long long> closed, fill;
   Call c;
-  if (head.fail() || fill.size() != closed.size() || !read_call(in, (int)closed.size(), capacity, c)) return false;
+  if (!read_sequences(line, capacity, resident, closed, fill, c)) return false;
   DecodeArgs a;
   memset(&a, 0, sizeof(a));
   a.geom = c.g;
@@ -72,10 +81,37 @@ static bool decode(const std::string &line) {
   return true;
 }
 
+static bool chunk(const std::string &line) {
+  long long capacity, rows;
+  std::vector<long long> closed, fill;
+  Call c;
+  if (!read_sequences(line, capacity, rows, closed, fill, c)) return false;
+  static unsigned char arena[1];  // not read by the rules
+  PrefillArgs a;
+  memset(&a, 0, sizeof(a));
+  a.cache = arena;
+  a.geom = c.g;
+  a.n_rows = (int)rows;
+  a.n_seg = 1;
+  a.min_first_prefix = a.min_other_prefix = 1ll << 40;
+  for (size_t b = 0; b < closed.size(); ++b)
+    for (int h = 0; h < c.p.Hkv; ++h) {
+      const bool past = c.p.policy[h] & SEGATTN_PAST;
+      const long long n = before(c.p, h, closed[b], fill[b]);
+      long long &most = past ? a.max_first_prefix : a.max_other_prefix, &least = past ? a.min_first_prefix : a.min_other_prefix;
+      most = std::max(most, n);
+      least = std::min(least, n);
+    }
+  const PrefillForm f = choose_prefill(c.p, a);
+  std::cout << (f.keysplit ? "keysplit " : "piped ") << (f.keysplit ? 8 : f.nw) << ' ' << (f.cut ? a.parts : 1) << ' '
+            << (f.cut ? a.parts_other : 1) << '\n';
+  return true;
+}
+
 int main() {
   for (std::string line; std::getline(std::cin, line);) {
     const std::string kind = line.substr(0, line.find(' '));
-    if (!(kind == "decode" && decode(line))) {
+    if (!(kind == "decode" && decode(line)) && !(kind == "chunk" && chunk(line))) {
       std::cout << "refused: " << line << '\n';
       return 1;
     }

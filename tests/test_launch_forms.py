@@ -54,3 +54,27 @@ def test_numbering_the_slices_of_a_decode_step_costs_no_second_round(forms):
         kinds.add(form)
         assert form != "numbered" or int(numbers) <= 256 or int(slices) > 256, answer
     assert kinds >= {"numbered", "searched"}
+
+
+def chunk_line(D, Hq, Hkv, policy, S, T, closed, fill, m):
+    text = lambda xs: ",".join(str(x) for x in xs)
+    return (f"chunk {D} {Hq} {Hkv} {''.join(map(str, policy))} {S} {T} {S * (max(closed) + 2)} {m} {text(closed)} "
+            f"{text([fill] * len(closed))}")
+
+
+def test_pieces_in_the_key_split_form_only_where_memory_lets_them(forms):
+    """Chunks whose 32-column workgroups would read the same keys over and over from beyond the L2s keep the pipelined pieces;
+    short ones, and few heads' worth of keys, take the key-split ones."""
+    bound = [chunk_line(128, 16, 2, (3, 1), 4096, 1024, (14,), 2085, 25),
+             chunk_line(128, 8, 8, (3, 3, 1, 1, 1, 1, 1, 1), 4096, 512, (14,), 234, 137),
+             chunk_line(128, 4, 1, (3,), 2048, 512, (13, 13, 13), 1019, 34),
+             chunk_line(128, 8, 1, (3,), 4096, 1024, (15,), 273, 29),
+             chunk_line(128, 4, 1, (3,), 4096, 512, (23, 23), 1634, 29)]
+    assert [x.split()[0] for x in forms(bound)] == ["piped"] * len(bound)
+    assert all(int(x.split()[2]) > 1 for x in forms(bound))
+    short = [chunk_line(128, 16, 2, (3, 1), 4096, 1024, (7,), 2085, 8),
+             chunk_line(128, 16, 4, (3, 1, 1, 1), 4096, 1024, (10, 10, 10), 2085, 34),
+             chunk_line(64, 16, 4, (3, 1, 1, 1), 4096, 1024, (6,), 300, 26),
+             chunk_line(128, 32, 8, (3, 3, 3, 3, 1, 1, 1, 1), 4096, 1024, (6,), 300, 1)]
+    assert [x.split()[0] for x in forms(short)] == ["keysplit"] * len(short)
+    assert all(int(x.split()[2]) > 1 for x in forms(short))
