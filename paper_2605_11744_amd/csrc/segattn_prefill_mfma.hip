@@ -1340,6 +1340,10 @@ PrefillForm choose_prefill(const Problem &p, PrefillArgs &a) {
   bool cut = a.parts > 1 || a.parts_other > 1;
   const UncutEstimate uncut = estimate_uncut(p, a, hs);
   bool keysplit = !forced && !cut && uncut.keysplit_pays;
+  // Nothing cut: the uncut launch's own estimates are the better ones behind less than a segment, where key-split pieces were
+  // taken though they lose (9 rows behind 556, 8/8 heads of 128, 9.9 -> 11.8 us, 9.8 uncut; 2 x 184 rows behind 403 11.5 ->
+  // 14.1, 11.2).  They also keep 4 x 19 rows behind 8K, 32/8 heads, uncut, which are 52 us so and 40 in pieces.
+  if (p.D == 128 && !cut) best = fmin(best, fmin(uncut.keysplit, uncut.piped));
   PrefillArgs b = a_in;
   if (p.tune_queue == 0 && plan_pieces(p, b, hs, PieceForm{32 / hs, p.D == 128 ? 1 : 2, 19, 0.29}, true) < best) {
     a = b;

@@ -78,3 +78,10 @@ def test_pieces_in_the_key_split_form_only_where_memory_lets_them(forms):
              chunk_line(128, 32, 8, (3, 3, 3, 3, 1, 1, 1, 1), 4096, 1024, (6,), 300, 1)]
     assert [x.split()[0] for x in forms(short)] == ["keysplit"] * len(short)
     assert all(int(x.split()[2]) > 1 for x in forms(short))
+
+
+def test_short_prefixes_are_not_cut_where_the_uncut_launch_is_shorter(forms):
+    """Chunks behind less than a segment: the uncut launch's own estimate counts, not the one for long prefixes."""
+    short = [chunk_line(128, 8, 8, (3, 1, 1, 1, 1, 1, 1, 1), 2048, 512, (0,), 556, 9),
+             chunk_line(128, 8, 8, (3, 3, 3, 3, 1, 1, 1, 1), 2048, 256, (0, 0), 403, 184)]
+    assert [x.split()[2:] for x in forms(short)] == [["1", "1"]] * 2
