@@ -203,13 +203,28 @@ static DkvSteps dkv_steps(const Problem &p, const BwdArgs &a) {
 // of 1.0 gained 1.3x in the mean of those taken, one lost 2 %; below, the one wave per SIMD that the dK/dV item leaves
 // the dQ items costs more than the idle end of a launch did (0.6x for a window of 5000 rows of 32/8 heads).  D = 64, two
 // workgroups per CU either way, beyond 0.22: 1.14x, none lost (beyond 600,000 wave-steps some did, 0.87 to 1.05x).
-// Groups of one head, and of fewer than four at D = 64, keep the split form of dQ, which is the faster one there (0.85x).
+// Groups of one head, and at D = 64 those that are no multiple of four, keep the split form of dQ, which is the faster one
+// there (0.85x).  At D = 64 two launches also share a long chain out among eight waves, in this one the dQ items walk theirs
+// alone and the dK/dV items with four.  That costs more than the second launch where there are few items and dQ's chain is
+// the longer one (3678 rows of 4/1 heads, all of the past, S = 128: 35 us in two launches, 69 in one), and where the dK/dV
+// items have a CU each and a chain far beyond dQ's, groups of eight heads and more (1024 rows of 16/1 heads, S = 512, 75
+// and 88; 1024 of 8/1 43 and 48; but 4096 of 8/1 with the past, S = 512, 92 and 77).  Of 2343 drawn windows (1, 2, 4 and 8 KV
+// heads, groups of 4 to 16) 2054 went beyond 0.22, 207 of them more than 3 % slower than in two launches; without these two kinds 60 of 1748
+// (1.26x at worst), and of the 306 that they take out 62 had gained more than 3 % (8 % in the mean).
 bool bwd_both_pays(const Problem &p, const BwdArgs &a) {
   if (p.tune_waves != 0 || p.tune_queue != 0) return false;
   if (p.g == 1 || (p.D == 64 && p.g % 4 != 0)) return false;
+  const long long total = a.cu_seqlens ? a.total : 0;
   const DkvSteps d = dkv_steps(p, a);
-  const double waves = 4 * device_cus(), steps = d.steps + count_steps(p, a.n, a.cu_seqlens ? a.total : 0, 0).steps;
-  if (p.D == 64 && steps > 600 * waves) return false;
+  const StepCount q = count_steps(p, a.n, total, 0);
+  const double cus = device_cus(), waves = 4 * cus, steps = d.steps + q.steps;
+  if (p.D == 64) {
+    if (steps > 600 * waves) return false;
+    const double dq_items = p.Hkv * (p.g / 4) * row_blocks(p, a.n, total, 32), dkv_items = p.Hkv * row_blocks(p, a.n, total, 32);
+    if (q.longest > 1.2 * d.chain && dq_items <= 0.83 * cus) return false;
+    if (d.chain > 150 && ((q.longest <= 0.125 * d.chain && dkv_items <= cus) || (q.longest <= 0.15 * d.chain && dkv_items <= cus / 4)))
+      return false;
+  }
   return d.chain * (1.5 / 4) > (p.D == 64 ? 0.22 : 1.0) * steps / waves;
 }
 // dK/dV: waves of a workgroup of the split form (D = 64: eight, or four with two workgroups per CU), 0: the other form.

@@ -4,6 +4,10 @@
 //       -> "numbered" | "searched" (every window cut by itself) | "even", slices, numbers by the longest windows
 //   chunk D Hq Hkv policy S T capacity rows closed,.. fill,..
 //       -> "keysplit" | "piped", waves of a workgroup, pieces of the PAST heads' prefixes at most, of the others'
+//   window D Hq Hkv policy S T sequences rows packed
+//       -> backward of `sequences` windows of `rows` rows (packed > 0: a batch of as many rows in all): "both" |
+//          "split" | "items" (dQ), waves of the split dK/dV form (0: the other one; "both": 4), query heads of a dQ
+//          workgroup, "packed" | "padded" (numbering of a packed batch's dQ items) | "dense"
 // (policy: a digit per KV head; closed, fill: closed segments and open rows of each sequence).  Needs no GPU: the rules then
 // take 256 compute units.
 #include <iostream>
@@ -108,10 +112,37 @@ static bool chunk(const std::string &line) {
   return true;
 }
 
+static bool window(const std::string &line) {
+  std::istringstream head(line), in(line);
+  std::string word;
+  int batch, rows;
+  long long total;
+  for (int i = 0; i < 7; ++i) head >> word;
+  head >> batch >> rows >> total;
+  in >> word;
+  Call c;
+  if (head.fail() || !read_call(in, batch, 0, c)) return false;
+  static int offsets[1];  // not read by the rules
+  BwdArgs a;
+  memset(&a, 0, sizeof(a));
+  a.n = rows;
+  a.total = total;
+  if (total > 0) a.cu_seqlens = offsets;
+  const int hs = c.p.g % 4 == 0 ? 4 : c.p.g % 2 == 0 ? 2 : 1;
+  const bool both = bwd_both_pays(c.p, a), split = !both && bwd_dq_split_pays(c.p, a);
+  const int per_wg = split ? 32 / hs : 128 / hs, seg = std::min(rows, c.p.S);
+  const bool packed = total > 0 && number_packed(c.p, total, (rows + c.p.S - 1) / c.p.S, (seg + per_wg - 1) / per_wg, per_wg);
+  std::cout << (both ? "both 4 " : split ? "split " : "items ");
+  if (!both) std::cout << bwd_dkv_split_waves(c.p, a) << ' ';
+  std::cout << hs << (packed ? " packed" : total > 0 ? " padded" : " dense") << '\n';
+  return true;
+}
+
 int main() {
   for (std::string line; std::getline(std::cin, line);) {
     const std::string kind = line.substr(0, line.find(' '));
-    if (!(kind == "decode" && decode(line)) && !(kind == "chunk" && chunk(line))) {
+    if (!(kind == "decode" && decode(line)) && !(kind == "chunk" && chunk(line)) &&
+        !(kind == "window" && window(line))) {
       std::cout << "refused: " << line << '\n';
       return 1;
     }

@@ -85,3 +85,30 @@ def test_short_prefixes_are_not_cut_where_the_uncut_launch_is_shorter(forms):
     short = [chunk_line(128, 8, 8, (3, 1, 1, 1, 1, 1, 1, 1), 2048, 512, (0,), 556, 9),
              chunk_line(128, 8, 8, (3, 3, 3, 3, 1, 1, 1, 1), 2048, 256, (0, 0), 403, 184)]
     assert [x.split()[2:] for x in forms(short)] == [["1", "1"]] * 2
+
+
+def window_line(D, Hq, Hkv, policy, S, T, B, n, total=0):
+    return f"window {D} {Hq} {Hkv} {''.join(map(str, policy))} {S} {T} {B} {n} {total}"
+
+
+def test_one_launch_backward_only_where_two_launches_are_not_faster(forms):
+    """Head dimension 64, one or two KV heads: windows whose longest chain the eight waves of the two split launches share out."""
+    faster_in_two = [window_line(64, 4, 1, (3,), 128, 32, 1, 3678),         # 35 us, 69 in one launch
+                     window_line(64, 4, 1, (3,), 512, 0, 1, 2964),          # 36, 58
+                     window_line(64, 8, 2, (3, 3), 128, 16, 1, 1616),       # 27, 35
+                     window_line(64, 12, 1, (1,), 1024, 256, 1, 677),       # 52, 60
+                     window_line(64, 16, 1, (3,), 512, 128, 1, 1013),
+                     window_line(64, 16, 1, (1,), 2048, 256, 1, 4096),
+                     window_line(64, 16, 1, (1,), 512, 128, 1, 1024),
+                     window_line(64, 8, 1, (1,), 512, 128, 1, 1024),
+                     window_line(64, 8, 1, (3,), 2048, 256, 1, 1024)]
+    assert [x.split()[0] == "both" for x in forms(faster_in_two)] == [False] * len(faster_in_two)
+    faster_in_one = [window_line(64, 16, 4, (3, 3, 1, 1), 512, 128, 8, 2100, 6547),
+                     window_line(64, 32, 8, (3, 1) * 4, 1024, 256, 1, 1500),
+                     window_line(64, 16, 4, (3, 1, 1, 1), 2048, 512, 1, 3000),
+                     window_line(64, 4, 1, (1,), 1024, 128, 1, 1500),
+                     window_line(64, 8, 1, (3,), 512, 128, 1, 4096),
+                     window_line(64, 16, 1, (3,), 512, 128, 1, 4096),
+                     window_line(128, 16, 4, (3, 1, 1, 1), 512, 128, 1, 747),
+                     window_line(128, 16, 2, (3, 1), 2048, 512, 2, 1402)]
+    assert [x.split()[0] for x in forms(faster_in_one)] == ["both"] * len(faster_in_one)
