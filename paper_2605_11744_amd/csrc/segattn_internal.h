@@ -114,7 +114,7 @@ struct PrefillArgs {
   const int *cu_seqlens; // SEQ mode, packed ragged batch: device [B+1] row offsets, else nullptr
   int packed;            // packed batch: its items are numbered over the row blocks there are (number_packed)
   long long total_rows;  // rows of the packed batch (lse is [Hq, total_rows] then)
-  int longest_steps;     // host: key steps of the longest workgroup, where the launcher has asked (choose_prefill)
+  int longest_steps;     // host: key steps of the longest workgroup if nothing is cut (choose_prefill)
   int n_seg;             // segments covered by the launch (1 in CTX mode)
   int q_blocks_per_seg;  // ceil(min(S, n_rows) / rows per workgroup); set by the launcher
   int pair_stride;       // spreads the (segment, sequence, head) groups of non-PAST heads over the XCDs (0 = 1)
@@ -533,6 +533,7 @@ struct PrefillForm {
   bool keysplit, cut;
 };
 PrefillForm choose_prefill(const Problem &p, PrefillArgs &a);
+int keysplit_waves(const Problem &p, const PrefillArgs &a, long long grid);  // of a workgroup of the key-split kernel
 hipError_t launch_prefill(const Problem &p, const PrefillArgs &a, hipStream_t st);
 // bytes of split-prefix workspace for `parts` pieces (fp32 outputs + LSEs of one segment of every sequence)
 __host__ __device__ inline unsigned long long part_ws_bytes(const Problem &p, int parts) {

@@ -282,12 +282,18 @@ static hipError_t launch_split_hs(const Problem &p, const PrefillArgs &a, int hs
   return launch_split<D, 1, NW>(p, a, grid, st);
 }
 
+// Sixteen waves share out long chains of head dimension 64 where every workgroup has a CU to itself, eight -> sixteen: 68 rows
+// behind 33K, 16/4 heads, with the commit 122 -> 101 us, 3 x 114 rows of 4/4 heads 109 -> 93, a prompt of 7953 rows, one
+// head, 31.9 -> 28.5.  Of 1466 drawn chunks that stay uncut 1.2x in the mean from 256 steps on, 1.04x with 96 to
+// 128 (none lost); not worth the larger merge where a chain is shorter (64 to 96 steps 0.97 to 1.04x, below 0.84 to 0.97x),
+// nor with more workgroups than CUs (two of eight waves fit one).
+int keysplit_waves(const Problem &p, const PrefillArgs &a, long long grid) {
+  return p.D == 64 && grid <= device_cus() && !a.packed && a.piece_rows.d == 0 && a.longest_steps >= 96 ? 16 : 8;
+}
+
 hipError_t launch_prefill_keysplit(const Problem &p, const PrefillArgs &a, int hs, long long grid, hipStream_t st) {
   if (p.D == 128) return launch_split_hs<128, 8>(p, a, hs, grid, st);
-  // Sixteen waves share out long chains where every workgroup has a CU to itself: 68 rows behind 33K, 16/4 heads of 64,
-  // 120 -> 99 us, 3 x 114 rows of 4/4 heads 127 -> 105.  Not worth the larger merge where a chain is short (64 steps
-  // 12.7 -> 13.1, 11 steps 7.1 -> 7.9).
-  if (grid <= device_cus() && !a.packed && a.piece_rows.d == 0 && a.longest_steps >= 96) return launch_split_hs<64, 16>(p, a, hs, grid, st);
+  if (keysplit_waves(p, a, grid) == 16) return launch_split_hs<64, 16>(p, a, hs, grid, st);
   return launch_split_hs<64, 8>(p, a, hs, grid, st);
 }
 

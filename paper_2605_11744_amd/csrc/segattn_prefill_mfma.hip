@@ -1301,6 +1301,7 @@ static double plan_pieces(const Problem &p, PrefillArgs &a, int hs, const PieceF
 struct UncutEstimate {
   double keysplit, piped;  // microseconds
   bool keysplit_pays;
+  double longest;  // key steps of the longest workgroup
 };
 static UncutEstimate estimate_uncut(const Problem &p, const PrefillArgs &a, int hs) {
   StepCount c;
@@ -1324,11 +1325,11 @@ static UncutEstimate estimate_uncut(const Problem &p, const PrefillArgs &a, int 
   if (p.D == 64) {
     const double split = 7.69 + 0.11 * c.longest + 4.48e-4 * c.steps + 2.37 * more_rounds(wgs, 2 * cus);
     const double piped = 8 + fmax(0.423 * c.longest, 1.49e-4 * c.steps) + 0.16 * more_rounds(wgs_piped, 3 * cus);
-    return {split, piped, split < 0.973 * piped};
+    return {split, piped, split < 0.973 * piped, c.longest};
   }
   const double split = 8.23 + 0.072 * c.longest + 1.1e-3 * c.steps + 3.59 * more_rounds(wgs, cus);
   const double piped = 8 + fmax(0.547 * c.longest, 8.4e-5 * c.steps) + 0.12 * more_rounds(wgs_piped, 2 * cus);
-  return {split, piped, split < 0.942 * piped};
+  return {split, piped, split < 0.942 * piped, c.longest};
 }
 
 PrefillForm choose_prefill(const Problem &p, PrefillArgs &a) {
@@ -1340,6 +1341,7 @@ PrefillForm choose_prefill(const Problem &p, PrefillArgs &a) {
   bool cut = a.parts > 1 || a.parts_other > 1;
   const UncutEstimate uncut = estimate_uncut(p, a, hs);
   bool keysplit = !forced && !cut && uncut.keysplit_pays;
+  a.longest_steps = (int)uncut.longest;
   // Nothing cut: the uncut launch's own estimates are the better ones behind less than a segment, where key-split pieces were
   // taken though they lose (9 rows behind 556, 8/8 heads of 128, 9.9 -> 11.8 us, 9.8 uncut; 2 x 184 rows behind 403 11.5 ->
   // 14.1, 11.2).  They also keep 4 x 19 rows behind 8K, 32/8 heads, uncut, which are 52 us so and 40 in pieces.

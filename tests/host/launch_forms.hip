@@ -4,6 +4,8 @@
 //       -> "numbered" | "searched" (every window cut by itself) | "even", slices, numbers by the longest windows
 //   chunk D Hq Hkv policy S T capacity rows closed,.. fill,..
 //       -> "keysplit" | "piped", waves of a workgroup, pieces of the PAST heads' prefixes at most, of the others'
+//   prompt D Hq Hkv policy S T sequences rows
+//       -> whole prompts of `rows` rows: "keysplit" | "piped", waves of a workgroup
 //   window D Hq Hkv policy S T sequences rows packed
 //       -> backward of `sequences` windows of `rows` rows (packed > 0: a batch of as many rows in all): "both" |
 //          "split" | "items" (dQ), waves of the split dK/dV form (0: the other one; "both": 4), query heads of a dQ
@@ -107,8 +109,29 @@ static bool chunk(const std::string &line) {
       least = std::min(least, n);
     }
   const PrefillForm f = choose_prefill(c.p, a);
-  std::cout << (f.keysplit ? "keysplit " : "piped ") << (f.keysplit ? 8 : f.nw) << ' ' << (f.cut ? a.parts : 1) << ' '
+  const long long grid = c.p.B * c.p.Hkv * (c.p.g / f.hs) * ((rows * f.hs + 31) / 32);  // of the key-split form, nothing cut
+  std::cout << (f.keysplit ? "keysplit " : "piped ") << (f.keysplit ? keysplit_waves(c.p, a, grid) : f.nw) << ' ' << (f.cut ? a.parts : 1) << ' '
             << (f.cut ? a.parts_other : 1) << '\n';
+  return true;
+}
+
+static bool prompt(const std::string &line) {
+  std::istringstream head(line), in(line);
+  std::string word;
+  int batch, rows;
+  for (int i = 0; i < 7; ++i) head >> word;
+  head >> batch >> rows;
+  in >> word;
+  Call c;
+  if (head.fail() || !read_call(in, batch, 0, c)) return false;
+  PrefillArgs a;
+  memset(&a, 0, sizeof(a));
+  a.n_rows = rows;
+  a.n_seg = (rows + c.p.S - 1) / c.p.S;
+  const PrefillForm f = choose_prefill(c.p, a);
+  const int per_wg = 32 / f.hs, seg = std::min(rows, c.p.S);
+  const long long grid = (long long)batch * c.p.Hkv * (c.p.g / f.hs) * a.n_seg * ((seg + per_wg - 1) / per_wg);
+  std::cout << (f.keysplit ? "keysplit " : "piped ") << (f.keysplit ? keysplit_waves(c.p, a, grid) : f.nw) << '\n';
   return true;
 }
 
@@ -142,7 +165,7 @@ int main() {
   for (std::string line; std::getline(std::cin, line);) {
     const std::string kind = line.substr(0, line.find(' '));
     if (!(kind == "decode" && decode(line)) && !(kind == "chunk" && chunk(line)) &&
-        !(kind == "window" && window(line))) {
+        !(kind == "prompt" && prompt(line)) && !(kind == "window" && window(line))) {
       std::cout << "refused: " << line << '\n';
       return 1;
     }

@@ -61,3 +61,19 @@ def test_reference_maximum_is_raised_late():
     o_ref, l_ref = orc.attend(q, k, v, seg_len=n, tail_len=0, kv_policy=[0])
     o, l = fwd_seq(w, q, k, v)
     assert_parity(o, l, o_ref, l_ref, fp32_check=False, what="ramp")
+
+
+LONG = [(3073, 4096, 512, 1), (3110, 4000, 0, 2), (4001, 2048, 2048, 1)]  # n, S, T, query heads of one KV head
+
+
+@pytest.mark.parametrize("n,S,T,g", LONG)
+def test_long_chains_of_few_heads(n, S, T, g):
+    """Prompts of one KV head of 64 with 96 and more key steps in a row (sixteen waves share them out): a last row
+    block of one row and a step of one key, a last round of the waves that most have no step in."""
+    w = W.small("ksl", index=845 + n % 10, seq_len=n, seg_len=S, tail_len=T, n_q_heads=g, n_kv_heads=1, head_dim=64, kv_policy=[1])
+    q, k, v = W.prefill_inputs(w)
+    rows = np.unique(np.r_[0:70, 1500:1600, n - 130:n])
+    o_ref, l_ref = orc.attend(q, k, v, seg_len=S, tail_len=T, kv_policy=[1], rows=rows)
+    o, l = fwd_seq(w, q, k, v)
+    assert np.isfinite(o).all() and np.isfinite(l).all()
+    assert_parity(o[:, rows], l[:, :, rows], o_ref, l_ref, fp32_check=False, what=f"n={n}")

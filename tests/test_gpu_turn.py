@@ -32,8 +32,10 @@ CASES = [
     (128, 2, 2, (3, 2), 512, 0, (24,), 0, 33),
     (64, 8, 2, (3, 1), 512, 128, (20, 2), 5, 3),
     (64, 2, 2, (2, 1), 512, 128, (16,), 9, 31),
-    # no room for pieces: one chain of 530 steps, sixteen waves
+    # no room for pieces: one chain of up to 530 steps, sixteen waves (test_launch_forms.py), one, two or four heads a workgroup
     (64, 16, 4, (3, 1, 1, 1), 2048, 512, (8,), 11, 68),
+    (64, 2, 2, (3, 1), 2048, 512, (4,), 11, 40),
+    (64, 4, 2, (1, 3), 2048, 512, (4,), 1999, 33),
 ]
 
 

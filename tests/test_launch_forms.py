@@ -112,3 +112,15 @@ def test_one_launch_backward_only_where_two_launches_are_not_faster(forms):
                      window_line(128, 16, 4, (3, 1, 1, 1), 512, 128, 1, 747),
                      window_line(128, 16, 2, (3, 1), 2048, 512, 2, 1402)]
     assert [x.split()[0] for x in forms(faster_in_one)] == ["both"] * len(faster_in_one)
+
+
+def test_long_uncut_chains_of_head_dimension_64_have_sixteen_waves(forms):
+    from test_gpu_keysplit import LONG
+    from test_gpu_turn import CASES
+    sixteen = [c for c in CASES if c[0] == 64 and c[6] in ((8,), (4,)) and c[8] in (33, 40, 68)]
+    assert [c[1] // c[2] for c in sixteen] == [4, 1, 2]  # every number of query heads of a workgroup
+    assert forms([chunk_line(*c) for c in sixteen]) == ["keysplit 16 1 1"] * 3
+    assert forms([f"prompt 64 {g} 1 1 {S} {T} 1 {n}" for n, S, T, g in LONG]) == ["keysplit 16"] * len(LONG)
+    others = [chunk_line(64, 16, 4, (1, 1, 1, 1), 2048, 512, (8,), 11, 68),          # a short chain
+              chunk_line(64, 16, 4, (3, 1, 1, 1), 2048, 512, (8,) * 8, 11, 68)]      # more workgroups than compute units
+    assert [x.split()[:2] for x in forms(others)] == [["keysplit", "8"]] * 2
