@@ -444,14 +444,12 @@ static hipError_t launch_both(const Problem &p, const BwdArgs &a, hipStream_t st
   const DkvSplitGrid g = dkv_split_grid(p, a);
   const long long items = dq_items(p, a, hs, (4 / hs) * 32, pa);
   if (items == 0 || g.items <= 0 || items + g.items > 0x7fffffffLL) return hipErrorInvalidValue;
-  if (pa.packed) {
-    if (hs == 4) return launch_both_items<D, 4, true>(p, pa, a, g, st);
-    if (hs == 2) return launch_both_items<D, 2, true>(p, pa, a, g, st);
-    return launch_both_items<D, 1, true>(p, pa, a, g, st);
+  if (hs == 4) return pa.packed ? launch_both_items<D, 4, true>(p, pa, a, g, st) : launch_both_items<D, 4, false>(p, pa, a, g, st);
+  if constexpr (D == 128) {  // (D = 64: groups of a multiple of four heads only, bwd_both_pays)
+    if (hs == 2) return pa.packed ? launch_both_items<D, 2, true>(p, pa, a, g, st) : launch_both_items<D, 2, false>(p, pa, a, g, st);
+    return pa.packed ? launch_both_items<D, 1, true>(p, pa, a, g, st) : launch_both_items<D, 1, false>(p, pa, a, g, st);
   }
-  if (hs == 4) return launch_both_items<D, 4, false>(p, pa, a, g, st);
-  if (hs == 2) return launch_both_items<D, 2, false>(p, pa, a, g, st);
-  return launch_both_items<D, 1, false>(p, pa, a, g, st);
+  return hipErrorInvalidValue;
 }
 hipError_t launch_bwd_both(const Problem &p, const BwdArgs &a, hipStream_t st) {
   return p.D == 128 ? launch_both<128>(p, a, st) : launch_both<64>(p, a, st);
