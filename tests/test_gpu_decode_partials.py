@@ -21,6 +21,10 @@ CASES = [
     (128, 8, 4, (1, 3, 0, 2), 1024, 256, (9, 1, 2), 77),
     (64, 4, 2, (1, 1), 2048, 512, (3, 1), 600),                  # no head with the past
     (128, 4, 2, (3, 3), 1024, 128, (5, 2), 511),                 # none without
+    # every window cut by itself, but a slice searched for: numbers by the longest windows would be mostly empty
+    (128, 16, 8, (3,) * 8, 1024, 128, (20, 2, 2), 77),
+    (64, 12, 3, (3, 1, 2), 1024, 256, (80, 1, 0, 3), 300),
+    (64, 8, 2, (3, 2), 1024, 256, (70, 3), 511),
 ]
 
 

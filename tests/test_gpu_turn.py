@@ -32,6 +32,10 @@ CASES = [
     (128, 2, 2, (3, 2), 512, 0, (24,), 0, 33),
     (64, 8, 2, (3, 1), 512, 128, (20, 2), 5, 3),
     (64, 2, 2, (2, 1), 512, 128, (16,), 9, 31),
+    (64, 2, 2, (2, 1), 512, 128, (40,), 9, 7),
+    (64, 4, 2, (3, 1), 512, 128, (40, 2), 77, 9),
+    # nothing to cut: a short chain, eight waves
+    (64, 8, 2, (1, 1), 512, 128, (3,), 100, 40),
     # no room for pieces: one chain of up to 530 steps, sixteen waves (test_launch_forms.py), one, two or four heads a workgroup
     (64, 16, 4, (3, 1, 1, 1), 2048, 512, (8,), 11, 68),
     (64, 2, 2, (3, 1), 2048, 512, (4,), 11, 40),

@@ -58,7 +58,7 @@ def test_numbering_the_slices_of_a_decode_step_costs_no_second_round(forms):
 
 def chunk_line(D, Hq, Hkv, policy, S, T, closed, fill, m):
     text = lambda xs: ",".join(str(x) for x in xs)
-    return (f"chunk {D} {Hq} {Hkv} {''.join(map(str, policy))} {S} {T} {S * (max(closed) + 2)} {m} {text(closed)} "
+    return (f"chunk {D} {Hq} {Hkv} {''.join(map(str, policy))} {S} {T} {S * (max(closed) + 1)} {m} {text(closed)} "
             f"{text([fill] * len(closed))}")
 
 
@@ -124,3 +124,36 @@ def test_long_uncut_chains_of_head_dimension_64_have_sixteen_waves(forms):
     others = [chunk_line(64, 16, 4, (1, 1, 1, 1), 2048, 512, (8,), 11, 68),          # a short chain
               chunk_line(64, 16, 4, (3, 1, 1, 1), 2048, 512, (8,) * 8, 11, 68)]      # more workgroups than compute units
     assert [x.split()[:2] for x in forms(others)] == [["keysplit", "8"]] * 2
+
+
+def test_backward_shapes_take_the_forms_they_were_written_for(forms):
+    """Every split form of dQ, and the split dK/dV form by itself, with each number of query heads a workgroup can have."""
+    from test_gpu_backward_split import ONE_LAUNCH_PACKED, TWO_LAUNCHES, TWO_LAUNCHES_PACKED
+    dense = forms([window_line(D, len(policy) * g, len(policy), policy, S, T, B, n) for D, g, S, T, policy, B, n, _ in TWO_LAUNCHES])
+    assert dense == [case[-1] + " dense" for case in TWO_LAUNCHES]
+    packed = forms([window_line(D, len(policy) * g, len(policy), policy, S, T, len(lens), max(lens), sum(lens))
+                    for D, g, S, T, policy, lens, _ in TWO_LAUNCHES_PACKED + ONE_LAUNCH_PACKED])
+    assert packed == [case[-1] + " packed" for case in TWO_LAUNCHES_PACKED + ONE_LAUNCH_PACKED]
+    split = {(case[0], x.split()[0], x.split()[2], x.split()[3]) for cases, got in ((TWO_LAUNCHES, dense), (TWO_LAUNCHES_PACKED, packed))
+             for case, x in zip(cases, got)}
+    assert split >= {(D, "split", hs, how) for D in (64, 128) for hs in "124" for how in ("dense", "packed")}
+    both = [window_line(D, g, 1, (3,), S, T, 2, n) for D, g in ((64, 8), (128, 2), (128, 8)) for n, S, T in ((31, 64, 8), (129, 128, 128), (430, 200, 64))]
+    assert {x.split()[0] for x in forms(both)} == {"both"}
+
+
+def test_decode_shapes_find_their_slices_in_every_way(forms):
+    from test_gpu_decode_partials import CASES
+    got = [x.split()[0] for x in forms([decode_line(*c) for c in CASES])]
+    assert got == ["even"] * 4 + ["numbered"] * 3 + ["searched"] * 3
+
+
+def test_turn_shapes_take_the_forms_they_were_written_for(forms):
+    from test_gpu_turn import CASES
+    got = [x.split() for x in forms([chunk_line(*c) for c in CASES])]
+    for case, (form, waves, first, other) in zip(CASES, got):
+        if case[8] <= 9 and max(case[6]) >= 20:  # the short chunks
+            assert form == "keysplit" and waves == "8" and int(first) > 1, case
+    pieces = {(c[0], c[1] // c[2]) for c, x in zip(CASES, got) if x[0] == "keysplit" and int(x[2]) > 1}
+    assert pieces >= {(D, g) for D in (64, 128) for g in (1, 2, 4)}
+    assert ["keysplit", "8", "1", "1"] in [x for c, x in zip(CASES, got) if c[0] == 64]
+    assert any(x[0] == "piped" and int(x[2]) > 1 for x in got)
