@@ -1,5 +1,6 @@
 // Backward of segment-level attention, validation kernels (fp32 FMA arithmetic, no MFMA) and their
-// row statistics (the bf16 dQ kernels form the same ones themselves).
+// row statistics (the bf16 dQ kernels form the same ones themselves; where dQ and dK/dV of a short window share a launch, the
+// statistics kernel here runs in front of it).
 //
 // Gradients of L = sum(O * dO) for O = softmax(scale Q K^T + M) V (Eq. 12 under the mask of
 // Eq. 13), with gradient stopped where the paper stops it: every visible key contributes to dQ;

@@ -159,8 +159,9 @@ static hipError_t allow_lds(K kern, int bytes, std::atomic<bool> &ready) {
 // the rounds of workgroups, fitted to 11,123 windows and packed batches of 360 to 65,000 rows (eight numbers of
 // heads, segments of 64 to 4096, every form of each timed): 0.6 % (D = 64) and 0.8 % (D = 128) slower than the best
 // form on average; against the forms for large launches alone 13 of them more than 3 % slower, none more than 7 %.
-// The split forms pay where those leave the chip waiting for a chain: 1024 rows, 32/8 heads of 64, 100 -> 48 us;
-// 445 rows, 16/2 heads of 128, 76 -> 48.  They don't where waves that stage tiles of their own are bound by L2 (8192
+// The split forms pay where those leave the chip waiting for a chain (groups of several heads where the two passes don't share
+// one launch, bwd_both_pays): backward of 1024 rows, own segment and tail, 8/8 heads of 64 49.5 -> 22.1 us, 12/4 heads 87 -> 38,
+// 16/1 heads 220 -> 75; 445 rows, 8/8 heads of 128, 39.7 -> 29.1; 4942 rows, 4/1 heads of 128, S = 163, 149 -> 103.  They don't where waves that stage tiles of their own are bound by L2 (8192
 // rows, 32/8 heads of 128, would lose 580 us), or by a further round of workgroups, however few they are (packed
 // sequences of 10 to 60 rows, 8/8 heads of 128, 340 workgroups: 30 -> 41).  A forced launch shape keeps the other forms.
 bool bwd_dq_split_pays(const Problem &p, const BwdArgs &a) {

@@ -40,8 +40,9 @@ struct BwdTile {
 
 // delta = sum_d dO * O of the lane's query row, from the dO operand registers (elements 16 kc + 8 hi .. +7 of
 // the row at element offset qoff) and the forward's output (bf16 or fp32); both half-waves get it.  Formed where
-// dO is held anyway: a kernel of its own read dO and O once more and cost a launch (8K window, 32 heads:
-// 25 us of 1600; 6.4K packed rows, 16 heads: 11 us of 137).
+// dO is held anyway: a kernel of its own reads dO and O once more and costs a launch (8K window, 32 heads:
+// 25 us of 1600).  Only where dQ and dK/dV share a launch do both need it before they start, and that kernel
+// (segattn_bwd_fp32.hip) runs in front: 11 us for 6.4K packed rows of 16 heads, which the shared launch more than earns back.
 template <int NC>
 __device__ __forceinline__ float row_delta(const void *out, bool out_fp32, long long qoff, int hi, const bf16x8 (&G)[NC]) {
   float part[NC];
