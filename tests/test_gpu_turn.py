@@ -31,7 +31,7 @@ CASES = [
     (128, 4, 2, (3, 1), 512, 64, (24,), 31, 17),
     (128, 2, 2, (3, 2), 512, 0, (24,), 0, 33),
     (64, 8, 2, (3, 1), 512, 128, (20, 2), 5, 3),
-    (64, 2, 2, (2, 1), 512, 128, (16,), 9, 31),
+    (64, 2, 2, (2, 1), 512, 128, (16,), 9, 31),              # no room for them: uncut
     (64, 2, 2, (2, 1), 512, 128, (40,), 9, 7),
     (64, 4, 2, (3, 1), 512, 128, (40, 2), 77, 9),
     # nothing to cut: a short chain, eight waves
