@@ -85,6 +85,18 @@ def test_short_prefixes_are_not_cut_where_the_uncut_launch_is_shorter(forms):
     short = [chunk_line(128, 8, 8, (3, 1, 1, 1, 1, 1, 1, 1), 2048, 512, (0,), 556, 9),
              chunk_line(128, 8, 8, (3, 3, 3, 3, 1, 1, 1, 1), 2048, 256, (0, 0), 403, 184)]
     assert [x.split()[2:] for x in forms(short)] == [["1", "1"]] * 2
+    few = [chunk_line(64, 3, 3, (1, 1, 1), 1024, 128, (51,), 641, 3), chunk_line(64, 2, 1, (0,), 2048, 256, (10,) * 4, 749, 4)]
+    assert [x.split()[2:] for x in forms(few)] == [["1", "1"]] * 2
+    assert forms([chunk_line(128, 24, 8, (3,) * 8, 1024, 256, (50,) * 6, 269, 5)]) == ["keysplit 8 1 1"]  # two rounds of pieces
+
+
+def test_longer_prefixes_are_cut_where_the_uncut_launch_only_seems_shorter(forms):
+    """A workspace that holds too few pieces for the pipelined form, some for the key-split one."""
+    longer = [chunk_line(128, 32, 8, (3, 3, 3, 3, 1, 1, 1, 1), 4096, 1024, (1, 1, 1), 2811, 14),
+              chunk_line(128, 32, 8, (3, 3, 1, 1, 1, 1, 1, 1), 4096, 1024, (1, 1, 1), 3188, 11),
+              chunk_line(128, 16, 2, (3, 1), 2048, 512, (1, 1, 1), 1180, 5),
+              chunk_line(128, 32, 8, (3, 1, 3, 1, 1, 1, 1, 1), 4096, 1024, (2,) * 4, 300, 19)]
+    assert [(x.split()[0], int(x.split()[2]) > 1) for x in forms(longer)] == [("keysplit", True)] * len(longer)
 
 
 def window_line(D, Hq, Hkv, policy, S, T, B, n, total=0):
