@@ -1197,9 +1197,10 @@ struct PieceForm {
   int rows, wgs_per_cu, item_steps;
   double step_us;
 };
-// Plans the pieces of one form (cut_only: the uncut launch is not among its candidates); returns the estimated
+// Plans the pieces of one form (piped: the estimate of the pipelined form's plan, where the key-split form is planned
+// beside it: then the uncut launch is not among the candidates; otherwise 0); returns the estimated
 // microseconds of the launch, infinite if nothing is to be cut and that is no candidate.
-static double plan_pieces(const Problem &p, PrefillArgs &a, int hs, const PieceForm &form, bool cut_only) {
+static double plan_pieces(const Problem &p, PrefillArgs &a, int hs, const PieceForm &form, double piped) {
   a.parts = a.parts_other = 1;
   a.piece_rows = FastDiv{0u, 0u, 0u};
   if (a.cache == nullptr || p.tune_waves != 0) return INFINITY;  // a forced workgroup shape runs unsplit
@@ -1225,7 +1226,7 @@ static double plan_pieces(const Problem &p, PrefillArgs &a, int hs, const PieceF
     return end + (other - idle * beside + wgs - 1) / wgs * lo;
   };
   double best = INFINITY;
-  if (!cut_only) {
+  if (piped == 0) {
     // Uncut, head_dim 128 runs half as long blocks of four waves where the chip has room for them.
     long long uncut = span(blocks * n_first, sf, blocks * n_other, so, form.item_steps);
     if (p.D == 128 && waves_d128(p, a, hs) == 4 && 2 * blocks * (n_first > 0 ? n_first : n_other) <= wgs) uncut = uncut * 2 / 3;
@@ -1268,7 +1269,7 @@ static double plan_pieces(const Problem &p, PrefillArgs &a, int hs, const PieceF
   auto least = [&](long long prefix, int most) { return most > 1 ? piece_count((int)prefix, m, a.piece_rows, most) : 1; };
   a.piece_list[0] = {out, lse, a.parts, n_first * p.g, least(a.min_first_prefix, a.parts), 0};
   a.piece_list[1] = {out + rows_first * p.D, lse + rows_first, a.parts_other, n_other * p.g, least(a.min_other_prefix, a.parts_other), n_first};
-  if (p.D == 64 || !cut_only) return best;
+  if (piped == 0) return best;
   // Key-split pieces of head dimension 128 are bound by memory as often as by their steps: 32 query columns read as many keys
   // as 256 do, and the workgroups of a piece (row blocks, sub-groups of a group's heads) share them in an L2 only where the
   // launch, which puts them `per` and a.parts apart, deals them to one XCD.  Fitted to 6504 timed chunks of 1 to 600 rows
@@ -1276,7 +1277,10 @@ static double plan_pieces(const Problem &p, PrefillArgs &a, int hs, const PieceF
   // TB/s beyond the L2s and 25 out of them.  By the steps alone 29 rows of two sequences behind 98K, 4/1 heads, took 67 us
   // where the pipelined pieces take 40, and 25 rows behind 59K, 16/2 heads, 58 (41); of 3901 drawn chunks 29 were more than 3 %
   // slower than with pipelined pieces alone (1.6x at worst), by the larger estimate 6 (1.1x) and 0.3 % fewer us in the mean.
-  // (Head dimension 64, half the bytes a step: 3 of 3103 by the steps.)
+  // Head dimension 64, half the bytes a step, goes by the steps, except where several row blocks read the same keys and both
+  // estimates of their bytes are a good part of the pipelined launch's time: 17 rows of six sequences behind 30K, 32/8 heads, six
+  // PAST, 116 us (87 pipelined), 21 of three behind 64K, 24/4 heads, 140 (103).  Of 8134 drawn chunks 60 were more than 4 % slower than
+  // with pipelined pieces alone, 9 without these; none of those that it keeps pipelined would be faster in key-split pieces.
   const long long first = blocks * n_first * a.parts, other = blocks * n_other * a.parts_other;
   const long long nhs = p.g / hs, per = (long long)p.B * n_first * nhs * a.parts;
   unsigned xcds = 0;  // that read a piece
@@ -1286,6 +1290,7 @@ static double plan_pieces(const Problem &p, PrefillArgs &a, int hs, const PieceF
   const double beyond = mb * p.B * ((double)n_first * sf * __builtin_popcount(xcds) + (double)n_other * so) / 7.6, l2 = mb * total / 25;
   const double us = 7.6 + row_heads * p.D * 8 / 5.0e6 + 4.3 * ceil((double)(first + other) / wgs) +
                     sqrt(sqrt(chain * chain * chain * chain + beyond * beyond * beyond * beyond + l2 * l2 * l2 * l2));
+  if (p.D == 64) return m > form.rows && l2 >= 0.28 * piped && beyond >= 0.45 * piped ? INFINITY : best;
   return fmax(best, us);
 }
 
@@ -1337,19 +1342,20 @@ PrefillForm choose_prefill(const Problem &p, PrefillArgs &a) {
   const int hs = fp32 ? 1 : heads_per_wg(p);
   const PrefillArgs a_in = a;
   if (fp32) return {hs, p.D == 128 ? waves_d128(p, a, hs) : 4, false, false};
-  double best = plan_pieces(p, a, hs, p.D == 128 ? PieceForm{(8 / hs) * 32, 1, 12, 0.87} : PieceForm{(4 / hs) * 32, 2, 12, 0.4}, false);
+  const double piped = plan_pieces(p, a, hs, p.D == 128 ? PieceForm{(8 / hs) * 32, 1, 12, 0.87} : PieceForm{(4 / hs) * 32, 2, 12, 0.4}, 0);
   bool cut = a.parts > 1 || a.parts_other > 1;
   const UncutEstimate uncut = estimate_uncut(p, a, hs);
   bool keysplit = !forced && !cut && uncut.keysplit_pays;
   a.longest_steps = (int)uncut.longest;
   PrefillArgs b = a_in;
   const PieceForm split = {32 / hs, p.D == 128 ? 1 : 2, 19, 0.29};
-  const double pieces = p.tune_queue == 0 ? plan_pieces(p, b, hs, split, true) : INFINITY;
+  const double pieces = p.tune_queue == 0 ? plan_pieces(p, b, hs, split, piped) : INFINITY;
   // Nothing cut for the pipelined form: behind a short prefix the uncut launch's own estimates are the better ones (9 rows behind
   // 556, 8/8 heads of 128, 9.9 us, in key-split pieces 11.8; 3 behind 769, 3/3 heads of 64, with the commit 13.3 and 15.6), and where there are
   // more key-split pieces than fit at once (5 rows of six sequences behind 51K, 24/8 heads, 503 and 699).  Otherwise they are
   // far too low behind longer ones, whose keys come from cold memory: 14 rows of three sequences behind 7K, 32/8 heads, 51 us
   // uncut and 40 in pieces, 34 behind 8K 59 and 45.  Of 17 drawn chunks the pieces lost at 51 steps and won from 52 on.
+  double best = piped;
   if (!cut) {
     const int n_first = heads_listed_first(p, a), n_other = p.Hkv - n_first;
     const bool short_prefix = (n_first == 0 || a.max_first_prefix < 1600) && (n_other == 0 || a.max_other_prefix < 1600);

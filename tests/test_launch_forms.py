@@ -69,7 +69,10 @@ def test_pieces_in_the_key_split_form_only_where_memory_lets_them(forms):
              chunk_line(128, 8, 8, (3, 3, 1, 1, 1, 1, 1, 1), 4096, 512, (14,), 234, 137),
              chunk_line(128, 4, 1, (3,), 2048, 512, (13, 13, 13), 1019, 34),
              chunk_line(128, 8, 1, (3,), 4096, 1024, (15,), 273, 29),
-             chunk_line(128, 4, 1, (3,), 4096, 512, (23, 23), 1634, 29)]
+             chunk_line(128, 4, 1, (3,), 4096, 512, (23, 23), 1634, 29),
+             chunk_line(64, 32, 8, (3, 3, 3, 3, 3, 1, 1, 1), 1024, 128, (29,) * 6, 616, 17),
+             chunk_line(64, 24, 4, (2, 2, 2, 1), 1024, 128, (62,) * 3, 625, 21),
+             chunk_line(64, 16, 4, (3, 3, 3, 1), 1024, 128, (59,) * 6, 678, 57)]
     assert [x.split()[0] for x in forms(bound)] == ["piped"] * len(bound)
     assert all(int(x.split()[2]) > 1 for x in forms(bound))
     short = [chunk_line(128, 16, 2, (3, 1), 4096, 1024, (7,), 2085, 8),
