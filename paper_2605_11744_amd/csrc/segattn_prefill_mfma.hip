@@ -1351,16 +1351,17 @@ PrefillForm choose_prefill(const Problem &p, PrefillArgs &a) {
   const PieceForm split = {32 / hs, p.D == 128 ? 1 : 2, 19, 0.29};
   const double pieces = p.tune_queue == 0 ? plan_pieces(p, b, hs, split, piped) : INFINITY;
   // Nothing cut for the pipelined form: behind a short prefix the uncut launch's own estimates are the better ones (9 rows behind
-  // 556, 8/8 heads of 128, 9.9 us, in key-split pieces 11.8; 3 behind 769, 3/3 heads of 64, with the commit 13.3 and 15.6), and where there are
-  // more key-split pieces than fit at once (5 rows of six sequences behind 51K, 24/8 heads, 503 and 699).  Otherwise they are
+  // 556, 8/8 heads of 128, 9.9 us, in key-split pieces 11.8; 3 behind 769, 3/3 heads of 64, with the commit 13.3 and 15.6).  They are
   // far too low behind longer ones, whose keys come from cold memory: 14 rows of three sequences behind 7K, 32/8 heads, 51 us
-  // uncut and 40 in pieces, 34 behind 8K 59 and 45.  Of 17 drawn chunks the pieces lost at 51 steps and won from 52 on.
+  // uncut and 40 in pieces, 34 behind 8K 59 and 45.  Of 17 drawn chunks the pieces lost at 51 steps and won from 52 on.  Raised by
+  // 1.3 they still count where more key-split pieces than fit at once make the difference larger (5 rows of six sequences behind
+  // 51K, 24/8 heads, 503 us uncut, 699 in pieces; 3 of six behind 24K, 40/8 heads, 369 and 297, stay in pieces).
   double best = piped;
   if (!cut) {
     const int n_first = heads_listed_first(p, a), n_other = p.Hkv - n_first;
     const bool short_prefix = (n_first == 0 || a.max_first_prefix < 1600) && (n_other == 0 || a.max_other_prefix < 1600);
     const long long wgs = (long long)p.B * (p.g / hs) * ((a.n_rows + split.rows - 1) / split.rows) * (n_first * b.parts + n_other * b.parts_other);
-    if (short_prefix || wgs > (long long)device_cus() * split.wgs_per_cu) best = fmin(best, fmin(uncut.keysplit, uncut.piped));
+    if (short_prefix || wgs > (long long)device_cus() * split.wgs_per_cu) best = fmin(best, (short_prefix ? 1 : 1.3) * fmin(uncut.keysplit, uncut.piped));
   }
   if (pieces < best) {
     a = b;

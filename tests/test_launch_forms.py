@@ -98,7 +98,8 @@ def test_longer_prefixes_are_cut_where_the_uncut_launch_only_seems_shorter(forms
     longer = [chunk_line(128, 32, 8, (3, 3, 3, 3, 1, 1, 1, 1), 4096, 1024, (1, 1, 1), 2811, 14),
               chunk_line(128, 32, 8, (3, 3, 1, 1, 1, 1, 1, 1), 4096, 1024, (1, 1, 1), 3188, 11),
               chunk_line(128, 16, 2, (3, 1), 2048, 512, (1, 1, 1), 1180, 5),
-              chunk_line(128, 32, 8, (3, 1, 3, 1, 1, 1, 1, 1), 4096, 1024, (2,) * 4, 300, 19)]
+              chunk_line(128, 32, 8, (3, 1, 3, 1, 1, 1, 1, 1), 4096, 1024, (2,) * 4, 300, 19),
+              chunk_line(128, 40, 8, (2,) * 7 + (1,), 512, 64, (46,) * 6, 503, 3)]
     assert [(x.split()[0], int(x.split()[2]) > 1) for x in forms(longer)] == [("keysplit", True)] * len(longer)
 
 
