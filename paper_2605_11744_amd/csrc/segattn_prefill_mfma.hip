@@ -1270,13 +1270,16 @@ static double plan_pieces(const Problem &p, PrefillArgs &a, int hs, const PieceF
   a.piece_list[0] = {out, lse, a.parts, n_first * p.g, least(a.min_first_prefix, a.parts), 0};
   a.piece_list[1] = {out + rows_first * p.D, lse + rows_first, a.parts_other, n_other * p.g, least(a.min_other_prefix, a.parts_other), n_first};
   if (piped == 0) return best;
-  // Key-split pieces of head dimension 128 are bound by memory as often as by their steps: 32 query columns read as many keys
+  // Key-split pieces are bound by memory as often as by their steps: 32 query columns read as many keys
   // as 256 do, and the workgroups of a piece (row blocks, sub-groups of a group's heads) share them in an L2 only where the
-  // launch, which puts them `per` and a.parts apart, deals them to one XCD.  Fitted to 6504 timed chunks of 1 to 600 rows
-  // behind up to 100K (7 % off on average): 8 us, 4.3 a round of workgroups, the merge's bytes, and 0.172 us a step against 7.6
-  // TB/s beyond the L2s and 25 out of them.  By the steps alone 29 rows of two sequences behind 98K, 4/1 heads, took 67 us
-  // where the pipelined pieces take 40, and 25 rows behind 59K, 16/2 heads, 58 (41); of 3901 drawn chunks 29 were more than 3 %
-  // slower than with pipelined pieces alone (1.6x at worst), by the larger estimate 6 (1.1x) and 0.3 % fewer us in the mean.
+  // launch, which puts them `per` and a.parts apart, deals them to one XCD.  Head dimension 128, fitted to 3461 of 10,866 timed chunks
+  // of 1 to 1200 rows behind up to 65K (6 % off on average; the pipelined plan's estimate 9 %): 8 us, 4.2 a round of workgroups, the
+  // merge's bytes, and 0.169 us a step against 8 TB/s beyond the L2s and 24 out of them; pipelined 7 us and 0.8 of its
+  // estimate.  By the steps alone 29 rows of two sequences behind 98K, 4/1 heads, took 67 us where the pipelined pieces take 40,
+  // and 25 rows behind 59K, 16/2 heads, 58 (41): of the 10,866, 185 were more than 3 % slower than with pipelined pieces alone.
+  // With the constant parts left out, 0.815 is where the losses to either choice are fewest: 39 of them to pipelined pieces, 20 to the
+  // steps alone.  112 rows behind 68K, 8/8 heads, still stay pipelined (69 us, 60 in key-split pieces); a little further, 25
+  // behind 32K, 16/4 heads, would not (33, 39).
   // Head dimension 64, half the bytes a step, goes by the steps, except where several row blocks read the same keys and both
   // estimates of their bytes are a good part of the pipelined launch's time: 17 rows of six sequences behind 30K, 32/8 heads, six
   // PAST, 116 us (87 pipelined), 21 of three behind 64K, 24/4 heads, 140 (103).  Of 8134 drawn chunks 60 were more than 4 % slower than
@@ -1286,12 +1289,12 @@ static double plan_pieces(const Problem &p, PrefillArgs &a, int hs, const PieceF
   unsigned xcds = 0;  // that read a piece
   for (int h = 0; h < (nhs < 8 ? nhs : 8); ++h)
     for (int r = 0; r < 8 && r * form.rows < m; ++r) xcds |= 1u << (h * a.parts + r * per) % 8;
-  const double mb = 128e-6 * p.D, chain = 0.172 * span(first, steps_first, other, steps_other, 0);  // mb: of a step
-  const double beyond = mb * p.B * ((double)n_first * sf * __builtin_popcount(xcds) + (double)n_other * so) / 7.6, l2 = mb * total / 25;
-  const double us = 7.6 + row_heads * p.D * 8 / 5.0e6 + 4.3 * ceil((double)(first + other) / wgs) +
+  const double mb = 128e-6 * p.D, chain = 0.169 * span(first, steps_first, other, steps_other, 0);  // mb: of a step
+  const double beyond = mb * p.B * ((double)n_first * sf * __builtin_popcount(xcds) + (double)n_other * so) / 8, l2 = mb * total / 24;
+  if (p.D == 64) return m > form.rows && l2 >= 0.29 * piped && beyond >= 0.43 * piped ? INFINITY : best;
+  const double us = 1.8 * (row_heads * p.D * 8 / 5.0e6) + 4.2 * ceil((double)(first + other) / wgs) +
                     sqrt(sqrt(chain * chain * chain * chain + beyond * beyond * beyond * beyond + l2 * l2 * l2 * l2));
-  if (p.D == 64) return m > form.rows && l2 >= 0.28 * piped && beyond >= 0.45 * piped ? INFINITY : best;
-  return fmax(best, us);
+  return us < 0.815 * piped ? best : INFINITY;
 }
 
 // Key-split form or hand-pipelined form, nothing cut?  Both are estimated in microseconds from their longest chain
@@ -1354,14 +1357,14 @@ PrefillForm choose_prefill(const Problem &p, PrefillArgs &a) {
   // 556, 8/8 heads of 128, 9.9 us, in key-split pieces 11.8; 3 behind 769, 3/3 heads of 64, with the commit 13.3 and 15.6).  They are
   // far too low behind longer ones, whose keys come from cold memory: 14 rows of three sequences behind 7K, 32/8 heads, 51 us
   // uncut and 40 in pieces, 34 behind 8K 59 and 45.  Of 17 drawn chunks the pieces lost at 51 steps and won from 52 on.  Raised by
-  // 1.3 they still count where more key-split pieces than fit at once make the difference larger (5 rows of six sequences behind
+  // 1.25 they still count where more key-split pieces than fit at once make the difference larger (5 rows of six sequences behind
   // 51K, 24/8 heads, 503 us uncut, 699 in pieces; 3 of six behind 24K, 40/8 heads, 369 and 297, stay in pieces).
   double best = piped;
   if (!cut) {
     const int n_first = heads_listed_first(p, a), n_other = p.Hkv - n_first;
     const bool short_prefix = (n_first == 0 || a.max_first_prefix < 1600) && (n_other == 0 || a.max_other_prefix < 1600);
     const long long wgs = (long long)p.B * (p.g / hs) * ((a.n_rows + split.rows - 1) / split.rows) * (n_first * b.parts + n_other * b.parts_other);
-    if (short_prefix || wgs > (long long)device_cus() * split.wgs_per_cu) best = fmin(best, (short_prefix ? 1 : 1.3) * fmin(uncut.keysplit, uncut.piped));
+    if (short_prefix || wgs > (long long)device_cus() * split.wgs_per_cu) best = fmin(best, (short_prefix ? 1 : 1.25) * fmin(uncut.keysplit, uncut.piped));
   }
   if (pieces < best) {
     a = b;

@@ -78,6 +78,8 @@ def test_pieces_in_the_key_split_form_only_where_memory_lets_them(forms):
     short = [chunk_line(128, 16, 2, (3, 1), 4096, 1024, (7,), 2085, 8),
              chunk_line(128, 16, 4, (3, 1, 1, 1), 4096, 1024, (10, 10, 10), 2085, 34),
              chunk_line(64, 16, 4, (3, 1, 1, 1), 4096, 1024, (6,), 300, 26),
+             chunk_line(128, 8, 8, (3, 3, 1, 1, 1, 1, 1, 1), 4096, 512, (9,), 670, 76),  # 35 us, pipelined 40
+             chunk_line(128, 4, 1, (3,), 2048, 256, (11,) * 3, 903, 22),                 # 33, 36
              chunk_line(128, 32, 8, (3, 3, 3, 3, 1, 1, 1, 1), 4096, 1024, (6,), 300, 1)]
     assert [x.split()[0] for x in forms(short)] == ["keysplit"] * len(short)
     assert all(int(x.split()[2]) > 1 for x in forms(short))
